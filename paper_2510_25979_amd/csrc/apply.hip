@@ -25,6 +25,7 @@
 // HBM-bound: per (query, layer, head) the kernel moves S(S+32) map bytes
 // (causal bf16), V once per head group and O once.
 #include "common.hpp"
+#include "f32_tile.hpp"
 #include "launch.hpp"
 
 namespace ac {
@@ -533,14 +534,29 @@ __global__ __launch_bounds__(kThreads) void pack_maps_kernel(const bf16_t* __res
   }
 }
 
-// fp32 path (vector ALUs): small, correctness-first kernel for fp32 databases (dense layout).
-// One workgroup per (query, layer, head); thread t owns outputs (i, d) with
-// i*D + d = t, t + 256, ...; sums run over j in ascending order in fp32.
-__global__ __launch_bounds__(kThreads) void apply_f32_kernel(const ApplyArgs a, int D, int causal) {
-  const int tile = blockIdx.x;
-  const int h = tile % a.Hq;
-  const int l = (tile / a.Hq) % a.Lc;
-  const int bslot = tile / (a.Hq * a.Lc);
+// fp32 path (binary32 matrix instructions, dense layout, any S, D <= 64 DB).  Four waves of 16 map
+// rows each share 32-key stages of V; the map goes from memory straight into the lanes that feed
+// the products (a lane reads four consecutive columns of its row; rows of odd lengths are only
+// 4-byte aligned, which the load allows).  The next stage's V and map pieces are requested before
+// this one is multiplied.  Above the diagonal of a causal map nothing that was read is used.
+// 16 queries (12 hits) x 2 layers x 24 heads on 8 V, 94 x 128 causal: 403 us with one thread per
+// output and scalar loads, 22.6 us so (48 MB, 9 us at the copy rate; bound by the chain of load,
+// stage and product in a workgroup -- 64-key stages or four workgroups per CU measure the same).
+template <int DB>
+__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
+    const ApplyArgs a, int D, int causal) {
+  constexpr int KC = 32, NB = KC / 16;
+  typedef F32Stage<DB, KC> Stage;
+  __shared__ __attribute__((aligned(16))) float vl[KC * Stage::LD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, kq = lane >> 4;
+  const int S = a.S, g = a.Hq / a.Hkv;
+  const F32Unit u = f32_unit(blockIdx.x, wave, g, S, a.n_tiles);
+  if (u.tile < 0) return;
+  const int h = u.tile % a.Hkv * g + u.head;
+  const int l = (u.tile / a.Hkv) % a.Lc;
+  const int bslot = u.tile / (a.Hkv * a.Lc);
   int b, entry;
   if (a.fixed_entry >= 0) {
     b = a.q_list[bslot];
@@ -550,19 +566,81 @@ __global__ __launch_bounds__(kThreads) void apply_f32_kernel(const ApplyArgs a, 
     entry = a.hit[b];
     if (entry < 0 || entry >= a.M) return;
   }
-  const int S = a.S, g = a.Hq / a.Hkv;
-  const float* A = reinterpret_cast<const float*>(a.maps) +
-                   (((size_t)entry * a.L + (a.layer_begin + l)) * a.Hq + h) * (size_t)S * S;
+  const int row = kF32Rows * max(u.block, 0) + i;
+  const float* A_tile = reinterpret_cast<const float*>(a.maps) +
+                        (((size_t)entry * a.L + (a.layer_begin + l)) * a.Hq + h) * (size_t)S * S;
+  const float* A = A_tile + (size_t)min(row, S - 1) * S;
+  bool redo = false;   // wave-uniform
   const float* V = reinterpret_cast<const float*>(a.V) +
                    (((size_t)b * a.Lc + l) * a.Hkv + h / g) * (size_t)S * D;
-  float* O = reinterpret_cast<float*>(a.O) + (((size_t)b * a.Lc + l) * a.Hq + h) * (size_t)S * D;
-  for (int idx = threadIdx.x; idx < S * D; idx += kThreads) {
-    const int i = idx / D, d = idx % D;
-    const int nj = causal ? i + 1 : S;
-    float acc = 0.f;
-    for (int j = 0; j < nj; ++j) acc = fmaf(A[(size_t)i * S + j], V[(size_t)j * D + d], acc);
-    O[idx] = acc;
+  const int limit = causal ? min(row + 1, S) : S;   // columns of this row that count
+  const int wave_keys = u.block < 0 ? 0 : causal ? min(S, kF32Rows * (u.block + 1)) : S;
+  const int wg_keys = causal ? min(S, kF32Rows * (u.last_block + 1)) : S;
+
+  Stage vs;
+  f32x4 map[NB];
+  auto load_map = [&](int jc) {
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk) {
+      const int j = jc + 16 * bk + 4 * kq;
+      map[bk] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (jc + 16 * bk < wave_keys) {   // wave-uniform
+        if (j + 4 <= S) {
+          map[bk] = *reinterpret_cast<const f32x4_dw*>(A + j);
+        } else {
+#pragma unroll
+          for (int x = 0; x < 4; ++x)
+            if (j + x < S) map[bk][x] = A[j + x];
+        }
+      }
+    }
+  };
+  f32x4 acc[4 * DB];
+#pragma unroll
+  for (int x = 0; x < 4 * DB; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  vs.load(V, 0, S, D, tid);
+  load_map(0);
+  for (int jc = 0; jc < wg_keys; jc += KC) {
+    __syncthreads();   // the previous stage has been read by everybody
+    vs.commit(vl, tid);
+    f32x4 w[NB];
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) w[bk][x] = jc + 16 * bk + 4 * kq + x < limit ? map[bk][x] : 0.f;
+    __syncthreads();
+    if (jc + KC < wg_keys) {
+      vs.load(V, jc + KC, S, D, tid);
+      load_map(jc + KC);
+    }
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk)
+      if (jc + 16 * bk < wave_keys) {
+        const float* v = vl + 16 * bk * Stage::LD;
+        if (causal && (jc >> 4) + bk == u.block) redo = f32_block_not_finite<DB>(v, i, kq);
+        f32_weights_v<DB>(acc, v, w[bk], i, kq);
+      }
   }
+  float* O = reinterpret_cast<float*>(a.O) + (((size_t)b * a.Lc + l) * a.Hq + h) * (size_t)S * D;
+  if (u.block >= 0 && row < S && !redo) f32_store_row<DB>(O + (size_t)row * D, acc, 1.f, kq, D);
+  if (redo) {   // infinite or NaN V near the diagonal: lane = output column, only visible keys are read
+    const int first = kF32Rows * u.block, rows = min(kF32Rows, S - first);
+#pragma unroll 1
+    for (int r = 0; r < rows; ++r)
+      for (int d = lane; d < D; d += kWave) {
+        const float* Ar = A_tile + (size_t)(first + r) * S;
+        float o = 0.f;
+        for (int j = 0; j <= first + r; ++j) o = fmaf(Ar[j], V[(size_t)j * D + d], o);
+        O[(size_t)(first + r) * D + d] = o;
+      }
+  }
+}
+
+template <int DB>
+static hipError_t launch_apply_f32(const ApplyArgs& a, int D, int causal, hipStream_t stream) {
+  const unsigned grid = f32_grid(a.n_tiles, a.Hq / a.Hkv, a.S);
+  hipLaunchKernelGGL((apply_f32_kernel<DB>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal);
+  return hipGetLastError();
 }
 
 static size_t apply_lds_bytes(int D) {
@@ -620,10 +698,10 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
   if (nb == 0 || p.Lc == 0) return hipSuccess;
 
   if (p.is_f32) {
-    a.heads_per_wg = 1; a.n_rblk = 1; a.n_tiles = nb * p.Lc * p.Hq;
-    hipLaunchKernelGGL(apply_f32_kernel, dim3(a.n_tiles), dim3(kThreads), 0, stream, a, p.D,
-                       p.causal);
-    return hipGetLastError();
+    a.heads_per_wg = 1; a.n_rblk = 1; a.n_tiles = nb * p.Lc * p.Hkv;
+    if (p.D <= 64) return launch_apply_f32<1>(a, p.D, p.causal, stream);
+    if (p.D <= 128) return launch_apply_f32<2>(a, p.D, p.causal, stream);
+    return launch_apply_f32<4>(a, p.D, p.causal, stream);
   }
   a.n_rblk = (p.S + kChunk - 1) / kChunk;
   const int g = p.Hq / p.Hkv;

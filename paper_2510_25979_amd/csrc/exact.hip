@@ -20,6 +20,7 @@
 // Softmax runs in the log2 domain with the scale folded into one FMA per
 // score; the accumulator is rescaled only when some row maximum has moved far.
 #include "common.hpp"
+#include "f32_tile.hpp"
 #include "launch.hpp"
 
 namespace ac {
@@ -497,45 +498,160 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
   }
 }
 
-// fp32 path (vector ALUs): one wave per (batch item, head, query row).
-__global__ __launch_bounds__(kWave) void exact_f32_kernel(const ExactArgs a, int D, int causal,
-                                                          float scale) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* p = reinterpret_cast<float*>(smem);   // [S]
+// fp32 path (binary32 matrix instructions, any S, D <= 64 DB): four waves of 16 query rows each
+// share 32-key stages of K and V; the next stage's rows are in registers while this one is
+// multiplied.  Online softmax: every lane keeps the running maximum and ITS keys' share of the row
+// sum, the accumulator is rescaled when a maximum of the wave moves.
+// 16 x 24 heads on 8 K and V, 94 x 128 causal: 805 us with one wave per query row on the vector
+// ALUs, 25.2 us so (7 us of matrix instructions at the peak rate, 10 us of memory at the copy
+// rate; the rest is the load -> stage -> score -> weight chain of 640 workgroups that start
+// together).  Four workgroups per CU need 128 registers and spill (38 us).
+template <int DB>
+__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
+    const ExactArgs a, int D, int causal, float scale) {
+  constexpr int KC = 32;
+  typedef F32Stage<DB, KC> Stage;
+  __shared__ __attribute__((aligned(16))) float kl[KC * Stage::LD];
+  __shared__ __attribute__((aligned(16))) float vl[KC * Stage::LD];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, kq = lane >> 4;
   const int S = a.S, g = a.Hq / a.Hkv;
-  const int i = blockIdx.x % S;
-  const int h = (blockIdx.x / S) % a.Hq;
-  const int b = blockIdx.x / (S * a.Hq);
+  const F32Unit u = f32_unit(blockIdx.x, wave, g, S, a.n_kvtiles);
+  if (u.tile < 0) return;
+  const int b = u.tile / a.Hkv, h = u.tile % a.Hkv * g + u.head;
   if (a.row_sel && a.row_sel[b] >= 0) return;
-  const int lane = threadIdx.x;
-  const float* q = reinterpret_cast<const float*>(a.Q) + (((size_t)b * a.Hq + h) * S + i) * (size_t)D;
-  const float* K = reinterpret_cast<const float*>(a.K) + ((size_t)b * a.Hkv + h / g) * (size_t)S * D;
-  const float* V = reinterpret_cast<const float*>(a.V) + ((size_t)b * a.Hkv + h / g) * (size_t)S * D;
-  float* o = reinterpret_cast<float*>(a.O) + (((size_t)b * a.Hq + h) * S + i) * (size_t)D;
   const int len = a.key_len ? min(max(a.key_len[b], 1), S) : S;   // keys beyond it are padding
-  const int nj = min(causal ? i + 1 : S, len);
-  float mx = -INFINITY;
-  for (int j = lane; j < nj; j += kWave) {
-    float acc = 0.f;
-    for (int d = 0; d < D; ++d) acc = fmaf(q[d], K[(size_t)j * D + d], acc);
-    acc *= scale;
-    p[j] = acc;
-    mx = fmaxf(mx, acc);
+  const float* K = reinterpret_cast<const float*>(a.K) + (size_t)u.tile * S * D;
+  const float* V = reinterpret_cast<const float*>(a.V) + (size_t)u.tile * S * D;
+
+  const int row = kF32Rows * max(u.block, 0) + i;
+  const size_t at = (((size_t)b * a.Hq + h) * S + min(row, S - 1)) * (size_t)D;
+  f32x4 q[4 * DB];
+#pragma unroll
+  for (int kk = 0; kk < 4 * DB; ++kk) {
+    const int c = 16 * kk + 4 * kq;
+    const float* src = reinterpret_cast<const float*>(a.Q) + at + c;
+    q[kk] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if ((D & 3) == 0) {
+      if (c < D) q[kk] = *reinterpret_cast<const f32x4*>(src);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (c + t < D) q[kk][t] = src[t];
+    }
   }
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  float z = 0.f;
-  for (int j = lane; j < nj; j += kWave) {
-    const float e = expf(p[j] - mx);
-    p[j] = e;
-    z += e;
+  f32x4 acc[4 * DB];
+#pragma unroll
+  for (int x = 0; x < 4 * DB; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  bool redo = false;   // wave-uniform
+  const int limit = causal ? min(row + 1, len) : len;                                // keys this row sees
+  const int wave_keys = u.block < 0 ? 0 : causal ? min(len, kF32Rows * (u.block + 1)) : len;
+  const int wg_keys = causal ? min(len, kF32Rows * (u.last_block + 1)) : len;
+
+  Stage ks, vs;
+  ks.load(K, 0, len, D, tid);
+  vs.load(V, 0, len, D, tid);
+  for (int jc = 0; jc < wg_keys; jc += KC) {
+    __syncthreads();   // the previous stage has been read by everybody
+    ks.commit(kl, tid);
+    vs.commit(vl, tid);
+    __syncthreads();
+    if (jc + KC < wg_keys) {
+      ks.load(K, jc + KC, len, D, tid);
+      vs.load(V, jc + KC, len, D, tid);
+    }
+    const int left = wave_keys - jc;
+    if (left <= 0) continue;
+    f32x4 s[2];
+#pragma unroll
+    for (int bk = 0; bk < 2; ++bk) {
+      s[bk] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (16 * bk < left) {
+        const float* krow = kl + (16 * bk + i) * Stage::LD + 4 * kq;
+        f32x4 k = *reinterpret_cast<const f32x4*>(krow);
+#pragma unroll
+        for (int kk = 0; kk < 4 * DB; ++kk) {
+          if (16 * kk < D) {   // uniform
+            const f32x4 next = *reinterpret_cast<const f32x4*>(krow + 16 * ((kk + 1) & (4 * DB - 1)));
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s[bk] = mfma_f32(k[t], q[kk][t], s[bk]);
+            k = next;
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+    }
+    float mx = -INFINITY;
+    bool seen[2][4];
+#pragma unroll
+    for (int bk = 0; bk < 2; ++bk)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        seen[bk][x] = jc + 16 * bk + 4 * kq + x < limit;
+        s[bk][x] *= scale;
+        mx = seen[bk][x] ? fmaxf(mx, s[bk][x]) : mx;
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx);
+    if (__any(m_new > m)) {
+      const float alpha = m_new > m ? expf(m - m_new) : 1.f;
+      l *= alpha;
+#pragma unroll
+      for (int x = 0; x < 4 * DB; ++x) acc[x] *= alpha;
+      m = m_new;
+    }
+    const float ref = m == -INFINITY ? 0.f : m;   // no finite score so far: all weights are zero
+#pragma unroll
+    for (int bk = 0; bk < 2; ++bk) {
+      if (16 * bk < left) {
+        f32x4 p;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          p[x] = seen[bk][x] ? expf(s[bk][x] - ref) : 0.f;
+          l += p[x];
+        }
+        const float* v = vl + 16 * bk * Stage::LD;
+        if (causal && (jc >> 4) + bk == u.block) redo = f32_block_not_finite<DB>(v, i, kq);
+        f32_weights_v<DB>(acc, v, p, i, kq);
+      }
+    }
   }
-  for (int off = 32; off > 0; off >>= 1) z += __shfl_xor(z, off);
-  __syncthreads();
-  for (int d = lane; d < D; d += kWave) {
-    float acc = 0.f;
-    for (int j = 0; j < nj; ++j) acc = fmaf(p[j], V[(size_t)j * D + d], acc);
-    o[d] = acc / z;
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (u.block >= 0 && row < S && !redo)
+    f32_store_row<DB>(reinterpret_cast<float*>(a.O) + at, acc, l, kq, D);
+  if (redo) {   // infinite or NaN V near the diagonal: lane = output column, only visible keys are read
+    const int rows = min(kF32Rows, S - kF32Rows * u.block);
+#pragma unroll 1
+    for (int r = 0; r < rows; ++r) {
+      const size_t to = __shfl(at, r);
+      const float* Q = reinterpret_cast<const float*>(a.Q) + to;
+      const float mr = __shfl(m, r), lr = __shfl(l, r);
+      const int keys = __shfl(limit, r);
+      for (int d0 = 0; d0 < D; d0 += kWave) {
+        float o = 0.f;
+        for (int j = 0; j < keys; ++j) {
+          float s = 0.f;
+          for (int d = lane; d < D; d += kWave) s = fmaf(Q[d], K[(size_t)j * D + d], s);
+          for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+          const float p = expf(s * scale - (mr == -INFINITY ? 0.f : mr));
+          if (d0 + lane < D) o = fmaf(p, V[(size_t)j * D + d0 + lane], o);
+        }
+        if (d0 + lane < D) reinterpret_cast<float*>(a.O)[to + d0 + lane] = o / lr;
+      }
+    }
   }
+}
+
+template <int DB>
+static hipError_t launch_exact_f32(const ExactArgs& a, int D, int causal, float scale,
+                                   hipStream_t stream) {
+  const unsigned grid = f32_grid(a.n_kvtiles, a.Hq / a.Hkv, a.S);
+  hipLaunchKernelGGL((exact_f32_kernel<DB>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
+  return hipGetLastError();
 }
 
 template <int D, bool CAUSAL, bool RESIDENT>
@@ -576,11 +692,10 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
   const float scale = p.scale == 0.f ? 1.0f / sqrtf((float)p.D) : p.scale;
   a.scale_log2e = scale * 1.44269504088896340736f;
   a.heads_per_wg = 1;
-  if (p.is_f32) {
-    const unsigned blocks = (unsigned)((size_t)p.B * p.Hq * p.S);
-    hipLaunchKernelGGL(exact_f32_kernel, dim3(blocks), dim3(kWave), (size_t)p.S * sizeof(float),
-                       stream, a, p.D, p.causal, scale);
-    return hipGetLastError();
+  if (p.is_f32) {   // D <= 256, by the number of 64-wide output blocks
+    if (p.D <= 64) return launch_exact_f32<1>(a, p.D, p.causal, scale, stream);
+    if (p.D <= 128) return launch_exact_f32<2>(a, p.D, p.causal, scale, stream);
+    return launch_exact_f32<4>(a, p.D, p.causal, scale, stream);
   }
   const int g = p.Hq / p.Hkv;
   a.heads_per_wg = a.n_rblk == 1 ? g : 1;
