@@ -13,7 +13,11 @@
 //     member of the exact top-k lies in one of the k groups with the best
 //     maxima (each such group holds at least one of the k best elements), so
 //     those k groups are re-scored row by row and the k best rows selected.
+//     Groups are contiguous and ascend, so among equal maxima the lower group
+//     number stands for the lower row and only the score has to be kept.
 // fp32 databases (and the L2 metric) use a vector-ALU phase 1 of the same shape.
+#include <type_traits>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -22,6 +26,7 @@ namespace ac {
 constexpr int kQPad = 8;            // fp16 elements of padding per staged query row
 constexpr int kValuRowsPerWg = 256;
 constexpr int kIdxNone = 0x7fffffff;
+constexpr int kMaxK = 64;           // AC_MAX_K of the C interface
 
 struct SearchArgs {
   const void* emb;
@@ -29,12 +34,12 @@ struct SearchArgs {
   const int32_t* map_of;
   int32_t N, E, B, k, metric;
   int32_t q0, nq;          // query super-block handled by this launch (phase 1)
-  int32_t rows_per_wg, G;  // group size and count (a group: the rows one partial result covers)
-  int32_t wg_rows;         // rows one phase-1 workgroup scans: the group, or four groups of 32
+  int32_t rows, G;         // group size and count (a group: the rows one partial result covers)
+  int32_t wg_rows;         // rows one phase-1 workgroup scans: one group (k = 1) or several
   float threshold;
-  float* part_s;           // [B][G]
-  int32_t* part_i;         // [B][G]
-  float* cand;             // [B][k * rows_per_wg] (k > 1 only)
+  float* part_s;           // [B][G] best score of each group
+  int32_t* part_i;         // [B][G] its row (k = 1 only)
+  float* cand;             // [B][k * rows] scores of the selected groups' rows (k > 1 only)
   int32_t* idx;
   float* score;
   int32_t* hit;
@@ -61,8 +66,30 @@ __device__ __forceinline__ void block_argmax(float& s, int& i, float* red_s, int
     if (ranks_before(red_s[w], red_i[w], s, i)) { s = red_s[w]; i = red_i[w]; }
 }
 
+// Largest x of the wave in every lane: four steps inside rows of 16 lanes, two across.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+#define AC_DPP_MAX(ctrl, rows) \
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, ctrl, rows, 0xf, false))
+  AC_DPP_MAX(0x111, 0xf);   // row_shr:1, 2, 4, 8
+  AC_DPP_MAX(0x112, 0xf);
+  AC_DPP_MAX(0x114, 0xf);
+  AC_DPP_MAX(0x118, 0xf);
+  AC_DPP_MAX(0x142, 0xa);   // lane 15 of a row into the next one
+  AC_DPP_MAX(0x143, 0xc);   // lane 31 into the upper half: lane 63 has seen them all
+#undef AC_DPP_MAX
+  return __builtin_amdgcn_readlane(x, 63);
+}
+// Scores as whole numbers in the same order (no NaN; zeros compare equal); 0 stands for "none".
+__device__ __forceinline__ uint32_t score_key(float s) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, s + 0.f);   // -0 becomes +0
+  return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float key_score(uint32_t k) {
+  return __builtin_bit_cast(float, k ^ (k >> 31 ? 0x80000000u : 0xffffffffu));
+}
+
 // ---------------------------------------------------------------- phase 1, matrix cores
-template <int KSMAX, int NQB>
+template <int KSMAX, int NQB, bool TOPK>
 __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int E = a.E, QS = E + kQPad;
@@ -97,7 +124,8 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
   const int row_begin = blockIdx.x * a.wg_rows;
   const int row_end = min(row_begin + a.wg_rows, a.N);
   const f16_t* emb = reinterpret_cast<const f16_t*>(a.emb);
-  for (int rb = row_begin + 32 * wave; rb < row_end; rb += 128) {
+  for (int pass = row_begin; pass < row_end; pass += 128) {   // the same trips for all four waves
+    const int rb = pass + 32 * wave;
     // database operand: lane (il, kh) holds emb[rb + il][16 ks + 8 kh .. +8); rows past the
     // end are clamped for the load and masked below
     const int rowc = min(rb + il, a.N - 1);
@@ -121,33 +149,45 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
       for (int v = 0; v < 16; ++v) {
         const int r = rb + mfma_row(v, kh);
         const float s = r < a.N ? acc[v] : -INFINITY;
-        if (s > best_s[qb]) { best_s[qb] = s; best_i[qb] = r; }
+        if (TOPK) {
+          best_s[qb] = fmaxf(best_s[qb], s);
+        } else if (s > best_s[qb]) {
+          best_s[qb] = s;
+          best_i[qb] = r;
+        }
+      }
+    }
+    if (TOPK) {   // group maxima leave as soon as a group is complete
+      const bool per_wave = a.rows == 32;   // a wave's 32 rows are a group: nothing to merge
+      const int gi = (per_wave ? rb : pass) / a.rows;
+      if (!per_wave && pass + 128 < row_end && (pass + 128) / a.rows == gi) continue;   // uniform
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) {
+        const float s = fmaxf(best_s[qb], __shfl_xor(best_s[qb], 32));
+        best_s[qb] = -INFINITY;
+        const int t = 32 * qb + il;
+        if (!per_wave) {
+          if (kh == 0) red_s[wave * 32 * NQB + t] = s;
+        } else if (kh == 0 && t < a.nq && rb < a.N) {
+          a.part_s[(size_t)(a.q0 + t) * a.G + gi] = s;
+        }
+      }
+      if (!per_wave) {   // one group per pass (or several passes): the four waves meet in LDS
+        __syncthreads();
+        for (int t = tid; t < a.nq; t += kThreads)
+          a.part_s[(size_t)(a.q0 + t) * a.G + gi] =
+              fmaxf(fmaxf(red_s[t], red_s[32 * NQB + t]), fmaxf(red_s[64 * NQB + t], red_s[96 * NQB + t]));
+        __syncthreads();
       }
     }
   }
+  if (TOPK) return;
   // combine the two lane halves
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb) {
     const float so = __shfl_xor(best_s[qb], 32);
     const int io = __shfl_xor(best_i[qb], 32);
     if (ranks_before(so, io, best_s[qb], best_i[qb])) { best_s[qb] = so; best_i[qb] = io; }
-  }
-  if (a.rows_per_wg == 32) {
-    // groups of 32 rows (top-k searches: the finalising kernel re-scores k whole groups per
-    // query, so small groups are cheap): a workgroup scans 128 rows in one pass and every
-    // wave's 32 rows are a group of their own -- nothing to merge
-    const int gi = 4 * blockIdx.x + wave;
-    if (kh == 0 && gi < a.G) {
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        const int t = 32 * qb + il;
-        if (t < a.nq) {
-          a.part_s[(size_t)(a.q0 + t) * a.G + gi] = best_s[qb];
-          a.part_i[(size_t)(a.q0 + t) * a.G + gi] = best_i[qb];
-        }
-      }
-    }
-    return;
   }
   // one group per workgroup: the four waves meet in LDS
 #pragma unroll
@@ -187,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
 // global piece each lane fetches.
 constexpr int kBigRows = 64;   // database rows per LDS chunk
 
-template <int KSMAX, int QPW>
+template <int KSMAX, int QPW, bool TOPK>
 __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_big_kernel(const SearchArgs a) {
   constexpr int E = 16 * KSMAX;               // this kernel is built for E = 128, 256, 512
   constexpr int EQ = E / 8;                   // 16-byte pieces per row
@@ -214,8 +254,8 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
     }
   }
 
-  const int row_begin = blockIdx.x * a.rows_per_wg;
-  const int row_end = min(row_begin + a.rows_per_wg, a.N);
+  const int row_begin = blockIdx.x * a.wg_rows;
+  const int row_end = min(row_begin + a.wg_rows, a.N);
   const int n_chunk = (row_end - row_begin + kBigRows - 1) / kBigRows;
   const f16_t* emb = reinterpret_cast<const f16_t*>(a.emb);
 
@@ -323,13 +363,29 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
 #pragma unroll
         for (int v = 3; v < 15; v += 2) mx = fmaxf(fmaxf(mx, acc[j][v]), acc[j][v + 1]);
         mx = fmaxf(mx, acc[j][15]);
-        const bool up = mx > best_s[j];
-        best_s[j] = up ? mx : best_s[j];
-        best_i[j] = up ? blk : best_i[j];
+        if (TOPK) {
+          best_s[j] = fmaxf(best_s[j], mx);
+        } else {
+          const bool up = mx > best_s[j];
+          best_s[j] = up ? mx : best_s[j];
+          best_i[j] = up ? blk : best_i[j];
+        }
       }
       // the next block's products must not start before these comparisons are done: a second
       // live set of result registers does not fit next to the query operands
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if (TOPK) {   // a group is one or several chunks: its maxima leave with its last chunk
+      const int next = cbase + kBigRows, gi = cbase / a.rows;
+      if (next >= row_end || next / a.rows != gi) {
+#pragma unroll
+        for (int j = 0; j < QPW; ++j) {
+          const float s = fmaxf(best_s[j], __shfl_xor(best_s[j], 32));
+          best_s[j] = -INFINITY;
+          const int qi = 32 * (QPW * wave + j) + il;
+          if (kh == 0 && qi < a.nq) a.part_s[(size_t)(a.q0 + qi) * a.G + gi] = s;
+        }
+      }
     }
   };
   // own copies landed (they are counted like loads), then everybody's
@@ -363,6 +419,7 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
     compute(cur, ch, true);
     publish();
   }
+  if (TOPK) return;
   // combine the two lane halves; every wave owns its queries, nothing else to merge
 #pragma unroll
   for (int j = 0; j < QPW; ++j) {
@@ -380,32 +437,13 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
 }
 
 // ------------------------------------------------------------- vector-ALU scoring
-template <typename T>
-__device__ __forceinline__ float load_as_float(const T* p) { return (float)(*p); }
-
-// score of one database row against the query staged in LDS as fp32
-template <typename T>
-__device__ __forceinline__ float row_score(const T* __restrict__ row, const float* __restrict__ qf,
-                                           int E, int metric) {
-  float acc = 0.f;
-  if (metric == 0) {
-    for (int e = 0; e < E; ++e) acc = fmaf(qf[e], load_as_float(row + e), acc);
-  } else {
-    for (int e = 0; e < E; ++e) {
-      const float d = qf[e] - load_as_float(row + e);
-      acc = fmaf(-d, d, acc);
-    }
-  }
-  return acc;
-}
-
 // phase 1 on the vector ALUs (binary32 databases, the Euclidean metric, and the fp16 widths that no
 // matrix-core kernel is built for).  A workgroup scores the 256 rows of its group against 4 QW
 // queries: rows and queries go through LDS in slices of 32 columns (as binary32; the next
 // slice is in registers meanwhile), wave w takes queries QW w .. QW w + QW - 1, a lane four rows
 // 64 apart, so one row read feeds QW queries, one (broadcast) query read four rows, and the
 // index is read once per 4 QW queries instead of once per query.  Every score is one chain of
-// fmas over ascending columns, the same as row_score.
+// fmas over ascending columns.
 // Bound by the vector ALUs: two instructions per element of q - e (Euclidean), one per product.
 // 100,000 x 128 fp32, 64 queries, Euclidean: 885 us with one row per thread and one query per
 // workgroup, 49 us so (42 us at the full issue rate).  Sixteen queries per workgroup leave some six
@@ -447,7 +485,7 @@ struct TileSlice {
   }
 };
 
-template <typename T, bool L2, int QW>
+template <typename T, bool L2, int QW, bool TOPK>
 __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs a) {
   constexpr int R = kValuRowsPerWg / kWave;   // rows of a lane
   __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
@@ -457,7 +495,7 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
   // the query blocks of one group get ids equal mod 8: one XCD reads the group's rows once
   const int nqb = (a.B + 4 * QW - 1) / (4 * QW), slot = blockIdx.x >> 3;
   const int gidx = slot / nqb * 8 + (blockIdx.x & 7), q0 = slot % nqb * (4 * QW);
-  if (gidx >= a.G) return;
+  if (gidx >= (a.N + kValuRowsPerWg - 1) / kValuRowsPerWg) return;
   const T* emb = reinterpret_cast<const T*>(a.emb);
   const T* qs = reinterpret_cast<const T*>(a.q);
   const int row0 = gidx * kValuRowsPerWg;
@@ -504,6 +542,23 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
       }
     }
   }
+  if (TOPK) {   // groups of 64 rows (those of one r) or of all 256
+#pragma unroll
+    for (int j = 0; j < QW; ++j) {
+      const int q = q0 + QW * wave + j;
+      float all = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int first = row0 + kWave * r;
+        const float s = key_score(wave_max(score_key(fmaxf(-INFINITY, first + lane < a.N ? acc[r][j] : -INFINITY))));
+        all = fmaxf(all, s);
+        if (a.rows == kWave && lane == 0 && q < a.B && first < a.N)
+          a.part_s[(size_t)q * a.G + first / kWave] = s;
+      }
+      if (a.rows != kWave && lane == 0 && q < a.B) a.part_s[(size_t)q * a.G + gidx] = all;
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < QW; ++j) {
     float s = -INFINITY;
@@ -526,14 +581,21 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
   }
 }
 
-template <typename T, bool L2>
-static hipError_t launch_valu(const SearchArgs& a, hipStream_t stream) {
+template <typename T, bool L2, bool TOPK>
+static hipError_t launch_valu_k(const SearchArgs& a, hipStream_t stream) {
   const int qw = a.B <= 4 ? 1 : a.B <= 8 ? 2 : 4;   // queries per wave
-  const dim3 grid((unsigned)((size_t)(a.G + 7) / 8 * 8 * ((a.B + 4 * qw - 1) / (4 * qw))));
-  if (qw == 1) hipLaunchKernelGGL((search_valu_kernel<T, L2, 1>), grid, dim3(kThreads), 0, stream, a);
-  else if (qw == 2) hipLaunchKernelGGL((search_valu_kernel<T, L2, 2>), grid, dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL((search_valu_kernel<T, L2, 4>), grid, dim3(kThreads), 0, stream, a);
+  const size_t blocks = (size_t)((a.N + kValuRowsPerWg - 1) / kValuRowsPerWg + 7) / 8 * 8;
+  const dim3 grid((unsigned)(blocks * ((a.B + 4 * qw - 1) / (4 * qw))));
+  if (qw == 1) hipLaunchKernelGGL((search_valu_kernel<T, L2, 1, TOPK>), grid, dim3(kThreads), 0, stream, a);
+  else if (qw == 2) hipLaunchKernelGGL((search_valu_kernel<T, L2, 2, TOPK>), grid, dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL((search_valu_kernel<T, L2, 4, TOPK>), grid, dim3(kThreads), 0, stream, a);
   return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_valu(const SearchArgs& a, hipStream_t stream) {
+  if (a.k > 1) return a.metric ? launch_valu_k<T, true, true>(a, stream) : launch_valu_k<T, false, true>(a, stream);
+  return a.metric ? launch_valu_k<T, true, false>(a, stream) : launch_valu_k<T, false, false>(a, stream);
 }
 
 // ------------------------------------------------------------------- phase 2
@@ -611,160 +673,219 @@ __global__ __launch_bounds__(kThreads) void finalize_top1_block_kernel(const Sea
   }
 }
 
-// k > 1: pick the k best groups, re-score their rows, pick the k best rows.
-// Selecting the k best of n items takes k rounds of a workgroup-wide arg-max in general; while
-// the items fit one per thread (n <= 256: the common case once the groups are small) every
-// thread instead counts the items that rank before its own -- the order is total, so that count
-// is the item's position -- and the first k positions are written directly: one pass, two
-// barriers, no rounds.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void finalize_topk_kernel(const SearchArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* qf = reinterpret_cast<float*>(smem);          // [E]
-  int* sel = reinterpret_cast<int*>(qf + a.E);         // [k] selected groups
-  __shared__ float red_s[4];
-  __shared__ int red_i[4];
-  typedef int i32x4 __attribute__((ext_vector_type(4)));
-  __shared__ __attribute__((aligned(16))) float item_s[kThreads];
-  __shared__ __attribute__((aligned(16))) int item_i[kThreads];
-  const int b = blockIdx.x, tid = threadIdx.x;
-  const int rpw = a.rows_per_wg;
-  const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
-  for (int e = tid; e < a.E; e += kThreads) qf[e] = load_as_float(q + e);
+// An item of a selection: score and number in one word that orders like them (higher score, then
+// lower number); 0 stands for "none".
+__device__ __forceinline__ uint64_t item_key(float s, int i) {
+  return (uint64_t)score_key(s) << 32 | (uint32_t)~i;
+}
 
-  // position of this thread's item (s, i) among the n <= 256 items held one per thread (threads
-  // without an item pass i = kIdxNone), and the number of items there are
-  auto position = [&](float s, int i, int n, int& n_items) {
-    item_s[tid] = s;
-    item_i[tid] = i;
-    __syncthreads();
-    int before = 0, count = 0;
-    // four items per read, no branches: every thread has stored an item (kIdxNone beyond n), so
-    // reading up to the next multiple of four is safe and the extra items do not count
-    for (int j = 0; j < n; j += 4) {
-      const f32x4 sj = *reinterpret_cast<const f32x4*>(item_s + j);
-      const i32x4 ij = *reinterpret_cast<const i32x4*>(item_i + j);
+// The k best of the items a wave holds (IPT per lane), drawn one after the other: the r-th best ends
+// up in lane r (k <= 64).  No barrier, no memory; the lane whose item was drawn looks for its next
+// one, which is why IPT is a compile-time number (16 guarded by the real count: 1,500 cycles a draw).
+template <int IPT>
+__device__ __forceinline__ uint64_t draw_best(const uint64_t (&item)[IPT], int k) {
+  const int lane = threadIdx.x & 63;
+  uint64_t best = 0, out = 0;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bool there = ij[t] != kIdxNone;
-        count += there ? 1 : 0;
-        before += (there && ranks_before(sj[t], ij[t], s, i)) ? 1 : 0;
+  for (int t = 0; t < IPT; ++t) best = max(best, item[t]);
+  for (int r = 0; r < k; ++r) {
+    const uint32_t top = wave_max((uint32_t)(best >> 32));
+    if (top == 0) break;   // nothing is left
+    const bool at = (uint32_t)(best >> 32) == top;
+    const unsigned long long who = __ballot(at);
+    const uint32_t low = (who & (who - 1)) ? wave_max(at ? (uint32_t)best : 0u)   // equal scores
+                                           : __builtin_amdgcn_readlane((uint32_t)best, (int)__builtin_ctzll(who));
+    const uint64_t pick = (uint64_t)top << 32 | low;
+    if (lane == r) out = pick;
+    if (best == pick) {   // one lane: its best item after this one
+      best = 0;
+#pragma unroll
+      for (int t = 0; t < IPT; ++t) {
+        const uint64_t x = item[t] < pick ? item[t] : 0;
+        best = max(best, x);
       }
-    }
-    __syncthreads();   // the arrays are used again
-    n_items = count;
-    return before;
-  };
-
-  // 1. the min(k, G) groups with the best maxima, in rank order
-  const int ng = min(a.k, a.G);
-  if (a.G <= kThreads) {
-    if (tid < ng) sel[tid] = -1;   // fewer groups with a maximum than ng: the rest stay empty
-    float s = -INFINITY;
-    int i = kIdxNone;
-    if (tid < a.G) {
-      s = a.part_s[(size_t)b * a.G + tid];
-      i = a.part_i[(size_t)b * a.G + tid];
-    }
-    int n_items;
-    const int pos = position(s, i, a.G, n_items);
-    if (i != kIdxNone && pos < ng) sel[pos] = i / rpw;
-  } else {
-    float last_s = INFINITY;
-    int last_i = -1;
-    for (int r = 0; r < ng; ++r) {
-      float s = -INFINITY;
-      int i = kIdxNone;
-      for (int gi = tid; gi < a.G; gi += kThreads) {
-        const float so = a.part_s[(size_t)b * a.G + gi];
-        const int io = a.part_i[(size_t)b * a.G + gi];
-        // only groups ranked strictly after the previous pick
-        if (ranks_before(last_s, last_i, so, io) && ranks_before(so, io, s, i)) { s = so; i = io; }
-      }
-      block_argmax(s, i, red_s, red_i);
-      if (tid == 0) sel[r] = (i == kIdxNone) ? -1 : i / rpw;
-      last_s = s; last_i = i;
     }
   }
-  __syncthreads();
+  return out;
+}
 
-  // 2. re-score every row of the selected groups, one row per thread -- or, when there are
-  // at most 128 (64) rows, two (four) threads per row, each walking its own contiguous part: a
-  // thread's walk is a chain of cache round trips, so the shorter the walk the better
-  float* cand = a.cand + (size_t)b * a.k * rpw;
-  const int n_rows = ng * rpw;
-  const int tpr = (n_rows <= 64 && a.E % 4 == 0) ? 4 : ((n_rows <= 128 && a.E % 2 == 0) ? 2 : 1);
-  if (tpr > 1) {   // one trip: thread tid takes part tid % tpr of row tid / tpr
-    const int slot = tid / tpr, part = tid % tpr, seg = a.E / tpr;
-    float s = 0.f;
-    bool live = false;
-    if (slot < n_rows) {
-      const int gsel = sel[slot / rpw];
-      const int r = gsel * rpw + slot % rpw;
-      if (gsel >= 0 && r < a.N) {
-        live = true;
-        s = row_score(reinterpret_cast<const T*>(a.emb) + (size_t)r * a.E + part * seg, qf + part * seg,
-                      seg, a.metric);
+constexpr int kItems = 16;   // most items of a lane
+
+// The k best of n items under the total order "higher score, then lower number", in rank order.
+// get(x) is item x as item_key (0: it does not rank, e.g. a NaN score); put(r, s, i) is called once
+// for every rank r < k, with kIdxNone where fewer than k items rank.  NT threads, lists[NT].
+// Up to 16 items per thread sit in registers: every wave draws its own k best, the first wave draws
+// the k best of those.  Four waves do it while they can hold the items -- sixteen are four to a SIMD
+// and take turns (1,563 items, k = 8: 9 us against 3 us).  More items than 16 per thread (some 16
+// million rows) take k rounds over memory.
+template <int NT, typename Get, typename Put>
+__device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint64_t* lists) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (n > kItems * NT) {
+    uint64_t last = ~0ull;
+    for (int r = 0; r < k; ++r) {
+      uint64_t best = 0;
+      for (int x = tid; x < n; x += NT) {
+        const uint64_t it = get(x);
+        if (it < last) best = max(best, it);
       }
+      lists[tid] = best;
+      __syncthreads();
+      for (int half = NT / 2; half > 0; half >>= 1) {
+        if (tid < half) lists[tid] = max(lists[tid], lists[tid + half]);
+        __syncthreads();
+      }
+      last = lists[0];
+      __syncthreads();
+      if (tid == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
     }
-    s += __shfl_xor(s, 1);
-    if (tpr == 4) s += __shfl_xor(s, 2);
-    if (part == 0 && slot < n_rows) cand[slot] = live ? s : -INFINITY;
-  } else
-  for (int slot = tid; slot < ng * rpw; slot += kThreads) {
-    const int gsel = sel[slot / rpw];
-    const int r = gsel * rpw + slot % rpw;
-    float s = -INFINITY;
-    if (gsel >= 0 && r < a.N)
-      s = row_score(reinterpret_cast<const T*>(a.emb) + (size_t)r * a.E, qf, a.E, a.metric);
-    cand[slot] = s;
-  }
-  __syncthreads();
-
-  // 3. the k best rows among the candidates, in rank order
-  if (ng * rpw <= kThreads) {
-    float s = -INFINITY;
-    int i = kIdxNone;
-    if (tid < ng * rpw) {
-      const int gsel = sel[tid / rpw];
-      const int row = gsel * rpw + tid % rpw;
-      const float so = cand[tid];
-      if (gsel >= 0 && row < a.N && so == so) { s = so; i = row; }   // a NaN score never ranks
-    }
-    int n_items;
-    const int pos = position(s, i, ng * rpw, n_items);
-    if (i != kIdxNone && pos < a.k) {
-      a.idx[(size_t)b * a.k + pos] = i;
-      a.score[(size_t)b * a.k + pos] = s;
-      if (pos == 0) write_hit(a, b, s, i);
-    }
-    if (tid >= n_items && tid < a.k) {   // fewer rows than k ranked at all
-      a.idx[(size_t)b * a.k + tid] = -1;
-      a.score[(size_t)b * a.k + tid] = -INFINITY;
-      if (tid == 0) write_hit(a, b, -INFINITY, kIdxNone);
-    }
+    __syncthreads();
     return;
   }
-  float last_s = INFINITY;
-  int last_i = -1;
-  for (int r = 0; r < a.k; ++r) {
-    float s = -INFINITY;
-    int i = kIdxNone;
-    for (int slot = tid; slot < ng * rpw; slot += kThreads) {
-      const int gsel = sel[slot / rpw];
-      const int row = gsel * rpw + slot % rpw;
-      if (gsel < 0 || row >= a.N) continue;
-      const float so = cand[slot];
-      if (ranks_before(last_s, last_i, so, row) && ranks_before(so, row, s, i)) { s = so; i = row; }
+  const int waves = n <= kItems * 256 ? 4 : NT / kWave, stride = waves * kWave;
+  auto draw = [&](auto ipt, int m, int step, int first, auto item_of) {
+    uint64_t item[decltype(ipt)::value];
+#pragma unroll
+    for (int t = 0; t < decltype(ipt)::value; ++t) {
+      const int x = t * step + first;
+      item[t] = x < m ? item_of(x) : 0;
     }
-    block_argmax(s, i, red_s, red_i);
-    if (tid == 0) {
-      a.idx[(size_t)b * a.k + r] = i == kIdxNone ? -1 : i;
-      a.score[(size_t)b * a.k + r] = s;
-      if (r == 0) write_hit(a, b, s, i);
-    }
-    last_s = s; last_i = i;
+    return draw_best(item, k);
+  };
+  auto draw_n = [&](int m, int step, int first, auto item_of) {
+    if (m <= step) return draw(std::integral_constant<int, 1>{}, m, step, first, item_of);
+    if (m <= 2 * step) return draw(std::integral_constant<int, 2>{}, m, step, first, item_of);
+    if (m <= 4 * step) return draw(std::integral_constant<int, 4>{}, m, step, first, item_of);
+    if (m <= 8 * step) return draw(std::integral_constant<int, 8>{}, m, step, first, item_of);
+    return draw(std::integral_constant<int, kItems>{}, m, step, first, item_of);
+  };
+  if (wave < waves) {
+    const uint64_t best = draw_n(n, stride, tid, get);
+    if (lane < k) lists[wave * k + lane] = best;
   }
+  __syncthreads();
+  if (wave == 0) {
+    const uint64_t best = draw_n(waves * k, kWave, lane, [&](int x) { return lists[x]; });
+    if (lane < k) put(lane, best ? key_score((uint32_t)(best >> 32)) : -INFINITY, best ? (int)~(uint32_t)best : kIdxNone);
+  }
+  __syncthreads();   // the lists and what put() wrote
+}
+
+// Columns [c, c + P) of a row as binary32, P = 16 bytes' worth.  fp16 rows are whole pieces (E % 8
+// == 0); fp32 rows may end in part of one and need not be 16-byte aligned.
+template <typename T>
+struct RowPiece;
+template <>
+struct RowPiece<f16_t> {
+  static constexpr int P = 8;
+  float v[P];
+  __device__ __forceinline__ void load(const f16_t* row, int c, int) {
+    const f16x8 w = *reinterpret_cast<const f16x8*>(row + c);
+#pragma unroll
+    for (int t = 0; t < P; ++t) v[t] = (float)w[t];
+  }
+};
+template <>
+struct RowPiece<float> {
+  static constexpr int P = 4;
+  float v[P];
+  __device__ __forceinline__ void load(const float* row, int c, int E) {
+    typedef f32x4 f32x4_dw __attribute__((aligned(4)));
+    if (c + P <= E) {
+      const f32x4 w = *reinterpret_cast<const f32x4_dw*>(row + c);
+#pragma unroll
+      for (int t = 0; t < P; ++t) v[t] = w[t];
+    } else {
+#pragma unroll
+      for (int t = 0; t < P; ++t) v[t] = c + t < E ? row[c + t] : 0.f;
+    }
+  }
+};
+
+// k > 1: pick the k best groups, re-score their rows, pick the k best rows.  One workgroup per
+// query.  Rows are re-scored by eight threads each, reading 16-byte pieces side by side, four rows
+// in flight per thread.  100,000 x 256, 64 queries, k = 8: 70 us with 256-row groups, a row per
+// thread read two bytes at a time, and k rounds of a workgroup-wide arg-max; 18 us so, of which the
+// two selections take 6 and 4 (1,563 and 512 items) and the 512 rows 6 (260 KB through one compute
+// unit's 64 bytes per clock).  Bound by that serial chain on as many compute units as queries.
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {
+  typedef RowPiece<T> Piece;
+  constexpr int P = Piece::P, U = 4, RPT = NT / 8;   // rows in flight per thread, rows per trip and step
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint64_t* lists = reinterpret_cast<uint64_t*>(smem);        // [NT] the waves' best
+  int* sel = reinterpret_cast<int*>(lists + NT);              // [kMaxK] selected groups
+  float* qf = reinterpret_cast<float*>(sel + kMaxK);          // [E rounded up to 4]
+  const int b = blockIdx.x, tid = threadIdx.x;
+  float* cand = cand_in_lds ? qf + ((a.E + 3) & ~3) : a.cand + (size_t)b * a.k * a.rows;
+  const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
+  for (int e = tid; e < ((a.E + 3) & ~3); e += NT) qf[e] = e < a.E ? (float)q[e] : 0.f;
+
+  // 1. the min(k, G) groups with the best maxima
+  const float* part = a.part_s + (size_t)b * a.G;
+  const int ng = min(a.k, a.G);
+  select_best<NT>(
+      a.G, ng, [&](int x) { return item_key(part[x], x); }, [&](int r, float, int i) { sel[r] = i; }, lists);
+
+  // 2. the scores of their rows
+  const int n_rows = ng * a.rows, shift = __builtin_ctz(a.rows);   // group sizes are powers of two
+  const int part8 = tid & 7;
+  for (int slot0 = tid >> 3; slot0 < n_rows; slot0 += U * RPT) {
+    const T* row[U];
+    bool live[U];
+    float acc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int slot = min(slot0 + u * RPT, n_rows - 1);
+      const int g = sel[slot >> shift];
+      const int r = g == kIdxNone ? a.N : (g << shift) + (slot & (a.rows - 1));
+      live[u] = slot0 + u * RPT < n_rows && r < a.N;
+      row[u] = reinterpret_cast<const T*>(a.emb) + (size_t)(r < a.N ? r : 0) * a.E;
+      acc[u] = 0.f;
+    }
+#pragma unroll 2
+    for (int c = P * part8; c < a.E; c += 8 * P) {
+      Piece e[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) e[u].load(row[u], c, a.E);
+#pragma unroll
+      for (int t = 0; t < P; ++t) {
+        const float qv = qf[c + t];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (a.metric == 0) {
+            acc[u] = fmaf(qv, e[u].v[t], acc[u]);
+          } else {
+            const float d = qv - e[u].v[t];
+            acc[u] = fmaf(-d, d, acc[u]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      acc[u] += __shfl_xor(acc[u], 1);
+      acc[u] += __shfl_xor(acc[u], 2);
+      acc[u] += __shfl_xor(acc[u], 4);
+      if (part8 == 0 && slot0 + u * RPT < n_rows)
+        cand[slot0 + u * RPT] = live[u] ? acc[u] : __builtin_nanf("");   // never ranks
+    }
+  }
+  __syncthreads();
+
+  // 3. the k best rows among them
+  select_best<NT>(
+      n_rows, a.k,
+      [&](int x) {
+        const float s = cand[x];
+        return s == s ? item_key(s, (sel[x >> shift] << shift) + (x & (a.rows - 1))) : 0;
+      },
+      [&](int r, float s, int i) {
+        a.idx[(size_t)b * a.k + r] = i == kIdxNone ? -1 : i;
+        a.score[(size_t)b * a.k + r] = s;
+        if (r == 0) write_hit(a, b, s, i);
+      },
+      lists);
 }
 
 // ------------------------------------------------------------------- host side
@@ -772,39 +893,63 @@ enum { kModeValu = 0, kModeMfma = 1, kModeMfmaBig = 2 };
 constexpr int kBigBatch = 64;   // above this many queries the query-stationary kernel is used
 constexpr int kBigRowsMin = 50000;   // and from this many database rows on, whatever the batch
 
-static void search_plan(int32_t N, int32_t mode, int32_t k, int32_t* rows_per_wg, int32_t* G,
-                        int32_t* wg_rows = nullptr) {
-  int rpw;
-  int scan = 0;   // rows per phase-1 workgroup when that is not the group
+// What the workspace is sized for: 8 bytes per (query, group), and for k > 1 the rows of k groups.
+static void search_plan(int32_t N, int32_t mode, int32_t k, int32_t* rows_per_group, int32_t* G) {
+  int rpg;
   if (mode == kModeMfma && k > 1 && N <= 32 * 1024) {
-    // top-k: the second phase re-scores k whole groups per query on the vector ALUs, so the
-    // groups are as small as the first phase can make them: the 32 rows of one wave.  Beyond
-    // about a thousand groups the k selection rounds over the group maxima cost more than the
-    // smaller groups save (140,000 rows, k = 4: 36 against 28 us).
-    rpw = 32;
-    scan = 128;
+    rpg = 32;   // the rows of one wave
   } else if (mode == kModeMfma) {
     // 128 rows per pass of a workgroup; more passes per workgroup for large databases so that
     // the query tile staged in LDS is amortised, while keeping >= ~1000 workgroups
     long c = ((long)N + 128L * 1024 - 1) / (128L * 1024);
     if (c < 1) c = 1;
     if (c > 8) c = 8;
-    rpw = 128 * (int)c;
+    rpg = 128 * (int)c;
   } else if (mode == kModeMfmaBig) {
     // chunks of 64 rows.  Loading the queries into registers and filling the copy pipeline
     // costs a workgroup as much as five chunks (measured), so a workgroup takes as many chunks
-    // as leave about 480 workgroups: just under two per compute unit, all resident at once.  With k > 1
-    // the second phase re-scores k whole groups per query, which caps the group size.
+    // as leave about 480 workgroups: just under two per compute unit, all resident at once.
+    // (k > 1: at most 16, so that the workspace for the rows of k groups stays small.)
     long c = ((long)N + 64L * 480 - 1) / (64L * 480);
     if (c < 1) c = 1;
     if (c > (k > 1 ? 16 : 64)) c = k > 1 ? 16 : 64;
-    rpw = kBigRows * (int)c;
+    rpg = kBigRows * (int)c;
   } else {
-    rpw = kValuRowsPerWg;
+    rpg = kValuRowsPerWg;
   }
-  *rows_per_wg = rpw;
-  *G = (N + rpw - 1) / rpw;
-  if (wg_rows) *wg_rows = scan ? scan : rpw;
+  *rows_per_group = rpg;
+  *G = (N + rpg - 1) / rpg;
+}
+
+// Groups of a top-k search.  k = 1 keeps one group per workgroup (search_plan).  For k > 1 the second phase
+// re-scores k whole groups per query, so the groups are the smallest that one phase-1 step can hand
+// out (the 32 rows of a wave, a chunk of 64, 64 lanes) or a power of two of it, as long as their
+// maxima and the rows of k of them fit the space that search_plan stands for, which per query is
+// 8 G + 4 k rows bytes (a position needs no row number: 4 instead of 8 bytes).  The largest power of two
+// within search_plan's own group always fits.  A workgroup scans whole groups.
+// 100,000 x 256, 64 queries, k = 8: 2,048 rows to re-score per query become 512.
+static void topk_plan(int32_t N, int32_t mode, int32_t k, int32_t* rows, int32_t* G, int32_t* wg_rows) {
+  int32_t rpg, g0;
+  search_plan(N, mode, k, &rpg, &g0);
+  const size_t space = (size_t)8 * g0 + (size_t)4 * k * rpg;
+  auto fits = [&](int32_t r) {
+    return (size_t)4 * ((N + r - 1) / r) + (size_t)4 * k * r <= space;
+  };
+  int32_t r = mode == kModeMfma ? 32 : kBigRows, scan = rpg;
+  if (mode == kModeMfma) {
+    if (!fits(r)) {   // otherwise whole passes of 128 rows
+      r = 128;
+      while (2 * r <= rpg && !fits(r)) r *= 2;
+    }
+    if (scan < 128) scan = 128;
+  } else if (mode == kModeMfmaBig) {
+    while (2 * r <= rpg && !fits(r)) r *= 2;
+  } else {
+    if (!fits(r)) r = rpg;   // 64 lanes or all 256 rows
+  }
+  *rows = r;
+  *G = (N + r - 1) / r;
+  *wg_rows = r > scan ? r : (scan + r - 1) / r * r;
 }
 
 static bool use_mfma(int32_t is_f16, int32_t metric, int32_t E) {
@@ -835,27 +980,56 @@ size_t search_workspace_bytes(int32_t N, int32_t E, int32_t B, int32_t k, int32_
 
 template <int KSMAX, int QPW>
 static hipError_t launch_f16_big(const SearchArgs& a, dim3 grid, hipStream_t stream) {
-  hipLaunchKernelGGL((search_f16_big_kernel<KSMAX, QPW>), grid, dim3(kThreads), 0, stream, a);
+  if (a.k > 1)
+    hipLaunchKernelGGL((search_f16_big_kernel<KSMAX, QPW, true>), grid, dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((search_f16_big_kernel<KSMAX, QPW, false>), grid, dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
+template <int KSMAX, int NQB, bool TOPK>
+static hipError_t launch_f16_one(const SearchArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
+  hipError_t e = ensure_lds<&search_f16_kernel<KSMAX, NQB, TOPK>>(lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((search_f16_kernel<KSMAX, NQB, TOPK>), grid, dim3(kThreads), lds, stream, a);
   return hipGetLastError();
 }
 
 template <int KSMAX, int NQB>
-static hipError_t launch_f16_one(const SearchArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
-  hipError_t e = ensure_lds<&search_f16_kernel<KSMAX, NQB>>(lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((search_f16_kernel<KSMAX, NQB>), grid, dim3(kThreads), lds, stream, a);
-  return hipGetLastError();
+static hipError_t launch_f16_k(const SearchArgs& a, dim3 grid, size_t lds, hipStream_t stream) {
+  return a.k > 1 ? launch_f16_one<KSMAX, NQB, true>(a, grid, lds, stream)
+                 : launch_f16_one<KSMAX, NQB, false>(a, grid, lds, stream);
 }
 
 template <int KSMAX>
 static hipError_t launch_f16_phase1(const SearchArgs& a, int nqb, dim3 grid, size_t lds,
                                     hipStream_t stream) {
   switch (nqb) {
-    case 1: return launch_f16_one<KSMAX, 1>(a, grid, lds, stream);
-    case 2: return launch_f16_one<KSMAX, 2>(a, grid, lds, stream);
-    case 4: return launch_f16_one<KSMAX, 4>(a, grid, lds, stream);
-    default: return launch_f16_one<KSMAX, 8>(a, grid, lds, stream);
+    case 1: return launch_f16_k<KSMAX, 1>(a, grid, lds, stream);
+    case 2: return launch_f16_k<KSMAX, 2>(a, grid, lds, stream);
+    case 4: return launch_f16_k<KSMAX, 4>(a, grid, lds, stream);
+    default: return launch_f16_k<KSMAX, 8>(a, grid, lds, stream);
   }
+}
+
+// A query's second phase is one workgroup.  1,024 threads shorten it when there are many groups to
+// pick from or many rows to re-score; below that the barriers of sixteen waves cost more.
+template <typename T, int NT>
+static hipError_t launch_topk_n(const SearchArgs& a, hipStream_t stream) {
+  const size_t lists = (size_t)NT * 8 + kMaxK * 4, query = (size_t)((a.E + 3) & ~3) * 4;
+  const size_t cand = (size_t)a.k * a.rows * 4;
+  const int in_lds = lists + query + cand <= 64 * 1024;   // the rows' scores: in LDS, else in the workspace
+  const size_t lds = lists + query + (in_lds ? cand : 0);
+  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT>>(lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((finalize_topk_kernel<T, NT>), dim3((unsigned)a.B), dim3(NT), lds, stream, a, in_lds);
+  return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
+  return a.G > 1024 || a.k * a.rows > 256 ? launch_topk_n<T, 1024>(a, stream)
+                                          : launch_topk_n<T, 256>(a, stream);
 }
 
 static size_t f16_lds_bytes(int nqb, int E) {
@@ -871,11 +1045,16 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   a.idx = p.idx; a.score = p.score; a.hit = p.hit;
   const int mode = search_mode(p.is_f16, p.metric, p.E, p.B, p.N);
   const bool mfma = mode == kModeMfma;
-  search_plan(p.N, mode, p.k, &a.rows_per_wg, &a.G, &a.wg_rows);
+  if (p.k > 1) {
+    topk_plan(p.N, mode, p.k, &a.rows, &a.G, &a.wg_rows);
+  } else {
+    search_plan(p.N, mode, p.k, &a.rows, &a.G);
+    a.wg_rows = a.rows;
+  }
   unsigned char* ws = reinterpret_cast<unsigned char*>(p.ws);
-  size_t part_bytes = ((size_t)p.B * a.G * 8 + 255) / 256 * 256;
+  const size_t part_bytes = ((size_t)p.B * a.G * (p.k > 1 ? 4 : 8) + 255) / 256 * 256;
   a.part_s = reinterpret_cast<float*>(ws);
-  a.part_i = reinterpret_cast<int32_t*>(ws + (size_t)p.B * a.G * 4);
+  a.part_i = p.k > 1 ? nullptr : reinterpret_cast<int32_t*>(ws + (size_t)p.B * a.G * 4);
   a.cand = reinterpret_cast<float*>(ws + part_bytes);
   a.q0 = 0; a.nq = p.B;
 
@@ -884,7 +1063,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
     // only while the query operands fit in the register file (E <= 256)
     const int ksmax = p.E <= 128 ? 8 : (p.E <= 256 ? 16 : 32);
     const int qpw_max = p.E <= 256 ? 2 : 1;
-    const dim3 grid((unsigned)a.G);
+    const dim3 grid((unsigned)((p.N + a.wg_rows - 1) / a.wg_rows));
     for (int q0 = 0; q0 < p.B; q0 += 128 * qpw_max) {
       a.q0 = q0;
       a.nq = p.B - q0 < 128 * qpw_max ? p.B - q0 : 128 * qpw_max;
@@ -914,8 +1093,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
       if (e != hipSuccess) return e;
     }
   } else {
-    hipError_t e = p.is_f16 ? (p.metric ? launch_valu<f16_t, true>(a, stream) : launch_valu<f16_t, false>(a, stream))
-                            : (p.metric ? launch_valu<float, true>(a, stream) : launch_valu<float, false>(a, stream));
+    const hipError_t e = p.is_f16 ? launch_valu<f16_t>(a, stream) : launch_valu<float>(a, stream);
     if (e != hipSuccess) return e;
   }
 
@@ -924,9 +1102,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   } else if (p.k == 1) {
     hipLaunchKernelGGL(finalize_top1_kernel, dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
   } else {
-    const size_t lds = (size_t)p.E * 4 + (size_t)p.k * 4;
-    if (p.is_f16) hipLaunchKernelGGL((finalize_topk_kernel<f16_t>), dim3((unsigned)p.B), dim3(kThreads), lds, stream, a);
-    else hipLaunchKernelGGL((finalize_topk_kernel<float>), dim3((unsigned)p.B), dim3(kThreads), lds, stream, a);
+    return p.is_f16 ? launch_topk<f16_t>(a, stream) : launch_topk<float>(a, stream);
   }
   return hipGetLastError();
 }

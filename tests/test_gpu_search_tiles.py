@@ -24,7 +24,10 @@ VALU_CASES = [
 @pytest.mark.parametrize("case", VALU_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
     *c[:4], str(c[4]).split(".")[-1], c[5]))
 def test_vector_alu_search_matches_the_oracle(ac, oracle_mod, case):  # noqa: F811
-    N, E, B, k, dt, metric = case
+    _check(ac, oracle_mod, *case)
+
+
+def _check(ac, oracle_mod, N, E, B, k, dt, metric):  # noqa: F811
     g = _gen(60 + N + E)
     emb = torch.randn(N, E, generator=g)
     emb = (emb / emb.norm(dim=1, keepdim=True)).to(dt)
@@ -34,3 +37,40 @@ def test_vector_alu_search_matches_the_oracle(ac, oracle_mod, case):  # noqa: F8
     m = ac.AC_IP if metric == "ip" else ac.AC_L2
     idx, score, hit = _run_search(ac, emb, q, k, 0.8, m)
     parity.check_search(oracle_mod, q, emb, k, 0.8, m, None, idx, score, hit)
+
+
+TOPK_CASES = [
+    # N, E, B, k, dtype, metric: the group sizes and list lengths of the second phase
+    (31, 64, 3, 31, torch.float16, "ip"),         # k = N, one group
+    (40000, 96, 10, 16, torch.float16, "ip"),     # 32-row groups, two workgroup passes' worth of them
+    (40000, 96, 10, 2, torch.float16, "ip"),      # one group per pass of 128 rows
+    (140001, 64, 40, 2, torch.float16, "ip"),     # one group per two passes, ragged end
+    (140001, 64, 5, 9, torch.float16, "ip"),      # one group per pass, two passes per workgroup
+    (150000, 128, 3, 2, torch.float16, "ip"),     # groups of several chunks, five-chunk workgroups
+    (150000, 128, 130, 8, torch.float16, "ip"),   # one chunk per group, two query blocks per wave
+    (66000, 512, 9, 64, torch.float16, "ip"),     # the longest lists, 4,096 rows to re-score
+    (30001, 20, 3, 2, torch.float32, "l2"),   # 64-row groups
+    (60001, 20, 3, 2, torch.float32, "l2"),       # 256-row groups
+    (1100000, 8, 2, 64, torch.float16, "ip"),     # more groups than registers hold
+]
+
+
+@pytest.mark.parametrize("case", TOPK_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
+    *c[:4], str(c[4]).split(".")[-1], c[5]))
+def test_topk_search_matches_the_oracle(ac, oracle_mod, case):  # noqa: F811
+    _check(ac, oracle_mod, *case)
+
+
+@pytest.mark.parametrize("case", [(5000, 64, 5, 40, torch.float16), (70000, 128, 4, 64, torch.float16),
+                                  (3000, 24, 3, 17, torch.float32)],
+                         ids=lambda c: "N%d-E%d-B%d-k%d-%s" % (*c[:4], str(c[4]).split(".")[-1]))
+def test_topk_of_equal_rows_names_the_lowest(ac, oracle_mod, case):  # noqa: F811
+    # small whole numbers: every score is exact, so ties are ties on both sides
+    N, E, B, k, dt = case
+    g = _gen(5)
+    kinds = torch.randint(-2, 3, (23, E), generator=g).to(dt)
+    emb = kinds[torch.randint(0, 23, (N,), generator=g)]
+    q = torch.randint(-2, 3, (B, E), generator=g).to(dt)
+    idx, score, _ = _run_search(ac, emb, q, k, 0.5, ac.AC_IP)
+    want, want_score, _ = oracle_mod.search(parity.to_np(q), parity.to_np(emb), k=k)
+    assert (idx.cpu().numpy() == want).all() and (score.cpu().numpy() == want_score).all()
