@@ -2,8 +2,8 @@
 // for inputs that are to be remembered.  For every selected item the kernel computes
 // O = softmax(scale * Q K^T) V like attention_exact, and ALSO writes the normalised map
 // A = softmax(scale * Q K^T) of every (layer, head), rounded once to bf16, into the item's slot
-// of the map store, in the store's layout; a second small kernel copies the item's feature
-// vector into the same slot of the feature store.  A later search that hits the slot makes
+// of the map store, in the store's layout, and copies the item's feature vector into the same
+// slot of the feature store.  A later search that hits the slot makes
 // attncache_apply reproduce this O from the stored map.
 //
 // The map has to be normalised before it is written, so the row statistics must be known before
@@ -30,9 +30,11 @@ struct InsertArgs {
   const void *Q, *K, *V;
   void *O, *maps;
   const int32_t *slot, *row_sel, *key_len;
+  const u32x4* feat;      // [B][feat_pieces] or nullptr
+  u32x4* emb;             // the feature store, rows of feat_pieces
+  int32_t feat_pieces;    // 16-byte pieces of a feature vector
   int32_t B, M, L, layer_begin, Lc, Hq, Hkv, S;
-  int32_t n_rblk, n_tiles;
-  int32_t heads_per_wg;   // query heads one workgroup walks (they share K and V)
+  int32_t n_tiles;   // KV groups: (item, layer, KV head)
   float scale_log2e;
 };
 
@@ -44,8 +46,16 @@ struct InsertArgs {
 //   RESIDENT (S <= 128): both chunks sit in the two stages for the whole tile and the workgroup
 //   walks all g query heads of the group -- K and V come from HBM once per group, and after the
 //   one barrier behind the copy the four waves never meet again.
-//   Streaming (S > 128): one head per workgroup; the copy of chunk c + 1 is in flight while chunk
-//   c is multiplied, one barrier per chunk; the statistics pass needs no V and copies none.
+//   Streaming (S > 128): the row blocks of all g heads of the group are units of 32 rows of one
+//   head, numbered row block first, head second, and a workgroup takes four consecutive ones, one
+//   per wave (g = 4: the same rows of all four heads).  Its waves see (nearly) the same keys, K and V
+//   are copied once for all of them, and only the lightest workgroup can have idle waves.
+//   The copy of chunk c + 1 is in flight while chunk c is multiplied, one barrier per chunk;
+//   the statistics pass needs no V and copies none.
+// Chunks and blocks beyond the sentence's length are not multiplied: their weights are zeros.
+// 16 items x 4 layers x 32 heads on 8 K and V, 288 x 128, causal, padded: 205 us per call with 128
+// rows of one head per workgroup and all keys multiplied, 134 us so,
+// without an extra launch for the feature vectors (520 MB, 101 us at the copy rate).
 constexpr int kIChunk = 64;   // keys per staged chunk
 
 template <int D, bool CAUSAL, bool PACKED, bool RESIDENT>
@@ -63,17 +73,16 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   const int il = lane & 31, kh = lane >> 5;
   const int S = a.S, g = a.Hq / a.Hkv;
 
-  // same id scheme as above: all row blocks of a head, and all heads that share K and V, get
-  // ids equal mod 8 (one XCD, one L2).  RESIDENT (S <= 128): both chunks of K and V sit in the
-  // two stages for the whole tile and the workgroup walks all heads_per_wg = g query heads
-  // that share them; between the one barrier after the copy and the end of the tile the four
-  // waves never meet again.
+  // all workgroups of a KV group get ids equal mod 8 (one XCD, one L2), heaviest first.
+  // RESIDENT (S <= 128): both chunks of K and V sit in the two stages for the whole tile and the
+  // workgroup walks all g query heads that share them; between the one barrier after the copy
+  // and the end of the tile the four waves never meet again.
   const int bid = blockIdx.x;
-  const int hslots = g / a.heads_per_wg;
+  const int n_units = RESIDENT ? 4 : g * (S >> 5), per_tile = (n_units + 3) >> 2;
   const int slot_id = bid >> 3;
-  const int grp = (slot_id / (hslots * a.n_rblk)) * 8 + (bid & 7);   // (item, layer, KV head)
-  const int hslot = (slot_id / a.n_rblk) % hslots;
-  const int R = a.n_rblk - 1 - slot_id % a.n_rblk;
+  const int grp = slot_id / per_tile * 8 + (bid & 7);   // (item, layer, KV head)
+  const int top = n_units - 1 - 4 * (slot_id % per_tile);
+  const int unit = RESIDENT ? wave : top - wave;
   if (grp >= a.n_tiles) return;
   const int kvh = grp % a.Hkv;
   const int l = (grp / a.Hkv) % a.Lc;
@@ -82,14 +91,20 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   const int len = a.key_len ? min(max(a.key_len[b], 1), S) : S;
   const int entry = a.slot ? a.slot[b] : -1;
   const bool keep = entry >= 0 && entry < a.M;   // anything else: compute O only
+  // the item's first workgroup also copies its feature vector into the same slot
+  if (a.feat && keep && l == 0 && kvh == 0 && slot_id % per_tile == 0)
+    for (int p = tid; p < a.feat_pieces; p += kThreads)
+      a.emb[(size_t)entry * a.feat_pieces + p] = a.feat[(size_t)b * a.feat_pieces + p];
 
   const size_t kv = (((size_t)b * a.Lc + l) * a.Hkv + kvh) * (size_t)S * D;
   const bf16_t* Ksrc = reinterpret_cast<const bf16_t*>(a.K) + kv;
   const bf16_t* Vsrc = reinterpret_cast<const bf16_t*>(a.V) + kv;
-  const int n_all = (S + kIChunk - 1) / kIChunk;
-  const int n_chunk = CAUSAL ? min(2 * (R + 1), n_all) : n_all;   // the same for all four waves
-  const int r0 = R * kChunk + 32 * wave;
-  const bool active = r0 < S;
+  // chunks the workgroup walks (the same for all four waves): up to its last diagonal, and only
+  // those that hold a visible key
+  const int last = RESIDENT || !CAUSAL ? S : 32 * (top / g + 1);
+  const int n_chunk = (min(last, len) + kIChunk - 1) / kIChunk;
+  const int r0 = RESIDENT ? 32 * unit : 32 * (max(unit, 0) / g);
+  const bool active = RESIDENT ? r0 < S : unit >= 0;
   const int n32 = S >> 5;
   const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
   bf16_t* At = nullptr;   // the current head's map in the store
@@ -155,13 +170,11 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   };
 
   u32x4 q[D / 16];
-  // 32-key blocks of chunk c this wave's rows see
+  // 32-key blocks of a row of this wave's maps, and those of chunk c that hold a visible key
+  const int row_blocks = CAUSAL ? (r0 >> 5) + 1 : n32;
   auto blocks = [&](int c) {
     if (!active) return 0;
-    const int j0 = c * kIChunk;
-    int nblk = min(kIChunk, S - j0) >> 5;
-    if (CAUSAL) nblk = min(nblk, (r0 - j0) / 32 + 1);
-    return max(nblk, 0);
+    return max(min(min(2, row_blocks - 2 * c), (len - c * kIChunk + 31) >> 5), 0);
   };
   // scores^T of key block jb of the staged chunk c (keys beyond the diagonal or in the padding
   // hidden; the first block of a row always has a visible key, so the running maximum is
@@ -263,9 +276,9 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
     if (n_chunk > 1) prefetch(kb1, vb1, 1, true);
     publish();
   }
-  const int n_heads = RESIDENT ? a.heads_per_wg : 1;   // streaming: one head per workgroup
+  const int n_heads = RESIDENT ? g : 1;   // streaming: one unit per wave
   for (int hl = 0; hl < n_heads; ++hl) {
-    const int h = kvh * g + hslot * a.heads_per_wg + hl;
+    const int h = kvh * g + (RESIDENT ? hl : max(unit, 0) % g);
     const size_t qo = (((size_t)b * a.Lc + l) * a.Hq + h) * (size_t)S * D;
     At = reinterpret_cast<bf16_t*>(a.maps) +
          (((size_t)(keep ? entry : 0) * a.L + (a.layer_begin + l)) * a.Hq + h) * tile_elems;
@@ -294,10 +307,11 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
     }
 
     if (active) {
-      // A dense causal map carries its zeros: the 32-column blocks right of the diagonal block
+      // Zeros: blocks in the padding, and in a dense causal map those right of the diagonal block
       // (the packed layout does not store them)
-      if (CAUSAL && !PACKED && keep) {
-        for (int kb = (r0 >> 5) + 1; kb < n32; ++kb)
+      if (keep) {
+        const int end = PACKED ? row_blocks : n32;
+        for (int kb = min(row_blocks, (len + 31) >> 5); kb < end; ++kb)
 #pragma unroll
           for (int q4 = 0; q4 < 4; ++q4) *map_piece(kb, q4) = u32x2{0u, 0u};
       }
@@ -308,23 +322,9 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   }
 }
 
-// feature vector of item b into row slot[b] of the feature store (16-byte pieces)
-__global__ __launch_bounds__(kThreads) void insert_features_kernel(const u32x4* __restrict__ feat,
-                                                                   u32x4* __restrict__ emb,
-                                                                   const int32_t* __restrict__ slot,
-                                                                   const int32_t* __restrict__ row_sel,
-                                                                   int32_t M, int32_t pieces) {
-  const int b = blockIdx.x;
-  if (row_sel && row_sel[b] >= 0) return;
-  const int entry = slot[b];
-  if (entry < 0 || entry >= M) return;
-  for (int p = threadIdx.x; p < pieces; p += kThreads)
-    emb[(size_t)entry * pieces + p] = feat[(size_t)b * pieces + p];
-}
-
 template <int D, bool CAUSAL, bool PACKED>
 static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t stream) {
-  if (a.n_rblk == 1)
+  if (a.S <= kChunk)
     hipLaunchKernelGGL((insert_bf16_kernel<D, CAUSAL, PACKED, true>), grid, dim3(kThreads), 0, stream, a);
   else
     hipLaunchKernelGGL((insert_bf16_kernel<D, CAUSAL, PACKED, false>), grid, dim3(kThreads), 0, stream, a);
@@ -343,26 +343,19 @@ static hipError_t launch_insert_d(const InsertArgs& a, dim3 grid, bool causal, b
 // Host launcher.  Shapes were validated by the caller (api.hip).
 hipError_t launch_insert(const InsertLaunch& p, hipStream_t stream) {
   if (p.B == 0 || p.Lc == 0) return hipSuccess;
-  if (p.feat) {
-    hipLaunchKernelGGL(insert_features_kernel, dim3((unsigned)p.B), dim3(kThreads), 0, stream,
-                       reinterpret_cast<const u32x4*>(p.feat), reinterpret_cast<u32x4*>(p.emb),
-                       p.slot, p.row_sel, p.M, p.emb_row_bytes / 16);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   InsertArgs a;
   a.Q = p.Q; a.K = p.K; a.V = p.V; a.O = p.O; a.maps = p.maps;
+  a.feat = reinterpret_cast<const u32x4*>(p.feat); a.emb = reinterpret_cast<u32x4*>(p.emb);
+  a.feat_pieces = p.emb_row_bytes / 16;
   a.slot = p.slot; a.row_sel = p.row_sel; a.key_len = p.key_len;
   a.B = p.B; a.M = p.M; a.L = p.L; a.layer_begin = p.layer_begin; a.Lc = p.Lc;
   a.Hq = p.Hq; a.Hkv = p.Hkv; a.S = p.S;
-  a.n_rblk = (p.S + kChunk - 1) / kChunk;
-  a.n_tiles = p.B * p.Lc * p.Hkv;   // KV groups: (item, layer, KV head)
+  a.n_tiles = p.B * p.Lc * p.Hkv;
   const float scale = p.scale == 0.f ? 1.0f / sqrtf((float)p.D) : p.scale;
   a.scale_log2e = scale * 1.44269504088896340736f;
-  const int g = p.Hq / p.Hkv;
-  a.heads_per_wg = a.n_rblk == 1 ? g : 1;
+  const int units = p.S <= kChunk ? 4 : p.Hq / p.Hkv * (p.S / 32);
   const int groups8 = (a.n_tiles + 7) / 8 * 8;   // padded to a multiple of 8
-  const dim3 grid((unsigned)((size_t)groups8 * (g / a.heads_per_wg) * a.n_rblk));
+  const dim3 grid((unsigned)((size_t)groups8 * ((units + 3) / 4)));
   return p.D == 64 ? launch_insert_d<64>(a, grid, p.causal, p.packed, stream)
                    : launch_insert_d<128>(a, grid, p.causal, p.packed, stream);
 }
