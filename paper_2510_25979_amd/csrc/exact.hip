@@ -5,8 +5,8 @@
 //   * resident (S <= 128): one workgroup = one (batch item, KV head); both 64-key chunks of K
 //     and V are copied into LDS once and the workgroup walks all g query heads that share
 //     them; after the one barrier behind the copy its four waves never meet again;
-//   * streaming (S > 128): one workgroup = one (batch item, query head, block of 128 query
-//     rows) that streams 64-key chunks of K and V through two LDS stages.
+//   * streaming (S > 128): one workgroup = four units of 32 query rows of the heads that share K
+//     and V, which streams 64-key chunks of them through two LDS stages.
 // A wave owns 32 query rows and walks the key blocks up to its diagonal.
 // Both products are formed transposed:
 //   S^T = K Q^T   -> a lane holds 16 keys of ONE query column, so the row
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
   // never meet again.  Longer sequences stream chunks through the stages, one head per tile.
 
   // per tile (the helpers below read these by reference)
-  int u = 0, h = 0, R = 0, b = 0, r0 = 0, n_chunk = 0;
+  int u = 0, h = 0, b = 0, r0 = 0, n_chunk = 0;
   int Sk = S;   // keys this tile's queries may see at all: the sentence's length in a padded batch
   bool active = false;
   const bf16_t* Ksrc = nullptr;
@@ -443,14 +443,19 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
       t = tn;
     }
   } else {
-    // one tile per workgroup: (K/V tile u, head, row block R), heaviest row blocks first
+    // Units of 32 query rows of one head, numbered row block first, head second; a workgroup
+    // takes four consecutive ones of a K/V tile, heaviest first, one per wave (g = 4: the same rows of
+    // all four heads).  Its waves see (nearly) the same keys, a chunk is copied once for all of
+    // them, and only the lightest workgroup of a tile can have idle waves.  128 rows of one head
+    // per workgroup before: 64 x 32 heads on 8 K and V, 288 x 128, causal 141 -> 105 us; 16 x 32 on 8,
+    // 1024 x 128 214 -> 195 us; one head per K and V and whole blocks of 128 rows are as they were.
     const int bid = blockIdx.x;
     const int slot = bid >> 3;
-    const int per_u = g * a.n_rblk;
+    const int n_units = g * (S >> 5), per_u = (n_units + 3) >> 2;
     u = (slot / per_u) * 8 + (bid & 7);   // ids equal mod 8 (one XCD) share K, V in its L2
     if (u >= a.n_kvtiles) return;
-    h = (u % a.Hkv) * g + (slot % per_u) / a.n_rblk;
-    R = a.n_rblk - 1 - (slot % per_u) % a.n_rblk;
+    const int top = n_units - 1 - 4 * (slot % per_u), unit = top - wave;
+    h = (u % a.Hkv) * g + max(unit, 0) % g;
     b = u / a.Hkv;
     if (a.row_sel && a.row_sel[b] >= 0) return;
     Ksrc = reinterpret_cast<const bf16_t*>(a.K) + (size_t)u * S * D;
@@ -458,17 +463,17 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
     kptr = Ksrc + crow * D + 8 * kpiece;
     vptr = Vsrc + crow * D + 8 * vpiece;
     Sk = a.key_len ? min(max(a.key_len[b], 1), S) : S;
-    const int last_key = CAUSAL ? min(Sk, kChunk * (R + 1)) : Sk;
+    const int last_key = CAUSAL ? min(Sk, 32 * (top / g + 1)) : Sk;
     n_chunk = (last_key + kLChunk - 1) / kLChunk;
-    r0 = R * kChunk + 32 * wave;
-    active = r0 < S;
+    r0 = 32 * (max(unit, 0) / g);
+    active = unit >= 0;
     begin_head();
     // Chunks below c_split are complete and fully visible to every wave of the workgroup
-    // (they lie left of the diagonal blocks of all 128 rows, and before a ragged end): the
+    // (they lie left of the diagonal blocks of all its rows, and before a ragged end): the
     // main loop runs only the test-free variant, two chunks per trip so that stages
     // alternate without pointer arithmetic.  The few chunks from c_split on go through the
     // masked variant.
-    const int c_split = CAUSAL ? min(2 * R, Sk / kLChunk) : Sk / kLChunk;
+    const int c_split = CAUSAL ? min(32 * (max(top - 3, 0) / g) / kLChunk, Sk / kLChunk) : Sk / kLChunk;
     prefetch(kb0, vb0, 0);
     int c = 0;
     for (; c + 1 < c_split; c += 2) {
@@ -698,9 +703,10 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
     return launch_exact_f32<4>(a, p.D, p.causal, scale, stream);
   }
   const int g = p.Hq / p.Hkv;
-  a.heads_per_wg = a.n_rblk == 1 ? g : 1;
+  a.heads_per_wg = g;
   const int u8 = (a.n_kvtiles + 7) / 8 * 8;
-  const dim3 grid((unsigned)((size_t)u8 * (g / a.heads_per_wg) * a.n_rblk));
+  const int per_u = a.n_rblk == 1 ? 1 : (g * (p.S / 32) + 3) / 4;   // workgroups of a K/V tile
+  const dim3 grid((unsigned)((size_t)u8 * per_u));
   if (p.D == 64)
     return p.causal ? launch_exact_bf16<64, true>(a, grid, stream)
                     : launch_exact_bf16<64, false>(a, grid, stream);
