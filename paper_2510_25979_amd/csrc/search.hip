@@ -89,10 +89,14 @@ __device__ __forceinline__ float key_score(uint32_t k) {
 }
 
 // ---------------------------------------------------------------- phase 1, matrix cores
+// KSMAX > 0: a wave keeps its 32 rows whole in registers (E <= 16 KSMAX, E % 16 == 0) and multiplies
+// them with one query block after the other.  KSMAX = 0, any E % 8 == 0 whose queries fit in LDS:
+// the rows pass through registers 64 columns at a time, every piece feeding all NQB query blocks
+// (20,000 x 768, 64 queries: 103 us per call on the vector ALUs, 28 us so).
 template <int KSMAX, int NQB, bool TOPK>
 __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int E = a.E, QS = E + kQPad;
+  const int E = a.E, QS = ((E + 15) & ~15) + kQPad;
   f16_t* qs = reinterpret_cast<f16_t*>(smem);                                 // [32 NQB][QS]
   float* red_s = reinterpret_cast<float*>(smem + (size_t)32 * NQB * QS * 2);  // [4][32 NQB]
   int* red_i = reinterpret_cast<int*>(red_s + 4 * 32 * NQB);
@@ -100,17 +104,18 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: keep it scalar
   const int il = lane & 31, kh = lane >> 5;
-  const int nks = E >> 4;
+  const int nks = (E + 15) >> 4;
+  const int q0 = a.q0 + 32 * NQB * blockIdx.y, nq = min(a.q0 + a.nq - q0, 32 * NQB);   // this workgroup's queries
 
-  // stage the query super-block, zero rows beyond nq
+  // stage the query super-block, zeros beyond nq and beyond an odd last half step
   {
     const int EQ = E >> 3;
     const u32x4* src = reinterpret_cast<const u32x4*>(reinterpret_cast<const f16_t*>(a.q) +
-                                                      (size_t)a.q0 * E);
-    for (int p = tid; p < 32 * NQB * EQ; p += kThreads) {
-      const int r = p / EQ, c = p % EQ;
+                                                      (size_t)q0 * E);
+    for (int p = tid; p < 32 * NQB * 2 * nks; p += kThreads) {
+      const int r = p / (2 * nks), c = p % (2 * nks);
       u32x4 w = {0u, 0u, 0u, 0u};
-      if (r < a.nq) w = src[(size_t)r * EQ + c];
+      if (r < nq && c < EQ) w = src[(size_t)r * EQ + c];
       *reinterpret_cast<u32x4*>(qs + r * QS + 8 * c) = w;
     }
   }
@@ -130,21 +135,9 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
     // end are clamped for the load and masked below
     const int rowc = min(rb + il, a.N - 1);
     const f16_t* erow = emb + (size_t)rowc * E + 8 * kh;
-    f16x8 e[KSMAX];
-#pragma unroll
-    for (int ks = 0; ks < KSMAX; ++ks)
-      if (ks < nks) e[ks] = *reinterpret_cast<const f16x8*>(erow + 16 * ks);
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-      f32x16 acc;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-      const f16_t* qrow = qs + (32 * qb + il) * QS + 8 * kh;
-#pragma unroll
-      for (int ks = 0; ks < KSMAX; ++ks)
-        if (ks < nks) acc = mfma_f16(e[ks], *reinterpret_cast<const f16x8*>(qrow + 16 * ks), acc);
-      // acc[v] = <emb[rb + mfma_row(v)], q[32 qb + il]>; rows ascend with v, so a strict
-      // comparison keeps the lowest row among equal scores
+    // acc[v] = <emb[rb + mfma_row(v)], q[32 qb + il]>; rows ascend with v, so a strict
+    // comparison keeps the lowest row among equal scores
+    auto rank = [&](int qb, const f32x16& acc) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int r = rb + mfma_row(v, kh);
@@ -156,6 +149,58 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
           best_i[qb] = r;
         }
       }
+    };
+    if constexpr (KSMAX > 0) {
+      f16x8 e[KSMAX];
+#pragma unroll
+      for (int ks = 0; ks < KSMAX; ++ks)
+        if (ks < nks) e[ks] = *reinterpret_cast<const f16x8*>(erow + 16 * ks);
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) {
+        f32x16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        const f16_t* qrow = qs + (32 * qb + il) * QS + 8 * kh;
+#pragma unroll
+        for (int ks = 0; ks < KSMAX; ++ks)
+          if (ks < nks) acc = mfma_f16(e[ks], *reinterpret_cast<const f16x8*>(qrow + 16 * ks), acc);
+        rank(qb, acc);
+      }
+    } else {
+      f32x16 acc[NQB];
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[qb][v] = 0.f;
+      struct Four { f16x8 e[4]; };
+      auto fetch = [&](int ks0) {   // steps past the end repeat a piece of the row, their products are skipped
+        Four f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int c = 16 * (ks0 + t);
+          f.e[t] = *reinterpret_cast<const f16x8*>(erow + (c + 8 * kh < E ? c : 0) - (8 * kh < E ? 0 : 8 * kh));
+          if (c + 8 * kh >= E) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) f.e[t][x] = (f16_t)0.f;
+          }
+        }
+        return f;
+      };
+      Four now = fetch(0);
+      for (int ks0 = 0; ks0 < nks; ks0 += 4) {
+        const Four next = fetch(ks0 + 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          if (ks0 + t < nks) {
+#pragma unroll
+            for (int qb = 0; qb < NQB; ++qb)
+              acc[qb] = mfma_f16(now.e[t], *reinterpret_cast<const f16x8*>(qs + (32 * qb + il) * QS + 8 * kh + 16 * (ks0 + t)),
+                                 acc[qb]);
+          }
+        now = next;
+      }
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) rank(qb, acc[qb]);
     }
     if (TOPK) {   // group maxima leave as soon as a group is complete
       const bool per_wave = a.rows == 32;   // a wave's 32 rows are a group: nothing to merge
@@ -168,14 +213,14 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
         const int t = 32 * qb + il;
         if (!per_wave) {
           if (kh == 0) red_s[wave * 32 * NQB + t] = s;
-        } else if (kh == 0 && t < a.nq && rb < a.N) {
-          a.part_s[(size_t)(a.q0 + t) * a.G + gi] = s;
+        } else if (kh == 0 && t < nq && rb < a.N) {
+          a.part_s[(size_t)(q0 + t) * a.G + gi] = s;
         }
       }
       if (!per_wave) {   // one group per pass (or several passes): the four waves meet in LDS
         __syncthreads();
-        for (int t = tid; t < a.nq; t += kThreads)
-          a.part_s[(size_t)(a.q0 + t) * a.G + gi] =
+        for (int t = tid; t < nq; t += kThreads)
+          a.part_s[(size_t)(q0 + t) * a.G + gi] =
               fmaxf(fmaxf(red_s[t], red_s[32 * NQB + t]), fmaxf(red_s[64 * NQB + t], red_s[96 * NQB + t]));
         __syncthreads();
       }
@@ -198,7 +243,7 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
     }
   }
   __syncthreads();
-  for (int t = tid; t < a.nq; t += kThreads) {
+  for (int t = tid; t < nq; t += kThreads) {
     float s = red_s[t];
     int i = red_i[t];
     for (int w = 1; w < 4; ++w) {
@@ -206,8 +251,8 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
       const int io = red_i[w * 32 * NQB + t];
       if (ranks_before(so, io, s, i)) { s = so; i = io; }
     }
-    a.part_s[(size_t)(a.q0 + t) * a.G + blockIdx.x] = s;
-    a.part_i[(size_t)(a.q0 + t) * a.G + blockIdx.x] = i;
+    a.part_s[(size_t)(q0 + t) * a.G + blockIdx.x] = s;
+    a.part_i[(size_t)(q0 + t) * a.G + blockIdx.x] = i;
   }
 }
 
@@ -437,6 +482,157 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
 }
 
 // ------------------------------------------------------------- vector-ALU scoring
+// Columns [c, c + P) of a row, P = 16 bytes' worth, and their values as binary32.  fp16 rows are
+// whole pieces (E % 8 == 0); fp32 rows may end in part of one and need not be 16-byte aligned.
+template <typename T>
+struct RowPiece;
+template <>
+struct RowPiece<f16_t> {
+  static constexpr int P = 8;
+  f16x8 w;
+  __device__ __forceinline__ void load(const f16_t* row, int c, int) {
+    w = *reinterpret_cast<const f16x8*>(row + c);
+  }
+  __device__ __forceinline__ float at(int t) const { return (float)w[t]; }
+};
+template <>
+struct RowPiece<float> {
+  static constexpr int P = 4;
+  f32x4 w;
+  __device__ __forceinline__ void load(const float* row, int c, int E) {
+    typedef f32x4 f32x4_dw __attribute__((aligned(4)));
+    if (c + P <= E) {
+      w = *reinterpret_cast<const f32x4_dw*>(row + c);
+    } else {
+#pragma unroll
+      for (int t = 0; t < P; ++t) w[t] = c + t < E ? row[c + t] : 0.f;
+    }
+  }
+  __device__ __forceinline__ float at(int t) const { return w[t]; }
+};
+
+// phase 1 for up to NQ <= 8 queries on the vector ALUs: a stream over the rows.  Eight threads
+// read a row side by side in 16-byte pieces, a thread has eight rows (32 apart) in flight, the
+// queries sit in LDS as binary32; a workgroup takes the 256 rows of a group.  Nothing but the queries
+// goes through LDS and no barrier sits in the loop, which is what a memory-bound (or, on a small
+// database, latency-bound) search wants: 1M x 128 fp32, one query, 96 us = 5.3 TB/s (165 us with a
+// thread per row); 200,000 x 768 fp16, one query, 68 us (210 us through the tiles below).  Beyond
+// eight queries the tiles win, their rows feed more queries.
+template <typename T, bool L2, int NQ, bool TOPK>
+__global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArgs a) {
+  typedef RowPiece<T> Piece;
+  constexpr int P = Piece::P, U = kValuRowsPerWg / 32;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int Ep = (a.E + 7) & ~7;
+  float* qf = reinterpret_cast<float*>(smem);           // [NQ][Ep]
+  __shared__ float red_s[4][NQ][TOPK ? 4 : 1];
+  __shared__ int red_i[4][NQ];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int slot = tid >> 3, part8 = tid & 7;
+  const int row0 = blockIdx.x * kValuRowsPerWg;
+  const T* emb = reinterpret_cast<const T*>(a.emb);
+  const T* row[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) row[u] = emb + (size_t)min(row0 + 32 * u + slot, a.N - 1) * a.E;
+  Piece now[U];   // the first pieces are on their way while the queries are staged
+  if (P * part8 < a.E) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) now[u].load(row[u], P * part8, a.E);
+  }
+  const int q0 = blockIdx.y * NQ;
+  const T* q = reinterpret_cast<const T*>(a.q) + (size_t)q0 * a.E;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j)
+    for (int c = tid; c < Ep; c += kThreads)
+      qf[j * Ep + c] = q0 + j < a.B && c < a.E ? (float)q[(size_t)j * a.E + c] : 0.f;
+  __syncthreads();
+  float acc[U][NQ];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) acc[u][j] = 0.f;
+  for (int c = P * part8; c < a.E; c += 8 * P) {
+    Piece next[U];
+    const int cn = min(c + 8 * P, a.E - 1) / P * P;   // past the end: any piece of the row, unused
+#pragma unroll
+    for (int u = 0; u < U; ++u) next[u].load(row[u], cn, a.E);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      float qv[P];
+#pragma unroll
+      for (int t = 0; t < P; ++t) qv[t] = qf[j * Ep + c + t];
+#pragma unroll
+      for (int t = 0; t < P; ++t)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (L2) {
+            const float d = qv[t] - now[u].at(t);
+            acc[u][j] = fmaf(-d, d, acc[u][j]);
+          } else {
+            acc[u][j] = fmaf(qv[t], now[u].at(t), acc[u][j]);
+          }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) now[u] = next[u];
+  }
+  // The eight threads of a row add up their parts of eight rows in three exchanges of half of what
+  // is left (four, two, one value), so that thread part8 ends up with row part8 of its eight: seven
+  // exchanges a query instead of 24, and every thread of the workgroup holds one row.
+  const int r = row0 + 32 * part8 + slot;
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = acc[u][j];
+#define AC_HALVE(n, bit, ctrl)                                                                       \
+  _Pragma("unroll") for (int u = 0; u < n; ++u) {                                                    \
+    const float keep = (part8 & bit) ? v[u + n] : v[u], give = (part8 & bit) ? v[u] : v[u + n];      \
+    v[u] = keep + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give),  \
+                                                                     ctrl, 0xf, 0xf, true));         \
+  }
+    AC_HALVE(4, 4, 0x141)   // row_half_mirror: lane 7 - p of the eight
+    AC_HALVE(2, 2, 0x4e)    // quad_perm 2 3 0 1: lane p ^ 2
+    AC_HALVE(1, 1, 0xb1)    // quad_perm 1 0 3 2: lane p ^ 1
+#undef AC_HALVE
+    const float s = fmaxf(-INFINITY, r < a.N ? v[0] : -INFINITY);   // a NaN never ranks
+    if (TOPK) {   // groups of 64 rows: threads 2 p and 2 p + 1 of every eight
+      float m = s;
+#pragma unroll
+      for (int off = 1; off < kWave; off = off == 1 ? 8 : 2 * off) m = fmaxf(m, __shfl_xor(m, off));
+      if (lane < 8) red_s[wave][j][TOPK ? lane >> 1 : 0] = m;
+    } else {
+      const bool ranks = r < a.N && v[0] == v[0];
+      const uint32_t top = wave_max(ranks ? score_key(s) : 0u);
+      const uint32_t low = wave_max(ranks && score_key(s) == top ? ~(uint32_t)r : 0u);   // lowest row
+      if (lane == 0) {
+        red_s[wave][j][0] = top ? key_score(top) : -INFINITY;
+        red_i[wave][j] = top ? (int)~low : kIdxNone;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid >= NQ || q0 + tid >= a.B) return;
+  const size_t out = (size_t)(q0 + tid) * a.G;
+  if (TOPK) {
+    float all = -INFINITY;
+    for (int p = 0; p < U / 2; ++p) {
+      const int pp = TOPK ? p : 0;
+      const float v = fmaxf(fmaxf(red_s[0][tid][pp], red_s[1][tid][pp]), fmaxf(red_s[2][tid][pp], red_s[3][tid][pp]));
+      all = fmaxf(all, v);
+      if (a.rows == 64 && row0 + 64 * p < a.N) a.part_s[out + row0 / 64 + p] = v;
+    }
+    if (a.rows != 64) a.part_s[out + blockIdx.x] = all;
+  } else {
+    float s = red_s[0][tid][0];
+    int i = red_i[0][tid];
+    for (int w = 1; w < 4; ++w)
+      if (ranks_before(red_s[w][tid][0], red_i[w][tid], s, i)) { s = red_s[w][tid][0]; i = red_i[w][tid]; }
+    a.part_s[out + blockIdx.x] = s;
+    a.part_i[out + blockIdx.x] = i;
+  }
+}
+
 // phase 1 on the vector ALUs (binary32 databases, the Euclidean metric, and the fp16 widths that no
 // matrix-core kernel is built for).  A workgroup scores the 256 rows of its group against 4 QW
 // queries: rows and queries go through LDS in slices of 32 columns (as binary32; the next
@@ -581,11 +777,29 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
   }
 }
 
+template <typename T, bool L2, int NQ, bool TOPK>
+static hipError_t launch_stream(const SearchArgs& a, hipStream_t stream) {
+  const size_t lds = (size_t)NQ * ((a.E + 7) & ~7) * 4;
+  hipError_t e = ensure_lds<&search_stream_kernel<T, L2, NQ, TOPK>>(lds);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)((a.N + kValuRowsPerWg - 1) / kValuRowsPerWg), (unsigned)((a.B + NQ - 1) / NQ));
+  hipLaunchKernelGGL((search_stream_kernel<T, L2, NQ, TOPK>), grid, dim3(kThreads), lds, stream, a);
+  return hipGetLastError();
+}
+
 template <typename T, bool L2, bool TOPK>
 static hipError_t launch_valu_k(const SearchArgs& a, hipStream_t stream) {
-  const int qw = a.B <= 4 ? 1 : a.B <= 8 ? 2 : 4;   // queries per wave
-  const size_t blocks = (size_t)((a.N + kValuRowsPerWg - 1) / kValuRowsPerWg + 7) / 8 * 8;
-  const dim3 grid((unsigned)(blocks * ((a.B + 4 * qw - 1) / (4 * qw))));
+  const size_t groups = (size_t)(a.N + kValuRowsPerWg - 1) / kValuRowsPerWg, groups8 = (groups + 7) / 8 * 8;
+  if (a.B <= 8 && a.E <= 4096) {   // (eight queries of 4,096 columns fill 128 KiB of LDS)
+    // one query per workgroup while the chip holds them all at once: a short call is a chain of
+    // latencies (1,024 x 128 fp32, four queries: 7.0 us with four per workgroup, 4.9 us with one)
+    if (groups * a.B <= 512) return launch_stream<T, L2, 1, TOPK>(a, stream);
+    return a.B == 1 ? launch_stream<T, L2, 1, TOPK>(a, stream) : a.B <= 4 ? launch_stream<T, L2, 4, TOPK>(a, stream) : launch_stream<T, L2, 8, TOPK>(a, stream);
+  }
+  // queries per wave: as many as leave some four workgroups per compute unit
+  auto blocks = [&](int qw) { return (size_t)((a.B + 4 * qw - 1) / (4 * qw)); };
+  const int qw = groups * blocks(4) >= 1024 ? 4 : groups * blocks(2) >= 1024 ? 2 : 1;
+  const dim3 grid((unsigned)(groups8 * blocks(qw)));
   if (qw == 1) hipLaunchKernelGGL((search_valu_kernel<T, L2, 1, TOPK>), grid, dim3(kThreads), 0, stream, a);
   else if (qw == 2) hipLaunchKernelGGL((search_valu_kernel<T, L2, 2, TOPK>), grid, dim3(kThreads), 0, stream, a);
   else hipLaunchKernelGGL((search_valu_kernel<T, L2, 4, TOPK>), grid, dim3(kThreads), 0, stream, a);
@@ -771,37 +985,6 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
   __syncthreads();   // the lists and what put() wrote
 }
 
-// Columns [c, c + P) of a row as binary32, P = 16 bytes' worth.  fp16 rows are whole pieces (E % 8
-// == 0); fp32 rows may end in part of one and need not be 16-byte aligned.
-template <typename T>
-struct RowPiece;
-template <>
-struct RowPiece<f16_t> {
-  static constexpr int P = 8;
-  float v[P];
-  __device__ __forceinline__ void load(const f16_t* row, int c, int) {
-    const f16x8 w = *reinterpret_cast<const f16x8*>(row + c);
-#pragma unroll
-    for (int t = 0; t < P; ++t) v[t] = (float)w[t];
-  }
-};
-template <>
-struct RowPiece<float> {
-  static constexpr int P = 4;
-  float v[P];
-  __device__ __forceinline__ void load(const float* row, int c, int E) {
-    typedef f32x4 f32x4_dw __attribute__((aligned(4)));
-    if (c + P <= E) {
-      const f32x4 w = *reinterpret_cast<const f32x4_dw*>(row + c);
-#pragma unroll
-      for (int t = 0; t < P; ++t) v[t] = w[t];
-    } else {
-#pragma unroll
-      for (int t = 0; t < P; ++t) v[t] = c + t < E ? row[c + t] : 0.f;
-    }
-  }
-};
-
 // k > 1: pick the k best groups, re-score their rows, pick the k best rows.  One workgroup per
 // query.  Rows are re-scored by eight threads each, reading 16-byte pieces side by side, four rows
 // in flight per thread.  100,000 x 256, 64 queries, k = 8: 70 us with 256-row groups, a row per
@@ -854,9 +1037,9 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           if (a.metric == 0) {
-            acc[u] = fmaf(qv, e[u].v[t], acc[u]);
+            acc[u] = fmaf(qv, e[u].at(t), acc[u]);
           } else {
-            const float d = qv - e[u].v[t];
+            const float d = qv - e[u].at(t);
             acc[u] = fmaf(-d, d, acc[u]);
           }
         }
@@ -889,7 +1072,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
 }
 
 // ------------------------------------------------------------------- host side
-enum { kModeValu = 0, kModeMfma = 1, kModeMfmaBig = 2 };
+enum { kModeValu = 0, kModeMfma = 1, kModeMfmaBig = 2, kModeMfmaWide = 3 };
 constexpr int kBigBatch = 64;   // above this many queries the query-stationary kernel is used
 constexpr int kBigRowsMin = 50000;   // and from this many database rows on, whatever the batch
 
@@ -935,13 +1118,14 @@ static void topk_plan(int32_t N, int32_t mode, int32_t k, int32_t* rows, int32_t
   auto fits = [&](int32_t r) {
     return (size_t)4 * ((N + r - 1) / r) + (size_t)4 * k * r <= space;
   };
-  int32_t r = mode == kModeMfma ? 32 : kBigRows, scan = rpg;
-  if (mode == kModeMfma) {
+  int32_t r = mode == kModeMfma || mode == kModeMfmaWide ? 32 : kBigRows, scan = rpg;
+  if (mode == kModeMfma || mode == kModeMfmaWide) {
     if (!fits(r)) {   // otherwise whole passes of 128 rows
       r = 128;
       while (2 * r <= rpg && !fits(r)) r *= 2;
     }
-    if (scan < 128) scan = 128;
+    // (a group of 256 rows need not be scanned by one workgroup when the groups are smaller)
+    if (scan < 128 || (mode == kModeMfmaWide && N <= 128 * 1024)) scan = 128;
   } else if (mode == kModeMfmaBig) {
     while (2 * r <= rpg && !fits(r)) r *= 2;
   } else {
@@ -956,8 +1140,17 @@ static bool use_mfma(int32_t is_f16, int32_t metric, int32_t E) {
   return is_f16 && metric == 0 && E % 16 == 0 && E <= 512;
 }
 
+static size_t f16_lds_bytes(int nqb, int E) {
+  return (size_t)32 * nqb * (((E + 15) & ~15) + kQPad) * 2 + (size_t)4 * 32 * nqb * 8;
+}
+constexpr size_t kF16Lds = 150 * 1024;
+
 static int search_mode(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N) {
-  if (!use_mfma(is_f16, metric, E)) return kModeValu;
+  if (!use_mfma(is_f16, metric, E)) {
+    // inner products of other fp16 widths: up to eight queries are a stream over the rows, which
+    // the vector ALUs follow; more are matrix work while a block of 32 queries fits in LDS
+    return is_f16 && metric == 0 && B > 8 && f16_lds_bytes(1, E) <= kF16Lds ? kModeMfmaWide : kModeValu;
+  }
   const bool big_shape = E == 128 || E == 256 || E == 512;   // instantiated widths
   // the query-stationary kernel streams a large database faster at any batch size (1M x 256:
   // 94 us against 105-126 us for 4..64 queries); below kBigRowsMin rows both are latency-bound
@@ -1032,10 +1225,6 @@ static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
                                           : launch_topk_n<T, 256>(a, stream);
 }
 
-static size_t f16_lds_bytes(int nqb, int E) {
-  return (size_t)32 * nqb * (E + kQPad) * 2 + (size_t)4 * 32 * nqb * 8;
-}
-
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   if (p.B == 0) return hipSuccess;
   SearchArgs a;
@@ -1044,7 +1233,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   a.threshold = p.threshold;
   a.idx = p.idx; a.score = p.score; a.hit = p.hit;
   const int mode = search_mode(p.is_f16, p.metric, p.E, p.B, p.N);
-  const bool mfma = mode == kModeMfma;
+  const bool mfma = mode == kModeMfma || mode == kModeMfmaWide;
   if (p.k > 1) {
     topk_plan(p.N, mode, p.k, &a.rows, &a.G, &a.wg_rows);
   } else {
@@ -1076,18 +1265,22 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
     }
   } else if (mfma) {
     // query super-blocks of 32 * nqb queries; the staged tile must fit in LDS
-    const int ksmax = p.E <= 128 ? 8 : (p.E <= 256 ? 16 : 32);
-    int max_nqb = 8;
-    while (max_nqb > 1 && f16_lds_bytes(max_nqb, p.E) > 150 * 1024) max_nqb >>= 1;
-    for (int q0 = 0; q0 < p.B; q0 += 32 * max_nqb) {
-      a.q0 = q0;
-      a.nq = p.B - q0 < 32 * max_nqb ? p.B - q0 : 32 * max_nqb;
-      int nqb = 1;
-      while (32 * nqb < a.nq) nqb <<= 1;
+    const int ksmax = mode == kModeMfmaWide ? 0 : p.E <= 128 ? 8 : (p.E <= 256 ? 16 : 32);
+    int max_nqb = mode == kModeMfmaWide ? 4 : 8;
+    while (max_nqb > 1 && f16_lds_bytes(max_nqb, p.E) > kF16Lds) max_nqb >>= 1;
+    // the full super-blocks are one launch (one after the other they left a small database with a
+    // handful of workgroups at a time), the rest of the queries one of their own size
+    const int full = p.B / (32 * max_nqb) * (32 * max_nqb);
+    for (a.q0 = 0; a.q0 < p.B; a.q0 += a.nq) {
+      a.nq = a.q0 < full ? full : p.B - a.q0;
+      int nqb = a.q0 < full ? max_nqb : 1;
+      while (32 * nqb < a.nq && a.q0 >= full) nqb <<= 1;
       const size_t lds = f16_lds_bytes(nqb, p.E);
-      const dim3 grid((unsigned)((p.N + a.wg_rows - 1) / a.wg_rows));
+      const dim3 grid((unsigned)((p.N + a.wg_rows - 1) / a.wg_rows), (unsigned)((a.nq + 32 * nqb - 1) / (32 * nqb)));
       hipError_t e;
-      if (ksmax == 8) e = launch_f16_phase1<8>(a, nqb, grid, lds, stream);
+      if (ksmax == 0) e = nqb == 1 ? launch_f16_k<0, 1>(a, grid, lds, stream)
+                        : nqb == 2 ? launch_f16_k<0, 2>(a, grid, lds, stream) : launch_f16_k<0, 4>(a, grid, lds, stream);
+      else if (ksmax == 8) e = launch_f16_phase1<8>(a, nqb, grid, lds, stream);
       else if (ksmax == 16) e = launch_f16_phase1<16>(a, nqb, grid, lds, stream);
       else e = launch_f16_phase1<32>(a, nqb, grid, lds, stream);
       if (e != hipSuccess) return e;

@@ -18,6 +18,18 @@ VALU_CASES = [
     (4000, 40, 17, 4, torch.float16, "ip"),     # one query past a block
     (1000, 8, 33, 1, torch.float16, "l2"),
     (700, 1000, 3, 1, torch.float16, "l2"),
+    (260, 5, 1, 1, torch.float32, "ip"),        # streams of up to eight queries: less than one piece per thread
+    (20001, 20, 4, 2, torch.float32, "l2"),     # groups of 64 rows
+    (60001, 37, 2, 2, torch.float32, "ip"),     # groups of 256 rows, odd width
+    (777, 131, 8, 5, torch.float32, "ip"),
+    (300, 520, 6, 1, torch.float16, "ip"),
+    (1000, 24, 9, 1, torch.float16, "ip"),      # wide or odd fp16 rows on the matrix cores: a half step left over
+    (515, 8, 40, 5, torch.float16, "ip"),       # less than one step
+    (2600, 1000, 70, 3, torch.float16, "ip"),   # two query super-blocks of two blocks
+    (40000, 520, 12, 2, torch.float16, "ip"),   # groups of one pass, two passes per workgroup
+    (3000, 2400, 33, 1, torch.float16, "ip"),   # queries that do not fit in LDS
+    (5000, 64, 64, 1, torch.float32, "l2"),     # a small database: one query per wave
+    (50000, 16, 64, 1, torch.float32, "ip"),    # two queries per wave
 ]
 
 
