@@ -1,13 +1,15 @@
 // Recompute branch of Algorithm 2: O = softmax(scale * Q K^T) V, causal or
 // dense, without ever writing the S x S map (flash-style online softmax).
 //
-// bf16 path (matrix cores, v_mfma_f32_32x32x16_bf16), one kernel in two variants:
+// bf16 path (matrix cores, v_mfma_f32_32x32x16_bf16), one kernel in two variants and a second one:
 //   * resident (S <= 128): one workgroup = one (batch item, KV head); both 64-key chunks of K
 //     and V are copied into LDS once and the workgroup walks all g query heads that share
 //     them; after the one barrier behind the copy its four waves never meet again;
 //   * streaming (S > 128): one workgroup = four units of 32 query rows of the heads that share K
 //     and V, which streams 64-key chunks of them through two LDS stages.
-// A wave owns 32 query rows and walks the key blocks up to its diagonal.
+//   * split (launches of few rows): the waves of a workgroup share 32 query rows and deal out its
+//     key blocks.
+// Otherwise a wave owns 32 query rows and walks the key blocks up to its diagonal.
 // Both products are formed transposed:
 //   S^T = K Q^T   -> a lane holds 16 keys of ONE query column, so the row
 //                    maximum and row sum are in-lane reductions plus one
@@ -503,6 +505,185 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
   }
 }
 
+// The same for a launch that leaves the chip idle: ALL waves of a workgroup share 32 query rows of
+// one head, wave w takes the 32-key blocks w, w + NW, ..., K straight from memory to the lanes that
+// multiply it, V through a wave-private LDS tile (the transposing read wants it there).  No barrier
+// sits in the loop, a block's successor is requested as its registers fall free, and the partial
+// results meet in LDS at the end.
+template <int D, bool CAUSAL, int NW>
+__global__ __launch_bounds__(NW * kWave, 2) void exact_bf16_split_kernel(const ExactArgs a) {
+  constexpr int PPR = D / 8, NV = 32 * PPR / kWave;   // V pieces per lane and block
+  static_assert(D / 8 % NW == 0, "the output pieces are dealt to the waves");
+  // the wave's V tile, and at the end the partial results [NW][D / 8][64] of four floats
+  __shared__ __attribute__((aligned(16))) f32x4 smem[NW * (D / 8) * kWave];
+  __shared__ float ms[NW][32], ls[NW][32];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31, kh = lane >> 5;
+  const int S = a.S, heads = a.B * a.Hq;
+  // heaviest row blocks first, neighbouring workgroups (and so the XCDs) on different heads
+  const int block = (S >> 5) - 1 - blockIdx.x / heads, bh = blockIdx.x % heads, b = bh / a.Hq;
+  if (a.row_sel && a.row_sel[b] >= 0) return;
+  const int tile = b * a.Hkv + bh % a.Hq / (a.Hq / a.Hkv);
+  const int Sk = a.key_len ? min(max(a.key_len[b], 1), S) : S;
+  const bf16_t* K = reinterpret_cast<const bf16_t*>(a.K) + (size_t)tile * S * D;
+  const bf16_t* V = reinterpret_cast<const bf16_t*>(a.V) + (size_t)tile * S * D;
+  const size_t at = ((size_t)bh * S + 32 * block) * D;
+  const int n_keys = CAUSAL ? min((Sk + 31) >> 5, block + 1) : (Sk + 31) >> 5;   // key blocks
+  bf16_t* vt = reinterpret_cast<bf16_t*>(smem) + wave * 32 * D;
+
+  u32x4 q[D / 16], k[D / 16], v[NV];
+  auto load_k = [&](int blk) {   // K operand of column step ks: row il, piece 2 ks + kh
+    const bf16_t* src = K + (size_t)(32 * blk + il) * D + 8 * kh;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) k[ks] = *reinterpret_cast<const u32x4*>(src + 16 * ks);
+  };
+  auto load_v = [&](int blk) {   // whole rows, side by side
+    const bf16_t* src = V + (size_t)(32 * blk) * D + 8 * lane;
+#pragma unroll
+    for (int n = 0; n < NV; ++n) v[n] = *reinterpret_cast<const u32x4*>(src + 8 * kWave * n);
+  };
+  {
+    const bf16_t* src = reinterpret_cast<const bf16_t*>(a.Q) + at + (size_t)il * D + 8 * kh;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) q[ks] = *reinterpret_cast<const u32x4*>(src + 16 * ks);
+  }
+  if (wave < n_keys) {
+    load_k(wave);
+    load_v(wave);
+  }
+  // V^T operand (see the kernel above): lane i of a group of 16 names key 4 kh + 8 half + i / 4 and
+  // four d from 32 db + 16 (il / 16) + 4 (i % 4)
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  auto vop = [&](int db, int s2) {
+    s16x4 part[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int t = lane & 15, j = 16 * s2 + 4 * kh + 8 * half + (t >> 2);
+      const int d0 = 32 * db + 16 * (il >> 4) + 4 * (t & 3);
+      part[half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(
+          vt + j * D + 8 * ((d0 >> 3) ^ v_piece_swizzle<D>(j)) + (d0 & 7)));
+    }
+    s16x8 w = {part[0][0], part[0][1], part[0][2], part[0][3], part[1][0], part[1][1], part[1][2], part[1][3]};
+    return __builtin_bit_cast(bf16x8, w);
+  };
+  // LDS operations of one wave execute in order: only the compiler has to keep them so
+  auto fence = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  f32x16 acc[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) acc[db][x] = 0.f;
+  float m = -INFINITY, l = 0.f;
+  for (int blk = wave; blk < n_keys; blk += NW) {
+    f32x16 s;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) s[x] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks)
+      s = mfma_bf16(__builtin_bit_cast(bf16x8, k[ks]), __builtin_bit_cast(bf16x8, q[ks]), s);
+    const bool more = blk + NW < n_keys;
+    if (more) load_k(blk + NW);
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      const int r = (n * kWave + lane) / PPR, c = lane % PPR;
+      *reinterpret_cast<u32x4*>(vt + r * D + 8 * (c ^ v_piece_swizzle<D>(r))) = v[n];
+    }
+    if (more) load_v(blk + NW);
+    fence();
+    if ((CAUSAL && blk == block) || 32 * blk + 32 > Sk) {
+      const int limit = (CAUSAL ? min(32 * block + il, Sk - 1) : Sk - 1) - 32 * blk - 4 * kh;
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        if (8 * (x >> 2) + (x & 3) > limit) s[x] = -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
+    const float cand = fmaxf(m, max_with_other_half(mx) * a.scale_log2e);
+    if (__any(cand > m + kRescaleSlack)) {
+      const float alpha = cand > m ? __builtin_amdgcn_exp2f(m - cand) : 1.f;
+      l *= alpha;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) acc[db][x] *= alpha;
+      m = cand;
+    }
+    const float ref = m == -INFINITY ? 0.f : m;   // no finite score so far: all weights are zero
+    typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
+    u32x4 p[2];
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {   // the sum is over the rounded weights, which V is multiplied with
+      const float e0 = __builtin_amdgcn_exp2f(fmaf(s[2 * w], a.scale_log2e, -ref));
+      const float e1 = __builtin_amdgcn_exp2f(fmaf(s[2 * w + 1], a.scale_log2e, -ref));
+      const uint32_t pk = pack_bf16(e0, e1);   // a copy: the cast wants an object, not a vector element
+      p[w >> 2][w & 3] = pk;
+      l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, l, false);
+    }
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+        acc[db] = mfma_bf16(vop(db, s2), __builtin_bit_cast(bf16x8, p[s2]), acc[db]);
+    fence();   // the tile is read before the next block's rows are written
+  }
+  l += __shfl_xor(l, 32);
+  if (kh == 0) {
+    ms[wave][il] = m;
+    ls[wave][il] = l;
+  }
+  __syncthreads();   // statistics are there, V tiles are no longer read
+  float top = -INFINITY, sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) top = fmaxf(top, ms[w][il]);
+  auto factor = [&](float mw) { return mw < top ? __builtin_amdgcn_exp2f(mw - top) : 1.f; };
+#pragma unroll
+  for (int w = 0; w < NW; ++w) sum = fmaf(ls[w][il], factor(ms[w][il]), sum);
+  const float mine = factor(m);
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq)
+      smem[(wave * (D / 8) + 4 * db + vq) * kWave + lane] =
+          f32x4{acc[db][4 * vq], acc[db][4 * vq + 1], acc[db][4 * vq + 2], acc[db][4 * vq + 3]} * mine;
+  __syncthreads();
+  const float inv = 1.0f / sum;
+  bf16_t* o = reinterpret_cast<bf16_t*>(a.O) + at + (size_t)il * D + 4 * kh;
+#pragma unroll
+  for (int n0 = 0; n0 < D / 8; n0 += NW) {   // columns 8 n + 4 kh and three more of row il
+    const int n = n0 + wave;
+    f32x4 r = smem[n * kWave + lane];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) r += smem[(w * (D / 8) + n) * kWave + lane];
+    *reinterpret_cast<u32x2*>(o + 8 * n) = u32x2{pack_bf16(r[0] * inv, r[1] * inv), pack_bf16(r[2] * inv, r[3] * inv)};
+  }
+}
+
+// A row next to infinite or NaN V on its diagonal block, key by key: lane = output column, only visible
+// keys are read.  m and l are the row's largest score and the sum of its weights.
+__device__ __forceinline__ void f32_row_by_key(const ExactArgs& a, const float* K, const float* V, size_t at,
+                                               int keys, float m, float l, float scale, int D, int lane) {
+  const float* Q = reinterpret_cast<const float*>(a.Q) + at;
+  for (int d0 = 0; d0 < D; d0 += kWave) {
+    float o = 0.f;
+    for (int j = 0; j < keys; ++j) {
+      float s = 0.f;
+      for (int d = lane; d < D; d += kWave) s = fmaf(Q[d], K[(size_t)j * D + d], s);
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+      const float p = expf(s * scale - (m == -INFINITY ? 0.f : m));
+      if (d0 + lane < D) o = fmaf(p, V[(size_t)j * D + d0 + lane], o);
+    }
+    if (d0 + lane < D) reinterpret_cast<float*>(a.O)[at + d0 + lane] = o / l;
+  }
+}
+
 // fp32 path (binary32 matrix instructions, any S, D <= 64 DB): four waves of 16 query rows each
 // share 32-key stages of K and V; the next stage's rows are in registers while this one is
 // multiplied.  Online softmax: every lane keeps the running maximum and ITS keys' share of the row
@@ -628,32 +809,190 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
   l += __shfl_xor(l, 32);
   if (u.block >= 0 && row < S && !redo)
     f32_store_row<DB>(reinterpret_cast<float*>(a.O) + at, acc, l, kq, D);
-  if (redo) {   // infinite or NaN V near the diagonal: lane = output column, only visible keys are read
+  if (redo) {
     const int rows = min(kF32Rows, S - kF32Rows * u.block);
-#pragma unroll 1
-    for (int r = 0; r < rows; ++r) {
-      const size_t to = __shfl(at, r);
-      const float* Q = reinterpret_cast<const float*>(a.Q) + to;
-      const float mr = __shfl(m, r), lr = __shfl(l, r);
-      const int keys = __shfl(limit, r);
-      for (int d0 = 0; d0 < D; d0 += kWave) {
-        float o = 0.f;
-        for (int j = 0; j < keys; ++j) {
-          float s = 0.f;
-          for (int d = lane; d < D; d += kWave) s = fmaf(Q[d], K[(size_t)j * D + d], s);
-          for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-          const float p = expf(s * scale - (mr == -INFINITY ? 0.f : mr));
-          if (d0 + lane < D) o = fmaf(p, V[(size_t)j * D + d0 + lane], o);
-        }
-        if (d0 + lane < D) reinterpret_cast<float*>(a.O)[to + d0 + lane] = o / lr;
-      }
+    for (int r = 0; r < rows; ++r)
+      f32_row_by_key(a, K, V, __shfl(at, r), __shfl(limit, r), __shfl(m, r), __shfl(l, r), scale, D, lane);
+  }
+}
+
+// The same rows for a launch that leaves the chip idle: ALL waves of a workgroup share one unit of 16
+// rows, wave w takes the 16-key blocks w, w + NW, ... straight from memory to the lanes that
+// multiply them (nothing is shared, so nothing goes through LDS and no barrier sits in the loop; a
+// block's successor is requested as its registers fall free), and the partial results meet in LDS
+// at the end.  The chain of a row gets NW times shorter and the launch has four times the
+// workgroups.
+template <int DB, int NW, bool FULL>   // FULL: D == 64 DB
+__global__ __launch_bounds__(NW * kWave, DB <= 2 ? 2 : 1) void exact_f32_split_kernel(
+    const ExactArgs a, int D, int causal, float scale) {
+  __shared__ __attribute__((aligned(16))) f32x4 part[NW][4 * DB][kWave];
+  __shared__ float ms[NW][kF32Rows], ls[NW][kF32Rows];
+  __shared__ int odd;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, kq = lane >> 4;
+  const int S = a.S, heads = a.B * a.Hq;
+  // heaviest row blocks first, neighbouring workgroups (and so the XCDs) on different heads
+  const int n_blk = (S + kF32Rows - 1) / kF32Rows, block = n_blk - 1 - blockIdx.x / heads;
+  const int bh = blockIdx.x % heads, b = bh / a.Hq;
+  if (a.row_sel && a.row_sel[b] >= 0) return;
+  const int tile = b * a.Hkv + bh % a.Hq / (a.Hq / a.Hkv);
+  const int len = a.key_len ? min(max(a.key_len[b], 1), S) : S;   // keys beyond it are padding
+  const float* K = reinterpret_cast<const float*>(a.K) + (size_t)tile * S * D;
+  const float* V = reinterpret_cast<const float*>(a.V) + (size_t)tile * S * D;
+  const int keys = causal ? min(len, kF32Rows * (block + 1)) : len;
+  const int n_keys = (keys + kF32Rows - 1) / kF32Rows;   // key blocks
+
+  // No load sits behind a lane's own test: rows past the end of the sentence and columns past D (a
+  // multiple of 16) repeat valid ones.  A hidden key's score is replaced, its V row zeroed (the last
+  // block of a sentence only); columns past D end up in results that nobody stores.
+  f32x4 k[4 * DB], v[4][DB];
+  auto col = [&](int c) { return FULL || c < D ? c : 0; };
+  auto load_k = [&](int blk) {
+    const float* src = K + (size_t)min(kF32Rows * blk + i, len - 1) * D + 4 * kq;
+#pragma unroll
+    for (int kk = 0; kk < 4 * DB; ++kk) k[kk] = *reinterpret_cast<const f32x4*>(src + col(16 * kk));
+  };
+  auto load_v = [&](int blk) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int key = kF32Rows * blk + 4 * kq + x;
+      const float* src = V + (size_t)min(key, len - 1) * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db) v[x][db] = *reinterpret_cast<const f32x4*>(src + col(64 * db + 4 * i));
     }
+  };
+  const int row = kF32Rows * block + i;
+  const size_t at = ((size_t)bh * S + min(row, S - 1)) * (size_t)D;
+  const float* Q = reinterpret_cast<const float*>(a.Q) + at;
+  f32x4 q[4 * DB];
+#pragma unroll
+  for (int kk = 0; kk < 4 * DB; ++kk) q[kk] = *reinterpret_cast<const f32x4*>(Q + col(16 * kk) + 4 * kq);
+  if (wave < n_keys) {
+    load_k(wave);
+    load_v(wave);
+  }
+  if (tid == 0) odd = 0;
+  f32x4 acc[4 * DB];
+#pragma unroll
+  for (int x = 0; x < 4 * DB; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  bool redo = false;
+  const int limit = causal ? min(row + 1, len) : len;   // keys this row sees
+  for (int blk = wave; blk < n_keys; blk += NW) {
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < 4 * DB; ++kk)
+      if (FULL || 16 * kk < D)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) s = mfma_f32(k[kk][t], q[kk][t], s);
+    if (blk + NW < n_keys) load_k(blk + NW);
+    float mx = -INFINITY;
+    bool seen[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      seen[x] = kF32Rows * blk + 4 * kq + x < limit;
+      s[x] *= scale;
+      mx = seen[x] ? fmaxf(mx, s[x]) : mx;
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx);
+    if (__any(m_new > m)) {
+      const float alpha = m_new > m ? expf(m - m_new) : 1.f;
+      l *= alpha;
+#pragma unroll
+      for (int x = 0; x < 4 * DB; ++x) acc[x] *= alpha;
+      m = m_new;
+    }
+    const float ref = m == -INFINITY ? 0.f : m;   // no finite score so far: all weights are zero
+    f32x4 p;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      p[x] = seen[x] ? expf(s[x] - ref) : 0.f;
+      l += p[x];
+    }
+    if (kF32Rows * (blk + 1) > len) {
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+          if (kF32Rows * blk + 4 * kq + x >= len) v[x][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (causal && blk == block) {
+      bool any = false;
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+#pragma unroll
+        for (int db = 0; db < DB; ++db) any |= f32_not_finite(v[x][db]);
+      redo = __any(any);
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[4 * db + t] = mfma_f32(v[x][db][t], p[x], acc[4 * db + t]);
+    if (blk + NW < n_keys) load_v(blk + NW);
+  }
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (lane < kF32Rows) {
+    ms[wave][lane] = m;
+    ls[wave][lane] = l;
+  }
+  __syncthreads();   // (also: `odd` has been cleared)
+  if (redo && lane == 0) odd = 1;
+  float top = -INFINITY, sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) top = fmaxf(top, ms[w][i]);
+  auto factor = [&](float mw) { return mw < top ? expf(mw - top) : 1.f; };
+#pragma unroll
+  for (int w = 0; w < NW; ++w) sum = fmaf(ls[w][i], factor(ms[w][i]), sum);
+  const float mine = factor(m);
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      part[wave][4 * db + x][lane] = f32x4{acc[4 * db][x], acc[4 * db + 1][x], acc[4 * db + 2][x], acc[4 * db + 3][x]} * mine;
+  __syncthreads();
+  if (!odd) {
+    float* o = reinterpret_cast<float*>(a.O) + at;
+    for (int n = wave; n < 4 * DB; n += NW) {   // columns 64 (n / 4) + 16 kq + 4 (n % 4) and three more
+      f32x4 r = part[0][n][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) r += part[w][n][lane];
+      r = f32x4{r[0] / sum, r[1] / sum, r[2] / sum, r[3] / sum};
+      const int d = 64 * (n >> 2) + 16 * kq + 4 * (n & 3);
+      if (row < S && d < D) *reinterpret_cast<f32x4*>(o + d) = r;
+    }
+  } else {
+    const int rows = min(kF32Rows, S - kF32Rows * block);
+    for (int r = wave; r < rows; r += NW)
+      f32_row_by_key(a, K, V, __shfl(at, r), __shfl(limit, r), __shfl(top, r), __shfl(sum, r), scale, D, lane);
   }
 }
 
 template <int DB>
 static hipError_t launch_exact_f32(const ExactArgs& a, int D, int causal, float scale,
                                    hipStream_t stream) {
+  const size_t units = (size_t)a.B * a.Hq * ((a.S + kF32Rows - 1) / kF32Rows);
+  // One unit per workgroup while the chip has room for its chains side by side: beyond these lines K
+  // and V, which only the other kernel shares between rows, cost more than the chains save.  us per
+  // call, four waves on one unit / on four: 8 heads of 400 x 128 (200 units) 15.6 / 50.1, 64 heads of
+  // 400 x 64 (1,600) 26.2 / 34.4, 128 of 94 x 128 (768) 12.4 / 17.1, 168 (1,008) 19.9 / 18.8, 192 of
+  // 128 x 128 (1,536) 24.7 / 24.6, 512 of 32 x 64 (1,024) 7.7 / 6.7, 128 of 32 x 64 (256) 4.8 / 5.9.
+  const size_t most = a.S <= 64 ? 512 : a.S < 128 ? 768 : 1536;
+  if (D % 16 == 0 && units <= most) {
+    constexpr int NW = 4;   // eight: 64 heads of 94 x 128 13.5 us, four 9.9
+    if (D == 64 * DB)
+      hipLaunchKernelGGL((exact_f32_split_kernel<DB, NW, true>), dim3((unsigned)units), dim3(NW * kWave), 0, stream, a, D,
+                         causal, scale);
+    else
+      hipLaunchKernelGGL((exact_f32_split_kernel<DB, NW, false>), dim3((unsigned)units), dim3(NW * kWave), 0, stream, a, D,
+                         causal, scale);
+    return hipGetLastError();
+  }
   const unsigned grid = f32_grid(a.n_kvtiles, a.Hq / a.Hkv, a.S);
   hipLaunchKernelGGL((exact_f32_kernel<DB>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
   return hipGetLastError();
@@ -687,6 +1026,13 @@ static hipError_t launch_exact_bf16(const ExactArgs& a, dim3 grid, hipStream_t s
                        : launch_exact_bf16_r<D, CAUSAL, false>(a, grid, stream);
 }
 
+constexpr int kSplitWaves = 4;   // eight: 8 heads of 1024 x 128 16.1 us, four 14.0
+template <int D, bool CAUSAL>
+static hipError_t launch_exact_split(const ExactArgs& a, size_t units, hipStream_t stream) {
+  hipLaunchKernelGGL((exact_bf16_split_kernel<D, CAUSAL, kSplitWaves>), dim3((unsigned)units), dim3(kSplitWaves * kWave), 0, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
   if (p.B == 0) return hipSuccess;
   ExactArgs a;
@@ -702,7 +1048,20 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
     if (p.D <= 128) return launch_exact_f32<2>(a, p.D, p.causal, scale, stream);
     return launch_exact_f32<4>(a, p.D, p.causal, scale, stream);
   }
+  const size_t units = (size_t)p.B * p.Hq * (p.S / 32);
+  // One unit per workgroup while that leaves room on the chip (as above).  The resident kernel walks
+  // the heads of a group one after the other and is left later where there are several, or one
+  // block of keys.  us per call, split / not: 8 heads of 1024 x 128 causal (256 units) 14.0 / 23.7, 64 of
+  // 288 x 128 (576) 12.2 / 10.2, 64 of 288 x 64 (576) 7.6 / 7.9, 24 of 512 x 64 dense (384) 9.0 / 9.7, 64
+  // of 512 x 64 (1,024) 14.0 / 11.3; 128 of 128 x 128 (512) 7.8 / 8.4, 160 (640) 9.8 / 8.0, 160 on 40 K and V
+  // (640) 10.0 / 16.0; 256 of 128 x 64 (1,024) 7.8 / 6.7, on 64 K and V 8.9 / 15.6; 640 of 32 x 128 8.5 / 9.7.
   const int g = p.Hq / p.Hkv;
+  const size_t most = p.S > 128 ? (p.D == 64 ? 576 : 320) / (p.causal ? 1 : 2)
+                      : p.S > 32 && g == 1 ? (p.causal ? 512 : 256) : p.D == 64 ? 1024 : 640;
+  if (units <= most) {
+    if (p.D == 64) return p.causal ? launch_exact_split<64, true>(a, units, stream) : launch_exact_split<64, false>(a, units, stream);
+    return p.causal ? launch_exact_split<128, true>(a, units, stream) : launch_exact_split<128, false>(a, units, stream);
+  }
   a.heads_per_wg = g;
   const int u8 = (a.n_kvtiles + 7) / 8 * 8;
   const int per_u = a.n_rblk == 1 ? 1 : (g * (p.S / 32) + 3) / 4;   // workgroups of a K/V tile

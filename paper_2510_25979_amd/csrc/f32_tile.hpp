@@ -97,6 +97,15 @@ __device__ __forceinline__ void f32_weights_v(f32x4 (&acc)[4 * DB], const float*
 // the diagonal hides some of its keys from some rows, and a hidden key must not touch a row even
 // then: 0 * inf, which a product over all 16 keys cannot avoid.  A wave that finds such a value in
 // its diagonal block forms its rows again after the loop, key by key.
+__device__ __forceinline__ bool f32_not_finite(const f32x4 r) {
+  bool odd = false;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float f = r[t];
+    odd |= (~__builtin_bit_cast(uint32_t, f) & 0x7f800000u) == 0u;
+  }
+  return odd;
+}
 template <int DB>
 __device__ __forceinline__ bool f32_block_not_finite(const float* __restrict__ v, int i, int kq) {
   constexpr int LD = F32Stage<DB, 64>::LD;
@@ -104,14 +113,8 @@ __device__ __forceinline__ bool f32_block_not_finite(const float* __restrict__ v
 #pragma unroll
   for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int b = 0; b < DB; ++b) {
-      const f32x4 r = *reinterpret_cast<const f32x4*>(v + (4 * kq + x) * LD + 64 * b + 4 * i);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const float f = r[t];
-        odd |= (~__builtin_bit_cast(uint32_t, f) & 0x7f800000u) == 0u;
-      }
-    }
+    for (int b = 0; b < DB; ++b)
+      odd |= f32_not_finite(*reinterpret_cast<const f32x4*>(v + (4 * kq + x) * LD + 64 * b + 4 * i));
   return __any(odd);
 }
 
