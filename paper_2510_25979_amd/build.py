@@ -6,7 +6,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattncache.so")
 SOURCES = ["api.hip", "apply.hip", "exact.hip", "insert.hip", "project.hip", "search.hip"]
-HEADERS = ["common.hpp", "f32_tile.hpp", "launch.hpp", os.path.join("..", "..", "include", "attncache.h")]
+HEADERS = ["common.hpp", "f32_tile.hpp", "launch.hpp", "split_tile.hpp", os.path.join("..", "..", "include", "attncache.h")]
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 instructions
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",

@@ -62,6 +62,18 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, p);
 }
 
+// max(x[l], x[l ^ 32]) in every lane l.  v_permlane32_swap_b32 exchanges the upper 32 lanes of
+// its first register with the lower 32 lanes of its second one, so two copies of x become
+// (lower half twice) and (upper half twice) without a trip through LDS.  Written as inline
+// assembly because the compiler builtin of the same name folds its two results into one in
+// this toolchain; the wait states around it cover the vector write -> lane permute -> vector
+// read sequence, which the compiler cannot see into.
+__device__ __forceinline__ float max_with_other_half(float x) {
+  float lo = x, hi = x;
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(lo), "+v"(hi));
+  return fmaxf(lo, hi);
+}
+
 // Permutation of the 16-byte pieces of a V row staged row-major in LDS for the transposing
 // read (ds_read_b64_tr_b16): piece p of key row r sits at position p ^ v_piece_swizzle(r).  One
 // such read instruction serves 32 lanes per LDS cycle: four consecutive keys x the two

@@ -24,6 +24,7 @@
 #include "common.hpp"
 #include "f32_tile.hpp"
 #include "launch.hpp"
+#include "split_tile.hpp"
 
 namespace ac {
 
@@ -59,18 +60,6 @@ struct ExactArgs {
 //   * the two 32-key blocks of a chunk take their softmax steps in an order that lets matrix
 //     and vector work of one wave overlap (see the chunk step below).
 constexpr int kLChunk = 64;
-
-// max(x[l], x[l ^ 32]) in every lane l.  v_permlane32_swap_b32 exchanges the upper 32 lanes of
-// its first register with the lower 32 lanes of its second one, so two copies of x become
-// (lower half twice) and (upper half twice) without a trip through LDS.  Written as inline
-// assembly because the compiler builtin of the same name folds its two results into one in
-// this toolchain; the wait states around it cover the vector write -> lane permute -> vector
-// read sequence, which the compiler cannot see into.
-__device__ __forceinline__ float max_with_other_half(float x) {
-  float lo = x, hi = x;
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(lo), "+v"(hi));
-  return fmaxf(lo, hi);
-}
 
 template <int D, bool CAUSAL, bool RESIDENT>
 __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel(const ExactArgs a) {
@@ -506,15 +495,11 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
 }
 
 // The same for a launch that leaves the chip idle: ALL waves of a workgroup share 32 query rows of
-// one head, wave w takes the 32-key blocks w, w + NW, ..., K straight from memory to the lanes that
-// multiply it, V through a wave-private LDS tile (the transposing read wants it there).  No barrier
-// sits in the loop, a block's successor is requested as its registers fall free, and the partial
-// results meet in LDS at the end.
+// one head, wave w takes the 32-key blocks w, w + NW, ..., and the partial results meet in LDS at the
+// end.  The chain of a row gets NW times shorter; the price is that nothing of K and V is shared.
 template <int D, bool CAUSAL, int NW>
 __global__ __launch_bounds__(NW * kWave, 2) void exact_bf16_split_kernel(const ExactArgs a) {
-  constexpr int PPR = D / 8, NV = 32 * PPR / kWave;   // V pieces per lane and block
-  static_assert(D / 8 % NW == 0, "the output pieces are dealt to the waves");
-  // the wave's V tile, and at the end the partial results [NW][D / 8][64] of four floats
+  // the waves' V tiles (half of it), and at the end their partial results
   __shared__ __attribute__((aligned(16))) f32x4 smem[NW * (D / 8) * kWave];
   __shared__ float ms[NW][32], ls[NW][32];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -526,54 +511,16 @@ __global__ __launch_bounds__(NW * kWave, 2) void exact_bf16_split_kernel(const E
   if (a.row_sel && a.row_sel[b] >= 0) return;
   const int tile = b * a.Hkv + bh % a.Hq / (a.Hq / a.Hkv);
   const int Sk = a.key_len ? min(max(a.key_len[b], 1), S) : S;
-  const bf16_t* K = reinterpret_cast<const bf16_t*>(a.K) + (size_t)tile * S * D;
-  const bf16_t* V = reinterpret_cast<const bf16_t*>(a.V) + (size_t)tile * S * D;
   const size_t at = ((size_t)bh * S + 32 * block) * D;
   const int n_keys = CAUSAL ? min((Sk + 31) >> 5, block + 1) : (Sk + 31) >> 5;   // key blocks
-  bf16_t* vt = reinterpret_cast<bf16_t*>(smem) + wave * 32 * D;
-
-  u32x4 q[D / 16], k[D / 16], v[NV];
-  auto load_k = [&](int blk) {   // K operand of column step ks: row il, piece 2 ks + kh
-    const bf16_t* src = K + (size_t)(32 * blk + il) * D + 8 * kh;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) k[ks] = *reinterpret_cast<const u32x4*>(src + 16 * ks);
-  };
-  auto load_v = [&](int blk) {   // whole rows, side by side
-    const bf16_t* src = V + (size_t)(32 * blk) * D + 8 * lane;
-#pragma unroll
-    for (int n = 0; n < NV; ++n) v[n] = *reinterpret_cast<const u32x4*>(src + 8 * kWave * n);
-  };
-  {
-    const bf16_t* src = reinterpret_cast<const bf16_t*>(a.Q) + at + (size_t)il * D + 8 * kh;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) q[ks] = *reinterpret_cast<const u32x4*>(src + 16 * ks);
-  }
+  SplitOperands<D> t(reinterpret_cast<const bf16_t*>(a.K) + (size_t)tile * S * D,
+                     reinterpret_cast<const bf16_t*>(a.V) + (size_t)tile * S * D,
+                     reinterpret_cast<bf16_t*>(smem) + wave * 32 * D, lane);
+  t.load_q(reinterpret_cast<const bf16_t*>(a.Q) + at);
   if (wave < n_keys) {
-    load_k(wave);
-    load_v(wave);
+    t.load_k(wave);
+    t.load_v(wave);
   }
-  // V^T operand (see the kernel above): lane i of a group of 16 names key 4 kh + 8 half + i / 4 and
-  // four d from 32 db + 16 (il / 16) + 4 (i % 4)
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef short s16x8 __attribute__((ext_vector_type(8)));
-  auto vop = [&](int db, int s2) {
-    s16x4 part[2];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int t = lane & 15, j = 16 * s2 + 4 * kh + 8 * half + (t >> 2);
-      const int d0 = 32 * db + 16 * (il >> 4) + 4 * (t & 3);
-      part[half] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(
-          vt + j * D + 8 * ((d0 >> 3) ^ v_piece_swizzle<D>(j)) + (d0 & 7)));
-    }
-    s16x8 w = {part[0][0], part[0][1], part[0][2], part[0][3], part[1][0], part[1][1], part[1][2], part[1][3]};
-    return __builtin_bit_cast(bf16x8, w);
-  };
-  // LDS operations of one wave execute in order: only the compiler has to keep them so
-  auto fence = [&]() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  };
   f32x16 acc[D / 32];
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
@@ -581,21 +528,12 @@ __global__ __launch_bounds__(NW * kWave, 2) void exact_bf16_split_kernel(const E
     for (int x = 0; x < 16; ++x) acc[db][x] = 0.f;
   float m = -INFINITY, l = 0.f;
   for (int blk = wave; blk < n_keys; blk += NW) {
-    f32x16 s;
-#pragma unroll
-    for (int x = 0; x < 16; ++x) s[x] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks)
-      s = mfma_bf16(__builtin_bit_cast(bf16x8, k[ks]), __builtin_bit_cast(bf16x8, q[ks]), s);
+    f32x16 s = t.scores();
     const bool more = blk + NW < n_keys;
-    if (more) load_k(blk + NW);
-#pragma unroll
-    for (int n = 0; n < NV; ++n) {
-      const int r = (n * kWave + lane) / PPR, c = lane % PPR;
-      *reinterpret_cast<u32x4*>(vt + r * D + 8 * (c ^ v_piece_swizzle<D>(r))) = v[n];
-    }
-    if (more) load_v(blk + NW);
-    fence();
+    if (more) t.load_k(blk + NW);
+    t.stage_v();
+    if (more) t.load_v(blk + NW);
+    wave_lds_fence();
     if ((CAUSAL && blk == block) || 32 * blk + 32 > Sk) {
       const int limit = (CAUSAL ? min(32 * block + il, Sk - 1) : Sk - 1) - 32 * blk - 4 * kh;
 #pragma unroll
@@ -627,12 +565,8 @@ __global__ __launch_bounds__(NW * kWave, 2) void exact_bf16_split_kernel(const E
       p[w >> 2][w & 3] = pk;
       l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pk), ones, l, false);
     }
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int db = 0; db < D / 32; ++db)
-        acc[db] = mfma_bf16(vop(db, s2), __builtin_bit_cast(bf16x8, p[s2]), acc[db]);
-    fence();   // the tile is read before the next block's rows are written
+    t.weights_v(acc, p);
+    wave_lds_fence();   // the tile is read before the next block's rows are written
   }
   l += __shfl_xor(l, 32);
   if (kh == 0) {
@@ -646,24 +580,7 @@ __global__ __launch_bounds__(NW * kWave, 2) void exact_bf16_split_kernel(const E
   auto factor = [&](float mw) { return mw < top ? __builtin_amdgcn_exp2f(mw - top) : 1.f; };
 #pragma unroll
   for (int w = 0; w < NW; ++w) sum = fmaf(ls[w][il], factor(ms[w][il]), sum);
-  const float mine = factor(m);
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int vq = 0; vq < 4; ++vq)
-      smem[(wave * (D / 8) + 4 * db + vq) * kWave + lane] =
-          f32x4{acc[db][4 * vq], acc[db][4 * vq + 1], acc[db][4 * vq + 2], acc[db][4 * vq + 3]} * mine;
-  __syncthreads();
-  const float inv = 1.0f / sum;
-  bf16_t* o = reinterpret_cast<bf16_t*>(a.O) + at + (size_t)il * D + 4 * kh;
-#pragma unroll
-  for (int n0 = 0; n0 < D / 8; n0 += NW) {   // columns 8 n + 4 kh and three more of row il
-    const int n = n0 + wave;
-    f32x4 r = smem[n * kWave + lane];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) r += smem[(w * (D / 8) + n) * kWave + lane];
-    *reinterpret_cast<u32x2*>(o + 8 * n) = u32x2{pack_bf16(r[0] * inv, r[1] * inv), pack_bf16(r[2] * inv, r[3] * inv)};
-  }
+  split_store<D, NW>(acc, factor(m), 1.0f / sum, smem, reinterpret_cast<bf16_t*>(a.O) + at, wave, lane);
 }
 
 // A row next to infinite or NaN V on its diagonal block, key by key: lane = output column, only visible

@@ -21,8 +21,11 @@
 // packed 16 x 32 blocks directly -- register group q (4 registers) of lane (row i, half kh) is
 // elements 4 kh .. 4 kh + 3 of piece (16 q + i % 16), i.e. one 8-byte store per group, and the 32
 // lanes of a 16-row half fill a contiguous 256-byte run.
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
+#include "split_tile.hpp"
 
 namespace ac {
 
@@ -322,8 +325,144 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   }
 }
 
+// The same for a launch that leaves the chip idle: ALL waves of a workgroup share one unit of 32 rows,
+// wave w takes the 32-key blocks w, w + NW, ... of both passes.  The statistics of the waves meet
+// between the passes, their partial outputs at the end.
+template <int D, bool CAUSAL, bool PACKED>
+__global__ __launch_bounds__(kThreads, 2) void insert_bf16_split_kernel(const InsertArgs a) {
+  constexpr int NW = kThreads / kWave;
+  // the waves' V tiles (half of it), and at the end their partial results
+  __shared__ __attribute__((aligned(16))) f32x4 smem[NW * (D / 8) * kWave];
+  __shared__ float ms[NW][32], ls[NW][32];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31, kh = lane >> 5;
+  const int S = a.S, heads = a.n_tiles / a.Hkv * a.Hq, n32 = S >> 5;
+  // heaviest row blocks first, neighbouring workgroups (and so the XCDs) on different heads
+  const int block = n32 - 1 - blockIdx.x / heads, u = blockIdx.x % heads;   // u: (item, layer, head)
+  const int h = u % a.Hq, bl = u / a.Hq, l = bl % a.Lc, b = bl / a.Lc;
+  if (a.row_sel && a.row_sel[b] >= 0) return;
+  const int len = a.key_len ? min(max(a.key_len[b], 1), S) : S;
+  const int entry = a.slot ? a.slot[b] : -1;
+  const bool keep = entry >= 0 && entry < a.M;   // anything else: compute O only
+  // the item's first workgroup also copies its feature vector into the same slot
+  if (a.feat && keep && l == 0 && h == 0 && block == n32 - 1)
+    for (int p = tid; p < a.feat_pieces; p += kThreads)
+      a.emb[(size_t)entry * a.feat_pieces + p] = a.feat[(size_t)b * a.feat_pieces + p];
+
+  const size_t kv = ((size_t)bl * a.Hkv + h / (a.Hq / a.Hkv)) * (size_t)S * D;
+  const size_t at = ((size_t)u * S + 32 * block) * D;
+  const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
+  bf16_t* At = reinterpret_cast<bf16_t*>(a.maps) +
+               (((size_t)(keep ? entry : 0) * a.L + (a.layer_begin + l)) * a.Hq + h) * tile_elems;
+  const int row_blocks = CAUSAL ? block + 1 : n32;
+  const int n_keys = min(row_blocks, (len + 31) >> 5);   // key blocks that hold a visible key
+  const int r16 = 2 * block + (il >> 4);
+  auto map_piece = [&](int kb, int q4) -> u32x2* {   // scores 4 q4 .. 4 q4 + 3 of this lane, key block kb
+    if (PACKED) {
+      const int blk = (CAUSAL ? packed_prefix(r16) : r16 * n32) + kb;
+      return reinterpret_cast<u32x2*>(At + (size_t)blk * 512 + (16 * q4 + (il & 15)) * 8 + 4 * kh);
+    }
+    return reinterpret_cast<u32x2*>(At + (size_t)(32 * block + il) * S + 32 * kb + 8 * q4 + 4 * kh);
+  };
+  SplitOperands<D> t(reinterpret_cast<const bf16_t*>(a.K) + kv, reinterpret_cast<const bf16_t*>(a.V) + kv,
+                     reinterpret_cast<bf16_t*>(smem) + wave * 32 * D, lane);
+  auto hide = [&](f32x16& s, int blk) {
+    if ((CAUSAL && blk == block) || 32 * blk + 32 > len) {   // wave-uniform: most blocks skip the tests
+      const int limit = (CAUSAL ? min(len - 1, 32 * block + il) : len - 1) - 32 * blk;
+#pragma unroll
+      for (int x = 0; x < 16; ++x)
+        if (mfma_row(x, kh) > limit) s[x] = -INFINITY;
+    }
+  };
+  t.load_q(reinterpret_cast<const bf16_t*>(a.Q) + at);
+  if (wave < n_keys) {
+    t.load_k(wave);
+    t.load_v(wave);
+  }
+  // zeros: blocks in the padding, and in a dense causal map those right of the diagonal block
+  if (keep)
+    for (int kb = n_keys + wave; kb < (PACKED ? row_blocks : n32); kb += NW)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) *map_piece(kb, q4) = u32x2{0u, 0u};
+
+  float m = -INFINITY, sum = 0.f;
+  for (int blk = wave; blk < n_keys; blk += NW) {
+    f32x16 s = t.scores();
+    t.load_k(blk + NW < n_keys ? blk + NW : wave);   // the last trip: the second pass's first block
+    hide(s, blk);
+    float mx = s[0];
+#pragma unroll
+    for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
+    const float m_new = fmaxf(m, max_with_other_half(mx) * a.scale_log2e);
+    const float ref = m_new == -INFINITY ? 0.f : m_new;   // no finite score so far
+    float part = 0.f;
+#pragma unroll
+    for (int x = 0; x < 16; ++x) part += __builtin_amdgcn_exp2f(fmaf(s[x], a.scale_log2e, -ref));
+    sum = sum * (m_new > m ? __builtin_amdgcn_exp2f(m - m_new) : 1.f) + part;
+    m = m_new;
+  }
+  sum += __shfl_xor(sum, 32);
+  if (kh == 0) {
+    ms[wave][il] = m;
+    ls[wave][il] = sum;
+  }
+  __syncthreads();
+  float top = -INFINITY, total = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) top = fmaxf(top, ms[w][il]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+    total = fmaf(ls[w][il], ms[w][il] < top ? __builtin_amdgcn_exp2f(ms[w][il] - top) : 1.f, total);
+  const float inv = 1.0f / total;
+
+  f32x16 acc[D / 32];
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int x = 0; x < 16; ++x) acc[db][x] = 0.f;
+  for (int blk = wave; blk < n_keys; blk += NW) {
+    f32x16 s = t.scores();
+    const bool more = blk + NW < n_keys;
+    if (more) t.load_k(blk + NW);
+    t.stage_v();
+    if (more) t.load_v(blk + NW);
+    wave_lds_fence();
+    hide(s, blk);
+#pragma unroll
+    for (int x = 0; x < 16; ++x) s[x] = __builtin_amdgcn_exp2f(fmaf(s[x], a.scale_log2e, -top)) * inv;
+    u32x4 p[2];
+#pragma unroll
+    for (int w = 0; w < 8; ++w) p[w >> 2][w & 3] = pack_bf16(s[2 * w], s[2 * w + 1]);
+    if (keep)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *map_piece(blk, q4) = q4 & 1 ? u32x2{p[q4 >> 1].z, p[q4 >> 1].w} : u32x2{p[q4 >> 1].x, p[q4 >> 1].y};
+    t.weights_v(acc, p);
+    wave_lds_fence();   // the tile is read before the next block's rows are written
+  }
+  __syncthreads();   // V tiles are no longer read
+  split_store<D, NW>(acc, 1.0f, 1.0f, smem, reinterpret_cast<bf16_t*>(a.O) + at, wave, lane);
+}
+
 template <int D, bool CAUSAL, bool PACKED>
 static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t stream) {
+  // One unit per workgroup while that leaves room on the chip (beyond, K and V, which only the other
+  // kernel shares between rows, cost more).  Up to 128 keys the other kernel walks the heads of a group
+  // one after the other, so the line rises with their number.  us per call, split / not: 8 heads of
+  // 1024 x 128 causal (256 units) 22.9 / 43.8, 32 of 512 x 128 (512) 19.9 / 25.3, 108 of 160 x 128 (540)
+  // 13.0 / 11.9, 72 of it dense (360) 12.5 / 11.4, 96 of 288 x 64 (864) 13.2 / 15.4, 64 of 512 x 64 (1,024) 20.4 / 20.9; 64 on 16 K and V of
+  // 128 x 128 (256) 7.3 / 22.3, 384 on 96 of 64 x 128 (768) 12.9 / 15.0, 8 on 8 of 128 x 128 (32) 6.8 / 8.1,
+  // 128 on 128 (512) 10.2 / 8.8, 256 on 256 of 32 x 64 (256) 5.0 / 4.4.
+  const int g = a.Hq / a.Hkv;
+  const size_t units = (size_t)(a.n_tiles / a.Hkv) * a.Hq * (a.S / 32);
+  const size_t most = a.S > 128 ? (CAUSAL ? (D == 64 ? 768 : 480) : (D == 64 ? 448 : 320))
+                      : g == 1  ? (a.S > 64 ? 128 : 0)
+                                : std::min(1024, g * (D == 64 ? 256 : a.S > 64 ? 176 : 128));
+  if (units <= most) {
+    hipLaunchKernelGGL((insert_bf16_split_kernel<D, CAUSAL, PACKED>), dim3((unsigned)units), dim3(kThreads), 0, stream, a);
+    return hipGetLastError();
+  }
   if (a.S <= kChunk)
     hipLaunchKernelGGL((insert_bf16_kernel<D, CAUSAL, PACKED, true>), grid, dim3(kThreads), 0, stream, a);
   else
