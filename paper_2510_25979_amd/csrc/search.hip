@@ -511,13 +511,13 @@ struct RowPiece<float> {
   __device__ __forceinline__ float at(int t) const { return w[t]; }
 };
 
-// phase 1 for up to NQ <= 8 queries on the vector ALUs: a stream over the rows.  Eight threads
+// phase 1 for NQ <= 8 queries per workgroup on the vector ALUs: a stream over the rows.  Eight threads
 // read a row side by side in 16-byte pieces, a thread has eight rows (32 apart) in flight, the
 // queries sit in LDS as binary32; a workgroup takes the 256 rows of a group.  Nothing but the queries
 // goes through LDS and no barrier sits in the loop, which is what a memory-bound (or, on a small
 // database, latency-bound) search wants: 1M x 128 fp32, one query, 96 us = 5.3 TB/s (165 us with a
-// thread per row); 200,000 x 768 fp16, one query, 68 us (210 us through the tiles below).  Beyond
-// eight queries the tiles win, their rows feed more queries.
+// thread per row); 200,000 x 768 fp16, one query, 68 us (210 us through the tiles below).  With many
+// queries the tiles win, their rows feed more queries (launch_valu_k).
 template <typename T, bool L2, int NQ, bool TOPK>
 __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArgs a) {
   typedef RowPiece<T> Piece;
@@ -790,11 +790,23 @@ static hipError_t launch_stream(const SearchArgs& a, hipStream_t stream) {
 template <typename T, bool L2, bool TOPK>
 static hipError_t launch_valu_k(const SearchArgs& a, hipStream_t stream) {
   const size_t groups = (size_t)(a.N + kValuRowsPerWg - 1) / kValuRowsPerWg, groups8 = (groups + 7) / 8 * 8;
-  if (a.B <= 8 && a.E <= 4096) {   // (eight queries of 4,096 columns fill 128 KiB of LDS)
-    // one query per workgroup while the chip holds them all at once: a short call is a chain of
-    // latencies (1,024 x 128 fp32, four queries: 7.0 us with four per workgroup, 4.9 us with one)
-    if (groups * a.B <= 512) return launch_stream<T, L2, 1, TOPK>(a, stream);
-    return a.B == 1 ? launch_stream<T, L2, 1, TOPK>(a, stream) : a.B <= 4 ? launch_stream<T, L2, 4, TOPK>(a, stream) : launch_stream<T, L2, 8, TOPK>(a, stream);
+  if (a.E <= 4096) {   // (eight queries of 4,096 columns fill 128 KiB of LDS)
+    constexpr bool kF16 = std::is_same<T, f16_t>::value;
+    // One query per workgroup while the chip holds them all (nearly) at once: a short call is a chain
+    // of latencies, and the other forms leave most of the chip idle.  1,024 x 128 fp32, four queries:
+    // 7.0 us with four per workgroup, 4.9 us with one.  More than eight queries, tiles below / one per
+    // workgroup: 64 against 1,000 x 256 fp16 23.6 / 7.7, 400 against 1,000 x 768 fp16 (1,600 workgroups)
+    // 119 / 34; fp32 64 against 1,000 x 256 17.2 / 9.9, 40 against 5,000 x 128 (800) 11.4 / 10.6, 200
+    // against 2,000 x 128 (1,600) 12.6 / 14.8.
+    if (groups * a.B <= (a.B <= 8 ? 512 : kF16 ? 2048 : 1024)) return launch_stream<T, L2, 1, TOPK>(a, stream);
+    // Larger databases: a stream per eight queries, as long as it beats the tiles.  fp16 tiles pay for
+    // the conversion of every element in LDS: 136,118 x 384, 16 queries 103 us, streams 73; x 256, 32
+    // queries 95 / 85, 64 queries 152 / 151; 200,000 x 128, 16 queries 51.6 / 49.0; x 96, 17 queries 58 / 64.
+    // fp32: 136,118 x 384, 9 queries 72 / 80.
+    if (a.B <= 8 || (kF16 && a.B <= (a.E >= 256 ? 64 : 16)))
+      return a.B == 1   ? launch_stream<T, L2, 1, TOPK>(a, stream)
+             : a.B <= 4 ? launch_stream<T, L2, 4, TOPK>(a, stream)
+                        : launch_stream<T, L2, 8, TOPK>(a, stream);
   }
   // queries per wave: as many as leave some four workgroups per compute unit
   auto blocks = [&](int qw) { return (size_t)((a.B + 4 * qw - 1) / (4 * qw)); };

@@ -30,6 +30,10 @@ VALU_CASES = [
     (3000, 2400, 33, 1, torch.float16, "ip"),   # queries that do not fit in LDS
     (5000, 64, 64, 1, torch.float32, "l2"),     # a small database: one query per wave
     (50000, 16, 64, 1, torch.float32, "ip"),    # two queries per wave
+    (20001, 37, 17, 3, torch.float32, "ip"),    # tiles again: odd width, one query past a block
+    (40000, 40, 33, 4, torch.float16, "l2"),    # and fp16 ones
+    (300, 520, 70, 5, torch.float16, "l2"),     # a small database: a stream per query
+    (70000, 264, 20, 2, torch.float16, "l2"),   # streams of eight queries, four left over
 ]
 
 
