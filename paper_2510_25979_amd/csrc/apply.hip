@@ -24,6 +24,8 @@
 //           only half of its bytes.
 // HBM-bound: per (query, layer, head) the kernel moves S(S+32) map bytes
 // (causal bf16), V once per head group and O once.
+#include <algorithm>
+
 #include "common.hpp"
 #include "f32_tile.hpp"
 #include "launch.hpp"
@@ -39,6 +41,7 @@ struct ApplyArgs {
   int32_t heads_per_wg;  // query heads handled by one workgroup (shares V)
   int32_t n_rblk;        // ceil(S / 128)
   int32_t n_tiles;       // B' * Lc * (Hq / heads_per_wg)
+  int32_t tile0;         // first tile of the launch (fp32 path, see launch_apply_f32)
   int32_t fixed_entry;   // >= 0: every listed query uses maps as this single entry
   int32_t n_list;        // number of valid q_list items when fixed_entry >= 0
   int32_t q_list[32];    // queries served by the staged entry
@@ -554,9 +557,10 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
   const int S = a.S, g = a.Hq / a.Hkv;
   const F32Unit u = f32_unit(blockIdx.x, wave, g, S, a.n_tiles);
   if (u.tile < 0) return;
-  const int h = u.tile % a.Hkv * g + u.head;
-  const int l = (u.tile / a.Hkv) % a.Lc;
-  const int bslot = u.tile / (a.Hkv * a.Lc);
+  const int tile = a.tile0 + u.tile;
+  const int h = tile % a.Hkv * g + u.head;
+  const int l = (tile / a.Hkv) % a.Lc;
+  const int bslot = tile / (a.Hkv * a.Lc);
   int b, entry;
   if (a.fixed_entry >= 0) {
     b = a.q_list[bslot];
@@ -637,10 +641,18 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
 }
 
 template <int DB>
-static hipError_t launch_apply_f32(const ApplyArgs& a, int D, int causal, hipStream_t stream) {
-  const unsigned grid = f32_grid(a.n_tiles, a.Hq / a.Hkv, a.S);
-  hipLaunchKernelGGL((apply_f32_kernel<DB>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal);
-  return hipGetLastError();
+static hipError_t launch_apply_f32(ApplyArgs a, int D, int causal, hipStream_t stream) {
+  // a launch has fewer than 2^32 threads: very many tiles of narrow heads take several
+  const int g = a.Hq / a.Hkv, n_tiles = a.n_tiles;
+  const size_t eights = (((size_t)1 << 32) - 1) / kThreads / f32_grid(8, g, a.S);
+  const int fit = 8 * (int)std::min<size_t>(std::max<size_t>(eights, 1), 1 << 27);
+  for (a.tile0 = 0; a.tile0 < n_tiles; a.tile0 += a.n_tiles) {
+    a.n_tiles = std::min(n_tiles - a.tile0, fit);
+    hipLaunchKernelGGL((apply_f32_kernel<DB>), dim3(f32_grid(a.n_tiles, g, a.S)), dim3(kThreads), 0, stream, a, D, causal);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 static size_t apply_lds_bytes(int D) {
@@ -692,7 +704,7 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
   a.maps = p.maps; a.hit = p.hit; a.V = p.V; a.O = p.O;
   a.M = p.M; a.L = p.L; a.layer_begin = p.layer_begin; a.Lc = p.Lc;
   a.Hq = p.Hq; a.Hkv = p.Hkv; a.S = p.S;
-  a.fixed_entry = p.fixed_entry; a.n_list = p.n_list;
+  a.fixed_entry = p.fixed_entry; a.n_list = p.n_list; a.tile0 = 0;
   for (int i = 0; i < 32; ++i) a.q_list[i] = i < p.n_list ? p.q_list[i] : 0;
   const int nb = p.fixed_entry >= 0 ? p.n_list : p.B;
   if (nb == 0 || p.Lc == 0) return hipSuccess;

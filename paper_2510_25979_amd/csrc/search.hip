@@ -33,7 +33,7 @@ struct SearchArgs {
   const void* q;
   const int32_t* map_of;
   int32_t N, E, B, k, metric;
-  int32_t q0, nq;          // query super-block handled by this launch (phase 1)
+  int32_t q0, nq;          // queries handled by this launch
   int32_t rows, G;         // group size and count (a group: the rows one partial result covers)
   int32_t wg_rows;         // rows one phase-1 workgroup scans: one group (k = 1) or several
   float threshold;
@@ -689,8 +689,8 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the query blocks of one group get ids equal mod 8: one XCD reads the group's rows once
-  const int nqb = (a.B + 4 * QW - 1) / (4 * QW), slot = blockIdx.x >> 3;
-  const int gidx = slot / nqb * 8 + (blockIdx.x & 7), q0 = slot % nqb * (4 * QW);
+  const int nqb = (a.nq + 4 * QW - 1) / (4 * QW), slot = blockIdx.x >> 3;
+  const int gidx = slot / nqb * 8 + (blockIdx.x & 7), q0 = a.q0 + slot % nqb * (4 * QW);
   if (gidx >= (a.N + kValuRowsPerWg - 1) / kValuRowsPerWg) return;
   const T* emb = reinterpret_cast<const T*>(a.emb);
   const T* qs = reinterpret_cast<const T*>(a.q);
@@ -703,7 +703,7 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
     for (int j = 0; j < QW; ++j) acc[r][j] = 0.f;
   TileSlice<T, kValuRowsPerWg * 8 / kThreads> es;
   TileSlice<T, 1> qt;
-  const int q_end = min(a.B, q0 + 4 * QW);
+  const int q_end = min(a.q0 + a.nq, q0 + 4 * QW);
   es.load(emb, row0, a.N, a.E, 0, tid);
   qt.load(qs, q0, q_end, a.E, 0, tid);
   for (int e0 = 0; e0 < a.E; e0 += kTileCols) {
@@ -748,10 +748,10 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
         const int first = row0 + kWave * r;
         const float s = key_score(wave_max(score_key(fmaxf(-INFINITY, first + lane < a.N ? acc[r][j] : -INFINITY))));
         all = fmaxf(all, s);
-        if (a.rows == kWave && lane == 0 && q < a.B && first < a.N)
+        if (a.rows == kWave && lane == 0 && q < q_end && first < a.N)
           a.part_s[(size_t)q * a.G + first / kWave] = s;
       }
-      if (a.rows != kWave && lane == 0 && q < a.B) a.part_s[(size_t)q * a.G + gidx] = all;
+      if (a.rows != kWave && lane == 0 && q < q_end) a.part_s[(size_t)q * a.G + gidx] = all;
     }
     return;
   }
@@ -770,11 +770,29 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
       if (ranks_before(so, io, s, i)) { s = so; i = io; }
     }
     const int q = q0 + QW * wave + j;
-    if (lane == 0 && q < a.B) {
+    if (lane == 0 && q < q_end) {
       a.part_s[(size_t)q * a.G + gidx] = s;
       a.part_i[(size_t)q * a.G + gidx] = i;
     }
   }
+}
+
+constexpr size_t kGridThreads = ((size_t)1 << 32) - 1;   // most threads of a launch in one dimension
+
+template <typename T, bool L2, int QW, bool TOPK>
+static hipError_t launch_tiles(SearchArgs a, size_t groups8, hipStream_t stream) {
+  // the grid is one-dimensional (groups x query blocks, so that it can choose the XCD): a large index
+  // with a large batch takes several launches
+  const size_t fit = kGridThreads / kThreads / groups8 * (4 * QW);   // queries of a launch
+  for (size_t q0 = 0; q0 < (size_t)a.B; q0 += fit) {
+    a.q0 = (int32_t)q0;
+    a.nq = (int32_t)((size_t)a.B - q0 < fit ? (size_t)a.B - q0 : fit);
+    const size_t blocks = (size_t)((a.nq + 4 * QW - 1) / (4 * QW));
+    hipLaunchKernelGGL((search_valu_kernel<T, L2, QW, TOPK>), dim3((unsigned)(groups8 * blocks)), dim3(kThreads), 0, stream, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <typename T, bool L2, int NQ, bool TOPK>
@@ -811,11 +829,9 @@ static hipError_t launch_valu_k(const SearchArgs& a, hipStream_t stream) {
   // queries per wave: as many as leave some four workgroups per compute unit
   auto blocks = [&](int qw) { return (size_t)((a.B + 4 * qw - 1) / (4 * qw)); };
   const int qw = groups * blocks(4) >= 1024 ? 4 : groups * blocks(2) >= 1024 ? 2 : 1;
-  const dim3 grid((unsigned)(groups8 * blocks(qw)));
-  if (qw == 1) hipLaunchKernelGGL((search_valu_kernel<T, L2, 1, TOPK>), grid, dim3(kThreads), 0, stream, a);
-  else if (qw == 2) hipLaunchKernelGGL((search_valu_kernel<T, L2, 2, TOPK>), grid, dim3(kThreads), 0, stream, a);
-  else hipLaunchKernelGGL((search_valu_kernel<T, L2, 4, TOPK>), grid, dim3(kThreads), 0, stream, a);
-  return hipGetLastError();
+  return qw == 1   ? launch_tiles<T, L2, 1, TOPK>(a, groups8, stream)
+         : qw == 2 ? launch_tiles<T, L2, 2, TOPK>(a, groups8, stream)
+                   : launch_tiles<T, L2, 4, TOPK>(a, groups8, stream);
 }
 
 template <typename T>
@@ -1011,7 +1027,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
   uint64_t* lists = reinterpret_cast<uint64_t*>(smem);        // [NT] the waves' best
   int* sel = reinterpret_cast<int*>(lists + NT);              // [kMaxK] selected groups
   float* qf = reinterpret_cast<float*>(sel + kMaxK);          // [E rounded up to 4]
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = a.q0 + blockIdx.x, tid = threadIdx.x;
   float* cand = cand_in_lds ? qf + ((a.E + 3) & ~3) : a.cand + (size_t)b * a.k * a.rows;
   const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
   for (int e = tid; e < ((a.E + 3) & ~3); e += NT) qf[e] = e < a.E ? (float)q[e] : 0.f;
@@ -1220,15 +1236,20 @@ static hipError_t launch_f16_phase1(const SearchArgs& a, int nqb, dim3 grid, siz
 // A query's second phase is one workgroup.  1,024 threads shorten it when there are many groups to
 // pick from or many rows to re-score; below that the barriers of sixteen waves cost more.
 template <typename T, int NT>
-static hipError_t launch_topk_n(const SearchArgs& a, hipStream_t stream) {
+static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
   const size_t lists = (size_t)NT * 8 + kMaxK * 4, query = (size_t)((a.E + 3) & ~3) * 4;
   const size_t cand = (size_t)a.k * a.rows * 4;
   const int in_lds = lists + query + cand <= 64 * 1024;   // the rows' scores: in LDS, else in the workspace
   const size_t lds = lists + query + (in_lds ? cand : 0);
   hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT>>(lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((finalize_topk_kernel<T, NT>), dim3((unsigned)a.B), dim3(NT), lds, stream, a, in_lds);
-  return hipGetLastError();
+  constexpr int kFit = (int)(kGridThreads / NT);   // queries of a launch
+  for (a.q0 = 0; e == hipSuccess && a.q0 < a.B; a.q0 += a.nq) {
+    a.nq = a.B - a.q0 < kFit ? a.B - a.q0 : kFit;
+    hipLaunchKernelGGL((finalize_topk_kernel<T, NT>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 template <typename T>

@@ -1,0 +1,61 @@
+/* Stands in for the HIP runtime so that the library's host code can run without a GPU: launches are
+ * written down instead of executed, every pointer is device memory.  Loaded with global visibility
+ * before the library, whose HIP calls then end up here. */
+#define _GNU_SOURCE
+#define __HIP_PLATFORM_AMD__ 1
+#include <dlfcn.h>
+#include <hip/hip_runtime_api.h>
+#include <stdio.h>
+#include <string.h>
+
+static char text[1 << 22];
+static size_t used;
+static hipError_t last = hipSuccess;
+static struct { dim3 grid, block; size_t lds; hipStream_t stream; } pushed;
+
+const char* recorded(void) { return text; }
+void forget(void) { used = 0; text[0] = 0; }
+
+/* What a launch has to keep to: fewer than 2^32 threads in each dimension of the grid, at most 1,024
+ * in a workgroup, at most 160 KiB of dynamic LDS. */
+static int fits(dim3 g, dim3 b, size_t lds) {
+  const unsigned long long top = 1ull << 32;
+  return g.x && g.y && g.z && (unsigned long long)g.x * b.x < top && (unsigned long long)g.y * b.y < top &&
+         (unsigned long long)g.z * b.z < top && (unsigned long long)b.x * b.y * b.z <= 1024 && lds <= 160 * 1024;
+}
+
+hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t s) {
+  Dl_info info;
+  (void)args; (void)s;
+  const char* name = dladdr(f, &info) && info.dli_sname ? info.dli_sname : "?";
+  used += (size_t)snprintf(text + used, sizeof text - used, "%s %u %u %u %u %zu\n", name, g.x, g.y, g.z, b.x, lds);
+  last = fits(g, b, lds) ? hipSuccess : hipErrorInvalidConfiguration;
+  return last;
+}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t s) {
+  pushed.grid = g; pushed.block = b; pushed.lds = lds; pushed.stream = s;
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* s) {
+  *g = pushed.grid; *b = pushed.block; *lds = pushed.lds; *s = pushed.stream;
+  return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  (void)p;
+  memset(a, 0, sizeof *a);
+  a->type = hipMemoryTypeDevice;
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  (void)s;
+  *st = hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) {
+  const hipError_t e = last;
+  last = hipSuccess;
+  return e;
+}
+hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute a, int v) { (void)f; (void)a; (void)v; return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { (void)s; *p = (void*)4096; return hipSuccess; }

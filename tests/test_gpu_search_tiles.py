@@ -90,3 +90,19 @@ def test_topk_of_equal_rows_names_the_lowest(ac, oracle_mod, case):  # noqa: F81
     idx, score, _ = _run_search(ac, emb, q, k, 0.5, ac.AC_IP)
     want, want_score, _ = oracle_mod.search(parity.to_np(q), parity.to_np(emb), k=k)
     assert (idx.cpu().numpy() == want).all() and (score.cpu().numpy() == want_score).all()
+
+
+def test_more_queries_than_one_launch_of_tiles_takes(ac):  # noqa: F811
+    # 39,064 groups of 256 rows (rounded up to eights) leave a launch of 2^32 threads room for 429 blocks of 16 queries
+    N, E, B = 10_000_000, 4, 8192
+    g = torch.Generator(device="cuda").manual_seed(3)
+    emb = torch.randn(N, E, generator=g, device="cuda")
+    rows = torch.randint(0, N, (B,), generator=g, device="cuda")
+    q = emb[rows] + 1e-3
+    idx, score, _ = _run_search(ac, emb, q, 1, 0.5, ac.AC_L2)
+    for b in (0, 429 * 16 - 1, 429 * 16, B - 1):
+        want = -(q[b].double() - emb.double()).square().sum(1)
+        best = want.max()
+        assert abs(score[b, 0].item() - best.item()) <= parity.REL_TIE * abs(best.item())
+        assert want[idx[b, 0].long()] >= best * (1 + parity.REL_TIE)
+    assert (idx >= 0).all() and (score <= 0).all()
