@@ -27,6 +27,9 @@ constexpr int kQPad = 8;            // fp16 elements of padding per staged query
 constexpr int kValuRowsPerWg = 256;
 constexpr int kIdxNone = 0x7fffffff;
 constexpr int kMaxK = 64;           // AC_MAX_K of the C interface
+// Maximum of a group (k > 1) in which no row ranks, every score being NaN.  -infinity is a score like
+// any other: a group that holds one comes before a group that holds none.
+constexpr float kNoRow = __builtin_nanf("");
 
 struct SearchArgs {
   const void* emb;
@@ -37,7 +40,7 @@ struct SearchArgs {
   int32_t rows, G;         // group size and count (a group: the rows one partial result covers)
   int32_t wg_rows;         // rows one phase-1 workgroup scans: one group (k = 1) or several
   float threshold;
-  float* part_s;           // [B][G] best score of each group
+  float* part_s;           // [B][G] best score of each group (k > 1: kNoRow where no row ranks)
   int32_t* part_i;         // [B][G] its row (k = 1 only)
   float* cand;             // [B][k * rows] scores of the selected groups' rows (k > 1 only)
   int32_t* idx;
@@ -121,10 +124,11 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
   }
   __syncthreads();
 
+  constexpr float none = TOPK ? kNoRow : -INFINITY;
   float best_s[NQB];
   int best_i[NQB];
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) { best_s[qb] = -INFINITY; best_i[qb] = kIdxNone; }
+  for (int qb = 0; qb < NQB; ++qb) { best_s[qb] = none; best_i[qb] = kIdxNone; }
 
   const int row_begin = blockIdx.x * a.wg_rows;
   const int row_end = min(row_begin + a.wg_rows, a.N);
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int r = rb + mfma_row(v, kh);
-        const float s = r < a.N ? acc[v] : -INFINITY;
+        const float s = r < a.N ? acc[v] : none;
         if (TOPK) {
           best_s[qb] = fmaxf(best_s[qb], s);
         } else if (s > best_s[qb]) {
@@ -209,7 +213,7 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
         const float s = fmaxf(best_s[qb], __shfl_xor(best_s[qb], 32));
-        best_s[qb] = -INFINITY;
+        best_s[qb] = none;
         const int t = 32 * qb + il;
         if (!per_wave) {
           if (kh == 0) red_s[wave * 32 * NQB + t] = s;
@@ -340,10 +344,11 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
     __builtin_amdgcn_sched_barrier(0);
   };
 
+  constexpr float none = TOPK ? kNoRow : -INFINITY;
   float best_s[QPW];
   int best_i[QPW];
 #pragma unroll
-  for (int j = 0; j < QPW; ++j) { best_s[j] = -INFINITY; best_i[j] = kIdxNone; }
+  for (int j = 0; j < QPW; ++j) { best_s[j] = none; best_i[j] = kIdxNone; }
 
   // RAGGED is a literal at both call sites and the body is inlined: the copy used for complete
   // chunks carries no per-row tests
@@ -392,7 +397,7 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
         for (int j = 0; j < QPW; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            if (rbase + 8 * (v >> 2) + (v & 3) >= row_end) acc[j][v] = -INFINITY;
+            if (rbase + 8 * (v >> 2) + (v & 3) >= row_end) acc[j][v] = none;
       }
       // Only WHICH 32-row block holds a lane's best score is remembered (one compare and two
       // selects per block and query block); the row inside that block is found by the
@@ -426,7 +431,7 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
 #pragma unroll
         for (int j = 0; j < QPW; ++j) {
           const float s = fmaxf(best_s[j], __shfl_xor(best_s[j], 32));
-          best_s[j] = -INFINITY;
+          best_s[j] = none;
           const int qi = 32 * (QPW * wave + j) + il;
           if (kh == 0 && qi < a.nq) a.part_s[(size_t)(a.q0 + qi) * a.G + gi] = s;
         }
@@ -595,16 +600,15 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
     AC_HALVE(2, 2, 0x4e)    // quad_perm 2 3 0 1: lane p ^ 2
     AC_HALVE(1, 1, 0xb1)    // quad_perm 1 0 3 2: lane p ^ 1
 #undef AC_HALVE
-    const float s = fmaxf(-INFINITY, r < a.N ? v[0] : -INFINITY);   // a NaN never ranks
     if (TOPK) {   // groups of 64 rows: threads 2 p and 2 p + 1 of every eight
-      float m = s;
+      float m = r < a.N ? v[0] : kNoRow;
 #pragma unroll
       for (int off = 1; off < kWave; off = off == 1 ? 8 : 2 * off) m = fmaxf(m, __shfl_xor(m, off));
       if (lane < 8) red_s[wave][j][TOPK ? lane >> 1 : 0] = m;
     } else {
-      const bool ranks = r < a.N && v[0] == v[0];
-      const uint32_t top = wave_max(ranks ? score_key(s) : 0u);
-      const uint32_t low = wave_max(ranks && score_key(s) == top ? ~(uint32_t)r : 0u);   // lowest row
+      const bool ranks = r < a.N && v[0] == v[0];   // a NaN never ranks
+      const uint32_t key = ranks ? score_key(v[0]) : 0u, top = wave_max(key);
+      const uint32_t low = wave_max(ranks && key == top ? ~(uint32_t)r : 0u);   // lowest row
       if (lane == 0) {
         red_s[wave][j][0] = top ? key_score(top) : -INFINITY;
         red_i[wave][j] = top ? (int)~low : kIdxNone;
@@ -615,7 +619,7 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
   if (tid >= NQ || q0 + tid >= a.B) return;
   const size_t out = (size_t)(q0 + tid) * a.G;
   if (TOPK) {
-    float all = -INFINITY;
+    float all = kNoRow;
     for (int p = 0; p < U / 2; ++p) {
       const int pp = TOPK ? p : 0;
       const float v = fmaxf(fmaxf(red_s[0][tid][pp], red_s[1][tid][pp]), fmaxf(red_s[2][tid][pp], red_s[3][tid][pp]));
@@ -742,11 +746,12 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
 #pragma unroll
     for (int j = 0; j < QW; ++j) {
       const int q = q0 + QW * wave + j;
-      float all = -INFINITY;
+      float all = kNoRow;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const int first = row0 + kWave * r;
-        const float s = key_score(wave_max(score_key(fmaxf(-INFINITY, first + lane < a.N ? acc[r][j] : -INFINITY))));
+        const bool ranks = first + lane < a.N && acc[r][j] == acc[r][j];
+        const float s = key_score(wave_max(ranks ? score_key(acc[r][j]) : 0u));   // (no key: a NaN)
         all = fmaxf(all, s);
         if (a.rows == kWave && lane == 0 && q < q_end && first < a.N)
           a.part_s[(size_t)q * a.G + first / kWave] = s;
@@ -1036,7 +1041,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
   const float* part = a.part_s + (size_t)b * a.G;
   const int ng = min(a.k, a.G);
   select_best<NT>(
-      a.G, ng, [&](int x) { return item_key(part[x], x); }, [&](int r, float, int i) { sel[r] = i; }, lists);
+      a.G, ng, [&](int x) { return part[x] == part[x] ? item_key(part[x], x) : 0; }, [&](int r, float, int i) { sel[r] = i; }, lists);
 
   // 2. the scores of their rows
   const int n_rows = ng * a.rows, shift = __builtin_ctz(a.rows);   // group sizes are powers of two

@@ -106,3 +106,27 @@ def test_more_queries_than_one_launch_of_tiles_takes(ac):  # noqa: F811
         assert abs(score[b, 0].item() - best.item()) <= parity.REL_TIE * abs(best.item())
         assert want[idx[b, 0].long()] >= best * (1 + parity.REL_TIE)
     assert (idx >= 0).all() and (score <= 0).all()
+
+
+@pytest.mark.parametrize("case", [
+    # N, E, B, k, dtype, metric: one per phase-1 kernel
+    (3000, 8, 3, 5, torch.float32, "l2"),        # streams, one query each
+    (60000, 8, 7, 5, torch.float32, "l2"),       # streams of eight queries
+    (3000, 8, 200, 5, torch.float32, "ip"),      # tiles
+    (3000, 64, 9, 5, torch.float16, "ip"),       # matrix cores, rows in registers
+    (3000, 520, 40, 5, torch.float16, "ip"),     # rows wider than that
+    (60000, 128, 9, 5, torch.float16, "ip"),     # queries in registers
+], ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (*c[:4], str(c[4]).split(".")[-1], c[5]))
+def test_topk_ranks_minus_infinity_before_rows_of_nan(ac, case):  # noqa: F811
+    # whole groups of NaN rows, then rows at -infinity, one finite row late among them
+    N, E, B, k, dt, metric = case
+    emb = torch.full((N, E), 0.5, dtype=dt)
+    emb[:N // 2, 0] = float("nan")
+    emb[N // 2:, E - 1] = float("-inf")
+    best = N - 20
+    emb[best, E - 1] = 0.25
+    m = ac.AC_IP if metric == "ip" else ac.AC_L2
+    idx, score, hit = _run_search(ac, emb, torch.ones(B, E, dtype=dt), k, -1e9, m)
+    want = torch.tensor([best, *range(N // 2, N // 2 + k - 1)], dtype=torch.int32)
+    assert (idx.cpu() == want).all() and (hit == best).all()
+    assert score[:, 0].isfinite().all() and (score[:, 1:] == float("-inf")).all()
