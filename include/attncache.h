@@ -200,7 +200,8 @@ int32_t attncache_destroy_db(attncache_db *db);
  *   score     DEVICE [B][k] float out: fp32 scores (see AC_IP / AC_L2).
  *   hit       DEVICE [B] int32 out: map entry (map_of[idx[b][0]]) for a hit,
  *             -1 for a miss.
- *   ws        DEVICE workspace of ws_bytes >= attncache_workspace_bytes().
+ *   ws        DEVICE workspace of ws_bytes >= attncache_workspace_bytes() for
+ *             this or any larger max_batch.
  *
  * B == 0 is a no-op.  Scores are accumulated in fp32; the order of the
  * additions depends on the kernel that serves the shape, so two rows whose
@@ -223,8 +224,8 @@ int32_t attncache_search(const attncache_db *db, const void *q, int32_t B,
  * the library's code object: every GPU the library runs on holds one copy
  * until the process ends.  The call allocates and frees nothing.
  *
- * Limit: shapes whose attncache_workspace_bytes() exceeds
- * AC_STATIC_SCRATCH_BYTES return AC_ERR_WORKSPACE (k = 1 fits up to about
+ * Limit: batches that need more workspace than AC_STATIC_SCRATCH_BYTES
+ * return AC_ERR_WORKSPACE (k = 1 fits up to about
  * 1,000 queries on a million-row index; large k on a large index does not).
  * All calls on one GPU share the one array: calls that overlap in time on
  * the same GPU (two streams, two threads, two handles) race and give wrong

@@ -181,8 +181,8 @@ int32_t attncache_workspace_bytes(const attncache_db_desc* desc, int32_t max_bat
   if (rc != AC_OK) return rc;
   if (max_batch < 0) return AC_ERR_SHAPE;
   if (k < 1 || k > AC_MAX_K || k > desc->n_emb) return AC_ERR_K_RANGE;
-  *out = ac::search_workspace_bytes(desc->n_emb, desc->emb_dim, max_batch, k,
-                                    desc->emb_dtype == AC_F16);
+  *out = ac::search_workspace_bytes_up_to(desc->n_emb, desc->emb_dim, max_batch, k,
+                                          desc->emb_dtype == AC_F16);
   return AC_OK;
 }
 

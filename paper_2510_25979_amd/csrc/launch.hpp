@@ -85,7 +85,8 @@ struct SearchLaunch {
   void* ws;
   size_t ws_bytes;
 };
-size_t search_workspace_bytes(int32_t N, int32_t E, int32_t B, int32_t k, int32_t is_f16);
+size_t search_workspace_bytes(int32_t N, int32_t E, int32_t B, int32_t k, int32_t is_f16);   // B queries
+size_t search_workspace_bytes_up_to(int32_t N, int32_t E, int32_t max_batch, int32_t k, int32_t is_f16);
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream);
 
 struct ProjectLaunch {

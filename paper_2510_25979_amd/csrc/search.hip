@@ -1204,6 +1204,15 @@ size_t search_workspace_bytes(int32_t N, int32_t E, int32_t B, int32_t k, int32_
   return need + 256;
 }
 
+// The same for any batch of up to max_batch queries.  Within a mode the size grows with the batch; the one
+// change of mode that changes the groups is at kBigBatch, where more queries can need less.
+size_t search_workspace_bytes_up_to(int32_t N, int32_t E, int32_t max_batch, int32_t k, int32_t is_f16) {
+  const size_t own = search_workspace_bytes(N, E, max_batch, k, is_f16);
+  if (max_batch <= kBigBatch) return own;
+  const size_t below = search_workspace_bytes(N, E, kBigBatch, k, is_f16);
+  return own > below ? own : below;
+}
+
 template <int KSMAX, int QPW>
 static hipError_t launch_f16_big(const SearchArgs& a, dim3 grid, hipStream_t stream) {
   if (a.k > 1)

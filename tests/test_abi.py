@@ -104,6 +104,21 @@ def test_workspace_sizes_follow_the_search_plan():
     assert ws(10000, 256, 128, 1) > ws(10000, 256, 64, 1)
 
 
+def test_workspace_for_up_to_a_batch_holds_every_smaller_batch():
+    """Above 64 queries the groups of a search can get larger and its need smaller."""
+    from paper_2510_25979_amd import binding
+    for N in (100, 3000, 30000, 49999, 50000, 140000, 1000000):
+        for E, dt in ((128, binding.AC_F16), (256, binding.AC_F16), (96, binding.AC_F16), (520, binding.AC_F16),
+                      (256, binding.AC_F32)):
+            d = binding.DbDesc(n_emb=N, emb_dim=E, emb_dtype=dt, metric=binding.AC_IP, n_entries=1, n_layers=1, n_q_heads=1,
+                               n_kv_heads=1, head_dim=64, seq_len=32, map_dtype=binding.AC_BF16, causal=1, maps_on_host=0,
+                               map_layout=0)
+            for k in (1, 2, 8, 64):
+                sizes = [binding.attncache_workspace_bytes(d, B, k)
+                         for B in (0, 1, 8, 9, 32, 63, 64, 65, 66, 100, 128, 129, 256, 257, 1000)]
+                assert sizes == sorted(sizes), (N, E, k, sizes)
+
+
 def test_product_path_does_not_touch_the_oracle():
     pkg = os.path.join(ROOT, "paper_2510_25979_amd")
     for dirpath, _, files in os.walk(pkg):
