@@ -123,10 +123,14 @@ def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> int:
 
 def _stream(stream: Optional[torch.cuda.Stream]) -> int:
     """The raw stream handle.  The current one is asked for directly: building a torch.cuda.Stream
-    object to read it from took 2.7 of the 9.5 us a call spent on the host (6.9 us so)."""
+    object to read it from took 2.7 of the 9.5 us a call spent on the host (6.9 us so).  The two
+    functions are not part of torch's documented interface; a torch without them goes the long way."""
     if stream is not None:
         return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
 
 
 class Database:

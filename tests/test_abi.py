@@ -119,6 +119,20 @@ def test_workspace_for_up_to_a_batch_holds_every_smaller_batch():
                 assert sizes == sorted(sizes), (N, E, k, sizes)
 
 
+def test_current_stream_without_the_undocumented_lookup(monkeypatch):
+    import types
+
+    import torch
+    from paper_2510_25979_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 55)
+    assert binding._stream(None) == 55
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert binding._stream(None) == 77
+    assert binding._stream(types.SimpleNamespace(cuda_stream=3)) == 3
+
+
 def test_product_path_does_not_touch_the_oracle():
     pkg = os.path.join(ROOT, "paper_2510_25979_amd")
     for dirpath, _, files in os.walk(pkg):
