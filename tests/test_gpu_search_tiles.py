@@ -68,6 +68,11 @@ TOPK_CASES = [
     (30001, 20, 3, 2, torch.float32, "l2"),   # 64-row groups
     (60001, 20, 3, 2, torch.float32, "l2"),       # 256-row groups
     (1100000, 8, 2, 64, torch.float16, "ip"),     # more groups than registers hold
+    (64, 64, 3, 64, torch.float16, "ip"),         # ranks by counting: all rows
+    (993, 64, 2, 2, torch.float16, "ip"),         # 32 groups, 16 to a draw; 64 rows are drawn
+    (1024, 64, 2, 64, torch.float16, "ip"),       # 1,024 rows, one per thread
+    (1100, 64, 2, 63, torch.float16, "ip"),       # more than that
+    (257, 5, 4, 4, torch.float32, "l2"),          # the last group holds one row
 ]
 
 
