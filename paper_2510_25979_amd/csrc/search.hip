@@ -25,10 +25,12 @@ namespace ac {
 
 constexpr int kQPad = 8;            // fp16 elements of padding per staged query row
 constexpr int kValuRowsPerWg = 256;
+constexpr int kNarrowBytes = 160;   // widest rows of search_row_kernel
 constexpr int kIdxNone = 0x7fffffff;
 constexpr int kMaxK = 64;           // AC_MAX_K of the C interface
 // Maximum of a group (k > 1) in which no row ranks, every score being NaN.  -infinity is a score like
-// any other: a group that holds one comes before a group that holds none.
+// any other: a group that holds one comes before a group that holds none.  (Rows past the end count as
+// -infinity: they are in the last group only, which no other group has to come after.)
 constexpr float kNoRow = __builtin_nanf("");
 
 struct SearchArgs {
@@ -145,7 +147,7 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int r = rb + mfma_row(v, kh);
-        const float s = r < a.N ? acc[v] : none;
+        const float s = r < a.N ? acc[v] : -INFINITY;
         if (TOPK) {
           best_s[qb] = fmaxf(best_s[qb], s);
         } else if (s > best_s[qb]) {
@@ -397,7 +399,7 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
         for (int j = 0; j < QPW; ++j)
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            if (rbase + 8 * (v >> 2) + (v & 3) >= row_end) acc[j][v] = none;
+            if (rbase + 8 * (v >> 2) + (v & 3) >= row_end) acc[j][v] = -INFINITY;
       }
       // Only WHICH 32-row block holds a lane's best score is remembered (one compare and two
       // selects per block and query block); the row inside that block is found by the
@@ -601,7 +603,7 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
     AC_HALVE(1, 1, 0xb1)    // quad_perm 1 0 3 2: lane p ^ 1
 #undef AC_HALVE
     if (TOPK) {   // groups of 64 rows: threads 2 p and 2 p + 1 of every eight
-      float m = r < a.N ? v[0] : kNoRow;
+      float m = r < a.N ? v[0] : -INFINITY;
 #pragma unroll
       for (int off = 1; off < kWave; off = off == 1 ? 8 : 2 * off) m = fmaxf(m, __shfl_xor(m, off));
       if (lane < 8) red_s[wave][j][TOPK ? lane >> 1 : 0] = m;
@@ -616,7 +618,7 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
     }
   }
   __syncthreads();
-  if (tid >= NQ || q0 + tid >= a.B) return;
+  if (tid >= NQ || q0 + tid >= a.B || row0 >= a.N) return;   // (the grid may be padded, see stream_groups)
   const size_t out = (size_t)(q0 + tid) * a.G;
   if (TOPK) {
     float all = kNoRow;
@@ -635,6 +637,61 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
     a.part_s[out + blockIdx.x] = s;
     a.part_i[out + blockIdx.x] = i;
   }
+}
+
+// phase 1 for narrow rows: a thread per row, a workgroup per group of 256 rows and query.  A row is a few
+// pieces, which leave the eight threads of the stream above little to share and the tiles below mostly
+// padding.  Every score is one chain of fmas over ascending columns.
+template <typename T, bool L2, bool TOPK>
+__global__ __launch_bounds__(kThreads) void search_row_kernel(const SearchArgs a) {
+  typedef RowPiece<T> Piece;
+  constexpr int P = Piece::P;
+  __shared__ __attribute__((aligned(16))) float qf[kNarrowBytes / sizeof(T)];
+  __shared__ float red_s[4];
+  __shared__ int red_i[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.y, gidx = blockIdx.x, r = gidx * kValuRowsPerWg + tid;
+  if (gidx * kValuRowsPerWg >= a.N) return;   // (padding)
+  const T* row = reinterpret_cast<const T*>(a.emb) + (size_t)min(r, a.N - 1) * a.E;
+  Piece now;   // on its way while the query is staged
+  now.load(row, 0, a.E);
+  if (tid < ((a.E + P - 1) & -P))
+    qf[tid] = tid < a.E ? (float)reinterpret_cast<const T*>(a.q)[(size_t)b * a.E + tid] : 0.f;
+  __syncthreads();
+  float s = 0.f;
+#pragma unroll 2
+  for (int c = 0; c < a.E; c += P) {
+    Piece next;
+    next.load(row, c + P < a.E ? c + P : c, a.E);
+#pragma unroll
+    for (int t = 0; t < P; ++t) {
+      const float q = qf[c + t];
+      const float d = q - now.at(t);
+      s = L2 ? fmaf(-d, d, s) : fmaf(q, now.at(t), s);
+    }
+    now = next;
+  }
+  const bool ranks = r < a.N && s == s;
+  const uint32_t key = ranks ? score_key(s) : 0u, top = wave_max(key);
+  if (TOPK && a.rows == kWave) {   // the wave's rows are a group
+    if (lane == 0 && r < a.N) a.part_s[(size_t)b * a.G + r / kWave] = key_score(top);
+    return;
+  }
+  const uint32_t low = TOPK ? 0u : wave_max(ranks && key == top ? ~(uint32_t)r : 0u);   // lowest row
+  if (lane == 0) {
+    red_s[wave] = TOPK || top ? key_score(top) : -INFINITY;
+    red_i[wave] = top ? (int)~low : kIdxNone;
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  s = red_s[0];
+  int i = red_i[0];
+  for (int w = 1; w < 4; ++w) {
+    if (TOPK) s = fmaxf(s, red_s[w]);
+    else if (ranks_before(red_s[w], red_i[w], s, i)) { s = red_s[w]; i = red_i[w]; }
+  }
+  a.part_s[(size_t)b * a.G + gidx] = s;
+  if (!TOPK) a.part_i[(size_t)b * a.G + gidx] = i;
 }
 
 // phase 1 on the vector ALUs (binary32 databases, the Euclidean metric, and the fp16 widths that no
@@ -800,36 +857,78 @@ static hipError_t launch_tiles(SearchArgs a, size_t groups8, hipStream_t stream)
   return hipSuccess;
 }
 
+// Groups of the grid: with a multiple of eight one XCD gets a group's rows for every query block, and they come
+// from its L2 after the first time.  22,464 x 768 fp16 (88 groups), nine queries, 24 us; 20,000 rows (79 groups) 42
+// unpadded.  Not where it would leave more than an eighth of the XCDs' time idle.
+static unsigned stream_groups(int32_t N) {
+  const unsigned groups = (unsigned)(((size_t)N + kValuRowsPerWg - 1) / kValuRowsPerWg), padded = (groups + 7) / 8 * 8;
+  return (padded - groups) * 8 <= groups ? padded : groups;
+}
+
+constexpr size_t kStreamLds = 128 * 1024;   // eight queries of 4,096 columns
+static size_t stream_lds(int nq, int E) { return (size_t)nq * ((E + 7) & ~7) * 4; }
+
 template <typename T, bool L2, int NQ, bool TOPK>
 static hipError_t launch_stream(const SearchArgs& a, hipStream_t stream) {
-  const size_t lds = (size_t)NQ * ((a.E + 7) & ~7) * 4;
+  const size_t lds = stream_lds(NQ, a.E);
   hipError_t e = ensure_lds<&search_stream_kernel<T, L2, NQ, TOPK>>(lds);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)((a.N + kValuRowsPerWg - 1) / kValuRowsPerWg), (unsigned)((a.B + NQ - 1) / NQ));
+  const dim3 grid(stream_groups(a.N), (unsigned)((a.B + NQ - 1) / NQ));
   hipLaunchKernelGGL((search_stream_kernel<T, L2, NQ, TOPK>), grid, dim3(kThreads), lds, stream, a);
   return hipGetLastError();
 }
 
 template <typename T, bool L2, bool TOPK>
+static hipError_t launch_rows(const SearchArgs& a, hipStream_t stream) {
+  const dim3 grid(stream_groups(a.N), (unsigned)a.B);
+  hipLaunchKernelGGL((search_row_kernel<T, L2, TOPK>), grid, dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
+// Rows so narrow that a thread reads one whole: 16 bytes always; more while the threads' reads, a row
+// apart, stay in the caches or the call is short.  (Rows 128 bytes apart fall on the same channels.)
+// us per call, this way / the best other one: 300,000 x 8 fp16, 8 queries 11.3 / 21.3; 4,000 x 40, 200
+// queries, Euclidean 8.4 / 12.0; 20,000 x 8 fp32, 64 queries 8.2 / 9.9; 20,000 x 32, 8 queries 9.5 / 6.8;
+// 20,000 x 37, one query 5.7 / 7.5, 8 queries 12.0 / 9.1.
+static bool narrow_rows(int32_t is_f16, int32_t E, int32_t B, int32_t N) {
+  const size_t bytes = (size_t)E * (is_f16 ? 2 : 4), pieces = (bytes + 15) / 16;
+  const size_t work = (size_t)((N + kValuRowsPerWg - 1) / kValuRowsPerWg) * B;   // workgroups
+  if (bytes > kNarrowBytes || bytes % 128 == 0 || B > 65535) return false;   // (B: a dimension of the grid)
+  return bytes <= 16 || work * pieces <= 3300 || (bytes <= 32 && work <= 16384) || (bytes <= 48 && work <= 8192) ||
+         (N * bytes <= 640 * 1024 && work * pieces <= (is_f16 ? 24000 : 5000));
+}
+
+template <typename T, bool L2, bool TOPK>
 static hipError_t launch_valu_k(const SearchArgs& a, hipStream_t stream) {
+  constexpr bool kF16 = std::is_same<T, f16_t>::value;
   const size_t groups = (size_t)(a.N + kValuRowsPerWg - 1) / kValuRowsPerWg, groups8 = (groups + 7) / 8 * 8;
-  if (a.E <= 4096) {   // (eight queries of 4,096 columns fill 128 KiB of LDS)
-    constexpr bool kF16 = std::is_same<T, f16_t>::value;
+  if (narrow_rows(kF16, a.E, a.B, a.N)) return launch_rows<T, L2, TOPK>(a, stream);
+  auto fits = [&](int nq) { return stream_lds(nq, a.E) <= kStreamLds; };
+  if (fits(1)) {
     // One query per workgroup while the chip holds them all (nearly) at once: a short call is a chain
     // of latencies, and the other forms leave most of the chip idle.  1,024 x 128 fp32, four queries:
     // 7.0 us with four per workgroup, 4.9 us with one.  More than eight queries, tiles below / one per
-    // workgroup: 64 against 1,000 x 256 fp16 23.6 / 7.7, 400 against 1,000 x 768 fp16 (1,600 workgroups)
-    // 119 / 34; fp32 64 against 1,000 x 256 17.2 / 9.9, 40 against 5,000 x 128 (800) 11.4 / 10.6, 200
-    // against 2,000 x 128 (1,600) 12.6 / 14.8.
-    if (groups * a.B <= (a.B <= 8 ? 512 : kF16 ? 2048 : 1024)) return launch_stream<T, L2, 1, TOPK>(a, stream);
-    // Larger databases: a stream per eight queries, as long as it beats the tiles.  fp16 tiles pay for
-    // the conversion of every element in LDS: 136,118 x 384, 16 queries 103 us, streams 73; x 256, 32
-    // queries 95 / 85, 64 queries 152 / 151; 200,000 x 128, 16 queries 51.6 / 49.0; x 96, 17 queries 58 / 64.
-    // fp32: 136,118 x 384, 9 queries 72 / 80.
-    if (a.B <= 8 || (kF16 && a.B <= (a.E >= 256 ? 64 : 16)))
-      return a.B == 1   ? launch_stream<T, L2, 1, TOPK>(a, stream)
-             : a.B <= 4 ? launch_stream<T, L2, 4, TOPK>(a, stream)
-                        : launch_stream<T, L2, 8, TOPK>(a, stream);
+    // workgroup: 64 against 1,000 x 256 fp16 23.6 / 7.7; fp32 64 against 1,000 x 256 17.2 / 9.9, 40 against 5,000 x 128 (800
+    // workgroups) 11.4 / 10.6, 200 against 2,000 x 128 (1,600) 12.6 / 14.8.  Very wide fp32 rows of a larger database
+    // are better shared: 20,000 x 8,192, four queries (316) 414 / 343 in tiles, but 64 x 4,608, 400 (400) 93 / 374.
+    const size_t one = groups <= 32 && kF16 ? 640 : !fits(8) && !kF16 ? (a.B <= 8 ? 256 : 512)
+                       : a.B <= 8 ? 512 : kF16 ? 1400 : 1024;
+    if (groups * a.B <= one) return launch_stream<T, L2, 1, TOPK>(a, stream);
+    // fp16 tiles pay for the conversion of every element in LDS: streams of four queries win while their
+    // workgroups are few.  One query each / four / tiles: 400 against 1,000 x 768 (1,600) 33 / 24 / 112; 200 against
+    // 4,000 x 264, Euclidean (3,200) 66 / 30 / 49, 400 of them (6,400) 66 / 44 / 73.
+    if (kF16 && a.B > 8 && fits(4) && groups * a.B <= 6500) return launch_stream<T, L2, 4, TOPK>(a, stream);
+    // Larger databases: a stream per eight queries, as long as it beats the tiles.
+    // fp16: 136,118 x 384, 16 queries 103 us in tiles, streams 73; x 256, 32
+    // queries 95 / 85, 64 queries 152 / 151; 200,000 x 128, 16 queries 51.6 / 49.0; x 96, 17 queries 58 / 64;
+    // 300,000 x 72, 16 queries 45 / 70.  fp32: 136,118 x 384, 9 queries 72 / 80.  Rows that leave LDS room for fewer
+    // queries: fp16 20,000 x 8,192, 8 queries 876 / 226 four each; 10,000 x 12,000, 32 queries 1,608 / 508 one each.
+    if (a.B == 1 || (a.B <= 8 && (kF16 || fits(8))) || (kF16 && a.B <= (a.E >= 256 ? 64 : a.E >= 96 ? 16 : 8))) {
+      if (a.B == 1 || !fits(4)) return launch_stream<T, L2, 1, TOPK>(a, stream);
+      // (five to eight queries of a database of few groups: two workgroups each, 20,000 x 768 fp16 29 -> 23 us)
+      if (a.B <= 4 || !fits(8) || (a.B <= 8 && groups <= 256)) return launch_stream<T, L2, 4, TOPK>(a, stream);
+      return launch_stream<T, L2, 8, TOPK>(a, stream);
+    }
   }
   // queries per wave: as many as leave some four workgroups per compute unit
   auto blocks = [&](int qw) { return (size_t)((a.B + 4 * qw - 1) / (4 * qw)); };
@@ -1050,7 +1149,7 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {
   typedef RowPiece<T> Piece;
-  constexpr int P = Piece::P, U = 4, RPT = NT / 8;   // rows in flight per thread, rows per trip and step
+  constexpr int P = Piece::P, RPT = NT / 8;   // rows per step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint64_t* lists = reinterpret_cast<uint64_t*>(smem);        // [NT] the waves' best
   int* sel = reinterpret_cast<int*>(lists + NT);              // [kMaxK] selected groups
@@ -1069,7 +1168,9 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
   // 2. the scores of their rows
   const int n_rows = ng * a.rows, shift = __builtin_ctz(a.rows);   // group sizes are powers of two
   const int part8 = tid & 7;
-  for (int slot0 = tid >> 3; slot0 < n_rows; slot0 += U * RPT) {
+  // (the last RPT rows or fewer alone: the other three of every thread would be repeats)
+  auto score_rows = [&](auto rows_in_flight, int slot0) {
+    constexpr int U = decltype(rows_in_flight)::value;
     const T* row[U];
     bool live[U];
     float acc[U];
@@ -1109,6 +1210,10 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
       if (part8 == 0 && slot0 + u * RPT < n_rows)
         cand[slot0 + u * RPT] = live[u] ? acc[u] : __builtin_nanf("");   // never ranks
     }
+  };
+  for (int first = 0; first < n_rows; first += 4 * RPT) {
+    if (n_rows - first > RPT) score_rows(std::integral_constant<int, 4>{}, first + (tid >> 3));
+    else score_rows(std::integral_constant<int, 1>{}, first + (tid >> 3));
   }
   __syncthreads();
 
@@ -1201,11 +1306,19 @@ static size_t f16_lds_bytes(int nqb, int E) {
 }
 constexpr size_t kF16Lds = 150 * 1024;
 
-static int search_mode(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N) {
+static int search_mode(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
   if (!use_mfma(is_f16, metric, E)) {
-    // inner products of other fp16 widths: up to eight queries are a stream over the rows, which
-    // the vector ALUs follow; more are matrix work while a block of 32 queries fits in LDS
-    return is_f16 && metric == 0 && B > 8 && f16_lds_bytes(1, E) <= kF16Lds ? kModeMfmaWide : kModeValu;
+    // Inner products of other fp16 widths: up to eight queries are a stream over the rows, which
+    // the vector ALUs follow; more are matrix work while a block of 32 queries fits in LDS and there
+    // are workgroups (256 rows and up to 128 queries each) to go round.  us per call, matrix cores /
+    // streams of one query / of four: 300 x 520, 64 queries 18.3 / 9.2 / 15.7; 1,000 x 520, 200 queries
+    // 38.9 / 20.2 / 15.6, 400 queries 30.9 / 34 / 20.6; 4,000 x 520, 16 queries 11.8 / 10.2 / 15.6, 32 queries 12.3 / 13.8 / 15.6,
+    // 200 queries 40 / 61 / 32; 7,500 x 1,536, 64 queries 37 / - / 49; 4,000 x 264, 400 queries 21.5 / 62 / 32; 20,000 x 136, 9 queries 8.1 / 13.5 / 10.3.
+    const size_t groups = (size_t)(N + kValuRowsPerWg - 1) / kValuRowsPerWg;
+    if (!is_f16 || metric != 0 || B <= 8 || f16_lds_bytes(1, E) > kF16Lds) return kModeValu;
+    if (k > 1) return kModeMfmaWide;   // whose groups of 32 rows leave less to re-score: 4,000 x 520, 64 queries, k = 4 22.2 / 37 / 29.8
+    if (groups * B <= 448 || (B > 32 && groups * ((B + 127) / 128) <= (B > 128 ? 32 : 16))) return kModeValu;
+    return groups <= 32 && narrow_rows(is_f16, E, B, N) ? kModeValu : kModeMfmaWide;
   }
   const bool big_shape = E == 128 || E == 256 || E == 512;   // instantiated widths
   // the query-stationary kernel streams a large database faster at any batch size (1M x 256:
@@ -1219,7 +1332,7 @@ size_t search_workspace_bytes(int32_t N, int32_t E, int32_t B, int32_t k, int32_
   size_t need = 0;
   for (int metric = 0; metric < 2; ++metric) {
     int32_t rpw, G;
-    search_plan(N, search_mode(is_f16, metric, E, B, N), k, &rpw, &G);
+    search_plan(N, search_mode(is_f16, metric, E, B, N, k), k, &rpw, &G);
     size_t bytes = ((size_t)B * G * 8 + 255) / 256 * 256;
     if (k > 1) bytes += (size_t)B * k * rpw * 4;
     if (bytes > need) need = bytes;
@@ -1271,8 +1384,9 @@ static hipError_t launch_f16_phase1(const SearchArgs& a, int nqb, dim3 grid, siz
 }
 
 // A query's second phase is one workgroup.  1,024 threads shorten it when there are many groups to
-// pick from or many rows to re-score (k groups, or all there are); below that the barriers of sixteen
-// waves cost more: 64 rows, k = 16 (two groups), 13.0 us with them, 7.7 us without.
+// pick from, or many or very wide rows to re-score (those of k groups, or of all there are); below that the barriers of
+// sixteen waves cost more.  Time with them over time without, 8 queries: 256 rows of 1,024 bytes 1.10,
+// 512 of them 0.84; 64 rows of 4,800 bytes 0.90, 256 of them 1.18; 128 rows of 9,600 bytes 0.83, 256 0.89.
 template <typename T, int NT>
 static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
   const size_t lists = (size_t)NT * 8 + kMaxK * 4, query = (size_t)((a.E + 3) & ~3) * 4;
@@ -1292,7 +1406,8 @@ static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
 
 template <typename T>
 static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
-  return a.G > 1024 || (a.k < a.G ? a.k : a.G) * a.rows > 256 ? launch_topk_n<T, 1024>(a, stream)
+  const int rows = (a.k < a.G ? a.k : a.G) * a.rows;
+  return a.G > 1024 || rows > 256 || a.E * sizeof(T) > 6000 ? launch_topk_n<T, 1024>(a, stream)
                                           : launch_topk_n<T, 256>(a, stream);
 }
 
@@ -1303,7 +1418,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   a.N = p.N; a.E = p.E; a.B = p.B; a.k = p.k; a.metric = p.metric;
   a.threshold = p.threshold;
   a.idx = p.idx; a.score = p.score; a.hit = p.hit;
-  const int mode = search_mode(p.is_f16, p.metric, p.E, p.B, p.N);
+  const int mode = search_mode(p.is_f16, p.metric, p.E, p.B, p.N, p.k);
   const bool mfma = mode == kModeMfma || mode == kModeMfmaWide;
   if (p.k > 1) {
     topk_plan(p.N, mode, p.k, &a.rows, &a.G, &a.wg_rows);

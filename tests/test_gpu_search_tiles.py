@@ -51,8 +51,36 @@ def _check(ac, oracle_mod, N, E, B, k, dt, metric):  # noqa: F811
     q[::3] = torch.randn(q[::3].shape, generator=g) / E ** 0.5
     q = q.to(dt)
     m = ac.AC_IP if metric == "ip" else ac.AC_L2
-    idx, score, hit = _run_search(ac, emb, q, k, 0.8, m)
-    parity.check_search(oracle_mod, q, emb, k, 0.8, m, None, idx, score, hit)
+    map_of = torch.randint(0, 50, (N,), generator=g).int() if B % 2 else None
+    idx, score, hit = _run_search(ac, emb, q, k, 0.8, m, map_of=map_of)
+    parity.check_search(oracle_mod, q, emb, k, 0.8, m, map_of, idx, score, hit)
+
+
+# One case at least for every kernel of the search and each of its variants, with the lists above and
+# those of test_gpu_parity_small.py (test_launch_coverage.py); ragged sizes.
+VARIANT_CASES = [(*c, k, torch.float16, "ip") for k in (1, 3) for c in [
+    # N, E, B: matrix cores, rows in registers: up to 128, 256, 512 columns by 1, 2, 4, 8 query blocks
+    (1001, 16, 130), (1001, 192, 1), (1001, 192, 65), (1001, 192, 130), (1001, 272, 33), (1001, 272, 65), (1001, 272, 130),
+    (777, 256, 130),                                          # queries in registers, two blocks per wave
+    (9001, 40, 17), (9001, 24, 33), (9001, 40, 65), (3001, 520, 140),   # other widths, 1, 2, 4 query blocks
+    (333, 136, 3), (20001, 72, 7), (70001, 40, 5),            # streams of one, four, eight queries
+    (1001, 520, 100),                                         # four each on a small database
+    (300, 8200, 65),                                          # rows that leave LDS room for four queries
+    (300, 3000, 301), (37, 36000, 9),                         # ... and for none: tiles
+]] + [(*c, k, dt, metric) for k in (1, 3) for metric in ("ip", "l2") for dt, c in [
+    (torch.float32, (333, 131, 3)), (torch.float32, (20001, 33, 7)), (torch.float32, (70001, 36, 5)),   # streams
+    (torch.float32, (701, 16, 500)), (torch.float32, (20001, 19, 100)), (torch.float32, (9001, 9, 500)),   # tiles, QW = 1, 2, 4
+    (torch.float32, (333, 7, 9)), (torch.float32, (999, 37, 5)),   # a thread per row, whole pieces and a part of one
+    (torch.float32, (400, 9000, 3)),                          # rows that leave LDS room for one query
+]] + [(*c, k, torch.float16, "l2") for k in (1, 3) for c in [
+    (333, 136, 3), (301, 64, 500), (70001, 40, 5), (12001, 40, 140), (30001, 24, 70), (30001, 24, 140), (999, 8, 65), (555, 72, 9),
+]]
+
+
+@pytest.mark.parametrize("case", VARIANT_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
+    *c[:4], str(c[4]).split(".")[-1], c[5]))
+def test_every_variant_matches_the_oracle(ac, oracle_mod, case):  # noqa: F811
+    _check(ac, oracle_mod, *case)
 
 
 TOPK_CASES = [

@@ -1,0 +1,67 @@
+"""The case lists of the GPU tests reach every kernel that the library can launch, by its own launch
+rules (host code on a recorder, no GPU): a rule that moves leaves no kernel untested unnoticed."""
+import subprocess
+
+import pytest
+
+from tests import launches
+from tests import test_gpu_parity_small as small
+from tests import test_gpu_search_tiles as tiles
+
+# fp16 rows of more than 2,360 columns, more than 64 queries and 128 groups: 5e9 products and more for
+# the oracle.  The variants with one query per wave, and all three of the Euclidean metric, are reached.
+NOT_RUN = {"search_valu_kernel<half, false, %d, %s>" % (q, k) for q in (2, 4) for k in ("true", "false")}
+
+
+def _kernels(*prefixes):
+    """Kernels of the built library: the handles that its host code passes to a launch."""
+    out = subprocess.run(["nm", "-D", launches.LIB], text=True, capture_output=True, check=True).stdout
+    names = [l.split()[-1] for l in out.splitlines() if " V " in l or " D " in l]
+    names = subprocess.run(["c++filt"], input="\n".join(names).replace("DF16_", "Dh"), text=True, capture_output=True,
+                           check=True).stdout.splitlines()
+    names = {n.replace("void ac::", "").replace("ac::", "").split("(")[0] for n in names}
+    return {n for n in names if n.startswith(prefixes)}
+
+
+def _reached(tmp_path, calls):
+    seen = set()
+    for call, (status, ls) in zip(calls, launches.record(calls, tmp_path)):
+        assert status == 0, call
+        seen |= {la[0] for la in ls}
+    return seen
+
+
+def _search(c):
+    return ("search", *c[:4], "f16" if "16" in str(c[4]) else "f32", c[5])
+
+
+def test_every_search_kernel_is_reached(tmp_path):
+    cases = (tiles.VALU_CASES + tiles.VARIANT_CASES + tiles.TOPK_CASES + small.SEARCH_CASES +
+             small._random_search_shapes(40, 20251128))
+    missing = _kernels("search_", "finalize_") - _reached(tmp_path, [_search(c) for c in cases])
+    assert missing == NOT_RUN
+
+
+@pytest.mark.parametrize("kernel", ["search_stream_kernel<float", "search_stream_kernel<half", "search_valu_kernel<float",
+                                    "search_row_kernel", "search_f16_kernel<0", "search_f16_kernel<16", "search_f16_big_kernel"])
+def test_queries_with_nan_reach_every_kind_of_search_kernel(tmp_path, kernel):
+    seen = _reached(tmp_path, [_search(c) for c in small.NAN_CASES])
+    assert any(k.startswith(kernel) for k in seen)
+
+
+@pytest.mark.parametrize("case,kernel", [
+    ((300, 520, 200, 1, "f16", "ip"), "search_stream_kernel<half, false, 1"),    # 38 us on the matrix cores, 12.5 so
+    ((1000, 520, 200, 1, "f16", "ip"), "search_stream_kernel<half, false, 4"),   # 39, 16
+    ((4000, 520, 100, 1, "f16", "ip"), "search_stream_kernel<half, false, 4"),
+    ((7500, 1536, 64, 1, "f16", "ip"), "search_f16_kernel<0, 2"),
+    ((1000, 4608, 8, 1, "f16", "ip"), "search_stream_kernel<half, false, 1"),    # 368 in tiles, 32
+    ((20000, 8192, 8, 1, "f16", "l2"), "search_stream_kernel<half, true, 4"),    # 943, 224
+    ((20000, 8192, 8, 1, "f32", "ip"), "search_valu_kernel<float"),              # 343, 379 in streams
+    ((300000, 8, 8, 1, "f16", "l2"), "search_row_kernel<half"),                  # 28 in streams, 11
+    ((20000, 20, 8, 1, "f32", "ip"), "search_row_kernel<float"),
+    ((20000, 37, 8, 1, "f32", "ip"), "search_stream_kernel<float, false, 4"),
+    ((100000, 128, 64, 1, "f32", "l2"), "search_valu_kernel<float, true, 4"),
+], ids=str)
+def test_the_kernel_that_measured_best_serves_the_shape(tmp_path, case, kernel):
+    (status, ls), = launches.record([("search", *case)], tmp_path)
+    assert status == 0 and ls[0][0].startswith(kernel), ls

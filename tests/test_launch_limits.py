@@ -15,7 +15,7 @@ def record(tmp_path_factory):
     # vector-ALU tiles: (groups of 256 rows, rounded up to 8) x (blocks of 16 queries)
     (("search", 10_000_000, 8, 8192, 1, "f32", "l2"), "search_valu_kernel", 39064 * 512),
     (("search", 20_000_000, 8, 8192, 2, "f32", "ip"), "search_valu_kernel", 78128 * 512),
-    (("search", 2_000_000_000, 8, 100, 1, "f16", "l2"), "search_valu_kernel", 7_812_504 * 7),
+    (("search", 2_000_000_000, 24, 100, 1, "f16", "l2"), "search_valu_kernel", 7_812_504 * 7),
     # a workgroup of 1,024 threads per query in the second phase
     (("search", 300_000, 64, 5_000_000, 2, "f16", "ip"), "finalize_topk_kernel", 5_000_000),
     # narrow binary32 heads: eight times as many workgroups as (item, layer, head) tiles
