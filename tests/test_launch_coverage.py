@@ -53,7 +53,7 @@ def test_queries_with_nan_reach_every_kind_of_search_kernel(tmp_path, kernel):
     ((300, 520, 200, 1, "f16", "ip"), "search_stream_kernel<half, false, 1"),    # 38 us on the matrix cores, 12.5 so
     ((1000, 520, 200, 1, "f16", "ip"), "search_stream_kernel<half, false, 4"),   # 39, 16
     ((4000, 520, 100, 1, "f16", "ip"), "search_stream_kernel<half, false, 4"),
-    ((7500, 1536, 64, 1, "f16", "ip"), "search_f16_kernel<0, 2"),
+    ((7500, 1536, 64, 1, "f16", "ip"), "search_f16_kernel<0, 1"),
     ((1000, 4608, 8, 1, "f16", "ip"), "search_stream_kernel<half, false, 1"),    # 368 in tiles, 32
     ((20000, 8192, 8, 1, "f16", "l2"), "search_stream_kernel<half, true, 4"),    # 943, 224
     ((20000, 8192, 8, 1, "f32", "ip"), "search_valu_kernel<float"),              # 343, 379 in streams
