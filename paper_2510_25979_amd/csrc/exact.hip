@@ -435,18 +435,20 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
     }
   } else {
     // Units of 32 query rows of one head, numbered row block first, head second; a workgroup
-    // takes four consecutive ones of a K/V tile, heaviest first, one per wave (g = 4: the same rows of
-    // all four heads).  Its waves see (nearly) the same keys, a chunk is copied once for all of
-    // them, and only the lightest workgroup of a tile can have idle waves.  128 rows of one head
-    // per workgroup before: 64 x 32 heads on 8 K and V, 288 x 128, causal 141 -> 105 us; 16 x 32 on 8,
-    // 1024 x 128 214 -> 195 us; one head per K and V and whole blocks of 128 rows are as they were.
+    // takes four consecutive ones of a K/V tile, one per wave (g = 4: the same rows of
+    // all four heads), the heaviest workgroup first.  Its waves see (nearly) the same keys and a chunk is
+    // copied once for all of them.  The fours are counted from the first rows, where chunks of 64 keys
+    // begin with the units, and what is left over are the last rows, by themselves: counted from the end, a workgroup had
+    // more chunks on its diagonals (320 heads, 192 x 128, causal 19.0 us, 17.3 so; 448 x 64 26.8 / 24.2).
+    // 128 rows of one head per workgroup before: 64 x 32 heads on 8 K and V, 288 x 128, causal 141 -> 105 us; 16 x 32 on 8,
+    // 1024 x 128 214 -> 195 us; with one head per K and V it is the same split.
     const int bid = blockIdx.x;
     const int slot = bid >> 3;
     const int n_units = g * (S >> 5), per_u = (n_units + 3) >> 2;
     u = (slot / per_u) * 8 + (bid & 7);   // ids equal mod 8 (one XCD) share K, V in its L2
     if (u >= a.n_kvtiles) return;
-    const int top = n_units - 1 - 4 * (slot % per_u), unit = top - wave;
-    h = (u % a.Hkv) * g + max(unit, 0) % g;
+    const int low = 4 * (per_u - 1 - slot % per_u), top = min(low + 3, n_units - 1), unit = low + 3 - wave;
+    h = (u % a.Hkv) * g + min(unit, top) % g;
     b = u / a.Hkv;
     if (a.row_sel && a.row_sel[b] >= 0) return;
     Ksrc = reinterpret_cast<const bf16_t*>(a.K) + (size_t)u * S * D;
@@ -456,15 +458,15 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
     Sk = a.key_len ? min(max(a.key_len[b], 1), S) : S;
     const int last_key = CAUSAL ? min(Sk, 32 * (top / g + 1)) : Sk;
     n_chunk = (last_key + kLChunk - 1) / kLChunk;
-    r0 = 32 * (max(unit, 0) / g);
-    active = unit >= 0;
+    r0 = 32 * (min(unit, top) / g);
+    active = unit <= top;
     begin_head();
     // Chunks below c_split are complete and fully visible to every wave of the workgroup
     // (they lie left of the diagonal blocks of all its rows, and before a ragged end): the
     // main loop runs only the test-free variant, two chunks per trip so that stages
     // alternate without pointer arithmetic.  The few chunks from c_split on go through the
     // masked variant.
-    const int c_split = CAUSAL ? min(32 * (max(top - 3, 0) / g) / kLChunk, Sk / kLChunk) : Sk / kLChunk;
+    const int c_split = CAUSAL ? min(32 * (low / g) / kLChunk, Sk / kLChunk) : Sk / kLChunk;
     prefetch(kb0, vb0, 0);
     int c = 0;
     for (; c + 1 < c_split; c += 2) {
@@ -971,10 +973,14 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
   // block of keys.  us per call, split / not: 8 heads of 1024 x 128 causal (256 units) 14.0 / 23.7, 64 of
   // 288 x 128 (576) 12.2 / 10.2, 64 of 288 x 64 (576) 7.6 / 7.9, 24 of 512 x 64 dense (384) 9.0 / 9.7, 64
   // of 512 x 64 (1,024) 14.0 / 11.3; 128 of 128 x 128 (512) 7.8 / 8.4, 160 (640) 9.8 / 8.0, 160 on 40 K and V
-  // (640) 10.0 / 16.0; 256 of 128 x 64 (1,024) 7.8 / 6.7, on 64 K and V 8.9 / 15.6; 640 of 32 x 128 8.5 / 9.7.
+  // (640) 10.0 / 16.0; 256 of 128 x 64 (1,024) 7.8 / 6.7, on 64 K and V 8.9 / 15.6; 640 of 32 x 128 8.5 / 9.7, but
+  // 600 on 150 K and V 8.8 / 7.1: two workgroups fit on a compute unit, the 513th begins a second round, which
+  // pays only where the resident kernel walks one head (few workgroups per XCD) or many.
+  // The lines lie where neither side loses more than 0.6 us over S; so some measured winners are beyond them.
   const int g = p.Hq / p.Hkv;
   const size_t most = p.S > 128 ? (p.D == 64 ? 576 : 320) / (p.causal ? 1 : 2)
-                      : p.S > 32 && g == 1 ? (p.causal ? 512 : 256) : p.D == 64 ? 1024 : 640;
+                      : p.S > 32 && g == 1 ? (p.causal ? 512 : 256)
+                      : p.D == 64 ? 1024 : p.S == 32 && g > 1 && g < 8 ? 512 : 640;
   if (units <= most) {
     if (p.D == 64) return p.causal ? launch_exact_split<64, true>(a, units, stream) : launch_exact_split<64, false>(a, units, stream);
     return p.causal ? launch_exact_split<128, true>(a, units, stream) : launch_exact_split<128, false>(a, units, stream);

@@ -52,13 +52,14 @@ struct InsertArgs {
 //   Streaming (S > 128): the row blocks of all g heads of the group are units of 32 rows of one
 //   head, numbered row block first, head second, and a workgroup takes four consecutive ones, one
 //   per wave (g = 4: the same rows of all four heads).  Its waves see (nearly) the same keys, K and V
-//   are copied once for all of them, and only the lightest workgroup can have idle waves.
+//   are copied once for all of them.  The fours are counted from the first rows, as in the exact
+//   kernel (57 items x 12 heads, 160 x 128, causal: 42 us counted from the end, 38 so).
 //   The copy of chunk c + 1 is in flight while chunk c is multiplied, one barrier per chunk;
 //   the statistics pass needs no V and copies none.
 // Chunks and blocks beyond the sentence's length are not multiplied: their weights are zeros.
-// 16 items x 4 layers x 32 heads on 8 K and V, 288 x 128, causal, padded: 205 us per call with 128
-// rows of one head per workgroup and all keys multiplied, 134 us so,
-// without an extra launch for the feature vectors (520 MB, 101 us at the copy rate).
+// 16 items x 4 layers x 32 heads on 8 K and V, 288 x 128, causal, padded: 203 us per call with 128
+// rows of one head per workgroup and all keys multiplied, 132 to 139 us so (several boxes),
+// without an extra launch for the feature vectors (520 MB, 93 us at the copy rate).
 constexpr int kIChunk = 64;   // keys per staged chunk
 
 template <int D, bool CAUSAL, bool PACKED, bool RESIDENT>
@@ -84,8 +85,8 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   const int n_units = RESIDENT ? 4 : g * (S >> 5), per_tile = (n_units + 3) >> 2;
   const int slot_id = bid >> 3;
   const int grp = slot_id / per_tile * 8 + (bid & 7);   // (item, layer, KV head)
-  const int top = n_units - 1 - 4 * (slot_id % per_tile);
-  const int unit = RESIDENT ? wave : top - wave;
+  const int low = 4 * (per_tile - 1 - slot_id % per_tile), top = min(low + 3, n_units - 1);
+  const int unit = RESIDENT ? wave : low + 3 - wave;
   if (grp >= a.n_tiles) return;
   const int kvh = grp % a.Hkv;
   const int l = (grp / a.Hkv) % a.Lc;
@@ -106,8 +107,8 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   // those that hold a visible key
   const int last = RESIDENT || !CAUSAL ? S : 32 * (top / g + 1);
   const int n_chunk = (min(last, len) + kIChunk - 1) / kIChunk;
-  const int r0 = RESIDENT ? 32 * unit : 32 * (max(unit, 0) / g);
-  const bool active = RESIDENT ? r0 < S : unit >= 0;
+  const int r0 = RESIDENT ? 32 * unit : 32 * (min(unit, top) / g);
+  const bool active = RESIDENT ? r0 < S : unit <= top;
   const int n32 = S >> 5;
   const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
   bf16_t* At = nullptr;   // the current head's map in the store
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   }
   const int n_heads = RESIDENT ? g : 1;   // streaming: one unit per wave
   for (int hl = 0; hl < n_heads; ++hl) {
-    const int h = kvh * g + (RESIDENT ? hl : max(unit, 0) % g);
+    const int h = kvh * g + (RESIDENT ? hl : min(unit, top) % g);
     const size_t qo = (((size_t)b * a.Lc + l) * a.Hq + h) * (size_t)S * D;
     At = reinterpret_cast<bf16_t*>(a.maps) +
          (((size_t)(keep ? entry : 0) * a.L + (a.layer_begin + l)) * a.Hq + h) * tile_elems;
