@@ -640,6 +640,28 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
   }
 }
 
+// The same for maps of a few rows, whose time is the chain above and not the work: one workgroup per (query,
+// layer, head), a thread per output, sums over ascending columns.  us per call, tiles / this: 256 heads of
+// 1 x 256 6.0 / 2.5, of 8 x 64 3.8 / 3.5, of 12 x 40 4.0 / 4.2.
+__global__ __launch_bounds__(kThreads) void apply_f32_small_kernel(const ApplyArgs a, int D, int causal) {
+  const int tile = blockIdx.x, h = tile % a.Hq, l = tile / a.Hq % a.Lc, bslot = tile / (a.Hq * a.Lc);
+  const int b = a.fixed_entry >= 0 ? a.q_list[bslot] : bslot;
+  const int entry = a.fixed_entry >= 0 ? a.fixed_entry : a.hit[b];
+  if (a.fixed_entry < 0 && (entry < 0 || entry >= a.M)) return;
+  const int S = a.S, g = a.Hq / a.Hkv;
+  const float* A = reinterpret_cast<const float*>(a.maps) +
+                   (((size_t)entry * a.L + (a.layer_begin + l)) * a.Hq + h) * (size_t)S * S;
+  const float* V = reinterpret_cast<const float*>(a.V) + (((size_t)b * a.Lc + l) * a.Hkv + h / g) * (size_t)S * D;
+  float* O = reinterpret_cast<float*>(a.O) + (((size_t)b * a.Lc + l) * a.Hq + h) * (size_t)S * D;
+  for (int idx = threadIdx.x; idx < S * D; idx += kThreads) {
+    const int i = idx / D, d = idx % D;
+    const int nj = causal ? i + 1 : S;
+    float acc = 0.f;
+    for (int j = 0; j < nj; ++j) acc = fmaf(A[(size_t)i * S + j], V[(size_t)j * D + d], acc);
+    O[idx] = acc;
+  }
+}
+
 template <int DB>
 static hipError_t launch_apply_f32(ApplyArgs a, int D, int causal, hipStream_t stream) {
   // a launch has fewer than 2^32 threads: very many tiles of narrow heads take several
@@ -711,6 +733,11 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
 
   if (p.is_f32) {
     a.heads_per_wg = 1; a.n_rblk = 1; a.n_tiles = nb * p.Lc * p.Hkv;
+    const size_t tiles = (size_t)nb * p.Lc * p.Hq;
+    if ((p.S <= 5 || (size_t)p.S * p.S * p.D <= 3400) && tiles < ((size_t)1 << 32) / kThreads) {
+      hipLaunchKernelGGL(apply_f32_small_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, stream, a, p.D, p.causal);
+      return hipGetLastError();
+    }
     if (p.D <= 64) return launch_apply_f32<1>(a, p.D, p.causal, stream);
     if (p.D <= 128) return launch_apply_f32<2>(a, p.D, p.causal, stream);
     return launch_apply_f32<4>(a, p.D, p.causal, stream);

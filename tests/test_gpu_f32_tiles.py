@@ -23,6 +23,9 @@ CASES = [
     (1, 5, 5, 65, 80, True),        # one key past the reuse stage
     (1, 2, 1, 129, 256, True),      # the widest rows
     (9, 1, 1, 47, 40, False),       # tiles not a multiple of eight
+    (3, 4, 2, 5, 256, True),        # reuse: a thread per output, more outputs than threads
+    (5, 3, 1, 16, 12, False),
+    (4, 2, 1, 16, 20, True),        # and the first size beyond
 ]
 
 

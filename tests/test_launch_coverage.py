@@ -65,3 +65,12 @@ def test_queries_with_nan_reach_every_kind_of_search_kernel(tmp_path, kernel):
 def test_the_kernel_that_measured_best_serves_the_shape(tmp_path, case, kernel):
     (status, ls), = launches.record([("search", *case)], tmp_path)
     assert status == 0 and ls[0][0].startswith(kernel), ls
+
+
+@pytest.mark.parametrize("S,D,kernel", [(1, 256, "apply_f32_small_kernel"), (5, 256, "apply_f32_small_kernel"),
+                                        (16, 12, "apply_f32_small_kernel"), (16, 64, "apply_f32_kernel<1>"),
+                                        (6, 256, "apply_f32_kernel<4>"), (94, 128, "apply_f32_kernel<2>")])
+def test_reuse_of_maps_of_a_few_rows_takes_a_thread_per_output(tmp_path, S, D, kernel):
+    # 256 heads of one row of 256: 6.6 us in tiles of 16 rows, 2.4 so
+    (status, ls), = launches.record([("apply", 64, 1, 4, 4, S, D, True, "f32")], tmp_path)
+    assert status == 0 and [la[0] for la in ls] == [kernel]
