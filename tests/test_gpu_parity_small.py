@@ -33,7 +33,7 @@ def _maps(M, L, H, S, dtype, causal, seed):
 APPLY_CASES = [
     # B, M, L, Hq, Hkv, S, D, causal, layer_begin, Lc, dtype
     (4, 16, 1, 2, 2, 32, 64, True, 0, 1, torch.float32),      # the tiny fp32 workload's shape
-    (3, 5, 2, 4, 2, 45, 24, False, 1, 1, torch.float32),      # odd sizes on the vector-ALU path
+    (3, 5, 2, 4, 2, 45, 24, False, 1, 1, torch.float32),      # odd sizes
     (5, 7, 3, 4, 4, 128, 64, True, 0, 3, torch.bfloat16),     # 1B-shaped heads
     (4, 6, 2, 8, 2, 128, 128, True, 1, 1, torch.bfloat16),    # 8B-shaped heads (4 share a V)
     (3, 4, 1, 2, 2, 96, 64, True, 0, 1, torch.bfloat16),      # one ragged block of rows
@@ -111,6 +111,7 @@ def test_apply_out_of_range_hit_is_a_miss_on_device(ac):
 
 # ------------------------------------------------------------------------- exact
 
+# (small launches: the kernels that split the keys of a unit; test_gpu_row_units.py makes large ones of the bf16 cases)
 EXACT_CASES = [
     # B, Hq, Hkv, S, D, causal, scale, dtype
     (4, 2, 2, 32, 64, True, 0.0, torch.float32),
@@ -155,14 +156,14 @@ def test_exact_matches_oracle(ac, oracle_mod, case):
 
 PADDED_CASES = [
     # B, Hq, Hkv, S, D, causal, dtype, lengths
-    (6, 2, 2, 128, 64, False, torch.bfloat16, [128, 1, 33, 64, 65, 100]),      # encoder-style, resident
+    (6, 2, 2, 128, 64, False, torch.bfloat16, [128, 1, 33, 64, 65, 100]),      # encoder-style
     (5, 4, 1, 128, 128, False, torch.bfloat16, [127, 96, 32, 31, 2]),          # four heads share K, V
     (4, 2, 2, 128, 64, True, torch.bfloat16, [128, 70, 5, 64]),                # causal: only the padding rows change
     (3, 2, 2, 96, 128, False, torch.bfloat16, [96, 40, 65]),
-    (5, 2, 1, 640, 64, False, torch.bfloat16, [640, 1, 64, 333, 577]),         # streaming: chunks in the padding are skipped
-    (4, 2, 2, 416, 128, True, torch.bfloat16, [416, 129, 200, 31]),            # streaming, causal, ragged S
+    (5, 2, 1, 640, 64, False, torch.bfloat16, [640, 1, 64, 333, 577]),         # chunks in the padding are skipped
+    (4, 2, 2, 416, 128, True, torch.bfloat16, [416, 129, 200, 31]),            # causal, ragged S
     (1, 1, 1, 1024, 128, False, torch.bfloat16, [700]),
-    (4, 3, 1, 45, 24, False, torch.float32, [45, 1, 17, 44]),                  # vector-ALU path
+    (4, 3, 1, 45, 24, False, torch.float32, [45, 1, 17, 44]),
     (3, 2, 2, 32, 64, True, torch.float32, [32, 9, 1]),
 ]
 
@@ -305,7 +306,7 @@ SEARCH_CASES = [
     (5000, 128, 300, 1, torch.float16, "ip", True),     # more than one query super-block
     (77, 48, 3, 64, torch.float16, "ip", False),        # k = AC_MAX_K > rows per group
     (3000, 256, 33, 8, torch.float16, "ip", True),
-    (600, 40, 7, 2, torch.float16, "ip", False),        # E % 16 != 0: vector-ALU path on fp16
+    (600, 40, 7, 2, torch.float16, "ip", False),        # E % 16 != 0: a thread per row
     (900, 64, 6, 2, torch.float16, "l2", False),
     (140000, 64, 40, 4, torch.float16, "ip", True),     # several row passes per workgroup
     (70001, 256, 130, 1, torch.float16, "ip", True),    # large batch: three chunks per workgroup, ragged end
@@ -643,8 +644,8 @@ INSERT_CASES = [
     (2, 1, 2, 1, 288, 64, True),      # three key chunks, ragged last row block
     (2, 1, 2, 2, 160, 128, False),    # dense maps, ragged last chunk
     (2, 1, 2, 1, 512, 128, True),     # four row blocks, up to eight 64-key chunks, shared K and V
-    (2, 2, 2, 2, 352, 64, False),     # dense maps, 32 keys in the last chunk, one wave in the last row block
-    (2, 1, 2, 2, 32, 64, True),       # a single 32-row block: one active wave, half a chunk of keys
+    (2, 2, 2, 2, 352, 64, False),     # dense maps, 32 keys in the last chunk
+    (2, 1, 2, 2, 32, 64, True),       # a single 32-row block, half a chunk of keys
     (2, 1, 4, 1, 32, 128, False),     # the same, four heads on one K and V
     (2, 1, 2, 2, 64, 128, True),      # exactly one chunk
 ]
@@ -707,8 +708,8 @@ def test_insert_stores_the_oracles_map_and_output(ac, oracle_mod, case, layout, 
 
 
 def _random_attention_shapes(n, seed):
-    """Seeded shapes across the bf16 kernels' variants: resident and streaming lengths (ragged
-    row blocks and key chunks), both head widths, head groupings, layouts, padded batches."""
+    """Seeded shapes across lengths on both sides of 128 (ragged row blocks and key chunks), both head
+    widths, head groupings, layouts, padded batches.  They are small launches; test_gpu_row_units.py runs large ones."""
     rng = np.random.default_rng(seed)
     shapes = []
     for _ in range(n):

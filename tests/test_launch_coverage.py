@@ -5,8 +5,11 @@ import subprocess
 import pytest
 
 from tests import launches
+from tests import test_gpu_f32_tiles as f32
 from tests import test_gpu_parity_small as small
+from tests import test_gpu_row_units as rows
 from tests import test_gpu_search_tiles as tiles
+from tests import test_gpu_split_units as split
 
 # fp16 rows of more than 2,360 columns, more than 64 queries and 128 groups: 5e9 products and more for
 # the oracle.  The variants with one query per wave, and all three of the Euclidean metric, are reached.
@@ -47,6 +50,29 @@ def test_every_search_kernel_is_reached(tmp_path):
 def test_queries_with_nan_reach_every_kind_of_search_kernel(tmp_path, kernel):
     seen = _reached(tmp_path, [_search(c) for c in small.NAN_CASES])
     assert any(k.startswith(kernel) for k in seen)
+
+
+def _dt(t):
+    return str(t).split(".")[-1].replace("bfloat", "bf").replace("float", "f")
+
+
+def test_every_attention_kernel_is_reached(tmp_path):
+    calls = []
+    for large, cases in ((False, rows.CASES), (True, rows.CASES + rows.LARGE_CASES)):
+        for Hq, Hkv, S, D, causal, lens in cases:
+            B = lens if isinstance(lens, int) else len(lens)
+            n = rows.copies(Hq, S, B) if large else 1
+            calls += [("exact", n * B, Hq, Hkv, S, D, causal, "bf16")]
+            calls += [("insert", n * B, 1, Hq, Hkv, S, D, causal, packed) for packed in (False, True)]
+    calls += [("exact", *c[:6], _dt(c[7])) for c in small.EXACT_CASES]
+    calls += [("exact", *c[:6], _dt(c[6])) for c in small.PADDED_CASES]
+    calls += [("exact", *c, "f32") for c in f32.CASES]
+    calls += [("exact", len(c[6]) * n, *c[:5], _dt(c[5])) for c in split.CASES for n in (1, split.copies(c))]
+    calls += [("insert", *c, packed) for c in small.INSERT_CASES for packed in (False, True)]
+    calls += [("apply", c[0], c[9], *c[3:8], _dt(c[10])) for c in small.APPLY_CASES]
+    calls += [("apply", c[0], 2, *c[1:], "f32") for c in f32.CASES]
+    missing = _kernels("exact_", "insert_", "apply_f32") - _reached(tmp_path, calls)
+    assert not missing
 
 
 @pytest.mark.parametrize("case,kernel", [
