@@ -121,16 +121,19 @@ def _dev(t: torch.Tensor, name: str, dtype=None, shape=None) -> int:
     return t.data_ptr()
 
 
+# Not part of torch's documented interface; a torch without them goes the long way (_stream).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream: Optional[torch.cuda.Stream]) -> int:
     """The raw stream handle.  The current one is asked for directly: building a torch.cuda.Stream
-    object to read it from took 2.7 of the 9.5 us a call spent on the host (6.9 us so).  The two
-    functions are not part of torch's documented interface; a torch without them goes the long way."""
+    object to read it from took 2.7 of the 9.5 us a call spent on the host (6.9 us so)."""
     if stream is not None:
         return stream.cuda_stream
-    try:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    except AttributeError:
+    if _raw_stream is None or _device is None:
         return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 class Database:

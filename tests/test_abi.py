@@ -120,16 +120,22 @@ def test_workspace_for_up_to_a_batch_holds_every_smaller_batch():
 
 
 def test_current_stream_without_the_undocumented_lookup(monkeypatch):
+    import importlib.util
     import types
 
     import torch
     from paper_2510_25979_amd import binding
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
-    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
-    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 55)
+    monkeypatch.setattr(binding, "_device", lambda: 4)
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 51 + device)
     assert binding._stream(None) == 55
-    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
-    assert binding._stream(None) == 77
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        with monkeypatch.context() as m:
+            m.delattr(torch._C, name)
+            other = importlib.util.module_from_spec(importlib.util.spec_from_file_location(
+                "paper_2510_25979_amd.binding_without", binding.__file__))
+            other.__spec__.loader.exec_module(other)
+            assert other._stream(None) == 77
     assert binding._stream(types.SimpleNamespace(cuda_stream=3)) == 3
 
 
