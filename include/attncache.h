@@ -81,12 +81,14 @@ extern "C" {
  * several feature vectors refer to one map entry the optional table map_of
  * gives the entry of each vector.
  *
- * Supported: emb_dtype AC_F16 with emb_dim % 8 == 0 (16-byte rows) and either
- * metric: metric AC_IP with emb_dim % 16 == 0 and emb_dim <= 512 runs on the
- * matrix cores, every other fp16 shape on the vector ALUs; emb_dtype AC_F32
- * with either metric and any emb_dim (vector ALUs).  map_dtype AC_BF16 with seq_len % 32 == 0 and head_dim
- * 64 or 128 (matrix-core path, either layout), or map_dtype AC_F32 with any
- * seq_len and head_dim <= 256 (vector-ALU path, dense layout only).
+ * Supported: emb_dtype AC_F16 with emb_dim % 8 == 0 (16-byte rows) or AC_F32
+ * with any emb_dim, either metric.  Inner products of fp16 rows run on the
+ * matrix cores where emb_dim % 16 == 0 and emb_dim <= 512, and for more than
+ * eight queries of other widths up to about 2,300 unless the database is small;
+ * everything else (fp32, AC_L2) runs on the vector ALUs.  map_dtype AC_BF16
+ * with seq_len % 32 == 0 and head_dim 64 or 128 (either layout), or map_dtype
+ * AC_F32 with any seq_len and head_dim <= 256 (binary32 matrix instructions,
+ * dense layout only).
  * n_q_heads % n_kv_heads == 0.
  */
 typedef struct {

@@ -40,10 +40,8 @@ struct ExactArgs {
   const int32_t* row_sel;
   const int32_t* key_len;   // real tokens per batch item of a right-padded batch, or nullptr
   int32_t B, Hq, Hkv, S;
-  int32_t heads_per_wg;
   int32_t n_rblk;
   int32_t n_kvtiles;
-  int32_t n_blocks;   // tiles of the launch (the grid of a routed resident launch is smaller)
   float scale_log2e;
 };
 
@@ -82,9 +80,9 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
   const float scale_log2e = __builtin_bit_cast(
       float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.scale_log2e) + (lane & 0)));
   // Sequences of up to 128 keys are RESIDENT: both 64-key chunks of K and V sit in the two
-  // stages for the whole tile, the workgroup walks all heads_per_wg query heads that share
+  // stages for the whole tile, the workgroup walks all g query heads that share
   // them, and between the one barrier after the copy and the end of the tile the four waves
-  // never meet again.  Longer sequences stream chunks through the stages, one head per tile.
+  // never meet again.  Longer sequences stream chunks through the stages, one 32-row unit per wave.
 
   // per tile (the helpers below read these by reference)
   int u = 0, h = 0, b = 0, r0 = 0, n_chunk = 0;
@@ -357,18 +355,12 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
     // out 64 candidates at a time: lane i tests candidate i (one vector load of the routing
     // flags, one round trip to memory for all of them) and the votes form a wave-uniform bit
     // mask that the walk below consumes with scalar bit operations.
-    const int hslots = g / a.heads_per_wg;
     int cand_base = 0;          // candidates cand_base .. cand_base + 63 are in `live`
     unsigned long long live = 0;
     auto scan = [&](int base) {
       // (tile numbers stay below 2^31 + 64 gridDim.x: unsigned 32-bit arithmetic is enough)
       const unsigned t = blockIdx.x + (unsigned)(base + lane) * gridDim.x;
-      bool work = false;
-      if (t < (unsigned)a.n_blocks) {
-        const int ti = (int)t;
-        const int ut = ((ti >> 3) / hslots) * 8 + (ti & 7);   // ids equal mod 8 (one XCD) share K, V
-        work = ut < a.n_kvtiles && !(a.row_sel && a.row_sel[ut / a.Hkv] >= 0);
-      }
+      const bool work = t < (unsigned)a.n_kvtiles && !(a.row_sel && a.row_sel[(int)t / a.Hkv] >= 0);
       cand_base = base;
       live = __ballot(work);
     };
@@ -382,7 +374,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
           return (int)(blockIdx.x + (unsigned)i * gridDim.x);
         }
         const int next = cand_base + 64;
-        if (blockIdx.x + (unsigned)next * gridDim.x >= (unsigned)a.n_blocks) return -1;
+        if (blockIdx.x + (unsigned)next * gridDim.x >= (unsigned)a.n_kvtiles) return -1;
         scan(next);
         from = next;
       }
@@ -390,9 +382,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
     scan(0);
     int h_first = 0;
     auto enter = [&](int t) {       // tile variables, and its K and V on their way
-      const int slot = t >> 3;
-      u = (slot / hslots) * 8 + (t & 7);
-      h_first = (u % a.Hkv) * g + (slot % hslots) * a.heads_per_wg;
+      u = t;
+      h_first = (u % a.Hkv) * g;
       b = u / a.Hkv;
       Ksrc = reinterpret_cast<const bf16_t*>(a.K) + (size_t)u * S * D;
       Vsrc = reinterpret_cast<const bf16_t*>(a.V) + (size_t)u * S * D;
@@ -409,7 +400,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
     while (true) {
       publish();
       const int rot = (t >> 3) & 3;
-      for (int hl = 0; hl < a.heads_per_wg; ++hl) {
+      for (int hl = 0; hl < g; ++hl) {
         h = h_first + hl;
         // causal work grows with the row block and wave i always runs on SIMD i: rotating the
         // wave -> row block assignment lets every SIMD see the same mix
@@ -417,7 +408,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void exact_bf16_kernel
         active = r0 < S;
         begin_head();
         for (int c = 0; c < n_chunk; ++c) tail_step(c ? kb1 : kb0, c ? vb1 : vb0, c);
-        if (hl + 1 == a.heads_per_wg) break;   // the last head is written after the next copies start
+        if (hl + 1 == g) break;   // the last head is written after the next copies start
         if (active) {
           const float inv = 1.0f / (l_run + __shfl_xor(l_run, 32));
           store_small(reinterpret_cast<bf16_t*>(a.O) + (((size_t)b * a.Hq + h) * S + r0) * (size_t)D, inv);
@@ -918,8 +909,7 @@ static hipError_t launch_exact_f32(const ExactArgs& a, int D, int causal, float 
 }
 
 template <int D, bool CAUSAL, bool RESIDENT>
-static hipError_t launch_exact_bf16_r(ExactArgs a, dim3 grid, hipStream_t stream) {
-  a.n_blocks = (int32_t)grid.x;
+static hipError_t launch_exact_bf16_r(const ExactArgs& a, dim3 grid, hipStream_t stream) {
   // resident launch: at most 32 workgroups per compute unit walk the tiles (enough of them for
   // the hardware to even out an uneven mix of hits and misses -- fewer, longer-lived workgroups
   // measured 2-5 % slower; a multiple of 8 keeps a workgroup's tiles on its own XCD)
@@ -961,7 +951,6 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
   a.n_kvtiles = p.B * p.Hkv;
   const float scale = p.scale == 0.f ? 1.0f / sqrtf((float)p.D) : p.scale;
   a.scale_log2e = scale * 1.44269504088896340736f;
-  a.heads_per_wg = 1;
   if (p.is_f32) {   // D <= 256, by the number of 64-wide output blocks
     if (p.D <= 64) return launch_exact_f32<1>(a, p.D, p.causal, scale, stream);
     if (p.D <= 128) return launch_exact_f32<2>(a, p.D, p.causal, scale, stream);
@@ -985,7 +974,6 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
     if (p.D == 64) return p.causal ? launch_exact_split<64, true>(a, units, stream) : launch_exact_split<64, false>(a, units, stream);
     return p.causal ? launch_exact_split<128, true>(a, units, stream) : launch_exact_split<128, false>(a, units, stream);
   }
-  a.heads_per_wg = g;
   const int u8 = (a.n_kvtiles + 7) / 8 * 8;
   const int per_u = a.n_rblk == 1 ? 1 : (g * (p.S / 32) + 3) / 4;   // workgroups of a K/V tile
   const dim3 grid((unsigned)((size_t)u8 * per_u));

@@ -41,8 +41,8 @@ struct InsertArgs {
   float scale_log2e;
 };
 
-// One workgroup = one (item, layer, group of query heads that share K and V, 128 query rows),
-// walking the keys in chunks of 64 -- twice per head, see above.  K and V reach the matrix cores
+// One workgroup = up to 128 query rows of one (item, layer, group of query heads that share K and V),
+// walking the keys in chunks of 64 -- twice, see above.  K and V reach the matrix cores
 // the way they do in the exact kernel: every chunk is copied global -> LDS directly (no data
 // registers, no ALU work) into one of two stages, rows unpadded with the 16-byte pieces
 // permuted (k_piece_swizzle, v_piece_swizzle), V^T fetched with the transposing LDS read.
