@@ -92,6 +92,9 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 __device__ __forceinline__ float key_score(uint32_t k) {
   return __builtin_bit_cast(float, k ^ (k >> 31 ? 0x80000000u : 0xffffffffu));
 }
+// What the second phase is handed as the maximum of a group (k > 1): where no row ranks, the NaN whose key
+// comes after that of -infinity (it is key_score(0)), so that the selection need not test for it.
+__device__ __forceinline__ float group_max(float s) { return s == s ? s : key_score(0u); }
 
 // ---------------------------------------------------------------- phase 1, matrix cores
 // KSMAX > 0: a wave keeps its 32 rows whole in registers (E <= 16 KSMAX, E % 16 == 0) and multiplies
@@ -220,14 +223,14 @@ __global__ __launch_bounds__(kThreads) void search_f16_kernel(const SearchArgs a
         if (!per_wave) {
           if (kh == 0) red_s[wave * 32 * NQB + t] = s;
         } else if (kh == 0 && t < nq && rb < a.N) {
-          a.part_s[(size_t)(q0 + t) * a.G + gi] = s;
+          a.part_s[(size_t)(q0 + t) * a.G + gi] = group_max(s);
         }
       }
       if (!per_wave) {   // one group per pass (or several passes): the four waves meet in LDS
         __syncthreads();
         for (int t = tid; t < nq; t += kThreads)
           a.part_s[(size_t)(q0 + t) * a.G + gi] =
-              fmaxf(fmaxf(red_s[t], red_s[32 * NQB + t]), fmaxf(red_s[64 * NQB + t], red_s[96 * NQB + t]));
+              group_max(fmaxf(fmaxf(red_s[t], red_s[32 * NQB + t]), fmaxf(red_s[64 * NQB + t], red_s[96 * NQB + t])));
         __syncthreads();
       }
     }
@@ -435,7 +438,7 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
           const float s = fmaxf(best_s[j], __shfl_xor(best_s[j], 32));
           best_s[j] = none;
           const int qi = 32 * (QPW * wave + j) + il;
-          if (kh == 0 && qi < a.nq) a.part_s[(size_t)(a.q0 + qi) * a.G + gi] = s;
+          if (kh == 0 && qi < a.nq) a.part_s[(size_t)(a.q0 + qi) * a.G + gi] = group_max(s);
         }
       }
     }
@@ -626,9 +629,9 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
       const int pp = TOPK ? p : 0;
       const float v = fmaxf(fmaxf(red_s[0][tid][pp], red_s[1][tid][pp]), fmaxf(red_s[2][tid][pp], red_s[3][tid][pp]));
       all = fmaxf(all, v);
-      if (a.rows == 64 && row0 + 64 * p < a.N) a.part_s[out + row0 / 64 + p] = v;
+      if (a.rows == 64 && row0 + 64 * p < a.N) a.part_s[out + row0 / 64 + p] = group_max(v);
     }
-    if (a.rows != 64) a.part_s[out + blockIdx.x] = all;
+    if (a.rows != 64) a.part_s[out + blockIdx.x] = group_max(all);
   } else {
     float s = red_s[0][tid][0];
     int i = red_i[0][tid];
@@ -690,7 +693,7 @@ __global__ __launch_bounds__(kThreads) void search_row_kernel(const SearchArgs a
     if (TOPK) s = fmaxf(s, red_s[w]);
     else if (ranks_before(red_s[w], red_i[w], s, i)) { s = red_s[w]; i = red_i[w]; }
   }
-  a.part_s[(size_t)b * a.G + gidx] = s;
+  a.part_s[(size_t)b * a.G + gidx] = TOPK ? group_max(s) : s;
   if (!TOPK) a.part_i[(size_t)b * a.G + gidx] = i;
 }
 
@@ -808,12 +811,12 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
       for (int r = 0; r < R; ++r) {
         const int first = row0 + kWave * r;
         const bool ranks = first + lane < a.N && acc[r][j] == acc[r][j];
-        const float s = key_score(wave_max(ranks ? score_key(acc[r][j]) : 0u));   // (no key: a NaN)
+        const float s = key_score(wave_max(ranks ? score_key(acc[r][j]) : 0u));
         all = fmaxf(all, s);
         if (a.rows == kWave && lane == 0 && q < q_end && first < a.N)
           a.part_s[(size_t)q * a.G + first / kWave] = s;
       }
-      if (a.rows != kWave && lane == 0 && q < q_end) a.part_s[(size_t)q * a.G + gidx] = all;
+      if (a.rows != kWave && lane == 0 && q < q_end) a.part_s[(size_t)q * a.G + gidx] = group_max(all);
     }
     return;
   }
@@ -1063,7 +1066,7 @@ constexpr int kCountPerDraw = 16;   // items that may be compared with all other
 // for every rank r < k, with kIdxNone where fewer than k items rank.  NT threads, lists[NT].
 // Few items for that many draws: every thread compares its item with all others (they pass by in LDS),
 // and the number that rank before it is its rank.  64 items, k = 64: 7.7 us per call where drawing takes
-// 34; 1,024 items and k = 64 31 / 41, but k = 32 31 / 25, so up to 16 items per draw.
+// 34; 1,024 items and k = 64 35 / 41, but k = 32 31 / 25, so up to 16 items per draw.
 // Otherwise up to 16 items per thread sit in registers: every wave draws its own k best, the first wave draws
 // the k best of those.  Four waves do it while they can hold the items -- sixteen are four to a SIMD
 // and take turns (1,563 items, k = 8: 9 us against 3 us).  More items than 16 per thread (some 16
@@ -1078,8 +1081,9 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
     const int ranked = __syncthreads_count(mine != 0);
     if (wave * kWave < n) {
       typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+      constexpr int kUnroll = NT == 256 ? 8 : 2;
       int before = 0;
-#pragma unroll 8
+#pragma unroll kUnroll
       for (int x = 0; x < n; x += 2) {   // (one past an odd n: a zero)
         const u64x2 o = *reinterpret_cast<const u64x2*>(lists + x);
         before += (o.x > mine) + (o.y > mine);
@@ -1163,12 +1167,14 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
   const float* part = a.part_s + (size_t)b * a.G;
   const int ng = min(a.k, a.G);
   select_best<NT>(
-      a.G, ng, [&](int x) { return part[x] == part[x] ? item_key(part[x], x) : 0; }, [&](int r, float, int i) { sel[r] = i; }, lists);
+      a.G, ng, [&](int x) { return item_key(part[x], x); }, [&](int r, float, int i) { sel[r] = i; }, lists);
 
   // 2. the scores of their rows
   const int n_rows = ng * a.rows, shift = __builtin_ctz(a.rows);   // group sizes are powers of two
   const int part8 = tid & 7;
-  // (the last RPT rows or fewer alone: the other three of every thread would be repeats)
+  // (the last RPT rows or fewer alone: the other three of every thread would be repeats.  The large form
+  // does without this and with less unrolling above: every call pays for the code it brings in, 0.3 us of 32
+  // at 100,000 x 256, 64 queries, k = 8.)
   auto score_rows = [&](auto rows_in_flight, int slot0) {
     constexpr int U = decltype(rows_in_flight)::value;
     const T* row[U];
@@ -1212,7 +1218,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
     }
   };
   for (int first = 0; first < n_rows; first += 4 * RPT) {
-    if (n_rows - first > RPT) score_rows(std::integral_constant<int, 4>{}, first + (tid >> 3));
+    if (NT > 256 || n_rows - first > RPT) score_rows(std::integral_constant<int, 4>{}, first + (tid >> 3));
     else score_rows(std::integral_constant<int, 1>{}, first + (tid >> 3));
   }
   __syncthreads();
