@@ -74,6 +74,11 @@ __device__ __forceinline__ float max_with_other_half(float x) {
   return fmaxf(lo, hi);
 }
 
+// The upper 32 lanes of a and the lower 32 lanes of b change places (the instruction above).
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+
 // Permutation of the 16-byte pieces of a V row staged row-major in LDS for the transposing
 // read (ds_read_b64_tr_b16): piece p of key row r sits at position p ^ v_piece_swizzle(r).  One
 // such read instruction serves 32 lanes per LDS cycle: four consecutive keys x the two
