@@ -543,13 +543,13 @@ __global__ __launch_bounds__(kThreads) void pack_maps_kernel(const bf16_t* __res
 // 4-byte aligned, which the load allows).  The next stage's V and map pieces are requested before
 // this one is multiplied.  Above the diagonal of a causal map nothing that was read is used.
 // 16 queries (12 hits) x 2 layers x 24 heads on 8 V, 94 x 128 causal: 403 us with one thread per
-// output and scalar loads, 22.6 us so (48 MB, 9 us at the copy rate; bound by the chain of load,
-// stage and product in a workgroup -- 64-key stages or four workgroups per CU measure the same).
-template <int DB>
-__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
-    const ApplyArgs a, int D, int causal) {
+// output and scalar loads, 20.5 us so (48 MB, 9 us at the copy rate; bound by the chain of load,
+// stage and product in a workgroup -- 64-key stages or four workgroups per CU measure the same; with map
+// pieces behind tests, which the compiler waited for before the products, 22.2 us).
+template <int DB, int COLS>
+__device__ __forceinline__ void apply_f32_tiles(const ApplyArgs& a, int D, int causal) {
   constexpr int KC = 32, NB = KC / 16;
-  typedef F32Stage<DB, KC> Stage;
+  typedef F32Stage<DB, KC, COLS> Stage;
   __shared__ __attribute__((aligned(16))) float vl[KC * Stage::LD];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -583,40 +583,42 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
 
   Stage vs;
   f32x4 map[NB];
+  // Four columns of the lane's row of each block from jc on (S >= 4).  Past the columns that count the last four of
+  // them are read again, at the end of a row shifted, which lane_map undoes: no load behind a test (the compiler
+  // waits for such a load where the branches meet), and none past the row.
+  const int last_col = max(wave_keys - 4, 0);
   auto load_map = [&](int jc) {
 #pragma unroll
-    for (int bk = 0; bk < NB; ++bk) {
-      const int j = jc + 16 * bk + 4 * kq;
-      map[bk] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (jc + 16 * bk < wave_keys) {   // wave-uniform
-        if (j + 4 <= S) {
-          map[bk] = *reinterpret_cast<const f32x4_dw*>(A + j);
-        } else {
-#pragma unroll
-          for (int x = 0; x < 4; ++x)
-            if (j + x < S) map[bk][x] = A[j + x];
-        }
-      }
-    }
+    for (int bk = 0; bk < NB; ++bk)
+      map[bk] = *reinterpret_cast<const f32x4_dw*>(A + min(jc + 16 * bk + 4 * kq, last_col));
+  };
+  auto lane_map = [&](int j0, f32x4 m) {
+    const int by = j0 + 4 * kq - last_col;   // columns the lane read too early (four or more: none counts)
+    const bool two = by > 0 && (by & 2), one = by > 0 && (by & 1);
+    m = two ? f32x4{m[2], m[3], m[2], m[3]} : m;
+    return one ? f32x4{m[1], m[2], m[3], m[3]} : m;
   };
   f32x4 acc[4 * DB];
 #pragma unroll
   for (int x = 0; x < 4 * DB; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int last_stage = (wg_keys - 1) / KC * KC;
   vs.load(V, 0, S, D, tid);
   load_map(0);
   for (int jc = 0; jc < wg_keys; jc += KC) {
+    vs.template mask<true>(jc, S, D, tid);
     __syncthreads();   // the previous stage has been read by everybody
     vs.commit(vl, tid);
     f32x4 w[NB];
 #pragma unroll
-    for (int bk = 0; bk < NB; ++bk)
+    for (int bk = 0; bk < NB; ++bk) {
+      const f32x4 m = lane_map(jc + 16 * bk, map[bk]);
 #pragma unroll
-      for (int x = 0; x < 4; ++x) w[bk][x] = jc + 16 * bk + 4 * kq + x < limit ? map[bk][x] : 0.f;
-    __syncthreads();
-    if (jc + KC < wg_keys) {
-      vs.load(V, jc + KC, S, D, tid);
-      load_map(jc + KC);
+      for (int x = 0; x < 4; ++x) w[bk][x] = jc + 16 * bk + 4 * kq + x < limit ? m[x] : 0.f;
     }
+    __syncthreads();
+    const int next = min(jc + KC, last_stage);   // (the last trip: once more, unused)
+    if (COLS != kAnyCols || jc + KC < wg_keys) vs.load(V, next, S, D, tid);
+    load_map(next);
 #pragma unroll
     for (int bk = 0; bk < NB; ++bk)
       if (jc + 16 * bk < wave_keys) {
@@ -626,7 +628,7 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
       }
   }
   float* O = reinterpret_cast<float*>(a.O) + (((size_t)b * a.Lc + l) * a.Hq + h) * (size_t)S * D;
-  if (u.block >= 0 && row < S && !redo) f32_store_row<DB>(O + (size_t)row * D, acc, 1.f, kq, D);
+  if (u.block >= 0 && row < S && !redo) f32_store_row<DB, COLS, false>(O + (size_t)row * D, acc, 1.f, kq, D);
   if (redo) {   // infinite or NaN V near the diagonal: lane = output column, only visible keys are read
     const int first = kF32Rows * u.block, rows = min(kF32Rows, S - first);
 #pragma unroll 1
@@ -640,11 +642,20 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(
   }
 }
 
+template <int DB>   // D == 64 DB
+__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(const ApplyArgs a, int causal) {
+  apply_f32_tiles<DB, kAllCols>(a, 64 * DB, causal);
+}
+template <int DB, int COLS>
+__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel_cols(const ApplyArgs a, int D, int causal) {
+  apply_f32_tiles<DB, COLS>(a, D, causal);
+}
+
 // The same for maps of a few rows, whose time is the chain above and not the work: one workgroup per (query,
 // layer, head), a thread per output, sums over ascending columns.  us per call, tiles / this: 256 heads of
 // 1 x 256 6.0 / 2.5, of 8 x 64 3.8 / 3.5, of 12 x 40 4.0 / 4.2.
 __global__ __launch_bounds__(kThreads) void apply_f32_small_kernel(const ApplyArgs a, int D, int causal) {
-  const int tile = blockIdx.x, h = tile % a.Hq, l = tile / a.Hq % a.Lc, bslot = tile / (a.Hq * a.Lc);
+  const int tile = a.tile0 + blockIdx.x, h = tile % a.Hq, l = tile / a.Hq % a.Lc, bslot = tile / (a.Hq * a.Lc);
   const int b = a.fixed_entry >= 0 ? a.q_list[bslot] : bslot;
   const int entry = a.fixed_entry >= 0 ? a.fixed_entry : a.hit[b];
   if (a.fixed_entry < 0 && (entry < 0 || entry >= a.M)) return;
@@ -670,7 +681,13 @@ static hipError_t launch_apply_f32(ApplyArgs a, int D, int causal, hipStream_t s
   const int fit = 8 * (int)std::min<size_t>(std::max<size_t>(eights, 1), 1 << 27);
   for (a.tile0 = 0; a.tile0 < n_tiles; a.tile0 += a.n_tiles) {
     a.n_tiles = std::min(n_tiles - a.tile0, fit);
-    hipLaunchKernelGGL((apply_f32_kernel<DB>), dim3(f32_grid(a.n_tiles, g, a.S)), dim3(kThreads), 0, stream, a, D, causal);
+    const dim3 grid(f32_grid(a.n_tiles, g, a.S));
+    if (D == 64 * DB)
+      hipLaunchKernelGGL((apply_f32_kernel<DB>), grid, dim3(kThreads), 0, stream, a, causal);
+    else if (D % 4 == 0)
+      hipLaunchKernelGGL((apply_f32_kernel_cols<DB, kVecCols>), grid, dim3(kThreads), 0, stream, a, D, causal);
+    else
+      hipLaunchKernelGGL((apply_f32_kernel_cols<DB, kAnyCols>), grid, dim3(kThreads), 0, stream, a, D, causal);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -734,9 +751,15 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
   if (p.is_f32) {
     a.heads_per_wg = 1; a.n_rblk = 1; a.n_tiles = nb * p.Lc * p.Hkv;
     const size_t tiles = (size_t)nb * p.Lc * p.Hq;
-    if ((p.S <= 5 || (size_t)p.S * p.S * p.D <= 3400) && tiles < ((size_t)1 << 32) / kThreads) {
-      hipLaunchKernelGGL(apply_f32_small_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, stream, a, p.D, p.causal);
-      return hipGetLastError();
+    if (p.S <= 5 || (size_t)p.S * p.S * p.D <= 3400) {   // (the other kernel reads rows of four columns or more)
+      constexpr size_t kFit = ((size_t)1 << 31) / kThreads;
+      for (size_t t0 = 0; t0 < tiles; t0 += kFit) {
+        a.tile0 = (int32_t)t0;
+        hipLaunchKernelGGL(apply_f32_small_kernel, dim3((unsigned)std::min(tiles - t0, kFit)), dim3(kThreads), 0, stream, a, p.D, p.causal);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
     }
     if (p.D <= 64) return launch_apply_f32<1>(a, p.D, p.causal, stream);
     if (p.D <= 128) return launch_apply_f32<2>(a, p.D, p.causal, stream);

@@ -599,14 +599,15 @@ __device__ __forceinline__ void f32_row_by_key(const ExactArgs& a, const float* 
 // multiplied.  Online softmax: every lane keeps the running maximum and ITS keys' share of the row
 // sum, the accumulator is rescaled when a maximum of the wave moves.
 // 16 x 24 heads on 8 K and V, 94 x 128 causal: 805 us with one wave per query row on the vector
-// ALUs, 25.2 us so (7 us of matrix instructions at the peak rate, 10 us of memory at the copy
-// rate; the rest is the load -> stage -> score -> weight chain of 640 workgroups that start
-// together).  Four workgroups per CU need 128 registers and spill (38 us).
-template <int DB>
+// ALUs, 20.8 us so (7 us of matrix instructions at the peak rate, which the vector instructions do not overlap
+// here, 10 us of memory at the copy rate; the rest is the load -> stage -> score -> weight chain of 640
+// workgroups that start together).  Four workgroups per CU need 128 registers and spill (38 us).
+template <int DB, int COLS>
 __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
     const ExactArgs a, int D, int causal, float scale) {
   constexpr int KC = 32;
-  typedef F32Stage<DB, KC> Stage;
+  typedef F32Stage<DB, KC, COLS> Stage;
+  if (COLS == kAllCols) D = 64 * DB;
   __shared__ __attribute__((aligned(16))) float kl[KC * Stage::LD];
   __shared__ __attribute__((aligned(16))) float vl[KC * Stage::LD];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -628,13 +629,16 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
   for (int kk = 0; kk < 4 * DB; ++kk) {
     const int c = 16 * kk + 4 * kq;
     const float* src = reinterpret_cast<const float*>(a.Q) + at + c;
-    q[kk] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if ((D & 3) == 0) {
-      if (c < D) q[kk] = *reinterpret_cast<const f32x4*>(src);
-    } else {
+    if constexpr (COLS == kAnyCols) {
+      q[kk] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int t = 0; t < 4; ++t)
         if (c + t < D) q[kk][t] = src[t];
+    } else {
+      q[kk] = *reinterpret_cast<const f32x4*>(COLS == kAllCols || c < D ? src : src - c);
+      if (COLS == kVecCols)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) q[kk][t] = c < D ? q[kk][t] : 0.f;
     }
   }
   f32x4 acc[4 * DB];
@@ -650,6 +654,8 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
   ks.load(K, 0, len, D, tid);
   vs.load(V, 0, len, D, tid);
   for (int jc = 0; jc < wg_keys; jc += KC) {
+    ks.template mask<false>(jc, len, D, tid);   // (scores of hidden keys are replaced)
+    vs.template mask<true>(jc, len, D, tid);
     __syncthreads();   // the previous stage has been read by everybody
     ks.commit(kl, tid);
     vs.commit(vl, tid);
@@ -669,7 +675,7 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
         f32x4 k = *reinterpret_cast<const f32x4*>(krow);
 #pragma unroll
         for (int kk = 0; kk < 4 * DB; ++kk) {
-          if (16 * kk < D) {   // uniform
+          if (COLS == kAllCols || 16 * kk < D) {   // uniform
             const f32x4 next = *reinterpret_cast<const f32x4*>(krow + 16 * ((kk + 1) & (4 * DB - 1)));
 #pragma unroll
             for (int t = 0; t < 4; ++t) s[bk] = mfma_f32(k[t], q[kk][t], s[bk]);
@@ -718,7 +724,7 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
   if (u.block >= 0 && row < S && !redo)
-    f32_store_row<DB>(reinterpret_cast<float*>(a.O) + at, acc, l, kq, D);
+    f32_store_row<DB, COLS, true>(reinterpret_cast<float*>(a.O) + at, acc, l, kq, D);
   if (redo) {
     const int rows = min(kF32Rows, S - kF32Rows * u.block);
     for (int r = 0; r < rows; ++r)
@@ -904,7 +910,12 @@ static hipError_t launch_exact_f32(const ExactArgs& a, int D, int causal, float 
     return hipGetLastError();
   }
   const unsigned grid = f32_grid(a.n_kvtiles, a.Hq / a.Hkv, a.S);
-  hipLaunchKernelGGL((exact_f32_kernel<DB>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
+  if (D == 64 * DB)
+    hipLaunchKernelGGL((exact_f32_kernel<DB, kAllCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
+  else if (D % 4 == 0)
+    hipLaunchKernelGGL((exact_f32_kernel<DB, kVecCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
+  else
+    hipLaunchKernelGGL((exact_f32_kernel<DB, kAnyCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
   return hipGetLastError();
 }
 

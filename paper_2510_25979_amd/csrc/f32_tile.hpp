@@ -24,35 +24,66 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// KC rows of up to 64 DB floats on their way from memory through registers to LDS.  Rows from
-// `valid` on and columns from D on become zeros: hidden keys then carry finite values whatever
-// the padding of a batch holds.  LDS rows are four floats longer than the data, which spreads the
-// 16-byte reads of 16 consecutive rows over all banks.
+// What is known of the head dimension when a kernel is compiled.  With all three forms in one kernel every piece
+// of a row was a load behind tests of its own (16 x 24 heads on 8 K and V, 94 x 128 causal: 24.0 us exact, 21.7 so;
+// 16 x 8 heads of 333 x 128 61 / 54).
+enum F32Cols {
+  kAnyCols = 0,   // any D: rows may start at any 4-byte address
+  kVecCols = 1,   // D % 4 == 0: whole 16-byte pieces
+  kAllCols = 2,   // D == 64 DB
+};
+
+// KC rows of up to 64 DB floats on their way from memory through registers to LDS.  LDS rows are four
+// floats longer than the data, which spreads the 16-byte reads of 16 consecutive rows over all banks.
 // (DB is 1, 2 or 4: from one piece of a thread to its next the row grows by a whole number and
 // the column stays, so one lane offset serves all of them.)
-template <int DB, int KC>
+template <int DB, int KC, int COLS>
 struct F32Stage {
   static constexpr int LD = 64 * DB + 4;
   static constexpr int N = KC * 16 * DB / kThreads, STEP = kThreads / (16 * DB);
   f32x4 r[N];
 
+  // Rows [row0, row0 + KC) of which those from `valid` (> row0) on do not exist.  No load sits behind a
+  // test: what does not exist repeats something that does, and mask() takes it out.
   __device__ __forceinline__ void load(const float* __restrict__ src, int row0, int valid, int D,
                                        int tid) {
     const int row = tid / (16 * DB), c = 4 * (tid % (16 * DB));
-    const unsigned off = (unsigned)(row * D + c);
     const float* base = src + (size_t)row0 * D;   // uniform
+    const int last = valid - 1 - row0;
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-      r[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (row0 + row + n * STEP < valid && c < D) {
-        const float* at = base + (size_t)(n * STEP) * D + off;
-        if ((D & 3) == 0) {
-          r[n] = *reinterpret_cast<const f32x4*>(at);
-        } else {
+      if constexpr (COLS == kAnyCols) {
+        // Clamped like the others, without the outer test, or without the vector form (which D % 4 != 0 never
+        // takes): 7 to 60 % longer at D = 33 or 199, the compiler then keeps every address or waits load by load.
+        r[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (row + n * STEP <= last && c < D) {
+          const float* at = base + (size_t)(n * STEP) * D + (unsigned)(row * D + c);
+          if ((D & 3) == 0) {
+            r[n] = *reinterpret_cast<const f32x4*>(at);
+          } else {
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
-            if (c + t < D) r[n][t] = at[t];
+            for (int t = 0; t < 4; ++t)
+              if (c + t < D) r[n][t] = at[t];
+          }
         }
+      } else {
+        const int at = min(row + n * STEP, last) * D;
+        r[n] = *reinterpret_cast<const f32x4*>(base + (unsigned)(at + (COLS == kAllCols || c < D ? c : 0)));
+      }
+    }
+  }
+  // Zeros in the rows from `valid` on (hidden keys then carry finite values whatever the padding of a
+  // batch holds), if ROWS, and in the columns from D on.
+  template <bool ROWS>
+  __device__ __forceinline__ void mask(int row0, int valid, int D, int tid) {
+    const int row = tid / (16 * DB), c = 4 * (tid % (16 * DB));
+    if (COLS == kAnyCols) return;
+    if ((ROWS && row0 + KC > valid) || (COLS == kVecCols && D < 64 * DB)) {   // uniform
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        const bool in = !ROWS || row0 + row + n * STEP < valid;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r[n][t] = in && (COLS == kAllCols || c < D) ? r[n][t] : 0.f;
       }
     }
   }
@@ -68,7 +99,7 @@ struct F32Stage {
 template <int DB>
 __device__ __forceinline__ void f32_weights_v(f32x4 (&acc)[4 * DB], const float* __restrict__ v,
                                               const f32x4 w, int i, int kq) {
-  constexpr int LD = F32Stage<DB, 64>::LD;
+  constexpr int LD = F32Stage<DB, 64, kAllCols>::LD;
   struct Rows { f32x4 b[DB]; };   // this lane's part of key 4 kq + x
   auto read = [&](int x) {
     Rows r;
@@ -108,7 +139,7 @@ __device__ __forceinline__ bool f32_not_finite(const f32x4 r) {
 }
 template <int DB>
 __device__ __forceinline__ bool f32_block_not_finite(const float* __restrict__ v, int i, int kq) {
-  constexpr int LD = F32Stage<DB, 64>::LD;
+  constexpr int LD = F32Stage<DB, 64, kAllCols>::LD;
   bool odd = false;
 #pragma unroll
   for (int x = 0; x < 4; ++x)
@@ -118,19 +149,29 @@ __device__ __forceinline__ bool f32_block_not_finite(const float* __restrict__ v
   return __any(odd);
 }
 
-// The lane's share of its output row: o points at the row, acc is divided by `by`.
-template <int DB>
+// x / by as the division gives it but for the last bit in rare cases: one reciprocal serves a whole row
+// (a division is ten instructions).  Infinities and NaN are those of the product.
+__device__ __forceinline__ float f32_divide(float x, float by, float inv) {
+  const float q = x * inv, rest = fmaf(-q, by, x);
+  return rest == rest ? fmaf(rest, inv, q) : q;
+}
+
+// The lane's share of its output row: o points at the row, acc is divided by `by` unless that is known to be 1.
+template <int DB, int COLS, bool DIVIDE>
 __device__ __forceinline__ void f32_store_row(float* __restrict__ o, const f32x4 (&acc)[4 * DB],
                                               float by, int kq, int D) {
+  const float inv = DIVIDE ? 1.f / by : 1.f;
 #pragma unroll
   for (int b = 0; b < DB; ++b)
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int d = 64 * b + 16 * kq + 4 * x;
-      const f32x4 w = {acc[4 * b][x] / by, acc[4 * b + 1][x] / by, acc[4 * b + 2][x] / by,
-                       acc[4 * b + 3][x] / by};
-      if ((D & 3) == 0) {
-        if (d < D) *reinterpret_cast<f32x4*>(o + d) = w;
+      f32x4 w = {acc[4 * b][x], acc[4 * b + 1][x], acc[4 * b + 2][x], acc[4 * b + 3][x]};
+      if (DIVIDE)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) w[t] = f32_divide(w[t], by, inv);
+      if constexpr (COLS != kAnyCols) {
+        if (COLS == kAllCols || d < D) *reinterpret_cast<f32x4*>(o + d) = w;
       } else {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -151,12 +192,17 @@ struct F32Unit {
 // nearly at once (up to kF32Spread workgroups) takes the heaviest workgroup of EVERY tile first,
 // so that no compute unit ends up with several heavy ones (384 heads of 94 x 128 causal, 640
 // workgroups: 29.5 -> 25.3 us exact, 25.4 -> 23.1 us reuse); a larger one finishes tile by tile,
-// while its K and V are in the L2.
+// while its K and V are in the L2.  Of the former every second 32 workgroups of an XCD go out in the other order, so
+// that the compute units (32 per XCD, filled one after the other) that got the heaviest get the lightest
+// next (the same shape 21.7 -> 20.8 and 21.9 -> 21.2 us).
 constexpr int kF32Spread = 2048;
+constexpr int kXcdCus = 32;
 __device__ __forceinline__ F32Unit f32_unit(int bid, int wave, int g, int S, int n_tiles) {
   const int n_units = g * ((S + kF32Rows - 1) / kF32Rows), per_tile = (n_units + 3) >> 2;
-  const int slot = bid >> 3, tiles8 = (n_tiles + 7) >> 3;
+  const int tiles8 = (n_tiles + 7) >> 3;
   const bool spread = gridDim.x <= kF32Spread;
+  int slot = bid >> 3;
+  if (spread && (slot & kXcdCus) && (slot | (kXcdCus - 1)) < (int)(gridDim.x >> 3)) slot ^= kXcdCus - 1;
   F32Unit u;
   u.tile = (spread ? slot % tiles8 : slot / per_tile) * 8 + (bid & 7);
   const int top = n_units - 1 - 4 * (spread ? slot / tiles8 : slot % per_tile), n = top - wave;

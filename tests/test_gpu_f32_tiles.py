@@ -26,6 +26,10 @@ CASES = [
     (3, 4, 2, 5, 256, True),        # reuse: a thread per output, more outputs than threads
     (5, 3, 1, 16, 12, False),
     (4, 2, 1, 16, 20, True),        # and the first size beyond
+    (2, 2, 1, 23, 33, True),        # rows of odd length of one, two and four output blocks
+    (2, 2, 1, 34, 99, False),
+    (1, 4, 2, 50, 199, True),
+    (16, 24, 8, 94, 128, True),     # workgroups for every compute unit two and a half times
 ]
 
 
