@@ -1028,73 +1028,56 @@ __device__ __forceinline__ uint64_t item_key(float s, int i) {
   return (uint64_t)score_key(s) << 32 | (uint32_t)~i;
 }
 
-// The k best of the items a wave holds (IPT per lane), drawn one after the other: the r-th best ends
-// up in lane r (k <= 64).  No barrier, no memory; the lane whose item was drawn looks for its next
-// one, which is why IPT is a compile-time number (16 guarded by the real count: 1,500 cycles a draw).
-template <int IPT>
-__device__ __forceinline__ uint64_t draw_best(const uint64_t (&item)[IPT], int k) {
-  const int lane = threadIdx.x & 63;
-  uint64_t best = 0, out = 0;
-#pragma unroll
-  for (int t = 0; t < IPT; ++t) best = max(best, item[t]);
-  for (int r = 0; r < k; ++r) {
-    const uint32_t top = wave_max((uint32_t)(best >> 32));
-    if (top == 0) break;   // nothing is left
-    const bool at = (uint32_t)(best >> 32) == top;
-    const unsigned long long who = __ballot(at);
-    const uint32_t low = (who & (who - 1)) ? wave_max(at ? (uint32_t)best : 0u)   // equal scores
-                                           : __builtin_amdgcn_readlane((uint32_t)best, (int)__builtin_ctzll(who));
-    const uint64_t pick = (uint64_t)top << 32 | low;
-    if (lane == r) out = pick;
-    if (best == pick) {   // one lane: its best item after this one
-      best = 0;
-#pragma unroll
-      for (int t = 0; t < IPT; ++t) {
-        const uint64_t x = item[t] < pick ? item[t] : 0;
-        best = max(best, x);
-      }
-    }
-  }
-  return out;
+constexpr int kItems = 16;          // most items of a thread
+constexpr int kCountPerDraw = 16;   // items per rank sought that are all compared with each other straight away
+// Up to 256 items and so few ranks: one wave draws the best again and again, without a barrier.  us per call, so / by
+// the two ways above: 1,895 x 256, two queries, k = 2 (60 groups, 64 rows) 9.7 / 13.2; 5,000 x 256, 64 queries, k = 8 16.6 /
+// 17.9.  Not for up to four items per rank: 700 x 128, 8 queries, k = 8 (11 groups) 12.2 / 11.7.
+constexpr int kDrawRanks = 8;
+
+// x of the lane that the DPP control names (a lane without one keeps its own).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint64_t dpp64(uint64_t x) {
+  const int lo = (int)(uint32_t)x, hi = (int)(uint32_t)(x >> 32);
+  return (uint64_t)(uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false) << 32 |
+         (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
 }
 
-constexpr int kItems = 16;   // most items of a lane
-constexpr int kCountPerDraw = 16;   // items that may be compared with all others rather than drawn k times
+// The best item of the lane's four, of its sixteen.
+__device__ __forceinline__ uint64_t quad_best(uint64_t x) {
+  x = max(x, dpp64<0xb1>(x));          // quad_perm 1 0 3 2
+  return max(x, dpp64<0x4e>(x));       // quad_perm 2 3 0 1
+}
+__device__ __forceinline__ uint64_t row_best(uint64_t x) {
+  x = quad_best(x);
+  x = max(x, dpp64<0x141>(x));         // row_half_mirror
+  return max(x, dpp64<0x140>(x));      // row_mirror
+}
 
 // The k best of n items under the total order "higher score, then lower number", in rank order.
 // get(x) is item x as item_key (0: it does not rank, e.g. a NaN score); put(r, s, i) is called once
-// for every rank r < k, with kIdxNone where fewer than k items rank.  NT threads, lists[NT].
-// Few items for that many draws: every thread compares its item with all others (they pass by in LDS),
-// and the number that rank before it is its rank.  64 items, k = 64: 7.7 us per call where drawing takes
-// 34; 1,024 items and k = 64 35 / 41, but k = 32 31 / 25, so up to 16 items per draw.
-// Otherwise up to 16 items per thread sit in registers: every wave draws its own k best, the first wave draws
-// the k best of those.  Four waves do it while they can hold the items -- sixteen are four to a SIMD
-// and take turns (1,563 items, k = 8: 9 us against 3 us).  More items than 16 per thread (some 16
-// million rows) take k rounds over memory.
+// for every rank r < k, with kIdxNone where fewer than k items rank.
+// An item's rank is the number of items before it, and few items need to be compared: the k-th best of the
+// maxima of 64 parts is a bound that k items reach and, in typical data, some 2 k to 4 k.  (Those that reach it
+// lie in k parts, so no data make them more than k / 64 of all.)  Drawing the best k times in every wave, then again
+// among what the waves drew, took 36 KB of code and 30.7 us per call of 100,000 x 256, 64 queries, k = 8, 141 at k = 64;
+// 23.6 and 63 so.
+// Few items for that many ranks are compared straight away, and few ranks of few items drawn (below).  More than 16
+// items per thread (some 16
+// million rows), or more that reach the bound than the list holds, take k rounds over memory.
+// NT threads, list[NT]: the items that are ranked, before them the best item of every part, behind them their number
+// and the bound.
 template <int NT, typename Get, typename Put>
-__device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint64_t* lists) {
+__device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint64_t* list) {
+  typedef uint32_t __attribute__((may_alias)) word;
+  word& count = *reinterpret_cast<word*>(list + NT - 2);
+  uint64_t& least = list[NT - 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (n <= NT && n <= kCountPerDraw * k) {
-    const uint64_t mine = tid < n ? get(tid) : 0;
-    lists[tid] = mine;
-    __syncthreads();
-    const int ranked = __syncthreads_count(mine != 0);
-    if (wave * kWave < n) {
-      typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-      constexpr int kUnroll = NT == 256 ? 8 : 2;
-      int before = 0;
-#pragma unroll kUnroll
-      for (int x = 0; x < n; x += 2) {   // (one past an odd n: a zero)
-        const u64x2 o = *reinterpret_cast<const u64x2*>(lists + x);
-        before += (o.x > mine) + (o.y > mine);
-      }
-      if (mine != 0 && before < k) put(before, key_score((uint32_t)(mine >> 32)), (int)~(uint32_t)mine);
-    }
-    if (tid >= ranked && tid < k) put(tid, -INFINITY, kIdxNone);
-    __syncthreads();
-    return;
-  }
-  if (n > kItems * NT) {
+  auto item_at = [&](int x) {
+    const uint64_t it = get(min(x, n - 1));   // (no load behind a test)
+    return x < n ? it : 0;
+  };
+  auto rounds = [&]() {
     uint64_t last = ~0ull;
     for (int r = 0; r < k; ++r) {
       uint64_t best = 0;
@@ -1102,60 +1085,147 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
         const uint64_t it = get(x);
         if (it < last) best = max(best, it);
       }
-      lists[tid] = best;
+      list[tid] = best;
       __syncthreads();
       for (int half = NT / 2; half > 0; half >>= 1) {
-        if (tid < half) lists[tid] = max(lists[tid], lists[tid + half]);
+        if (tid < half) list[tid] = max(list[tid], list[tid + half]);
         __syncthreads();
       }
-      last = lists[0];
+      last = list[0];
       __syncthreads();
       if (tid == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
     }
     __syncthreads();
+  };
+  // list[0, m) is there: ranks of the items in it that rank at all
+  auto rank = [&](int m) {
+    uint64_t mine = tid < m ? list[tid] : 0;
+    const int ranked = __syncthreads_count(mine != 0);
+    if (wave * kWave < m) {
+      typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+      int before = 0;
+#pragma unroll 4
+      for (int x = 0; x + 1 < m; x += 2) {
+        const u64x2 o = *reinterpret_cast<const u64x2*>(list + x);
+        before += (o.x > mine) + (o.y > mine);
+      }
+      if (m & 1) before += list[m - 1] > mine;
+      if (mine != 0 && before < k) put(before, key_score((uint32_t)(mine >> 32)), (int)~(uint32_t)mine);
+    }
+    if (tid >= ranked && tid < k) put(tid, -INFINITY, kIdxNone);
+    __syncthreads();
+  };
+  // list := the items that reach the bound.  A thread's first four items stay in registers, others are fetched again.
+  auto collect = [&]() {
+    uint64_t it[4], best = 0;
+    auto fetch = [&](int x) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) it[t] = item_at(x + t * NT);
+    };
+    auto best_of = [&]() {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) best = max(best, it[t]);
+    };
+    if (n > 4 * NT) {
+#pragma unroll 1
+      for (int x = 4 * NT + tid; x < n; x += 4 * NT) {
+        fetch(x);
+        best_of();
+      }
+    }
+    fetch(tid);
+    best_of();
+    // parts: NT / 64 neighbouring lanes, or whole waves where there are at least two of them for every rank
+    const bool waves = 2 * k <= NT / kWave;   // uniform
+    const int parts = waves ? NT / kWave : kWave;
+    if (NT == 1024 || waves) best = row_best(best);
+    else best = quad_best(best);
+    if (waves) {
+      best = max(best, dpp64<0x142, 0xa>(best));   // lane 15 of a row into the next one
+      best = max(best, dpp64<0x143, 0xc>(best));   // lane 31 into the upper half: lane 63 has seen them all
+      if (lane == kWave - 1) list[wave] = best;
+    } else if (tid % (NT / kWave) == 0) {
+      list[tid / (NT / kWave)] = best;
+    }
+    if (tid == 0) count = 0;
+    __syncthreads();
+    if (wave == 0) {
+      const uint64_t mine = lane < parts ? list[lane] : 0;
+      int before = 0;
+#pragma unroll 4
+      for (int x = 0; x < parts; ++x) before += list[x] > mine;
+      if (__popcll(__ballot(mine != 0)) < k) {
+        if (lane == 0) least = 1;   // fewer parts than that hold an item: all of them count
+      } else if (mine != 0 && before == k - 1) {
+        least = mine;
+      }
+    }
+    __syncthreads();
+    const uint64_t bound = least;
+#pragma unroll 1
+    for (int x0 = wave * kWave;;) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const bool in = it[t] >= bound;
+        const unsigned long long who = __ballot(in);
+        if (who == 0) continue;   // (wave-uniform: most)
+        int at = 0;
+        if (lane == 0) at = (int)atomicAdd(&count, (uint32_t)__popcll(who));
+        at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1));
+        if (in && at < NT - 2) list[at] = it[t];
+      }
+      if ((x0 += 4 * NT) >= n) break;
+      fetch(x0 + lane);
+    }
+    __syncthreads();
+  };
+  int m = n;
+  if (k <= kDrawRanks && n <= 4 * kWave && n > 4 * k) {
+    if (wave == 0) {
+      uint64_t it[4], last = ~0ull;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) it[t] = item_at(t * kWave + lane);
+#pragma unroll 1
+      for (int r = 0; r < k; ++r) {
+        uint64_t best = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) best = max(best, it[t] < last ? it[t] : 0);
+        best = row_best(best);
+        best = max(best, dpp64<0x142, 0xa>(best));
+        best = max(best, dpp64<0x143, 0xc>(best));
+        last = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(best >> 32), 63) << 32 |
+               (uint32_t)__builtin_amdgcn_readlane((uint32_t)best, 63);
+        if (lane == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
+      }
+    }
+    __syncthreads();
     return;
   }
-  const int waves = n <= kItems * 256 ? 4 : NT / kWave, stride = waves * kWave;
-  auto draw = [&](auto ipt, int m, int step, int first, auto item_of) {
-    uint64_t item[decltype(ipt)::value];
-#pragma unroll
-    for (int t = 0; t < decltype(ipt)::value; ++t) {
-      const int x = t * step + first;
-      item[t] = x < m ? item_of(x) : 0;
-    }
-    return draw_best(item, k);
-  };
-  auto draw_n = [&](int m, int step, int first, auto item_of) {
-    if (m <= step) return draw(std::integral_constant<int, 1>{}, m, step, first, item_of);
-    if (m <= 2 * step) return draw(std::integral_constant<int, 2>{}, m, step, first, item_of);
-    if (m <= 4 * step) return draw(std::integral_constant<int, 4>{}, m, step, first, item_of);
-    if (m <= 8 * step) return draw(std::integral_constant<int, 8>{}, m, step, first, item_of);
-    return draw(std::integral_constant<int, kItems>{}, m, step, first, item_of);
-  };
-  if (wave < waves) {
-    const uint64_t best = draw_n(n, stride, tid, get);
-    if (lane < k) lists[wave * k + lane] = best;
+  if (n <= NT && n <= kCountPerDraw * k) {
+    list[tid] = item_at(tid);
+    __syncthreads();
+  } else if (n <= kItems * NT) {
+    collect();
+    m = (int)count;
+    if (m > NT - 2) m = NT + 1;
+    __syncthreads();   // (the rounds and the next selection write what was just read)
   }
-  __syncthreads();
-  if (wave == 0) {
-    const uint64_t best = draw_n(waves * k, kWave, lane, [&](int x) { return lists[x]; });
-    if (lane < k) put(lane, best ? key_score((uint32_t)(best >> 32)) : -INFINITY, best ? (int)~(uint32_t)best : kIdxNone);
-  }
-  __syncthreads();   // the lists and what put() wrote
+  if (m > NT) rounds();
+  else rank(m);
 }
 
 // k > 1: pick the k best groups, re-score their rows, pick the k best rows.  One workgroup per
 // query.  Rows are re-scored by eight threads each, reading 16-byte pieces side by side, four rows
 // in flight per thread.  100,000 x 256, 64 queries, k = 8: 70 us with 256-row groups, a row per
-// thread read two bytes at a time, and k rounds of a workgroup-wide arg-max; 18 us so, of which the
-// two selections take 6 and 4 (1,563 and 512 items) and the 512 rows 6 (260 KB through one compute
-// unit's 64 bytes per clock).  Bound by that serial chain on as many compute units as queries.
-template <typename T, int NT>
+// thread read two bytes at a time, and k rounds of a workgroup-wide arg-max; 10 us so.  Bound by the serial
+// chain of a selection among 1,563 groups, 512 rows (260 KB through one compute unit's 64 bytes per clock) and
+// a selection among those, on as many compute units as queries.
+template <typename T, int NT, bool L2>
 __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {
   typedef RowPiece<T> Piece;
   constexpr int P = Piece::P, RPT = NT / 8;   // rows per step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  uint64_t* lists = reinterpret_cast<uint64_t*>(smem);        // [NT] the waves' best
+  uint64_t* lists = reinterpret_cast<uint64_t*>(smem);        // [NT] for the selections
   int* sel = reinterpret_cast<int*>(lists + NT);              // [kMaxK] selected groups
   float* qf = reinterpret_cast<float*>(sel + kMaxK);          // [E rounded up to 4]
   const int b = a.q0 + blockIdx.x, tid = threadIdx.x;
@@ -1199,7 +1269,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
         const float qv = qf[c + t];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          if (a.metric == 0) {
+          if (!L2) {
             acc[u] = fmaf(qv, e[u].at(t), acc[u]);
           } else {
             const float d = qv - e[u].at(t);
@@ -1393,18 +1463,18 @@ static hipError_t launch_f16_phase1(const SearchArgs& a, int nqb, dim3 grid, siz
 // pick from, or many or very wide rows to re-score (those of k groups, or of all there are); below that the barriers of
 // sixteen waves cost more.  Time with them over time without, 8 queries: 256 rows of 1,024 bytes 1.10,
 // 512 of them 0.84; 64 rows of 4,800 bytes 0.90, 256 of them 1.18; 128 rows of 9,600 bytes 0.83, 256 0.89.
-template <typename T, int NT>
+template <typename T, int NT, bool L2>
 static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
   const size_t lists = (size_t)NT * 8 + kMaxK * 4, query = (size_t)((a.E + 3) & ~3) * 4;
   const size_t cand = (size_t)a.k * a.rows * 4;
   const int in_lds = lists + query + cand <= 64 * 1024;   // the rows' scores: in LDS, else in the workspace
   const size_t lds = lists + query + (in_lds ? cand : 0);
-  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT>>(lds);
+  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT, L2>>(lds);
   if (e != hipSuccess) return e;
   constexpr int kFit = (int)(kGridThreads / NT);   // queries of a launch
   for (a.q0 = 0; e == hipSuccess && a.q0 < a.B; a.q0 += a.nq) {
     a.nq = a.B - a.q0 < kFit ? a.B - a.q0 : kFit;
-    hipLaunchKernelGGL((finalize_topk_kernel<T, NT>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
+    hipLaunchKernelGGL((finalize_topk_kernel<T, NT, L2>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
     e = hipGetLastError();
   }
   return e;
@@ -1413,8 +1483,9 @@ static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
 template <typename T>
 static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
   const int rows = (a.k < a.G ? a.k : a.G) * a.rows;
-  return a.G > 1024 || rows > 256 || a.E * sizeof(T) > 6000 ? launch_topk_n<T, 1024>(a, stream)
-                                          : launch_topk_n<T, 256>(a, stream);
+  const bool large = a.G > 1024 || rows > 256 || a.E * sizeof(T) > 6000;
+  if (a.metric) return large ? launch_topk_n<T, 1024, true>(a, stream) : launch_topk_n<T, 256, true>(a, stream);
+  return large ? launch_topk_n<T, 1024, false>(a, stream) : launch_topk_n<T, 256, false>(a, stream);
 }
 
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {

@@ -163,3 +163,27 @@ def test_topk_ranks_minus_infinity_before_rows_of_nan(ac, case):  # noqa: F811
     want = torch.tensor([best, *range(N // 2, N // 2 + k - 1)], dtype=torch.int32)
     assert (idx.cpu() == want).all() and (hit == best).all()
     assert score[:, 0].isfinite().all() and (score[:, 1:] == float("-inf")).all()
+
+
+@pytest.mark.parametrize("order", ["ascending", "descending", "equal", "blocks", "few"])
+@pytest.mark.parametrize("N,E,k", [(700, 128, 5), (9000, 128, 4), (9000, 128, 64), (70000, 128, 8), (70000, 128, 64),
+                                   (300000, 128, 9), (900, 128, 1), (5000, 64, 2), (3000, 256, 8),
+                                   (200, 128, 8), (40001, 40, 3)])
+def test_the_best_few_of_scores_in_any_order(ac, N, E, k, order):  # noqa: F811
+    """Selections of the second phase where the best groups are neighbours, all equal, or nearly all unranked.  Scores are
+    whole numbers below 2^24 (256 a + b, exact), so the answer is exact: descending, lower row first."""
+    r = torch.arange(N)
+    v = {"ascending": r, "descending": N - 1 - r, "equal": torch.full((N,), 77), "blocks": (r * 7919 // 64) % 5000,
+         "few": r}[order]
+    emb = torch.zeros(N, E, dtype=torch.float16)
+    emb[:, 0], emb[:, 1] = (v // 256).half(), (v % 256).half()
+    if order == "few":   # fewer rows rank than are asked for
+        emb[torch.arange(N) % (N // 2) != 3] = float("nan")
+    q = torch.zeros(9, E, dtype=torch.float16)
+    q[:, 0], q[:, 1] = 256.0, 1.0
+    idx, score, hit = _run_search(ac, emb, q, k, 0.0, ac.AC_IP)
+    ranked = torch.nonzero(torch.isfinite(emb[:, 0])).flatten()
+    want = ranked[torch.sort(v[ranked], descending=True, stable=True).indices][:k].int()
+    n = len(want)
+    assert (idx[:, :n].cpu() == want).all() and (idx[:, n:] == -1).all()
+    assert (score[:, :n].cpu() == v[want.long()].float()).all() and (hit.cpu() == want[0]).all()
