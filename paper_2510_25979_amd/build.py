@@ -1,12 +1,15 @@
-"""Build libattncache.so (HIP, gfx950 only) in-tree next to the sources."""
+"""Build libattncache.so (HIP, gfx950 only) and the binding's tensor check in-tree next to the sources."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattncache.so")
 SOURCES = ["api.hip", "apply.hip", "exact.hip", "insert.hip", "project.hip", "search.hip"]
 HEADERS = ["common.hpp", "f32_tile.hpp", "launch.hpp", "split_tile.hpp", os.path.join("..", "..", "include", "attncache.h")]
+ARG = os.path.join(HERE, "_tensor_arg.so")
+ARG_SOURCE = "tensor_arg.cpp"
 
 # -packed-fp32-ops is switched off: the compiler must not form packed fp32 instructions
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",
@@ -15,19 +18,34 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(os.path.join(CSRC, f)) > t for f in SOURCES + HEADERS)
+    def older(out, sources):
+        return not os.path.exists(out) or any(os.path.getmtime(os.path.join(CSRC, f)) > os.path.getmtime(out)
+                                              for f in sources)
+    return older(LIB, SOURCES + HEADERS) or older(ARG, [ARG_SOURCE])
+
+
+def _arg_command():
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+             f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] +
+            [f"-I{p}" for p in include_paths() + [sysconfig.get_path("include")]] +
+            [os.path.join(CSRC, ARG_SOURCE), f"-L{torch_lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", ARG])
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
     if not force and not stale():
         return LIB
-    cmd = ["hipcc"] + FLAGS + [os.path.join(CSRC, f) for f in SOURCES] + ["-o", LIB]
+    commands = [["hipcc"] + FLAGS + [os.path.join(CSRC, f) for f in SOURCES] + ["-o", LIB], _arg_command()]
     if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
+        for c in commands:
+            print(" ".join(c))
+    running = [subprocess.Popen(c) for c in commands]
+    codes = [p.wait() for p in running]
+    for c, code in zip(commands, codes):
+        if code:
+            raise subprocess.CalledProcessError(code, c)
     return LIB
 
 
