@@ -1,7 +1,7 @@
 // What the ctypes binding asks of every tensor argument, in one native call: is it a plain GPU tensor,
 // contiguous, of the expected type and shape, and where does it start?  In Python these are six attribute look-ups and
 // two tuples, 0.5 us a tensor and half of what a call of the library costs on the host (attention_exact with five
-// tensors: 7.4 us a call so far, PYUS us so).
+// tensors: 7.3 us a call so far, 5.9 us so).
 //
 // Only the answer "yes" is given here.  Anything else -- a subclass, a tensor without storage, a wrong shape -- is None,
 // and the Python code behind it decides and says what is wrong.
