@@ -16,6 +16,7 @@
 //     Groups are contiguous and ascend, so among equal maxima the lower group
 //     number stands for the lower row and only the score has to be kept.
 // fp32 databases (and the L2 metric) use a vector-ALU phase 1 of the same shape.
+// Both phases are one launch, a workgroup per query, for databases of some 100 KB to 1 MB (search_small).
 #include <type_traits>
 
 #include "common.hpp"
@@ -521,6 +522,23 @@ struct RowPiece<float> {
   __device__ __forceinline__ float at(int t) const { return w[t]; }
 };
 
+// The eight threads of a row add up their parts of eight rows in three exchanges of half of what is left (four, two,
+// one value), so that thread part8 ends up with row part8 of its eight: seven exchanges instead of 24, and every
+// thread holds one row.
+__device__ __forceinline__ float row_of_eight(float (&v)[8], int part8) {
+#define AC_HALVE(n, bit, ctrl)                                                                       \
+  _Pragma("unroll") for (int u = 0; u < n; ++u) {                                                    \
+    const float keep = (part8 & bit) ? v[u + n] : v[u], give = (part8 & bit) ? v[u] : v[u + n];      \
+    v[u] = keep + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give),  \
+                                                                     ctrl, 0xf, 0xf, true));         \
+  }
+  AC_HALVE(4, 4, 0x141)   // row_half_mirror: lane 7 - p of the eight
+  AC_HALVE(2, 2, 0x4e)    // quad_perm 2 3 0 1: lane p ^ 2
+  AC_HALVE(1, 1, 0xb1)    // quad_perm 1 0 3 2: lane p ^ 1
+#undef AC_HALVE
+  return v[0];
+}
+
 // phase 1 for NQ <= 8 queries per workgroup on the vector ALUs: a stream over the rows.  Eight threads
 // read a row side by side in 16-byte pieces, a thread has eight rows (32 apart) in flight, the
 // queries sit in LDS as binary32; a workgroup takes the 256 rows of a group.  Nothing but the queries
@@ -586,33 +604,21 @@ __global__ __launch_bounds__(kThreads) void search_stream_kernel(const SearchArg
 #pragma unroll
     for (int u = 0; u < U; ++u) now[u] = next[u];
   }
-  // The eight threads of a row add up their parts of eight rows in three exchanges of half of what
-  // is left (four, two, one value), so that thread part8 ends up with row part8 of its eight: seven
-  // exchanges a query instead of 24, and every thread of the workgroup holds one row.
   const int r = row0 + 32 * part8 + slot;
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = acc[u][j];
-#define AC_HALVE(n, bit, ctrl)                                                                       \
-  _Pragma("unroll") for (int u = 0; u < n; ++u) {                                                    \
-    const float keep = (part8 & bit) ? v[u + n] : v[u], give = (part8 & bit) ? v[u] : v[u + n];      \
-    v[u] = keep + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give),  \
-                                                                     ctrl, 0xf, 0xf, true));         \
-  }
-    AC_HALVE(4, 4, 0x141)   // row_half_mirror: lane 7 - p of the eight
-    AC_HALVE(2, 2, 0x4e)    // quad_perm 2 3 0 1: lane p ^ 2
-    AC_HALVE(1, 1, 0xb1)    // quad_perm 1 0 3 2: lane p ^ 1
-#undef AC_HALVE
+    const float s = row_of_eight(v, part8);
     if (TOPK) {   // groups of 64 rows: threads 2 p and 2 p + 1 of every eight
-      float m = r < a.N ? v[0] : -INFINITY;
+      float m = r < a.N ? s : -INFINITY;
 #pragma unroll
       for (int off = 1; off < kWave; off = off == 1 ? 8 : 2 * off) m = fmaxf(m, __shfl_xor(m, off));
       if (lane < 8) red_s[wave][j][TOPK ? lane >> 1 : 0] = m;
     } else {
-      const bool ranks = r < a.N && v[0] == v[0];   // a NaN never ranks
-      const uint32_t key = ranks ? score_key(v[0]) : 0u, top = wave_max(key);
+      const bool ranks = r < a.N && s == s;   // a NaN never ranks
+      const uint32_t key = ranks ? score_key(s) : 0u, top = wave_max(key);
       const uint32_t low = wave_max(ranks && key == top ? ~(uint32_t)r : 0u);   // lowest row
       if (lane == 0) {
         red_s[wave][j][0] = top ? key_score(top) : -INFINITY;
@@ -1053,6 +1059,14 @@ __device__ __forceinline__ uint64_t row_best(uint64_t x) {
   x = max(x, dpp64<0x141>(x));         // row_half_mirror
   return max(x, dpp64<0x140>(x));      // row_mirror
 }
+// The best item of the wave, in every lane.
+__device__ __forceinline__ uint64_t wave_best(uint64_t x) {
+  x = row_best(x);
+  x = max(x, dpp64<0x142, 0xa>(x));    // lane 15 of a row into the next one
+  x = max(x, dpp64<0x143, 0xc>(x));    // lane 31 into the upper half: lane 63 has seen them all
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(x >> 32), 63) << 32 |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)x, 63);
+}
 
 // The k best of n items under the total order "higher score, then lower number", in rank order.
 // get(x) is item x as item_key (0: it does not rank, e.g. a NaN score); put(r, s, i) is called once
@@ -1138,14 +1152,12 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
     // parts: NT / 64 neighbouring lanes, or whole waves where there are at least two of them for every rank
     const bool waves = 2 * k <= NT / kWave;   // uniform
     const int parts = waves ? NT / kWave : kWave;
-    if (NT == 1024 || waves) best = row_best(best);
-    else best = quad_best(best);
     if (waves) {
-      best = max(best, dpp64<0x142, 0xa>(best));   // lane 15 of a row into the next one
-      best = max(best, dpp64<0x143, 0xc>(best));   // lane 31 into the upper half: lane 63 has seen them all
-      if (lane == kWave - 1) list[wave] = best;
-    } else if (tid % (NT / kWave) == 0) {
-      list[tid / (NT / kWave)] = best;
+      best = wave_best(best);
+      if (lane == 0) list[wave] = best;
+    } else {
+      best = NT == 1024 ? row_best(best) : quad_best(best);
+      if (tid % (NT / kWave) == 0) list[tid / (NT / kWave)] = best;
     }
     if (tid == 0) count = 0;
     __syncthreads();
@@ -1190,11 +1202,7 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
         uint64_t best = 0;
 #pragma unroll
         for (int t = 0; t < 4; ++t) best = max(best, it[t] < last ? it[t] : 0);
-        best = row_best(best);
-        best = max(best, dpp64<0x142, 0xa>(best));
-        best = max(best, dpp64<0x143, 0xc>(best));
-        last = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(best >> 32), 63) << 32 |
-               (uint32_t)__builtin_amdgcn_readlane((uint32_t)best, 63);
+        last = wave_best(best);
         if (lane == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
       }
     }
@@ -1308,10 +1316,120 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
       lists);
 }
 
+// ------------------------------------------------------------- both phases in one launch
+// For a database so small that one compute unit reads all of it in about the time that a second launch takes: one
+// workgroup per query scores every row, eight threads a row as in the stream above, and picks the best k itself.
+// Bound by the latency of its first loads, then by the 64 bytes per clock of a compute unit: a thread has U rows of C
+// pieces in flight, U C = 8 (128 KB a workgroup and step), the next ones while these are multiplied.  U is taken so
+// that rows and columns fill the steps (small_rows).  us per call, the two launches before / this: four queries on
+// 1,024 x 128 fp32 6.9 / 6.5, on 512 x 128 6.8 / 4.9, on 256 x 512 fp16 10.4 / 5.4, the best 8 of that 17.2 / 7.3, and
+// one launch less on the host (2.7).
+constexpr int kSmallThreads = 1024;
+template <typename T, bool L2, bool TOPK, int U>
+__global__ __launch_bounds__(kSmallThreads) void search_small_kernel(const SearchArgs a) {
+  typedef RowPiece<T> Piece;
+  constexpr int P = Piece::P, NT = kSmallThreads, RPT = NT / 8, C = 8 / U, STEP = 8 * P * C;   // columns of a step
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint64_t* lists = reinterpret_cast<uint64_t*>(smem);                  // [NT] for the selection
+  const int Ep = (a.E + 63) & ~63;
+  float* qf = reinterpret_cast<float*>(lists + NT);                     // [Ep]
+  float* cand = qf + Ep;                                                // [N], TOPK only
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slot = tid >> 3, part8 = tid & 7, last_piece = (a.E - 1) / P * P;
+  const T* emb = reinterpret_cast<const T*>(a.emb);
+  struct Pieces { Piece p[U][C]; };
+  auto fetch = [&](int row0, int c0) {   // what lies past the end repeats something that does not
+    Pieces f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const T* row = emb + (size_t)min(row0 + RPT * u + slot, a.N - 1) * a.E;
+#pragma unroll
+      for (int i = 0; i < C; ++i) f.p[u][i].load(row, min(c0 + P * (part8 + 8 * i), last_piece), a.E);
+    }
+    return f;
+  };
+  Pieces now = fetch(0, 0);   // on their way while the query is staged
+  const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
+  for (int c = tid; c < Ep; c += NT) qf[c] = c < a.E ? (float)q[c] : 0.f;
+  __syncthreads();
+  uint64_t best = 0;
+  float acc[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) acc[u] = 0.f;
+  int row0 = 0, c0 = 0;
+#pragma unroll 1
+  while (true) {
+    const bool done = c0 + STEP >= a.E;   // with these rows
+    const int next_row = done ? row0 + RPT * U : row0, next_c = done ? 0 : c0 + STEP;
+    const bool more = next_row < a.N;
+    Pieces next;
+    if (more) next = fetch(next_row, next_c);
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+      const int c = c0 + P * (part8 + 8 * i);
+      if (c < a.E) {
+#pragma unroll
+        for (int t = 0; t < P; ++t) {
+          const float qv = qf[c + t];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (L2) {
+              const float d = qv - now.p[u][i].at(t);
+              acc[u] = fmaf(-d, d, acc[u]);
+            } else {
+              acc[u] = fmaf(qv, now.p[u][i].at(t), acc[u]);
+            }
+          }
+        }
+      }
+    }
+    if (done) {
+      const float s = row_of_eight(acc, part8);   // thread p of a row's eight: row RPT p + slot of the first U
+      const int r = row0 + RPT * part8 + slot;
+      if (part8 < U && r < a.N) {
+        if (TOPK) cand[r] = s;
+        else if (s == s) best = max(best, item_key(s, r));   // a NaN never ranks
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc[u] = 0.f;
+    }
+    if (!more) break;
+    now = next;
+    row0 = next_row;
+    c0 = next_c;
+  }
+  if (TOPK) {
+    __syncthreads();
+    select_best<NT>(
+        a.N, a.k, [&](int x) { return cand[x] == cand[x] ? item_key(cand[x], x) : 0; },
+        [&](int r, float s, int i) {
+          a.idx[(size_t)b * a.k + r] = i == kIdxNone ? -1 : i;
+          a.score[(size_t)b * a.k + r] = s;
+          if (r == 0) write_hit(a, b, s, i);
+        },
+        lists);
+    return;
+  }
+  best = wave_best(best);
+  if (lane == 0) lists[wave] = best;
+  __syncthreads();
+  if (wave != 0) return;
+  best = row_best(lists[lane & (NT / kWave - 1)]);
+  if (lane == 0) {
+    const float s = best ? key_score((uint32_t)(best >> 32)) : -INFINITY;
+    const int i = best ? (int)~(uint32_t)best : kIdxNone;
+    a.idx[b] = i == kIdxNone ? -1 : i;
+    a.score[b] = s;
+    write_hit(a, b, s, i);
+  }
+}
+
 // ------------------------------------------------------------------- host side
 enum { kModeValu = 0, kModeMfma = 1, kModeMfmaBig = 2, kModeMfmaWide = 3 };
 constexpr int kBigBatch = 64;   // above this many queries the query-stationary kernel is used
 constexpr int kBigRowsMin = 50000;   // and from this many database rows on, whatever the batch
+constexpr int kSmallBatch = 256;     // queries of a single-launch search: a compute unit each, one round
 
 // What the workspace is sized for: 8 bytes per (query, group), and for k > 1 the rows of k groups.
 static void search_plan(int32_t N, int32_t mode, int32_t k, int32_t* rows_per_group, int32_t* G) {
@@ -1488,6 +1606,59 @@ static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
   return large ? launch_topk_n<T, 1024, false>(a, stream) : launch_topk_n<T, 256, false>(a, stream);
 }
 
+// Steps of a workgroup of search_small_kernel that takes 128 u rows at a time.
+static long small_steps(bool f16, int32_t E, int32_t N, int u) {
+  const int cols = (f16 ? 512 : 256) / u;
+  return (((long)N + 128 * u - 1) / (128 * u)) * ((E + cols - 1) / cols);
+}
+// The u of the fewest steps (of equals the most rows, whose parts are added up the fewest times).
+static int small_rows(bool f16, int32_t E, int32_t N) {
+  int best = 8;
+  for (int u = 4; u >= 1; u /= 2)
+    if (small_steps(f16, E, N, u) < small_steps(f16, E, N, best)) best = u;
+  return best;
+}
+
+// Where one launch is faster than two.  A step of 128 KB costs 1 us (fp16 Euclidean, which converts and subtracts
+// vector by vector, 1.7), the launch and the sums 3 us (top-k 5.5); the two launches cost 5 us and what their rows'
+// length adds, which is why the limits grow with E.  us per call, four queries, two launches / one:
+//   fp32 inner, k = 1    64 columns: 2 steps 6.1 / 4.5, 4 steps 6.0 / 6.6; 128: 4 steps 6.9 / 6.5, 8 steps 7.0 / 10.6;
+//                        512: 8 steps 12.3 / 10.8
+//   fp16 inner, k = 1    128 columns: 2 steps 6.3 / 4.8, 4 steps 6.4 / 7.1; 256: 4 steps 7.7 / 7.0; 512: 8 steps 10.6 / 10.8
+//   fp16 Euclidean, k = 1   128 columns: 2 steps 6.15 / 6.1, 4 steps 6.1 / 9.6; 512: 2 steps 8.8 / 6.3, 4 steps 8.9 / 9.9
+//   fp16 inner, k = 8    128 columns: 2 steps 11.2 / 6.8, 8 steps 12.2 / 13.0; 512: 8 steps 17.6 / 12.8
+// More queries than compute units take a second round here, and the matrix cores more queries at a time: 4,096 queries,
+// 96 x 825 fp16 15.0 / 61.7.
+static bool search_small(bool f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
+  if (B > kSmallBatch) return false;
+  const long steps = small_steps(f16, E, N, small_rows(f16, E, N));
+  if (k > 1) {
+    const long limit = !f16 ? 3 + E / 64 : (metric ? 1 : 2) + (E < 96 ? 0 : 1 + E / 192);
+    return steps <= (limit < 8 ? limit : 8);
+  }
+  if (!f16) return steps <= (E < 384 ? 2 + E / 64 : 8);
+  const int limit = metric ? 1 + (E + 128) / 256 : E < 256 ? 2 : 4;
+  return steps <= (limit < 4 ? limit : 4);
+}
+
+template <typename T, bool L2, bool TOPK>
+static hipError_t launch_small_k(const SearchArgs& a, hipStream_t stream) {
+  const size_t lds = (size_t)kSmallThreads * 8 + (size_t)((a.E + 63) & ~63) * 4 + (TOPK ? (size_t)a.N * 4 : 0);
+  const dim3 grid((unsigned)a.B), block(kSmallThreads);
+  switch (small_rows(std::is_same<T, f16_t>::value, a.E, a.N)) {
+    case 1: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 1>), grid, block, lds, stream, a); break;
+    case 2: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 2>), grid, block, lds, stream, a); break;
+    case 4: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 4>), grid, block, lds, stream, a); break;
+    default: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 8>), grid, block, lds, stream, a);
+  }
+  return hipGetLastError();
+}
+template <typename T>
+static hipError_t launch_small(const SearchArgs& a, hipStream_t stream) {
+  if (a.metric) return a.k > 1 ? launch_small_k<T, true, true>(a, stream) : launch_small_k<T, true, false>(a, stream);
+  return a.k > 1 ? launch_small_k<T, false, true>(a, stream) : launch_small_k<T, false, false>(a, stream);
+}
+
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   if (p.B == 0) return hipSuccess;
   SearchArgs a;
@@ -1495,6 +1666,9 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   a.N = p.N; a.E = p.E; a.B = p.B; a.k = p.k; a.metric = p.metric;
   a.threshold = p.threshold;
   a.idx = p.idx; a.score = p.score; a.hit = p.hit;
+  a.q0 = 0; a.nq = p.B;
+  if (search_small(p.is_f16, p.metric, p.E, p.B, p.N, p.k))
+    return p.is_f16 ? launch_small<f16_t>(a, stream) : launch_small<float>(a, stream);
   const int mode = search_mode(p.is_f16, p.metric, p.E, p.B, p.N, p.k);
   const bool mfma = mode == kModeMfma || mode == kModeMfmaWide;
   if (p.k > 1) {
@@ -1508,7 +1682,6 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   a.part_s = reinterpret_cast<float*>(ws);
   a.part_i = p.k > 1 ? nullptr : reinterpret_cast<int32_t*>(ws + (size_t)p.B * a.G * 4);
   a.cand = reinterpret_cast<float*>(ws + part_bytes);
-  a.q0 = 0; a.nq = p.B;
 
   if (mode == kModeMfmaBig) {
     // query super-blocks of 128 * QPW queries (4 waves x QPW blocks of 32); two blocks per wave

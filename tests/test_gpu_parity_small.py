@@ -398,7 +398,7 @@ NAN_CASES = [
     (50021, 256, 6, 1, torch.float16, "ip"),     # query-stationary kernel, one query block per wave
     (60000, 128, 140, 1, torch.float16, "ip"),   # query-stationary kernel, two query blocks per wave
     (60000, 128, 33, 3, torch.float16, "ip"),    # query-stationary kernel + re-scoring top-k
-    (777, 40, 5, 2, torch.float32, "l2"),        # a thread per row, top-k
+    (777, 40, 5, 2, torch.float32, "l2"),        # one launch, top-k
     (777, 44, 3, 1, torch.float32, "l2"),        # streams of one query
     (777, 132, 8, 1, torch.float32, "ip"),
     (50001, 36, 7, 1, torch.float32, "ip"),      # streams of four queries
@@ -406,7 +406,11 @@ NAN_CASES = [
     (70001, 40, 6, 3, torch.float16, "l2"),
     (20001, 20, 100, 1, torch.float32, "l2"),    # tiles
     (20001, 20, 100, 3, torch.float32, "ip"),
-    (333, 16, 5, 1, torch.float16, "l2"),        # a thread per row
+    (333, 16, 5, 1, torch.float16, "l2"),        # one launch
+    (333, 72, 5, 1, torch.float32, "ip"),        # the same, other steps and top-k
+    (333, 72, 5, 3, torch.float32, "l2"),
+    (4101, 12, 5, 2, torch.float32, "l2"),       # a thread per row
+    (2501, 8, 5, 1, torch.float16, "ip"),
     (9001, 40, 33, 1, torch.float16, "ip"),      # other fp16 widths on the matrix cores
     (3000, 520, 17, 4, torch.float16, "ip"),
 ]

@@ -34,6 +34,15 @@ VALU_CASES = [
     (40000, 40, 33, 4, torch.float16, "l2"),    # and fp16 ones
     (300, 520, 70, 5, torch.float16, "l2"),     # a small database: a stream per query
     (70000, 264, 20, 2, torch.float16, "l2"),   # streams of eight queries, four left over
+    # one launch: 128, 256, 512 or 1,024 rows a step by 512, 256, 128 or 64 columns of fp16, half of that of fp32; edges
+    (128, 512, 3, 1, torch.float16, "ip"), (127, 264, 256, 1, torch.float16, "l2"), (129, 520, 5, 1, torch.float16, "ip"),
+    (128, 256, 3, 1, torch.float32, "ip"), (127, 131, 7, 1, torch.float32, "l2"), (129, 257, 2, 3, torch.float32, "ip"),
+    (256, 256, 3, 1, torch.float16, "ip"), (255, 72, 256, 5, torch.float32, "l2"), (257, 136, 3, 2, torch.float16, "l2"),
+    (255, 72, 9, 1, torch.float32, "ip"), (190, 121, 9, 1, torch.float32, "l2"), (129, 127, 4, 2, torch.float32, "ip"),
+    (512, 128, 3, 1, torch.float16, "ip"), (511, 33, 5, 1, torch.float32, "l2"), (513, 64, 255, 4, torch.float32, "ip"),
+    (1024, 64, 3, 1, torch.float16, "ip"), (1025, 61, 3, 64, torch.float32, "ip"), (2048, 31, 2, 2, torch.float32, "l2"),
+    (1023, 128, 4, 1, torch.float32, "ip"), (120, 1024, 3, 8, torch.float32, "l2"), (100, 300, 2, 3, torch.float32, "ip"),
+    (100, 904, 2, 64, torch.float16, "l2"), (1024, 64, 257, 1, torch.float16, "ip"),   # (one query too many: two launches)
 ]
 
 
@@ -67,14 +76,17 @@ VARIANT_CASES = [(*c, k, torch.float16, "ip") for k in (1, 3) for c in [
     (1001, 520, 100),                                         # four each on a small database
     (300, 8200, 65),                                          # rows that leave LDS room for four queries
     (300, 3000, 301), (37, 36000, 9),                         # ... and for none: tiles
+    # matrix cores, just past what one launch takes
+    (2501, 16, 3), (37, 16, 300), (37, 192, 300), (37, 256, 300), (1501, 192, 65), (2501, 16, 65), (777, 272, 1),
 ]] + [(*c, k, dt, metric) for k in (1, 3) for metric in ("ip", "l2") for dt, c in [
     (torch.float32, (333, 131, 3)), (torch.float32, (20001, 33, 7)), (torch.float32, (70001, 36, 5)),   # streams
     (torch.float32, (701, 16, 500)), (torch.float32, (20001, 19, 100)), (torch.float32, (9001, 9, 500)),   # tiles, QW = 1, 2, 4
     (torch.float32, (333, 7, 9)), (torch.float32, (999, 37, 5)),   # a thread per row, whole pieces and a part of one
     (torch.float32, (400, 9000, 3)),                          # rows that leave LDS room for one query
+    (torch.float32, (4101, 7, 9)),                            # a thread per row, past what one launch takes
 ]] + [(*c, k, torch.float16, "l2") for k in (1, 3) for c in [
     (333, 136, 3), (301, 64, 500), (70001, 40, 5), (12001, 40, 140), (30001, 24, 70), (30001, 24, 140), (999, 8, 65), (555, 72, 9),
-]]
+]] + [(2501, 8, 1, 1, torch.float16, "ip")]
 
 
 @pytest.mark.parametrize("case", VARIANT_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
