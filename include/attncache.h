@@ -387,12 +387,14 @@ int32_t attncache_cache_reset(attncache_db *db);
  *              nearest even once, after normalisation).
  *   model_dim, hidden_dim, emb_dim   multiples of 8; emb_dim <= 2048;
  *              B <= 65535 (AC_ERR_SHAPE otherwise).  B == 0 is a no-op.
- *   workspace  DEVICE, at least attncache_project_workspace_bytes(...) bytes
- *              (0 is returned for non-positive sizes), 16-byte aligned;
- *              contents are scratch.  AC_ERR_WORKSPACE if too small.
+ *   workspace  DEVICE, attncache_project_workspace_bytes(...) bytes (0 is
+ *              returned for non-positive sizes), 16-byte aligned; contents are
+ *              scratch.  AC_ERR_WORKSPACE if too small.
  *
- * Four launches on `stream`; deterministic (partial sums are added in a fixed
- * order).  Weights and inputs are only read.
+ * Two to four launches on `stream` by size; deterministic (partial sums are
+ * added in a fixed order).  A workspace that is large enough, but smaller than
+ * attncache_project_workspace_bytes(...) for these sizes, takes four.  Weights
+ * and inputs are only read.
  */
 size_t attncache_project_workspace_bytes(int32_t B, int32_t model_dim,
                                          int32_t hidden_dim, int32_t emb_dim);

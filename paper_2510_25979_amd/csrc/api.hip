@@ -568,7 +568,7 @@ int32_t attncache_project(const void* h, const int32_t* seq_len, const float* W1
   if (!aligned16(h) || !aligned16(W1) || !aligned16(b1) || !aligned16(W2) || !aligned16(b2) ||
       !aligned16(feat) || !aligned16(workspace))
     return AC_ERR_ALIGN;
-  if (workspace_bytes < ac::project_workspace_bytes(B, model_dim, hidden_dim, emb_dim))
+  if (workspace_bytes < ac::project_workspace_least(B, model_dim, hidden_dim, emb_dim))
     return AC_ERR_WORKSPACE;
   if (may_query(reinterpret_cast<hipStream_t>(stream))) {
     const int32_t rc = all_device({h, seq_len, W1, b1, W2, b2, feat, workspace});
@@ -576,7 +576,7 @@ int32_t attncache_project(const void* h, const int32_t* seq_len, const float* W1
   }
   ac::ProjectLaunch p;
   p.h = h; p.seq_len = seq_len; p.W1 = W1; p.b1 = b1; p.W2 = W2; p.b2 = b2;
-  p.feat = feat; p.ws = workspace;
+  p.feat = feat; p.ws = workspace; p.ws_bytes = workspace_bytes;
   p.B = B; p.S = S; p.dm = model_dim; p.hid = hidden_dim; p.E = emb_dim;
   p.h_is_f32 = h_dtype == AC_F32; p.feat_is_f16 = feat_dtype == AC_F16;
   p.normalize = normalize != 0;

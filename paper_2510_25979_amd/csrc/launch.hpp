@@ -96,9 +96,11 @@ struct ProjectLaunch {
   const float *W2, *b2;     // device [E][hid], [E] or nullptr
   void* feat;               // device [B][E], fp16 or fp32
   void* ws;
+  size_t ws_bytes;
   int32_t B, S, dm, hid, E, h_is_f32, feat_is_f16, normalize;
 };
-size_t project_workspace_bytes(int32_t B, int32_t dm, int32_t hid, int32_t E);
+size_t project_workspace_least(int32_t B, int32_t dm, int32_t hid, int32_t E);   // what a call cannot do without
+size_t project_workspace_bytes(int32_t B, int32_t dm, int32_t hid, int32_t E);   // what it is fastest with
 hipError_t launch_project(const ProjectLaunch& p, hipStream_t stream);
 
 }  // namespace ac

@@ -1,6 +1,6 @@
 // Feature projector (AttnCache Algorithm 1, f = feature_projector(h); Sec. 3.1
 // "Feature Projector": two MLP layers that lower the dimension of the input
-// embedding).  Four small kernels, all in binary32:
+// embedding).  Four small kernels, all in binary32 (small sizes: two, see further down):
 //
 //   pool_kernel     x[b][i]  = mean over the sentence's tokens of h[b][t][i]      HBM-bound
 //   dense_kernel    P1[z]    = partial products of x with W1 over K-slice z       fp32 matrix cores
@@ -21,6 +21,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "row_stream.hpp"
 
 namespace ac {
 namespace {
@@ -275,6 +276,208 @@ __global__ __launch_bounds__(kThreads) void finish_kernel(const float* __restric
   }
 }
 
+// ---- small projections in two or three launches -----------------------------
+// Where the four launches above take longer than their work, pooling and the first layer are one launch and the second
+// layer, bias, norm and cast another (or two, fused_plan).
+//
+// pool_dense_kernel: grid (ceil(dm / 128), ceil(B / Q), ceil(hid / rows)), 16 waves.  A workgroup pools 128 columns of Q
+// queries (the waves share the queries, so that one query alone still has 16 waves on its tokens) and forms the partial
+// products of these 128 contraction indices with its rows of W1: eight threads a row, a sum per query each.  The first rows
+// of W1 are on their way while the tokens are added up.  Bound by the latency of the two round trips to memory, then by
+// the 64 bytes per clock of a compute unit and its vector ALUs.
+//   out[z][b][j] = sum over k in [128 z, 128 z + 128) of W1[j][k] x[b][k]
+constexpr int kFusedCols = 128, kFusedThreads = 1024, kFusedRows = 256;   // rows: two of each thread
+constexpr int32_t kFusedBatch = 256;
+
+// The eight threads of a row add up their parts for Q queries: thread p ends up with query p % Q.
+template <int Q>
+__device__ __forceinline__ float query_of_eight(float (&v)[Q], int part8) {
+  auto from = [](float x, auto ctrl) {
+    const int bits = __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true);
+    return __builtin_bit_cast(float, bits);
+  };
+  const std::integral_constant<int, 0x141> mirror;    // lane 7 - p of the eight
+  const std::integral_constant<int, 0x4e> swap2;      // lane p ^ 2
+  const std::integral_constant<int, 0xb1> swap1;      // lane p ^ 1
+#pragma unroll
+  for (int q = 0; q < Q; ++q) v[q] += from(v[q], mirror);
+  if (Q == 4) {   // half of the queries each
+#pragma unroll
+    for (int q = 0; q < Q / 2; ++q) {
+      const float keep = (part8 & 2) ? v[q + Q / 2] : v[q], give = (part8 & 2) ? v[q] : v[q + Q / 2];
+      v[q] = keep + from(give, swap2);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] += from(v[q], swap2);
+  }
+  if (Q == 1) return v[0] + from(v[0], swap1);
+  const float keep = (part8 & 1) ? v[Q > 1] : v[0], give = (part8 & 1) ? v[0] : v[Q > 1];
+  return keep + from(give, swap1);
+}
+
+template <typename T, int Q>
+__global__ __launch_bounds__(kFusedThreads) void pool_dense_kernel(const T* __restrict__ h, const int32_t* __restrict__ seq_len,
+                                                                   const float* __restrict__ W1, float* __restrict__ out, int S,
+                                                                   int dm, int hid, int B, int rows) {
+  constexpr int VEC = PoolVec<T>::VEC, LPR = kFusedCols / VEC, RPW = kWave / LPR;   // lanes per row, rows per wave and load
+  constexpr int NW = kFusedThreads / kWave, RPT = kFusedThreads / 8, UNROLL = 8, I = kFusedRows / RPT, C = kFusedCols / 32;
+  __shared__ float ps[NW][kFusedCols];
+  __shared__ __attribute__((aligned(16))) float xs[Q][kFusedCols];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slot = tid >> 3, part8 = tid & 7;
+  const int c0 = kFusedCols * blockIdx.x, b0 = Q * blockIdx.y, j_begin = rows * blockIdx.z, j_end = min(j_begin + rows, hid);
+  f32x4 w[I][C];
+  auto fetch = [&](int i, int j0) {   // rows and columns past the end repeat what does not lie there (dm is a multiple of 8)
+    const float* row = W1 + (size_t)min(j0 + RPT * i + slot, hid - 1) * dm;
+#pragma unroll
+    for (int c = 0; c < C; ++c) w[i][c] = *reinterpret_cast<const f32x4*>(row + min(c0 + 32 * c + 4 * part8, dm - 4));
+  };
+#pragma unroll
+  for (int i = 0; i < I; ++i) fetch(i, j_begin);
+  // pooling: NW / Q waves a query, RPW tokens a wave and load
+  constexpr int per = NW / Q;
+  const int nq = min(Q, B - b0);
+  float acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+  const int mine = wave / per;   // the query
+  if (mine < nq) {
+    const int s = min(max(seq_len ? seq_len[b0 + mine] : S, 1), S);
+    const int t0 = (wave % per) * RPW, sub = lane / LPR;
+    const int col = min(c0 + VEC * (lane % LPR), dm - VEC);   // (columns past the end are zeroed below)
+    const T* src = h + (size_t)(b0 + mine) * S * dm + col;
+    for (int t = t0; t < s; t += UNROLL * per * RPW) {
+      u32x4 v[UNROLL];
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const int first = t + u * per * RPW;   // wave-uniform
+        v[u] = u32x4{0u, 0u, 0u, 0u};
+        if (first < s) v[u] = *reinterpret_cast<const u32x4*>(src + (size_t)min(first + sub, s - 1) * dm);
+      }
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        if (t + u * per * RPW + sub >= s) v[u] = u32x4{0u, 0u, 0u, 0u};
+        pool_add<VEC>(acc, v[u]);
+      }
+    }
+  }
+  // the RPW lanes of a column piece add up
+#pragma unroll
+  for (int off = 32; off >= LPR; off /= 2)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] += __shfl_xor(acc[v], off);
+  if (lane < LPR)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) ps[wave][VEC * lane + v] = acc[v];
+  __syncthreads();
+  if (tid < Q * kFusedCols) {
+    const int q = tid / kFusedCols, c = tid % kFusedCols;   // q: wave-uniform
+    float x = 0.f;
+    if (q < nq && c0 + c < dm) {
+#pragma unroll
+      for (int w = 0; w < per; ++w) x += ps[q * per + w][c];
+      x /= (float)min(max(seq_len ? seq_len[b0 + q] : S, 1), S);
+    }
+    xs[q][c] = x;
+  }
+  __syncthreads();
+  f32x4 x[Q][C];
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+#pragma unroll
+    for (int c = 0; c < C; ++c) x[q][c] = *reinterpret_cast<const f32x4*>(&xs[q][32 * c + 4 * part8]);
+  float* dst = out + ((size_t)blockIdx.x * B + b0 + part8) * hid;   // thread p of a row's eight writes query p
+  const bool whole = c0 + kFusedCols <= dm;
+#pragma unroll 1
+  for (int j0 = j_begin; j0 < j_end; j0 += RPT * I) {
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+      if (!whole)   // (a product of a zero with a weight of another column would be NaN where that is infinite)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (c0 + 32 * c + 4 * part8 >= dm) w[i][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      float sum[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        float v = 0.f;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v = fmaf(w[i][c][t], x[q][c][t], v);
+        sum[q] = v;
+      }
+      if (j0 + RPT * I < j_end) fetch(i, j0 + RPT * I);
+      const float v = query_of_eight<Q>(sum, part8);
+      const int j = j0 + RPT * i + slot;
+      if (part8 < nq && j < j_end) dst[j] = v;
+    }
+  }
+}
+
+// dense_finish_kernel: grid (B, parts).  A workgroup adds up the partial products of its query (in slice order within a group
+// of threads, then over the groups), activates them and streams its rows of W2 past them.  With all rows in one workgroup
+// (PARTS = false) norm and cast follow as above, otherwise the sums are left to finish_kernel: part[E / 4][B][4].
+template <typename OUT, int U, bool PARTS>
+__global__ __launch_bounds__(kStreamThreads) void dense_finish_kernel(const float* __restrict__ part, int nz,
+                                                                      const float* __restrict__ b1, const float* __restrict__ W2,
+                                                                      const float* __restrict__ b2, OUT* __restrict__ feat, int B,
+                                                                      int hid, int E, int rows, int normalize) {
+  constexpr int NT = kStreamThreads;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  f32x4* red = reinterpret_cast<f32x4*>(smem);            // [NT]
+  float* x = reinterpret_cast<float*>(red + NT);          // [hid], zeros to the next multiple of 64
+  float* y = x + ((hid + 63) & ~63);                      // [E]
+  __shared__ float wsum[NT / kWave];
+  const int b = blockIdx.x, tid = threadIdx.x, e0 = PARTS ? rows * blockIdx.y : 0;
+  const int n4 = hid >> 2, groups = NT / n4, g = tid / n4, i = tid - g * n4;   // n4 <= NT
+  stream_rows<float, false, U>(
+      W2 + (size_t)e0 * hid, PARTS ? min(rows, E - e0) : E, hid, x,
+      [&] {
+        if (g < groups) {
+          f32x4 v = {0.f, 0.f, 0.f, 0.f};
+          const f32x4* src = reinterpret_cast<const f32x4*>(part + (size_t)b * hid) + i;
+#pragma unroll 4
+          for (int z = g; z < nz; z += groups) v += src[(size_t)z * B * n4];
+          red[tid] = v;
+        }
+        __syncthreads();
+        if (tid < n4) {
+          f32x4 v = red[tid];
+          for (int k = 1; k < min(groups, nz); ++k) v += red[tid + k * n4];
+          if (b1) v += *reinterpret_cast<const f32x4*>(b1 + 4 * tid);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) x[4 * tid + t] = fmaxf(v[t], 0.f);
+        }
+        for (int c = hid + tid; c < ((hid + 63) & ~63); c += NT) x[c] = 0.f;
+      },
+      [&](int e, float s) {
+        if (PARTS) feat[granule_at((e0 + e) >> 2, b, B) + ((e0 + e) & 3)] = s;
+        else y[e] = s;
+      });
+  if (PARTS) return;
+  __syncthreads();
+  float sq = 0.f;
+  for (int e = tid; e < E; e += NT) {
+    const float v = b2 ? b2[e] + y[e] : y[e];
+    y[e] = v;
+    sq += v * v;
+  }
+  float mul = 1.f;
+  if (normalize) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sq += __shfl_xor(sq, off);
+    if ((tid & 63) == 0) wsum[tid >> 6] = sq;
+    __syncthreads();
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) total += wsum[w];
+    if (total > 0.f) mul = 1.f / sqrtf(total);
+  }
+  for (int e = tid; e < E; e += NT) feat[(size_t)b * E + e] = (OUT)(y[e] * mul);
+}
+
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // How one layer's contraction index is split: waves per workgroup, workgroups
@@ -297,14 +500,108 @@ DenseSplit dense_split(int32_t B, int32_t J, int32_t K) {
 
 size_t dense_lds(const DenseSplit& s) { return sizeof(float) * s.n_waves * 16 * kWave; }   // <= 64 KiB
 
+// How a small projection is split, and whether it is small.  us per call in a graph, four launches / so (bf16 in, 256 out):
+//   dm 512, hid 128      8 x 500 tokens 20.2 / 8.9, 256 x 16 16.2 / 9.9
+//   dm 1024, hid 256     1 x 16 13.2 / 9.1, 128 x 100 19.0 / 13.5, 256 x 16 (512 workgroups) 20.4 / 17.2
+//   dm 2048, hid 512     16 x 90 18.1 / 14.1, 64 x 128 padded 21.6 / 18.3, 128 x 16 (512 workgroups) 21.6 / 23.3
+//   dm 4096, hid 1024    1 x 1024 38.0 / 18.0, 8 x 16 21.2 / 17.7, 32 x 16 (256 workgroups) 22.4 / 23.7
+// so the partial products (workgroups of four queries x hidden units) are what the line is drawn at.  Further out, wide
+// hidden layers (hid 1528, dm 72, 151 queries 33 / 88) and many rows of W2 for each of many queries lose: every query
+// streams all of W2 past itself.  Three launches gain little where the hidden layer is wide and the first one short (11 x 67
+// tokens, dm 1056, hid 872, out 480 18.8 / 21.5).
+struct FusedPlan { bool use; int nz, Q, rows, parts, rows2; };
+FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32_t E, bool f32) {
+  FusedPlan f = {false, ceil_div(dm, kFusedCols), 4, 0, 1, E};
+  if (B > kFusedBatch || hid > 1024) return f;
+  const long wgs4 = (long)f.nz * ceil_div(B, 4), steps = stream_steps(4, E, hid, stream_unroll(4, E, hid));
+  if (steps > 4 && hid > 768 && dm > 512 && dm < 2 * hid) return f;
+  if (steps > 16 || steps * B > 1024 || wgs4 > 512 || wgs4 * hid > 128 * 1024) return f;
+  f.use = true;
+  long least = 0;
+  for (int Q = 1; Q <= 4; Q *= 2) {
+    const int wgs = f.nz * ceil_div(B, Q);
+    if (wgs > 256 && Q < 4) continue;
+    const int rows = ceil_div(ceil_div(hid, std::max(1, 256 / wgs)), kFusedRows) * kFusedRows;
+    // a compute unit each where there are so few: bytes of W1, vector instructions in bytes of the same time, bytes of tokens
+    const long cost = 512L * rows + 180L * rows * Q + (long)Q * S * kFusedCols * (f32 ? 4 : 2);
+    if (least == 0 || cost < least) { least = cost; f.Q = Q; f.rows = rows; }
+  }
+  if (steps > 4) {   // 128 rows at least: fewer leave threads without one
+    f.rows2 = ceil_div(ceil_div(E, std::min((int)(steps + 1) / 2, std::max(1, 256 / B))), 128) * 128;
+    f.parts = ceil_div(E, f.rows2);
+    if (f.parts == 1) f.rows2 = E;
+  }
+  return f;
+}
+size_t fused_bytes(const FusedPlan& f, int32_t B, int32_t hid, int32_t E) {
+  return f.use ? sizeof(float) * ((size_t)f.nz * B * hid + (f.parts > 1 ? (size_t)B * E : 0)) : 0;
+}
+
+template <typename T>
+void launch_pool_dense(const ProjectLaunch& p, const FusedPlan& f, float* part, hipStream_t stream) {
+  const dim3 grid(f.nz, ceil_div(p.B, f.Q), ceil_div(p.hid, f.rows));
+  auto go = [&](auto q) {
+    pool_dense_kernel<T, decltype(q)::value><<<grid, kFusedThreads, 0, stream>>>(static_cast<const T*>(p.h), p.seq_len, p.W1, part,
+                                                                                 p.S, p.dm, p.hid, p.B, f.rows);
+  };
+  if (f.Q == 1) go(std::integral_constant<int, 1>{});
+  else if (f.Q == 2) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 4>{});
+}
+
+template <typename OUT, bool PARTS>
+void launch_dense_finish(const ProjectLaunch& p, const FusedPlan& f, const float* part, OUT* out, hipStream_t stream) {
+  const size_t lds = 16 * kStreamThreads + sizeof(float) * (size_t)(((p.hid + 63) & ~63) + (PARTS ? 0 : p.E));
+  auto go = [&](auto u) {
+    dense_finish_kernel<OUT, decltype(u)::value, PARTS><<<dim3(p.B, f.parts), kStreamThreads, lds, stream>>>(
+        part, f.nz, p.b1, p.W2, p.b2, out, p.B, p.hid, p.E, f.rows2, p.normalize);
+  };
+  switch (stream_unroll(RowPiece<float>::P, f.rows2, p.hid)) {
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    default: go(std::integral_constant<int, 8>{});
+  }
+}
+
+void launch_finish(const ProjectLaunch& p, const float* part, int nz, hipStream_t stream) {
+  if (p.feat_is_f16)
+    finish_kernel<f16_t><<<p.B, kThreads, 0, stream>>>(part, nz, p.b2, static_cast<f16_t*>(p.feat), p.B, p.E, p.normalize);
+  else
+    finish_kernel<float><<<p.B, kThreads, 0, stream>>>(part, nz, p.b2, static_cast<float*>(p.feat), p.B, p.E, p.normalize);
+}
+
 }  // namespace
 
-size_t project_workspace_bytes(int32_t B, int32_t dm, int32_t hid, int32_t E) {
+size_t project_workspace_least(int32_t B, int32_t dm, int32_t hid, int32_t E) {
   const DenseSplit s1 = dense_split(B, hid, dm), s2 = dense_split(B, E, hid);
   return sizeof(float) * ((size_t)B * dm + (size_t)s1.nz * B * hid + (size_t)s2.nz * B * E);
 }
 
+size_t project_workspace_bytes(int32_t B, int32_t dm, int32_t hid, int32_t E) {
+  size_t bytes = project_workspace_least(B, dm, hid, E);
+  for (int32_t b = std::min(B, kFusedBatch); b >= 1; --b)   // a smaller batch may want more
+    bytes = std::max(bytes, fused_bytes(fused_plan(b, 1, dm, hid, E, false), b, hid, E));
+  return bytes;
+}
+
 hipError_t launch_project(const ProjectLaunch& p, hipStream_t stream) {
+  const FusedPlan f = fused_plan(p.B, p.S, p.dm, p.hid, p.E, p.h_is_f32);
+  if (f.use && p.ws_bytes >= fused_bytes(f, p.B, p.hid, p.E)) {
+    float* part = static_cast<float*>(p.ws);
+    if (p.h_is_f32) launch_pool_dense<float>(p, f, part, stream);
+    else launch_pool_dense<bf16_t>(p, f, part, stream);
+    if (f.parts > 1) {
+      float* y = part + (size_t)f.nz * p.B * p.hid;
+      launch_dense_finish<float, true>(p, f, part, y, stream);
+      launch_finish(p, y, 1, stream);
+    } else if (p.feat_is_f16) {
+      launch_dense_finish<f16_t, false>(p, f, part, static_cast<f16_t*>(p.feat), stream);
+    } else {
+      launch_dense_finish<float, false>(p, f, part, static_cast<float*>(p.feat), stream);
+    }
+    return hipGetLastError();
+  }
   const DenseSplit s1 = dense_split(p.B, p.hid, p.dm), s2 = dense_split(p.B, p.E, p.hid);
   float* x = static_cast<float*>(p.ws);
   float* p1 = x + (size_t)p.B * p.dm;
@@ -337,12 +634,7 @@ hipError_t launch_project(const ProjectLaunch& p, hipStream_t stream) {
     case 2: layer2(std::integral_constant<int, 2>{}); break;
     default: layer2(std::integral_constant<int, 4>{}); break;
   }
-  if (p.feat_is_f16)
-    finish_kernel<f16_t><<<p.B, kThreads, 0, stream>>>(p2, s2.nz, p.b2, static_cast<f16_t*>(p.feat),
-                                                       p.B, p.E, p.normalize);
-  else
-    finish_kernel<float><<<p.B, kThreads, 0, stream>>>(p2, s2.nz, p.b2, static_cast<float*>(p.feat),
-                                                       p.B, p.E, p.normalize);
+  launch_finish(p, p2, s2.nz, stream);
   return hipGetLastError();
 }
 

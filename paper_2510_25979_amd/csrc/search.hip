@@ -21,6 +21,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "row_stream.hpp"
 
 namespace ac {
 
@@ -493,52 +494,6 @@ __global__ __launch_bounds__(kThreads, (KSMAX == 32 ? 1 : 2)) void search_f16_bi
 }
 
 // ------------------------------------------------------------- vector-ALU scoring
-// Columns [c, c + P) of a row, P = 16 bytes' worth, and their values as binary32.  fp16 rows are
-// whole pieces (E % 8 == 0); fp32 rows may end in part of one and need not be 16-byte aligned.
-template <typename T>
-struct RowPiece;
-template <>
-struct RowPiece<f16_t> {
-  static constexpr int P = 8;
-  f16x8 w;
-  __device__ __forceinline__ void load(const f16_t* row, int c, int) {
-    w = *reinterpret_cast<const f16x8*>(row + c);
-  }
-  __device__ __forceinline__ float at(int t) const { return (float)w[t]; }
-};
-template <>
-struct RowPiece<float> {
-  static constexpr int P = 4;
-  f32x4 w;
-  __device__ __forceinline__ void load(const float* row, int c, int E) {
-    typedef f32x4 f32x4_dw __attribute__((aligned(4)));
-    if (c + P <= E) {
-      w = *reinterpret_cast<const f32x4_dw*>(row + c);
-    } else {
-#pragma unroll
-      for (int t = 0; t < P; ++t) w[t] = c + t < E ? row[c + t] : 0.f;
-    }
-  }
-  __device__ __forceinline__ float at(int t) const { return w[t]; }
-};
-
-// The eight threads of a row add up their parts of eight rows in three exchanges of half of what is left (four, two,
-// one value), so that thread part8 ends up with row part8 of its eight: seven exchanges instead of 24, and every
-// thread holds one row.
-__device__ __forceinline__ float row_of_eight(float (&v)[8], int part8) {
-#define AC_HALVE(n, bit, ctrl)                                                                       \
-  _Pragma("unroll") for (int u = 0; u < n; ++u) {                                                    \
-    const float keep = (part8 & bit) ? v[u + n] : v[u], give = (part8 & bit) ? v[u] : v[u + n];      \
-    v[u] = keep + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, give),  \
-                                                                     ctrl, 0xf, 0xf, true));         \
-  }
-  AC_HALVE(4, 4, 0x141)   // row_half_mirror: lane 7 - p of the eight
-  AC_HALVE(2, 2, 0x4e)    // quad_perm 2 3 0 1: lane p ^ 2
-  AC_HALVE(1, 1, 0xb1)    // quad_perm 1 0 3 2: lane p ^ 1
-#undef AC_HALVE
-  return v[0];
-}
-
 // phase 1 for NQ <= 8 queries per workgroup on the vector ALUs: a stream over the rows.  Eight threads
 // read a row side by side in 16-byte pieces, a thread has eight rows (32 apart) in flight, the
 // queries sit in LDS as binary32; a workgroup takes the 256 rows of a group.  Nothing but the queries
@@ -1319,16 +1274,12 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
 // ------------------------------------------------------------- both phases in one launch
 // For a database so small that one compute unit reads all of it in about the time that a second launch takes: one
 // workgroup per query scores every row, eight threads a row as in the stream above, and picks the best k itself.
-// Bound by the latency of its first loads, then by the 64 bytes per clock of a compute unit: a thread has U rows of C
-// pieces in flight, U C = 8 (128 KB a workgroup and step), the next ones while these are multiplied.  U is taken so
-// that rows and columns fill the steps (small_rows).  us per call, the two launches before / this: four queries on
-// 1,024 x 128 fp32 6.9 / 6.5, on 512 x 128 6.8 / 4.9, on 256 x 512 fp16 10.4 / 5.4, the best 8 of that 17.2 / 7.3, and
-// one launch less on the host (2.7).
-constexpr int kSmallThreads = 1024;
+// us per call, the two launches before / this: four queries on 1,024 x 128 fp32 6.9 / 6.5, on 512 x 128 6.8 / 4.9, on
+// 256 x 512 fp16 10.4 / 5.4, the best 8 of that 17.2 / 7.3, and one launch less on the host (2.7).
+constexpr int kSmallThreads = kStreamThreads;
 template <typename T, bool L2, bool TOPK, int U>
 __global__ __launch_bounds__(kSmallThreads) void search_small_kernel(const SearchArgs a) {
-  typedef RowPiece<T> Piece;
-  constexpr int P = Piece::P, NT = kSmallThreads, RPT = NT / 8, C = 8 / U, STEP = 8 * P * C;   // columns of a step
+  constexpr int NT = kSmallThreads;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint64_t* lists = reinterpret_cast<uint64_t*>(smem);                  // [NT] for the selection
   const int Ep = (a.E + 63) & ~63;
@@ -1336,69 +1287,18 @@ __global__ __launch_bounds__(kSmallThreads) void search_small_kernel(const Searc
   float* cand = qf + Ep;                                                // [N], TOPK only
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int slot = tid >> 3, part8 = tid & 7, last_piece = (a.E - 1) / P * P;
   const T* emb = reinterpret_cast<const T*>(a.emb);
-  struct Pieces { Piece p[U][C]; };
-  auto fetch = [&](int row0, int c0) {   // what lies past the end repeats something that does not
-    Pieces f;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const T* row = emb + (size_t)min(row0 + RPT * u + slot, a.N - 1) * a.E;
-#pragma unroll
-      for (int i = 0; i < C; ++i) f.p[u][i].load(row, min(c0 + P * (part8 + 8 * i), last_piece), a.E);
-    }
-    return f;
-  };
-  Pieces now = fetch(0, 0);   // on their way while the query is staged
   const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
-  for (int c = tid; c < Ep; c += NT) qf[c] = c < a.E ? (float)q[c] : 0.f;
-  __syncthreads();
   uint64_t best = 0;
-  float acc[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) acc[u] = 0.f;
-  int row0 = 0, c0 = 0;
-#pragma unroll 1
-  while (true) {
-    const bool done = c0 + STEP >= a.E;   // with these rows
-    const int next_row = done ? row0 + RPT * U : row0, next_c = done ? 0 : c0 + STEP;
-    const bool more = next_row < a.N;
-    Pieces next;
-    if (more) next = fetch(next_row, next_c);
-#pragma unroll
-    for (int i = 0; i < C; ++i) {
-      const int c = c0 + P * (part8 + 8 * i);
-      if (c < a.E) {
-#pragma unroll
-        for (int t = 0; t < P; ++t) {
-          const float qv = qf[c + t];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if (L2) {
-              const float d = qv - now.p[u][i].at(t);
-              acc[u] = fmaf(-d, d, acc[u]);
-            } else {
-              acc[u] = fmaf(qv, now.p[u][i].at(t), acc[u]);
-            }
-          }
-        }
-      }
-    }
-    if (done) {
-      const float s = row_of_eight(acc, part8);   // thread p of a row's eight: row RPT p + slot of the first U
-      const int r = row0 + RPT * part8 + slot;
-      if (part8 < U && r < a.N) {
+  stream_rows<T, L2, U>(
+      emb, a.N, a.E, qf,
+      [&] {
+        for (int c = tid; c < Ep; c += NT) qf[c] = c < a.E ? (float)q[c] : 0.f;
+      },
+      [&](int r, float s) {
         if (TOPK) cand[r] = s;
         else if (s == s) best = max(best, item_key(s, r));   // a NaN never ranks
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc[u] = 0.f;
-    }
-    if (!more) break;
-    now = next;
-    row0 = next_row;
-    c0 = next_c;
-  }
+      });
   if (TOPK) {
     __syncthreads();
     select_best<NT>(
@@ -1606,19 +1506,6 @@ static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
   return large ? launch_topk_n<T, 1024, false>(a, stream) : launch_topk_n<T, 256, false>(a, stream);
 }
 
-// Steps of a workgroup of search_small_kernel that takes 128 u rows at a time.
-static long small_steps(bool f16, int32_t E, int32_t N, int u) {
-  const int cols = (f16 ? 512 : 256) / u;
-  return (((long)N + 128 * u - 1) / (128 * u)) * ((E + cols - 1) / cols);
-}
-// The u of the fewest steps (of equals the most rows, whose parts are added up the fewest times).
-static int small_rows(bool f16, int32_t E, int32_t N) {
-  int best = 8;
-  for (int u = 4; u >= 1; u /= 2)
-    if (small_steps(f16, E, N, u) < small_steps(f16, E, N, best)) best = u;
-  return best;
-}
-
 // Where one launch is faster than two.  A step of 128 KB costs 1 us (fp16 Euclidean, which converts and subtracts
 // vector by vector, 1.7), the launch and the sums 3 us (top-k 5.5); the two launches cost 5 us and what their rows'
 // length adds, which is why the limits grow with E.  us per call, four queries, two launches / one:
@@ -1631,7 +1518,8 @@ static int small_rows(bool f16, int32_t E, int32_t N) {
 // 96 x 825 fp16 15.0 / 61.7.
 static bool search_small(bool f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
   if (B > kSmallBatch) return false;
-  const long steps = small_steps(f16, E, N, small_rows(f16, E, N));
+  const int P = f16 ? 8 : 4;
+  const long steps = stream_steps(P, N, E, stream_unroll(P, N, E));
   if (k > 1) {
     const long limit = !f16 ? 3 + E / 64 : (metric ? 1 : 2) + (E < 96 ? 0 : 1 + E / 192);
     return steps <= (limit < 8 ? limit : 8);
@@ -1645,7 +1533,7 @@ template <typename T, bool L2, bool TOPK>
 static hipError_t launch_small_k(const SearchArgs& a, hipStream_t stream) {
   const size_t lds = (size_t)kSmallThreads * 8 + (size_t)((a.E + 63) & ~63) * 4 + (TOPK ? (size_t)a.N * 4 : 0);
   const dim3 grid((unsigned)a.B), block(kSmallThreads);
-  switch (small_rows(std::is_same<T, f16_t>::value, a.E, a.N)) {
+  switch (stream_unroll(RowPiece<T>::P, a.N, a.E)) {
     case 1: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 1>), grid, block, lds, stream, a); break;
     case 2: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 2>), grid, block, lds, stream, a); break;
     case 4: hipLaunchKernelGGL((search_small_kernel<T, L2, TOPK, 4>), grid, block, lds, stream, a); break;

@@ -77,6 +77,25 @@ CASES = [
     (130, 9, 520, 264, 2048, torch.bfloat16, torch.float32, True, True, True),     # widest feature vector
     (3, 1000, 264, 136, 64, torch.bfloat16, torch.float16, True, True, True),      # long sentences: several pooling rounds
     (2, 300, 128, 64, 32, torch.float32, torch.float32, False, False, True),       # the same with fp32 hidden states
+    # two launches: slices of 128 columns, 256 rows of W1, one, two or four queries, 128 rows of W2; edges
+    (4, 5, 128, 256, 128, torch.bfloat16, torch.float16, False, True, True),
+    (3, 33, 136, 264, 136, torch.float32, torch.float32, True, True, False),
+    (5, 65, 120, 248, 120, torch.bfloat16, torch.float32, True, False, True),
+    (90, 12, 768, 192, 256, torch.bfloat16, torch.float32, True, True, True),      # two queries, the last alone
+    (101, 7, 1032, 256, 64, torch.float32, torch.float16, True, True, False),      # four, one left over
+    (2, 700, 1024, 520, 8, torch.bfloat16, torch.float32, True, True, True),       # rows of W1 over several workgroups
+    (256, 4, 128, 64, 1024, torch.float32, torch.float32, True, True, True),       # the most queries
+    # three: several workgroups to the rows of W2
+    (2, 40, 512, 1024, 256, torch.bfloat16, torch.float32, True, True, True),
+    (9, 20, 264, 872, 488, torch.float32, torch.float16, True, False, True),
+    (33, 3, 256, 512, 512, torch.bfloat16, torch.float16, False, True, False),
+    # four, with one, two and four slices of the first layer
+    (257, 3, 32, 24, 40, torch.bfloat16, torch.float32, True, True, False),
+    (257, 3, 32, 24, 40, torch.float32, torch.float16, True, True, True),
+    (260, 2, 64, 40, 24, torch.bfloat16, torch.float32, True, True, False),
+    (260, 2, 64, 40, 24, torch.float32, torch.float16, True, True, True),
+    (300, 9, 264, 136, 64, torch.float32, torch.float32, True, True, False),
+    (257, 400, 264, 136, 64, torch.bfloat16, torch.float16, True, True, True),     # several pooling rounds
 ]
 
 
@@ -180,6 +199,31 @@ def test_projector_and_search_replayed_from_a_hip_graph(ac):
         torch.cuda.synchronize()
         assert torch.equal(got[0], feat) and torch.equal(got[1], idx) and torch.equal(got[2], score)
     db.close()
+
+
+@pytest.mark.parametrize("B,S,dm,hid,E", [(64, 20, 2048, 512, 256), (12, 9, 4096, 1024, 256)])
+def test_a_workspace_for_four_launches_takes_four(ac, oracle_mod, B, S, dm, hid, E):
+    """Pooled input and four partial results a layer: less than fewer launches want, and nothing behind it is touched."""
+    x = _inputs(31, B, S, dm, hid, E, torch.bfloat16)
+    least = 4 * B * (dm + 4 * hid + 4 * E)
+    assert least < ac.attncache_project_workspace_bytes(B, dm, hid, E)
+    ws = torch.full((least + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    feat = torch.full((B, E), 7.0, device="cuda")
+    ac.attncache_project(*(t.cuda() for t in x), feat, ws[:least])
+    _check(oracle_mod, feat, *x, None, True)
+    assert (ws[least:] == 0xA5).all()
+    with pytest.raises(ac.AttnCacheError) as e:
+        ac.attncache_project(*(t.cuda() for t in x), feat, ws[:least - 16])
+
+
+def test_infinite_weights_of_the_last_columns_stay_where_they_are(ac, oracle_mod):
+    """-inf in the last column of W1 silences its hidden unit (inputs there are positive); no NaN from padded columns."""
+    h, W1, b1, W2, b2 = _inputs(32, 3, 5, 136, 40, 24, torch.float32)
+    h[..., -1] = h[..., -1].abs() + 0.1
+    W1[5, -1] = float("-inf")
+    feat = _run(ac, h, W1, b1, W2, b2, torch.float32)
+    W1[5], b1[5] = 0.0, -1.0
+    _check(oracle_mod, feat, h, W1, b1, W2, b2, None, True)
 
 
 def test_projector_error_codes(ac):
