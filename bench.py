@@ -365,12 +365,12 @@ def run_projector(ac, synth, args, w):
     flops = 2.0 * B * (dm * hid + hid * E)
     return {"ms": p_ms, "model_dim": dm, "hidden_dim": hid, "emb_dim": E,
             "dtype": "f32 (bf16 hidden states in)",
-            "roofline": {"kernel": "pool_kernel (token mean; dominant of the four launches)",
+            "roofline": {"kernel": "token mean (pool_dense_kernel with the first layer, or pool_kernel), the first launch",
                          "bound": "hbm", "achieved": B * S * dm * 2 / (p_ms * 1e-3) / 1e9,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": B * S * dm * 2 / (p_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                          "note": "whole projector time against the bytes of the hidden states; "
-                                 f"the two layers add {flops / 1e9:.2f} GFLOP on the fp32 matrix cores"}}
+                                 f"the two layers add {flops / 1e9:.2f} GFLOP in fp32"}}
 
 
 def run_insert(ac, args, traffic, w, Q, K, V):
