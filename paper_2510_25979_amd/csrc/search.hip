@@ -989,11 +989,11 @@ __device__ __forceinline__ uint64_t item_key(float s, int i) {
   return (uint64_t)score_key(s) << 32 | (uint32_t)~i;
 }
 
-constexpr int kItems = 16;          // most items of a thread
 constexpr int kCountPerDraw = 16;   // items per rank sought that are all compared with each other straight away
-// Up to 256 items and so few ranks: one wave draws the best again and again, without a barrier.  us per call, so / by
-// the two ways above: 1,895 x 256, two queries, k = 2 (60 groups, 64 rows) 9.7 / 13.2; 5,000 x 256, 64 queries, k = 8 16.6 /
-// 17.9.  Not for up to four items per rank: 700 x 128, 8 queries, k = 8 (11 groups) 12.2 / 11.7.
+constexpr int kRankMost = 384;      // items that are compared with each other after the bound has been applied
+// Up to 256 items and so few ranks: one wave draws the best again and again, without a barrier.  us per call, by bound and
+// comparison / so: 1,895 x 256, two queries, k = 2 (60 groups, 64 rows) 13.2 / 9.7; 5,000 x 256, 64 queries, k = 8 17.9 /
+// 16.6.  Not for up to four items per rank: 700 x 128, 8 queries, k = 8 (11 groups) 11.7 / 12.2.
 constexpr int kDrawRanks = 8;
 
 // x of the lane that the DPP control names (a lane without one keeps its own).
@@ -1027,44 +1027,28 @@ __device__ __forceinline__ uint64_t wave_best(uint64_t x) {
 // get(x) is item x as item_key (0: it does not rank, e.g. a NaN score); put(r, s, i) is called once
 // for every rank r < k, with kIdxNone where fewer than k items rank.
 // An item's rank is the number of items before it, and few items need to be compared: the k-th best of the
-// maxima of 64 parts is a bound that k items reach and, in typical data, some 2 k to 4 k.  (Those that reach it
-// lie in k parts, so no data make them more than k / 64 of all.)  Drawing the best k times in every wave, then again
-// among what the waves drew, took 36 KB of code and 30.7 us per call of 100,000 x 256, 64 queries, k = 8, 141 at k = 64;
-// 23.6 and 63 so.
-// Few items for that many ranks are compared straight away, and few ranks of few items drawn (below).  More than 16
-// items per thread (some 16
-// million rows), or more that reach the bound than the list holds, take k rounds over memory.
-// NT threads, list[NT]: the items that are ranked, before them the best item of every part, behind them their number
-// and the bound.
+// maxima of 64 parts is a bound that k items reach and, in unordered data, some 2 k to 4 k.  Drawing the best k times in
+// every wave, then again among what the waves drew, took 36 KB of code and 30.7 us per call of 100,000 x 256, 64 queries,
+// k = 8, 141 at k = 64; 23.6 and 57 so.
+// Where the best items are neighbours (a database ordered by similarity) they share few parts and any number of items may
+// reach the bound.  Then they are counted in 256 equal ranges of keys up to the best one, which raises the bound to where
+// at most kRankMost reach it, whatever the data (the same call at k = 64 with runs of 1,000 rows alike: 58 us; k rounds of a
+// workgroup-wide arg-max 220).
+// Few items for that many ranks are compared straight away, and few ranks of few items drawn (above).
+// NT threads, list[NT]: the items that are ranked, before them the best item of every part or the counts, behind them
+// the best item, two numbers (items that reach the bound, and how many of them there were counted) and the bound.
 template <int NT, typename Get, typename Put>
 __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint64_t* list) {
   typedef uint32_t __attribute__((may_alias)) word;
+  constexpr int MOST = kRankMost < NT - 3 ? kRankMost : NT - 3, BINS = 256;
+  uint64_t& top = list[NT - 3];
   word& count = *reinterpret_cast<word*>(list + NT - 2);
+  word& reach = *(reinterpret_cast<word*>(list + NT - 2) + 1);
   uint64_t& least = list[NT - 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto item_at = [&](int x) {
     const uint64_t it = get(min(x, n - 1));   // (no load behind a test)
     return x < n ? it : 0;
-  };
-  auto rounds = [&]() {
-    uint64_t last = ~0ull;
-    for (int r = 0; r < k; ++r) {
-      uint64_t best = 0;
-      for (int x = tid; x < n; x += NT) {
-        const uint64_t it = get(x);
-        if (it < last) best = max(best, it);
-      }
-      list[tid] = best;
-      __syncthreads();
-      for (int half = NT / 2; half > 0; half >>= 1) {
-        if (tid < half) list[tid] = max(list[tid], list[tid + half]);
-        __syncthreads();
-      }
-      last = list[0];
-      __syncthreads();
-      if (tid == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
-    }
-    __syncthreads();
   };
   // list[0, m) is there: ranks of the items in it that rank at all
   auto rank = [&](int m) {
@@ -1083,6 +1067,49 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
     }
     if (tid >= ranked && tid < k) put(tid, -INFINITY, kIdxNone);
     __syncthreads();
+  };
+  // The bound rises until at most MOST items reach it, k of them at least.  Fewer than k items lie above `top`, so each
+  // pass leaves those and one range, and the last one, whose ranges are single keys, no more than k.
+  auto raise = [&]() {
+    word* bins = reinterpret_cast<word*>(list);
+    do {
+      const uint64_t low = least, high = top;
+      const int shift = max(64 - 8 - (int)__clzll(high - low), 0);
+      if (tid < BINS) bins[tid] = 0;
+      __syncthreads();
+#pragma unroll 1
+      for (int x = tid; x < n; x += NT) {
+        const uint64_t it = get(x);
+        if (it >= low) atomicAdd(&bins[(uint32_t)((min(it, high) - low) >> shift)], 1u);
+      }
+      __syncthreads();
+      if (wave == 0) {
+        uint32_t own[4], sum = 0;   // a lane: four neighbouring ranges
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sum += own[t] = bins[4 * lane + t];
+        uint32_t above = sum;
+        for (int off = 1; off < kWave; off <<= 1) {
+          const uint32_t next = __shfl_down(above, off);
+          above += lane + off < kWave ? next : 0;
+        }
+        above -= sum;   // items of the lanes behind this one
+        if (above < (uint32_t)k && above + sum >= (uint32_t)k) {   // one lane
+          int bin = 0;
+#pragma unroll
+          for (int t = 3; t >= 0; --t)
+            if (above < (uint32_t)k) {
+              above += own[t];
+              bin = 4 * lane + t;
+            }
+          const uint64_t from = low + ((uint64_t)bin << shift);
+          least = from;
+          top = min(high, from + ((1ull << shift) - 1));
+          reach = above;
+        }
+        if (lane == 0) count = 0;
+      }
+      __syncthreads();
+    } while (reach > (uint32_t)MOST);
   };
   // list := the items that reach the bound.  A thread's first four items stay in registers, others are fetched again.
   auto collect = [&]() {
@@ -1126,25 +1153,32 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
       } else if (mine != 0 && before == k - 1) {
         least = mine;
       }
+      if (mine != 0 && before == 0) top = mine;
     }
     __syncthreads();
-    const uint64_t bound = least;
 #pragma unroll 1
-    for (int x0 = wave * kWave;;) {
+    for (;;) {
+      const uint64_t bound = least;
+#pragma unroll 1
+      for (int x0 = wave * kWave;;) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const bool in = it[t] >= bound;
-        const unsigned long long who = __ballot(in);
-        if (who == 0) continue;   // (wave-uniform: most)
-        int at = 0;
-        if (lane == 0) at = (int)atomicAdd(&count, (uint32_t)__popcll(who));
-        at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1));
-        if (in && at < NT - 2) list[at] = it[t];
+        for (int t = 0; t < 4; ++t) {
+          const bool in = it[t] >= bound;
+          const unsigned long long who = __ballot(in);
+          if (who == 0) continue;   // (wave-uniform: most)
+          int at = 0;
+          if (lane == 0) at = (int)atomicAdd(&count, (uint32_t)__popcll(who));
+          at = __builtin_amdgcn_readfirstlane(at) + __popcll(who & ((1ull << lane) - 1));
+          if (in && at < MOST) list[at] = it[t];
+        }
+        if ((x0 += 4 * NT) >= n) break;
+        fetch(x0 + lane);
       }
-      if ((x0 += 4 * NT) >= n) break;
-      fetch(x0 + lane);
+      __syncthreads();
+      if (count <= (uint32_t)MOST) break;
+      raise();
+      fetch(tid);
     }
-    __syncthreads();
   };
   int m = n;
   if (k <= kDrawRanks && n <= 4 * kWave && n > 4 * k) {
@@ -1167,14 +1201,11 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
   if (n <= NT && n <= kCountPerDraw * k) {
     list[tid] = item_at(tid);
     __syncthreads();
-  } else if (n <= kItems * NT) {
+  } else {
     collect();
     m = (int)count;
-    if (m > NT - 2) m = NT + 1;
-    __syncthreads();   // (the rounds and the next selection write what was just read)
   }
-  if (m > NT) rounds();
-  else rank(m);
+  rank(m);
 }
 
 // k > 1: pick the k best groups, re-score their rows, pick the k best rows.  One workgroup per
