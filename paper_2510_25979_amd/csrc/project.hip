@@ -24,7 +24,6 @@
 #include "row_stream.hpp"
 
 namespace ac {
-namespace {
 
 constexpr int kPoolWaves = 8;
 
@@ -478,13 +477,13 @@ __global__ __launch_bounds__(kStreamThreads) void dense_finish_kernel(const floa
   for (int e = tid; e < E; e += NT) feat[(size_t)b * E + e] = (OUT)(y[e] * mul);
 }
 
-int ceil_div(int a, int b) { return (a + b - 1) / b; }
+static int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // How one layer's contraction index is split: waves per workgroup, workgroups
 // along K (= partial results in global memory) and indices per wave.  Aim: about
 // one wave per SIMD of the chip (1024), at least 32 indices per wave.
 struct DenseSplit { int n_waves, nz, slice; };
-DenseSplit dense_split(int32_t B, int32_t J, int32_t K) {
+static DenseSplit dense_split(int32_t B, int32_t J, int32_t K) {
   const int tiles = ceil_div(B, 32) * ceil_div(J, 32);
   // waves per tile: about two per SIMD of the chip in total, 32 indices each at least
   const int want = std::min(std::max(1, 2048 / tiles), std::min(std::max(1, K / 32), 64));
@@ -498,7 +497,7 @@ DenseSplit dense_split(int32_t B, int32_t J, int32_t K) {
   return d;   // slices past K are empty and contribute zeros
 }
 
-size_t dense_lds(const DenseSplit& s) { return sizeof(float) * s.n_waves * 16 * kWave; }   // <= 64 KiB
+static size_t dense_lds(const DenseSplit& s) { return sizeof(float) * s.n_waves * 16 * kWave; }   // <= 64 KiB
 
 // How a small projection is split, and whether it is small.  us per call in a graph, four launches / so (bf16 in, 256 out):
 //   dm 512, hid 128      8 x 500 tokens 20.2 / 8.9, 256 x 16 16.2 / 9.9
@@ -510,7 +509,7 @@ size_t dense_lds(const DenseSplit& s) { return sizeof(float) * s.n_waves * 16 * 
 // streams all of W2 past itself.  Three launches gain little where the hidden layer is wide and the first one short (11 x 67
 // tokens, dm 1056, hid 872, out 480 18.8 / 21.5).
 struct FusedPlan { bool use; int nz, Q, rows, parts, rows2; };
-FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32_t E, bool f32) {
+static FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32_t E, bool f32) {
   FusedPlan f = {false, ceil_div(dm, kFusedCols), 4, 0, 1, E};
   if (B > kFusedBatch || hid > 1024) return f;
   const long wgs4 = (long)f.nz * ceil_div(B, 4), steps = stream_steps(4, E, hid, stream_unroll(4, E, hid));
@@ -533,12 +532,12 @@ FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32_t E, b
   }
   return f;
 }
-size_t fused_bytes(const FusedPlan& f, int32_t B, int32_t hid, int32_t E) {
+static size_t fused_bytes(const FusedPlan& f, int32_t B, int32_t hid, int32_t E) {
   return f.use ? sizeof(float) * ((size_t)f.nz * B * hid + (f.parts > 1 ? (size_t)B * E : 0)) : 0;
 }
 
 template <typename T>
-void launch_pool_dense(const ProjectLaunch& p, const FusedPlan& f, float* part, hipStream_t stream) {
+static void launch_pool_dense(const ProjectLaunch& p, const FusedPlan& f, float* part, hipStream_t stream) {
   const dim3 grid(f.nz, ceil_div(p.B, f.Q), ceil_div(p.hid, f.rows));
   auto go = [&](auto q) {
     pool_dense_kernel<T, decltype(q)::value><<<grid, kFusedThreads, 0, stream>>>(static_cast<const T*>(p.h), p.seq_len, p.W1, part,
@@ -550,7 +549,7 @@ void launch_pool_dense(const ProjectLaunch& p, const FusedPlan& f, float* part, 
 }
 
 template <typename OUT, bool PARTS>
-void launch_dense_finish(const ProjectLaunch& p, const FusedPlan& f, const float* part, OUT* out, hipStream_t stream) {
+static void launch_dense_finish(const ProjectLaunch& p, const FusedPlan& f, const float* part, OUT* out, hipStream_t stream) {
   const size_t lds = 16 * kStreamThreads + sizeof(float) * (size_t)(((p.hid + 63) & ~63) + (PARTS ? 0 : p.E));
   auto go = [&](auto u) {
     dense_finish_kernel<OUT, decltype(u)::value, PARTS><<<dim3(p.B, f.parts), kStreamThreads, lds, stream>>>(
@@ -564,14 +563,12 @@ void launch_dense_finish(const ProjectLaunch& p, const FusedPlan& f, const float
   }
 }
 
-void launch_finish(const ProjectLaunch& p, const float* part, int nz, hipStream_t stream) {
+static void launch_finish(const ProjectLaunch& p, const float* part, int nz, hipStream_t stream) {
   if (p.feat_is_f16)
     finish_kernel<f16_t><<<p.B, kThreads, 0, stream>>>(part, nz, p.b2, static_cast<f16_t*>(p.feat), p.B, p.E, p.normalize);
   else
     finish_kernel<float><<<p.B, kThreads, 0, stream>>>(part, nz, p.b2, static_cast<float*>(p.feat), p.B, p.E, p.normalize);
 }
-
-}  // namespace
 
 size_t project_workspace_least(int32_t B, int32_t dm, int32_t hid, int32_t E) {
   const DenseSplit s1 = dense_split(B, hid, dm), s2 = dense_split(B, E, hid);

@@ -3,7 +3,8 @@ HIP runtime (launch_recorder.c), in a process of its own, without a GPU.
 
 record(calls) -> one (status, [(kernel, grid_x, grid_y, grid_z, block, lds), ...]) per call.  A call is
 ("search", N, E, B, k, "f16"|"f32", "ip"|"l2"), ("exact", B, Hq, Hkv, S, D, causal, "bf16"|"f32"),
-("insert", B, Lc, Hq, Hkv, S, D, causal, packed) or ("apply", B, Lc, Hq, Hkv, S, D, causal, "bf16"|"f32")."""
+("insert", B, Lc, Hq, Hkv, S, D, causal, packed), ("apply", B, Lc, Hq, Hkv, S, D, causal, "bf16"|"f32") or
+("project", B, S, dm, hid, E, "bf16"|"f32", "f16"|"f32", biases[, bytes of workspace])."""
 import ctypes
 import json
 import os
@@ -16,6 +17,13 @@ PTR, F32, F16, BF16 = 4096, 0, 1, 2   # never dereferenced
 HUGE = 1 << 62
 
 
+def plain(symbols):
+    """Kernel names as they are written.  c++filt does not know _Float16 and bf16: builtin types stand in for them."""
+    text = "\n".join(symbols).replace("DF16_", "Dh").replace("DF16b", "g")
+    out = subprocess.run(["c++filt"], input=text, text=True, capture_output=True, check=True).stdout
+    return [n.replace("void ac::", "").replace("ac::", "").replace("__float128", "bf16").split("(")[0] for n in out.splitlines()]
+
+
 def record(calls, build_dir, lib=LIB):
     rec = os.path.join(str(build_dir), "liblaunch_recorder.so")
     if not os.path.exists(rec):
@@ -25,8 +33,7 @@ def record(calls, build_dir, lib=LIB):
                          capture_output=True, check=True).stdout
     got = json.loads(out)
     names = sorted({la[0] for _, ls in got for la in ls})
-    plain = subprocess.run(["c++filt"], input="\n".join(names).replace("DF16_", "Dh"), text=True, capture_output=True, check=True).stdout
-    nice = {n: p.replace("void ac::", "").replace("ac::", "").split("(")[0] for n, p in zip(names, plain.splitlines())}
+    nice = dict(zip(names, plain(names)))
     return [(st, [(nice[la[0]], *la[1:]) for la in ls]) for st, ls in got]
 
 
@@ -59,6 +66,11 @@ def _main(rec, path):
             B, Lc, Hq, Hkv, S, D, causal, packed = c
             h = db(1, 16, F16, 0, 1, Lc, Hq, Hkv, D, S, BF16, int(causal), int(packed))
             st = L.attncache_insert(h, None, p, None, None, p, p, p, p, B, 0, Lc, f32(0), None)
+        elif fn == "project":
+            B, S, dm, hid, E, dt, feat, biases, *ws = c
+            bias = p if biases else None
+            st = L.attncache_project(p, p, p, bias, p, bias, p, B, S, dm, hid, E, BF16 if dt == "bf16" else F32,
+                                     F16 if feat == "f16" else F32, 1, p, sz(ws[0] if ws else HUGE), None)
         else:
             B, Lc, Hq, Hkv, S, D, causal, dt = c
             h = db(1, 16, F16, 0, 1, Lc, Hq, Hkv, D, S, BF16 if dt == "bf16" else F32, int(causal), 0)

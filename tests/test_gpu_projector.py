@@ -81,7 +81,13 @@ CASES = [
     (4, 5, 128, 256, 128, torch.bfloat16, torch.float16, False, True, True),
     (3, 33, 136, 264, 136, torch.float32, torch.float32, True, True, False),
     (5, 65, 120, 248, 120, torch.bfloat16, torch.float32, True, False, True),
-    (90, 12, 768, 192, 256, torch.bfloat16, torch.float32, True, True, True),      # two queries, the last alone
+    (90, 12, 768, 192, 256, torch.bfloat16, torch.float32, True, True, True),      # four queries, two left over
+    (33, 9, 1024, 256, 256, torch.bfloat16, torch.float16, True, True, True),      # two, the last alone
+    (95, 5, 320, 64, 304, torch.float32, torch.float32, True, True, False),
+    (115, 3, 8, 544, 8, torch.float32, torch.float16, False, False, True),         # ... and three workgroups to the rows of W1
+    (23, 300, 2048, 512, 256, torch.bfloat16, torch.float32, True, True, True),    # two workgroups, several pooling rounds
+    (1, 7, 72, 48, 280, torch.bfloat16, torch.float16, False, True, True),         # steps of 512 and of 1,024 rows of W2
+    (2, 7, 32, 8, 24, torch.float32, torch.float16, True, True, False),
     (101, 7, 1032, 256, 64, torch.float32, torch.float16, True, True, False),      # four, one left over
     (2, 700, 1024, 520, 8, torch.bfloat16, torch.float32, True, True, True),       # rows of W1 over several workgroups
     (256, 4, 128, 64, 1024, torch.float32, torch.float32, True, True, True),       # the most queries
@@ -89,6 +95,9 @@ CASES = [
     (2, 40, 512, 1024, 256, torch.bfloat16, torch.float32, True, True, True),
     (9, 20, 264, 872, 488, torch.float32, torch.float16, True, False, True),
     (33, 3, 256, 512, 512, torch.bfloat16, torch.float16, False, True, False),
+    (1, 20, 248, 168, 560, torch.float32, torch.float32, False, True, True),       # ... in steps of 256, 512 and 1,024 rows
+    (1, 7, 160, 96, 1320, torch.bfloat16, torch.float16, True, False, True),
+    (2, 20, 256, 80, 1552, torch.float32, torch.float32, True, True, False),
     # four, with one, two and four slices of the first layer
     (257, 3, 32, 24, 40, torch.bfloat16, torch.float32, True, True, False),
     (257, 3, 32, 24, 40, torch.float32, torch.float16, True, True, True),

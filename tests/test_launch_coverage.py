@@ -7,6 +7,7 @@ import pytest
 from tests import launches
 from tests import test_gpu_f32_tiles as f32
 from tests import test_gpu_parity_small as small
+from tests import test_gpu_projector as proj
 from tests import test_gpu_row_units as rows
 from tests import test_gpu_search_tiles as tiles
 from tests import test_gpu_split_units as split
@@ -19,10 +20,7 @@ NOT_RUN = {"search_valu_kernel<half, false, %d, %s>" % (q, k) for q in (2, 4) fo
 def _kernels(*prefixes):
     """Kernels of the built library: the handles that its host code passes to a launch."""
     out = subprocess.run(["nm", "-D", launches.LIB], text=True, capture_output=True, check=True).stdout
-    names = [l.split()[-1] for l in out.splitlines() if " V " in l or " D " in l]
-    names = subprocess.run(["c++filt"], input="\n".join(names).replace("DF16_", "Dh"), text=True, capture_output=True,
-                           check=True).stdout.splitlines()
-    names = {n.replace("void ac::", "").replace("ac::", "").split("(")[0] for n in names}
+    names = launches.plain(l.split()[-1] for l in out.splitlines() if " V " in l or " D " in l)
     return {n for n in names if n.startswith(prefixes)}
 
 
@@ -72,6 +70,15 @@ def test_every_attention_kernel_is_reached(tmp_path):
     calls += [("apply", c[0], c[9], *c[3:8], _dt(c[10])) for c in small.APPLY_CASES]
     calls += [("apply", c[0], 2, *c[1:], "f32") for c in f32.CASES]
     missing = _kernels("exact_", "insert_", "apply_f32") - _reached(tmp_path, calls)
+    assert not missing
+
+
+def _project(c):
+    return ("project", *c[:5], _dt(c[5]), _dt(c[6]), c[9])
+
+
+def test_every_projector_kernel_is_reached(tmp_path):
+    missing = _kernels("pool_", "dense_", "finish_") - _reached(tmp_path, [_project(c) for c in proj.CASES])
     assert not missing
 
 
