@@ -504,18 +504,41 @@ static size_t dense_lds(const DenseSplit& s) { return sizeof(float) * s.n_waves 
 //   dm 1024, hid 256     1 x 16 13.2 / 9.1, 128 x 100 19.0 / 13.5, 256 x 16 (512 workgroups) 20.4 / 17.2
 //   dm 2048, hid 512     16 x 90 18.1 / 14.1, 64 x 128 padded 21.6 / 18.3, 128 x 16 (512 workgroups) 21.6 / 23.3
 //   dm 4096, hid 1024    1 x 1024 38.0 / 18.0, 8 x 16 21.2 / 17.7, 32 x 16 (256 workgroups) 22.4 / 23.7
-// so the partial products (workgroups of four queries x hidden units) are what the line is drawn at.  Further out, wide
-// hidden layers (hid 1528, dm 72, 151 queries 33 / 88) and many rows of W2 for each of many queries lose: every query
-// streams all of W2 past itself.  Three launches gain little where the hidden layer is wide and the first one short (11 x 67
-// tokens, dm 1056, hid 872, out 480 18.8 / 21.5).
-struct FusedPlan { bool use; int nz, Q, rows, parts, rows2; };
+// so the partial products (workgroups of four queries x hidden units, a query and unit of each workgroup being 128
+// products) are what the line is drawn at.  Of 19,500 drawn sizes those with dm and hid multiples of 32 gain 1.10 times on
+// average from half of that line to three quarters, 1.08 from there to the line, 0.97 up to a quarter beyond, 0.95 further
+// on.  Many rows of W2 for each of many queries lose, every query streams all of W2 past itself.
+//
+// Rows of W1 and W2 that do not start on 128-byte lines cost extra lines in every slice of 128 columns, and hidden layers
+// that leave a step over W2 half empty cost whole steps.  For such widths the gain is estimated, fitted to the same sizes, in us:
+//   6 for the launches, less 2.6 per 1,024 hidden units, 1.1 per 1,024 rows of W1 times queries that a compute unit works
+//   off, 1.4 more per 1,024 rows off the lines, 0.3 per step off the lines, 1 for the third launch and 0.03 per MB of
+//   tokens that several workgroups pool again; and 0.4 per 128 tokens where the pooling launch leaves the chip idle.
+// us per call, four / fused, and what is taken: 20 x 83 tokens, 3432 -> 856 -> 256 24.5 / 30.7, four; 130 x 169, 1384 -> 344 ->
+// 512 33.0 / 39.6, four; 4 x 30, 2872 -> 712 -> 128 20.3 / 16.2, fused.  Of the drawn sizes 16,390 are fused: 1.46 times on
+// average, 0.84 at worst, 127 below 0.98 (by the line alone 293, 0.78 at worst); those that this refuses 0.96 on average.
+struct FusedPlan { bool fits, use; int nz, Q, rows, parts, rows2; };
+
+static double fused_gain(const FusedPlan& f, int32_t B, int32_t S, int32_t dm, int32_t hid, bool f32) {
+  const int z = ceil_div(hid, f.rows), bytes = f32 ? 4 : 2;
+  const double kilo_rows = (double)ceil_div(f.nz * ceil_div(B, f.Q) * z, 256) * f.rows / 1024;   // rows of W1 a compute unit reads
+  const double steps2 = (double)ceil_div(B * f.parts, 256) * stream_steps(4, f.rows2, hid, stream_unroll(4, f.rows2, hid));
+  const int pools = ceil_div(dm, kWave * (f32 ? PoolVec<float>::VEC : PoolVec<bf16_t>::VEC)) * B;   // workgroups of pool_kernel
+  double us = 6 - 2.6 * hid / 1024 - 1.1 * kilo_rows * f.Q;
+  if (dm % 32) us -= 1.4 * kilo_rows;
+  if (hid % 32) us -= 0.3 * steps2;
+  if (f.parts > 1) us -= 1;
+  us -= 0.03e-6 * bytes * dm * B * S * (z - 1);
+  us += 0.4 * std::max(S / 128. - 1, 0.) * std::min(1., 256. / pools);
+  return us;
+}
+
 static FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32_t E, bool f32) {
-  FusedPlan f = {false, ceil_div(dm, kFusedCols), 4, 0, 1, E};
+  FusedPlan f = {false, false, ceil_div(dm, kFusedCols), 4, 0, 1, E};
   if (B > kFusedBatch || hid > 1024) return f;
   const long wgs4 = (long)f.nz * ceil_div(B, 4), steps = stream_steps(4, E, hid, stream_unroll(4, E, hid));
-  if (steps > 4 && hid > 768 && dm > 512 && dm < 2 * hid) return f;
   if (steps > 16 || steps * B > 1024 || wgs4 > 512 || wgs4 * hid > 128 * 1024) return f;
-  f.use = true;
+  f.fits = true;   // (whatever the length of the sentences, which the size of the workspace does not know)
   long least = 0;
   for (int Q = 1; Q <= 4; Q *= 2) {
     const int wgs = f.nz * ceil_div(B, Q);
@@ -530,10 +553,11 @@ static FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32
     f.parts = ceil_div(E, f.rows2);
     if (f.parts == 1) f.rows2 = E;
   }
+  f.use = (dm % 32 == 0 && hid % 32 == 0) || fused_gain(f, B, S, dm, hid, f32) > 0;
   return f;
 }
 static size_t fused_bytes(const FusedPlan& f, int32_t B, int32_t hid, int32_t E) {
-  return f.use ? sizeof(float) * ((size_t)f.nz * B * hid + (f.parts > 1 ? (size_t)B * E : 0)) : 0;
+  return f.fits ? sizeof(float) * ((size_t)f.nz * B * hid + (f.parts > 1 ? (size_t)B * E : 0)) : 0;
 }
 
 template <typename T>

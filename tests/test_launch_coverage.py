@@ -107,3 +107,31 @@ def test_reuse_of_maps_of_a_few_rows_takes_a_thread_per_output(tmp_path, S, D, k
     # 256 heads of one row of 256: 6.6 us in tiles of 16 rows, 2.4 so
     (status, ls), = launches.record([("apply", 64, 1, 4, 4, S, D, True, "f32")], tmp_path)
     assert status == 0 and [la[0] for la in ls] == [kernel]
+
+
+@pytest.mark.parametrize("case,launched", [
+    ((64, 128, 2048, 512, 256), 2),     # us, four launches / fewer: 21.6 / 18.3
+    ((32, 16, 4096, 1024, 256), 4),     # 22.4 / 23.7, beyond the line
+    ((16, 16, 4096, 1024, 512), 3),     # 23.7 / 22.3, on it
+    ((20, 83, 3432, 856, 256), 4),      # 24.5 / 30.7, rows off the 128-byte lines
+    ((66, 48, 680, 696, 512), 4),       # 20.4 / 25.3
+    ((130, 169, 1384, 344, 512), 4),    # 33.0 / 39.6
+    ((4, 30, 2872, 712, 128), 2),       # 20.3 / 16.2
+    ((3, 1887, 1024, 600, 256), 3),     # 46.6 / 19.1, long sentences
+], ids=str)
+def test_the_projector_takes_the_launches_that_measured_best(tmp_path, case, launched):
+    (status, ls), = launches.record([("project", *case, "bf16", "f16", True)], tmp_path)
+    assert status == 0 and len(ls) == launched, ls
+
+
+def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
+    """Where the launches depend on the sentences' length, the workspace, which does not know it, is enough for the fewest."""
+    import ctypes
+    lib = ctypes.CDLL(launches.LIB)
+    lib.attncache_project_workspace_bytes.restype = ctypes.c_size_t
+    for B, dm, hid, E in [(16, 1744, 872, 480), (20, 3432, 856, 256), (6, 1024, 600, 256), (70, 2048, 512, 256)]:
+        ws = lib.attncache_project_workspace_bytes(B, dm, hid, E)
+        calls = [("project", b, S, dm, hid, E, "bf16", "f16", True, *bytes) for b in (1, B // 2, B) for S in (1, 100, 3000)
+                 for bytes in ((), (ws,))]
+        got = launches.record(calls, tmp_path)
+        assert got[::2] == got[1::2] and all(status == 0 for status, _ in got)
