@@ -653,9 +653,10 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel_co
 
 // The same for maps of a few rows, whose time is the chain above and not the work: one workgroup per (query,
 // layer, head), a thread per output, sums over ascending columns.  us per call, tiles / this: 256 heads of
-// 1 x 256 6.0 / 2.5, of 8 x 64 3.8 / 3.5, of 12 x 40 4.0 / 4.2.
-__global__ __launch_bounds__(kThreads) void apply_f32_small_kernel(const ApplyArgs a, int D, int causal) {
-  const int tile = a.tile0 + blockIdx.x, h = tile % a.Hq, l = tile / a.Hq % a.Lc, bslot = tile / (a.Hq * a.Lc);
+// 1 x 256 6.0 / 2.5, of 8 x 64 3.8 / 3.5, of 12 x 40 4.0 / 4.2.  The first workgroup takes (b0, l0, h0): several
+// launches may have more (query, layer, head) triples between them than 32 bits count.
+__global__ __launch_bounds__(kThreads) void apply_f32_small_kernel(const ApplyArgs a, int D, int causal, int b0, int l0, int h0) {
+  const int th = h0 + blockIdx.x, tl = l0 + th / a.Hq, h = th % a.Hq, l = tl % a.Lc, bslot = b0 + tl / a.Lc;
   const int b = a.fixed_entry >= 0 ? a.q_list[bslot] : bslot;
   const int entry = a.fixed_entry >= 0 ? a.fixed_entry : a.hit[b];
   if (a.fixed_entry < 0 && (entry < 0 || entry >= a.M)) return;
@@ -749,18 +750,20 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
   if (nb == 0 || p.Lc == 0) return hipSuccess;
 
   if (p.is_f32) {
-    a.heads_per_wg = 1; a.n_rblk = 1; a.n_tiles = nb * p.Lc * p.Hkv;
+    a.heads_per_wg = 1; a.n_rblk = 1;
     const size_t tiles = (size_t)nb * p.Lc * p.Hq;
     if (p.S <= 5 || (size_t)p.S * p.S * p.D <= 3400) {   // (the other kernel reads rows of four columns or more)
       constexpr size_t kFit = ((size_t)1 << 31) / kThreads;
       for (size_t t0 = 0; t0 < tiles; t0 += kFit) {
-        a.tile0 = (int32_t)t0;
-        hipLaunchKernelGGL(apply_f32_small_kernel, dim3((unsigned)std::min(tiles - t0, kFit)), dim3(kThreads), 0, stream, a, p.D, p.causal);
+        const size_t l0 = t0 / p.Hq;
+        hipLaunchKernelGGL(apply_f32_small_kernel, dim3((unsigned)std::min(tiles - t0, kFit)), dim3(kThreads), 0, stream, a, p.D,
+                           p.causal, (int)(l0 / p.Lc), (int)(l0 % p.Lc), (int)(t0 % p.Hq));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
       return hipSuccess;
     }
+    a.n_tiles = nb * p.Lc * p.Hkv;
     if (p.D <= 64) return launch_apply_f32<1>(a, p.D, p.causal, stream);
     if (p.D <= 128) return launch_apply_f32<2>(a, p.D, p.causal, stream);
     return launch_apply_f32<4>(a, p.D, p.causal, stream);

@@ -26,9 +26,11 @@ static int fits(dim3 g, dim3 b, size_t lds) {
 
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t lds, hipStream_t s) {
   Dl_info info;
-  (void)args; (void)s;
+  (void)s;
   const char* name = dladdr(f, &info) && info.dli_sname ? info.dli_sname : "?";
   used += (size_t)snprintf(text + used, sizeof text - used, "%s %u %u %u %u %zu\n", name, g.x, g.y, g.z, b.x, lds);
+  if (strstr(name, "apply_f32_small_kernel"))   /* where the launch starts: query, layer, head */
+    used += (size_t)snprintf(text + used - 1, sizeof text - used, " %d %d %d\n", *(int*)args[3], *(int*)args[4], *(int*)args[5]) - 1;
   last = fits(g, b, lds) ? hipSuccess : hipErrorInvalidConfiguration;
   return last;
 }

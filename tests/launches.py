@@ -1,7 +1,8 @@
 """Which kernels a call launches, and how: the library's host code on a recorder in the place of the
 HIP runtime (launch_recorder.c), in a process of its own, without a GPU.
 
-record(calls) -> one (status, [(kernel, grid_x, grid_y, grid_z, block, lds), ...]) per call.  A call is
+record(calls) -> one (status, [(kernel, grid_x, grid_y, grid_z, block, lds), ...]) per call; apply_f32_small_kernel
+adds the (query, layer, head) that its launch starts with.  A call is
 ("search", N, E, B, k, "f16"|"f32", "ip"|"l2"), ("exact", B, Hq, Hkv, S, D, causal, "bf16"|"f32"),
 ("insert", B, Lc, Hq, Hkv, S, D, causal, packed), ("apply", B, Lc, Hq, Hkv, S, D, causal, "bf16"|"f32") or
 ("project", B, S, dm, hid, E, "bf16"|"f32", "f16"|"f32", biases[, bytes of workspace])."""

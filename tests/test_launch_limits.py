@@ -27,3 +27,16 @@ def test_a_grid_that_does_not_fit_is_split(record, call, kernel, covered):
     mine = [la for la in ls if la[0].startswith(kernel)]
     assert len(mine) > 1 and sum(la[1] * la[2] for la in mine) >= covered
     assert all(la[1] * la[4] < 2**32 for la in ls)
+
+
+@pytest.mark.parametrize("B,Lc,Hq", [(3_000_000, 1, 4), (700_001, 3, 6), (600_000_000, 1, 4), (3, 900_000_001, 2)])
+def test_launches_of_small_maps_start_where_the_last_one_ended(record, B, Lc, Hq):
+    """A workgroup per (query, layer, head), 2^31 and more of them in the last two."""
+    (status, ls), = record(("apply", B, Lc, Hq, Hq, 1, 1, True, "f32"))
+    assert status == 0 and len(ls) > 1
+    done = 0
+    for kernel, gx, gy, gz, block, _, b, l, h in ls:
+        assert kernel == "apply_f32_small_kernel" and gy == gz == 1 and gx * block < 2**32
+        assert 0 <= h < Hq and 0 <= l < Lc and (b * Lc + l) * Hq + h == done
+        done += gx
+    assert done == B * Lc * Hq
