@@ -617,7 +617,7 @@ __device__ __forceinline__ void apply_f32_tiles(const ApplyArgs& a, int D, int c
     }
     __syncthreads();
     const int next = min(jc + KC, last_stage);   // (the last trip: once more, unused)
-    if (COLS != kAnyCols || jc + KC < wg_keys) vs.load(V, next, S, D, tid);
+    vs.load(V, next, S, D, tid);
     load_map(next);
 #pragma unroll
     for (int bk = 0; bk < NB; ++bk)
@@ -687,6 +687,8 @@ static hipError_t launch_apply_f32(ApplyArgs a, int D, int causal, hipStream_t s
       hipLaunchKernelGGL((apply_f32_kernel<DB>), grid, dim3(kThreads), 0, stream, a, causal);
     else if (D % 4 == 0)
       hipLaunchKernelGGL((apply_f32_kernel_cols<DB, kVecCols>), grid, dim3(kThreads), 0, stream, a, D, causal);
+    else if (DB == 1 && D < 4)
+      hipLaunchKernelGGL((apply_f32_kernel_cols<1, kFewCols>), grid, dim3(kThreads), 0, stream, a, D, causal);
     else
       hipLaunchKernelGGL((apply_f32_kernel_cols<DB, kAnyCols>), grid, dim3(kThreads), 0, stream, a, D, causal);
     const hipError_t e = hipGetLastError();

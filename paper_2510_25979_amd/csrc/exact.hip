@@ -629,7 +629,7 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
   for (int kk = 0; kk < 4 * DB; ++kk) {
     const int c = 16 * kk + 4 * kq;
     const float* src = reinterpret_cast<const float*>(a.Q) + at + c;
-    if constexpr (COLS == kAnyCols) {
+    if constexpr (COLS == kAnyCols || COLS == kFewCols) {
       q[kk] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int t = 0; t < 4; ++t)
@@ -914,6 +914,8 @@ static hipError_t launch_exact_f32(const ExactArgs& a, int D, int causal, float 
     hipLaunchKernelGGL((exact_f32_kernel<DB, kAllCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
   else if (D % 4 == 0)
     hipLaunchKernelGGL((exact_f32_kernel<DB, kVecCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
+  else if (DB == 1 && D < 4)
+    hipLaunchKernelGGL((exact_f32_kernel<1, kFewCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
   else
     hipLaunchKernelGGL((exact_f32_kernel<DB, kAnyCols>), dim3(grid), dim3(kThreads), 0, stream, a, D, causal, scale);
   return hipGetLastError();

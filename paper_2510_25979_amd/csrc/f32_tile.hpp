@@ -24,13 +24,15 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// What is known of the head dimension when a kernel is compiled.  With all three forms in one kernel every piece
+// What is known of the head dimension when a kernel is compiled.  With all forms in one kernel every piece
 // of a row was a load behind tests of its own (16 x 24 heads on 8 K and V, 94 x 128 causal: 24.0 us exact, 21.7 so;
-// 16 x 8 heads of 333 x 128 61 / 54).
+// 16 x 8 heads of 333 x 128 61 / 54).  Rows of any length in single floats behind tests took, exact / reuse, 35.0 / 26.8 us at
+// 333 x 33 and 144 / 89 at 333 x 199; in pieces of four that may overlap 31.9 / 21.5 and 128 / 77.
 enum F32Cols {
-  kAnyCols = 0,   // any D: rows may start at any 4-byte address
+  kAnyCols = 0,   // any D >= 4: rows may start at any 4-byte address
   kVecCols = 1,   // D % 4 == 0: whole 16-byte pieces
   kAllCols = 2,   // D == 64 DB
+  kFewCols = 3,   // D < 4: single floats, behind one test
 };
 
 // KC rows of up to 64 DB floats on their way from memory through registers to LDS.  LDS rows are four
@@ -44,32 +46,30 @@ struct F32Stage {
   f32x4 r[N];
 
   // Rows [row0, row0 + KC) of which those from `valid` (> row0) on do not exist.  No load sits behind a
-  // test: what does not exist repeats something that does, and mask() takes it out.
+  // test of its own: what does not exist repeats something that does, and mask() takes it out.  The end of a row
+  // that is no whole piece is read with what lies before it, and mask() shifts it.
   __device__ __forceinline__ void load(const float* __restrict__ src, int row0, int valid, int D,
                                        int tid) {
     const int row = tid / (16 * DB), c = 4 * (tid % (16 * DB));
     const float* base = src + (size_t)row0 * D;   // uniform
     const int last = valid - 1 - row0;
+    if constexpr (COLS == kFewCols) {
+#pragma unroll
+      for (int n = 0; n < N; ++n) r[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (c == 0)
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+          for (int t = 0; t < 3; ++t)
+            if (t < D) r[n][t] = base[min(row + n * STEP, last) * D + t];
+      return;
+    }
+    const int col = COLS == kAllCols ? c : COLS == kVecCols ? (c < D ? c : 0) : min(c, D - 4);
 #pragma unroll
     for (int n = 0; n < N; ++n) {
-      if constexpr (COLS == kAnyCols) {
-        // Clamped like the others, without the outer test, or without the vector form (which D % 4 != 0 never
-        // takes): 7 to 60 % longer at D = 33 or 199, the compiler then keeps every address or waits load by load.
-        r[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (row + n * STEP <= last && c < D) {
-          const float* at = base + (size_t)(n * STEP) * D + (unsigned)(row * D + c);
-          if ((D & 3) == 0) {
-            r[n] = *reinterpret_cast<const f32x4*>(at);
-          } else {
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-              if (c + t < D) r[n][t] = at[t];
-          }
-        }
-      } else {
-        const int at = min(row + n * STEP, last) * D;
-        r[n] = *reinterpret_cast<const f32x4*>(base + (unsigned)(at + (COLS == kAllCols || c < D ? c : 0)));
-      }
+      const float* at = base + (unsigned)(min(row + n * STEP, last) * D + col);
+      if constexpr (COLS == kAnyCols) r[n] = *reinterpret_cast<const f32x4_dw*>(at);
+      else r[n] = *reinterpret_cast<const f32x4*>(at);
     }
   }
   // Zeros in the rows from `valid` on (hidden keys then carry finite values whatever the padding of a
@@ -77,13 +77,24 @@ struct F32Stage {
   template <bool ROWS>
   __device__ __forceinline__ void mask(int row0, int valid, int D, int tid) {
     const int row = tid / (16 * DB), c = 4 * (tid % (16 * DB));
-    if (COLS == kAnyCols) return;
-    if ((ROWS && row0 + KC > valid) || (COLS == kVecCols && D < 64 * DB)) {   // uniform
+    if (COLS == kAnyCols) {
+      const int by = c - (D - 4);   // columns that were read too early (four or more: none counts)
+      const bool two = by > 0 && (by & 2), one = by > 0 && (by & 1);
+#pragma unroll
+      for (int n = 0; n < N; ++n) {
+        r[n] = two ? f32x4{r[n][2], r[n][3], r[n][2], r[n][3]} : r[n];
+        r[n] = one ? f32x4{r[n][1], r[n][2], r[n][3], r[n][3]} : r[n];
+      }
+    }
+    if ((ROWS && row0 + KC > valid) || COLS == kAnyCols || (COLS == kVecCols && D < 64 * DB)) {   // uniform
 #pragma unroll
       for (int n = 0; n < N; ++n) {
         const bool in = !ROWS || row0 + row + n * STEP < valid;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) r[n][t] = in && (COLS == kAllCols || c < D) ? r[n][t] : 0.f;
+        for (int t = 0; t < 4; ++t) {
+          const bool col = COLS == kAnyCols ? c + t < D : COLS == kVecCols ? c < D : true;
+          r[n][t] = in && col ? r[n][t] : 0.f;
+        }
       }
     }
   }
@@ -170,7 +181,7 @@ __device__ __forceinline__ void f32_store_row(float* __restrict__ o, const f32x4
       if (DIVIDE)
 #pragma unroll
         for (int t = 0; t < 4; ++t) w[t] = f32_divide(w[t], by, inv);
-      if constexpr (COLS != kAnyCols) {
+      if constexpr (COLS == kVecCols || COLS == kAllCols) {
         if (COLS == kAllCols || d < D) *reinterpret_cast<f32x4*>(o + d) = w;
       } else {
 #pragma unroll

@@ -30,6 +30,17 @@ CASES = [
     (2, 2, 1, 34, 99, False),
     (1, 4, 2, 50, 199, True),
     (16, 24, 8, 94, 128, True),     # workgroups for every compute unit two and a half times
+    (2, 2, 1, 60, 1, True),         # rows of less than one piece
+    (1, 3, 1, 61, 2, False),
+    (2, 2, 2, 59, 3, True),
+    (2, 2, 1, 50, 5, True),         # rows of one piece and part of another
+    (1, 2, 1, 40, 6, False),
+    (3, 1, 1, 33, 7, True),
+    (1, 2, 2, 31, 66, True),        # and of the second and fourth output block
+    (1, 2, 1, 47, 127, False),
+    (1, 1, 1, 65, 130, True),
+    (1, 2, 1, 33, 253, False),
+    (2, 1, 1, 20, 255, True),
 ]
 
 
@@ -86,3 +97,27 @@ def test_a_value_that_is_not_finite_reaches_only_the_rows_that_see_its_key(ac, o
         assert not np.isfinite(got[:, :, j0:, 5]).any()
         got[:, :, j0:, 5] = want[:, :, j0:, 5]
         assert np.abs(got - want).max() <= parity.TOL[torch.float32]
+
+
+@pytest.mark.parametrize("D", [3, 5, 21, 67, 131, 254])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_the_end_of_a_row_stays_in_its_column(ac, oracle_mod, D, bad):  # noqa: F811
+    """Rows that are no whole pieces are read in pieces that overlap: a value that is not finite shows in its own column only."""
+    Hq, Hkv, S, j0 = 2, 1, 61, 37
+    g = _gen(13 + D)
+    Q, K, V = (torch.randn(1, h, S, D, generator=g) for h in (Hq, Hkv, Hkv))
+    for c in {D - 1, max(0, D - 4), max(0, D - 5)}:
+        clean, dirty = V.clone(), V.clone()
+        clean[0, 0, j0, c], dirty[0, 0, j0, c] = 0.0, bad
+        want, P = oracle_mod.attention_exact(parity.to_np(Q), parity.to_np(K), parity.to_np(clean), causal=False, return_map=True)
+        O = torch.zeros(1, Hq, S, D, device="cuda")
+        ac.attention_exact(Q.cuda(), K.cuda(), dirty.cuda(), O, causal=False)
+        maps = torch.from_numpy(P.astype(np.float32)).reshape(1, 1, Hq, S, S)
+        db = ac.attncache_build_db(torch.zeros(1, 16).cuda(), maps.cuda(), n_kv_heads=Hkv, head_dim=D, causal=False)
+        O2 = torch.zeros(1, 1, Hq, S, D, device="cuda")
+        ac.attncache_apply(db, torch.zeros(1, dtype=torch.int32).cuda(), dirty[:, None].cuda(), O2)
+        db.close()
+        for got in (O.cpu().numpy(), O2[:, 0].cpu().numpy()):
+            assert not np.isfinite(got[..., c]).any()
+            got[..., c] = want[..., c]
+            assert np.abs(got - want).max() <= parity.TOL[torch.float32]
