@@ -555,7 +555,7 @@ __device__ __forceinline__ void apply_f32_tiles(const ApplyArgs& a, int D, int c
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, kq = lane >> 4;
   const int S = a.S, g = a.Hq / a.Hkv;
-  const F32Unit u = f32_unit(blockIdx.x, wave, g, S, a.n_tiles);
+  const F32Unit u = f32_unit<true>(blockIdx.x, wave, g, S, a.n_tiles);
   if (u.tile < 0) return;
   const int tile = a.tile0 + u.tile;
   const int h = tile % a.Hkv * g + u.head;
@@ -616,9 +616,14 @@ __device__ __forceinline__ void apply_f32_tiles(const ApplyArgs& a, int D, int c
       for (int x = 0; x < 4; ++x) w[bk][x] = jc + 16 * bk + 4 * kq + x < limit ? m[x] : 0.f;
     }
     __syncthreads();
-    const int next = min(jc + KC, last_stage);   // (the last trip: once more, unused)
-    vs.load(V, next, S, D, tid);
-    load_map(next);
+    // The next stage.  Whole pieces of narrow rows are requested without a test, in the last trip once more and unused:
+    // 2 x 8 heads of 600 x 128 36.7 us with the test, 35.4 without.  Wide rows lose by it (16 x 24 heads of 94 x 160, all
+    // keys 28.2 / 30.9) and so do rows that end in part of a block (of 94 x 80, causal 13.0 / 14.1).
+    if ((COLS == kAllCols && DB <= 2) || jc + KC < wg_keys) {
+      const int next = min(jc + KC, last_stage);
+      vs.load(V, next, S, D, tid);
+      load_map(next);
+    }
 #pragma unroll
     for (int bk = 0; bk < NB; ++bk)
       if (jc + 16 * bk < wave_keys) {
@@ -642,12 +647,14 @@ __device__ __forceinline__ void apply_f32_tiles(const ApplyArgs& a, int D, int c
   }
 }
 
+// Three workgroups per compute unit, also of the widest rows (168 registers, two of them spilled): with two, as eight
+// registers more had it, 16 x 24 heads of 94 x 160, all keys, take 33.3 us instead of 28.2, 32 x 12 of 128 x 256 37.5 instead of 34.6.
 template <int DB>   // D == 64 DB
-__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel(const ApplyArgs a, int causal) {
+__global__ __launch_bounds__(kThreads, 3) void apply_f32_kernel(const ApplyArgs a, int causal) {
   apply_f32_tiles<DB, kAllCols>(a, 64 * DB, causal);
 }
 template <int DB, int COLS>
-__global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void apply_f32_kernel_cols(const ApplyArgs a, int D, int causal) {
+__global__ __launch_bounds__(kThreads, 3) void apply_f32_kernel_cols(const ApplyArgs a, int D, int causal) {
   apply_f32_tiles<DB, COLS>(a, D, causal);
 }
 

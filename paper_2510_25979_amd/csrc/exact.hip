@@ -614,7 +614,7 @@ __global__ __launch_bounds__(kThreads, DB <= 2 ? 3 : 2) void exact_f32_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, kq = lane >> 4;
   const int S = a.S, g = a.Hq / a.Hkv;
-  const F32Unit u = f32_unit(blockIdx.x, wave, g, S, a.n_kvtiles);
+  const F32Unit u = f32_unit<(DB <= 2)>(blockIdx.x, wave, g, S, a.n_kvtiles);
   if (u.tile < 0) return;
   const int b = u.tile / a.Hkv, h = u.tile % a.Hkv * g + u.head;
   if (a.row_sel && a.row_sel[b] >= 0) return;

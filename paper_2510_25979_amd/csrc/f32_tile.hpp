@@ -205,15 +205,17 @@ struct F32Unit {
 // workgroups: 29.5 -> 25.3 us exact, 25.4 -> 23.1 us reuse); a larger one finishes tile by tile,
 // while its K and V are in the L2.  Of the former every second 32 workgroups of an XCD go out in the other order, so
 // that the compute units (32 per XCD, filled one after the other) that got the heaviest get the lightest
-// next (the same shape 21.7 -> 20.8 and 21.9 -> 21.2 us).
+// next (the same shape 21.7 -> 20.8 and 21.9 -> 21.2 us).  Not where a compute unit holds two workgroups (exact, D > 128):
+// the third 32 then wait for the lightest to end, 16 x 24 heads of 94 x 256 43.3 us so, 39.6 in one order.
 constexpr int kF32Spread = 2048;
 constexpr int kXcdCus = 32;
+template <bool MIRROR>
 __device__ __forceinline__ F32Unit f32_unit(int bid, int wave, int g, int S, int n_tiles) {
   const int n_units = g * ((S + kF32Rows - 1) / kF32Rows), per_tile = (n_units + 3) >> 2;
   const int tiles8 = (n_tiles + 7) >> 3;
   const bool spread = gridDim.x <= kF32Spread;
   int slot = bid >> 3;
-  if (spread && (slot & kXcdCus) && (slot | (kXcdCus - 1)) < (int)(gridDim.x >> 3)) slot ^= kXcdCus - 1;
+  if (MIRROR && spread && (slot & kXcdCus) && (slot | (kXcdCus - 1)) < (int)(gridDim.x >> 3)) slot ^= kXcdCus - 1;
   F32Unit u;
   u.tile = (spread ? slot % tiles8 : slot / per_tile) * 8 + (bid & 7);
   const int top = n_units - 1 - 4 * (spread ? slot / tiles8 : slot % per_tile), n = top - wave;

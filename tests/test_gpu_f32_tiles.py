@@ -2,11 +2,14 @@
 stages of 32 and 64 keys, output blocks of 64 columns, units of one head and 16 rows dealt to four
 waves.  Bars: the fp32 bar of tests/parity.py (a sum of S products is within S * 2^-24 of its
 terms, here below 3e-5)."""
+import ctypes
+import subprocess
+
 import numpy as np
 import pytest
 import torch
 
-from tests import parity
+from tests import launches, parity
 from tests.test_gpu_parity_small import _gen, _maps, ac  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -121,3 +124,22 @@ def test_the_end_of_a_row_stays_in_its_column(ac, oracle_mod, D, bad):  # noqa: 
             assert not np.isfinite(got[..., c]).any()
             got[..., c] = want[..., c]
             assert np.abs(got - want).max() <= parity.TOL[torch.float32]
+
+
+def test_three_workgroups_of_every_reuse_kernel_fit_a_compute_unit(ac):  # noqa: F811
+    """168 vector registers a thread (of 512 per lane and SIMD, in eights) leave room for three waves on each SIMD, 53 KB
+    of LDS for three workgroups."""
+    class Attributes(ctypes.Structure):   # hipFuncAttributes
+        _fields_ = [("binary", ctypes.c_int), ("cache", ctypes.c_int), ("const", ctypes.c_size_t), ("local", ctypes.c_size_t),
+                    ("max_dynamic", ctypes.c_int), ("max_threads", ctypes.c_int), ("regs", ctypes.c_int),
+                    ("carveout", ctypes.c_int), ("ptx", ctypes.c_int), ("shared", ctypes.c_size_t)]
+    lib, seen = ctypes.CDLL(launches.LIB), 0
+    out = subprocess.run(["nm", "-D", launches.LIB], text=True, capture_output=True, check=True).stdout
+    for line in out.splitlines():
+        kind, name = line.split()[-2:]
+        if kind == "V" and "apply_f32_kernel" in name:
+            at = Attributes()
+            assert lib.hipFuncGetAttributes(ctypes.byref(at), ctypes.byref(ctypes.c_char.in_dll(lib, name))) == 0
+            assert 0 < at.regs <= 168 and at.shared <= 160 * 1024 // 3, (name, at.regs, at.shared)
+            seen += 1
+    assert seen == 10
