@@ -991,10 +991,13 @@ __device__ __forceinline__ uint64_t item_key(float s, int i) {
 
 constexpr int kCountPerDraw = 16;   // items per rank sought that are all compared with each other straight away
 constexpr int kRankMost = 384;      // items that are compared with each other after the bound has been applied
-// Up to 256 items and so few ranks: one wave draws the best again and again, without a barrier.  us per call, by bound and
-// comparison / so: 1,895 x 256, two queries, k = 2 (60 groups, 64 rows) 13.2 / 9.7; 5,000 x 256, 64 queries, k = 8 17.9 /
-// 16.6.  Not for up to four items per rank: 700 x 128, 8 queries, k = 8 (11 groups) 11.7 / 12.2.
-constexpr int kDrawRanks = 8;
+// Few ranks are drawn, the best again and again: up to eight of 256 items by one wave without a barrier, up to two of more
+// by all waves with a barrier each.  us per call, by bound and comparison / so: 1,895 x 256, two queries, k = 2 (60
+// groups, 64 rows) 13.2 / 9.7; 5,000 x 256, 64 queries, k = 8 17.9 / 16.6; 117,042 x 64, three, k = 2 (1,829 groups) 14.9 /
+// 13.6; 82,156 x 256 fp32, one, k = 2 27.6 / 26.1.  A draw costs what comparing 14 items does, and two less of them than
+// there are: 16 queries, the best 8 of 40 rows compared 5.2, drawn 6.0, of 64 5.5 / 6.0, of 128 6.4 / 6.0; the best 4 of
+// 20 5.0 / 5.0, of 64 5.5 / 5.0.
+constexpr int kDrawRanks = 8, kDrawItems = 14;
 
 // x of the lane that the DPP control names (a lane without one keeps its own).
 template <int CTRL, int ROWS = 0xf>
@@ -1034,7 +1037,7 @@ __device__ __forceinline__ uint64_t wave_best(uint64_t x) {
 // reach the bound.  Then they are counted in 256 equal ranges of keys up to the best one, which raises the bound to where
 // at most kRankMost reach it, whatever the data (the same call at k = 64 with runs of 1,000 rows alike: 58 us; k rounds of a
 // workgroup-wide arg-max 220).
-// Few items for that many ranks are compared straight away, and few ranks of few items drawn (above).
+// Few items for that many ranks are compared straight away, and few ranks drawn (above).
 // NT threads, list[NT]: the items that are ranked, before them the best item of every part or the counts, behind them
 // the best item, two numbers (items that reach the bound, and how many of them there were counted) and the bound.
 template <int NT, typename Get, typename Put>
@@ -1131,8 +1134,9 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
     }
     fetch(tid);
     best_of();
-    // parts: NT / 64 neighbouring lanes, or whole waves where there are at least two of them for every rank
-    const bool waves = 2 * k <= NT / kWave;   // uniform
+    // parts: NT / 64 neighbouring lanes, or whole waves where there are two of them for every rank and as many as ranks
+    // have items (with fewer no bound is found and all items are compared: 295 x 64 fp32, 271 queries, k = 8 27.0 / 19.9)
+    const bool waves = 2 * k <= NT / kWave && k * kWave <= n;   // uniform
     const int parts = waves ? NT / kWave : kWave;
     if (waves) {
       best = wave_best(best);
@@ -1175,24 +1179,31 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
         fetch(x0 + lane);
       }
       __syncthreads();
-      if (count <= (uint32_t)MOST) break;
+      if (__builtin_expect(count <= (uint32_t)MOST, 1)) break;
       raise();
       fetch(tid);
     }
   };
   int m = n;
-  if (k <= kDrawRanks && n <= 4 * kWave && n > 4 * k) {
-    if (wave == 0) {
+  const bool all = n > 4 * kWave;   // waves (uniform)
+  if (k <= (all ? 2 : kDrawRanks) && n <= 4 * NT && n > kDrawItems * (k - 2)) {
+    if (all || wave == 0) {
       uint64_t it[4], last = ~0ull;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) it[t] = item_at(t * kWave + lane);
+      for (int t = 0; t < 4; ++t) it[t] = item_at(t * (all ? NT : kWave) + tid);
 #pragma unroll 1
       for (int r = 0; r < k; ++r) {
         uint64_t best = 0;
 #pragma unroll
         for (int t = 0; t < 4; ++t) best = max(best, it[t] < last ? it[t] : 0);
         last = wave_best(best);
-        if (lane == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
+        if (all) {
+          if (lane == 0) list[16 * r + wave] = last;
+          __syncthreads();
+          last = list[16 * r + (lane & (NT / kWave - 1))];
+          last = NT == 1024 ? row_best(last) : quad_best(last);
+        }
+        if (tid == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
       }
     }
     __syncthreads();

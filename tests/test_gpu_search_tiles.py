@@ -219,7 +219,8 @@ def _neighbours(N, kind):
 
 @pytest.mark.parametrize("kind", ["runs", "ties", "outlier", "waves"])
 @pytest.mark.parametrize("N,E,k", [(32768, 128, 2), (5000, 128, 64), (30000, 256, 57), (100000, 64, 64), (300000, 64, 33),
-                                   (1100000, 8, 64), (1024, 64, 16)])
+                                   (1100000, 8, 64), (1024, 64, 16), (300, 64, 2), (9000, 128, 2), (70000, 128, 2),
+                                   (295, 64, 8), (20311, 128, 8), (40, 64, 8), (90, 64, 8)])
 def test_the_best_few_where_they_are_neighbours(ac, N, E, k, kind):  # noqa: F811
     """More items reach the first bound of a selection than are ranked; scores below 2^19 are exact, and so is the answer."""
     v = _neighbours(N, kind)
@@ -233,6 +234,27 @@ def test_the_best_few_where_they_are_neighbours(ac, N, E, k, kind):  # noqa: F81
     assert (score.cpu() == v[want.long()].float()).all()
 
 
+def _search_us(ac, emb, q, k):  # noqa: F811
+    """us per call of ten in a row, the best of twelve."""
+    N, B = len(emb), len(q)
+    maps, map_of = torch.zeros(1, 1, 1, 8, 8, device="cuda"), torch.zeros(N, dtype=torch.int32, device="cuda")
+    db = ac.attncache_build_db(emb, maps, n_kv_heads=1, head_dim=8, map_of=map_of)
+    ws = torch.empty(ac.attncache_workspace_bytes(db.desc, B, k), dtype=torch.uint8, device="cuda")
+    out = (torch.empty(B, k, dtype=torch.int32, device="cuda"), torch.empty(B, k, device="cuda"),
+           torch.empty(B, dtype=torch.int32, device="cuda"))
+    times = []
+    for _ in range(12):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            ac.attncache_search(db, q, k, 0.5, *out, ws)
+        b.record()
+        b.synchronize()
+        times.append(100 * a.elapsed_time(b))
+    db.close()
+    return min(times)
+
+
 @pytest.mark.parametrize("N,E", [(5000, 128), (100000, 256)])
 def test_neighbours_that_score_alike_cost_what_others_cost(ac, N, E):  # noqa: F811
     """64 queries, k = 64, rows in runs of 1,000 alike and unordered rows: 1.05 times the time at most; 2.5 to 3.8 with
@@ -241,21 +263,15 @@ def test_neighbours_that_score_alike_cost_what_others_cost(ac, N, E):  # noqa: F
     for run in (1, 1000):
         raw = torch.randn((N + run - 1) // run, E, generator=g).repeat_interleave(run, 0)[:N] + 0.1 * torch.randn(N, E, generator=g)
         emb = torch.nn.functional.normalize(raw, dim=-1).half().cuda()
-        q = emb[torch.randint(0, N, (64,), generator=g).cuda()].contiguous()
-        maps = torch.zeros(1, 1, 1, 8, 8, device="cuda")
-        db = ac.attncache_build_db(emb, maps, n_kv_heads=1, head_dim=8, map_of=torch.zeros(N, dtype=torch.int32, device="cuda"))
-        ws = torch.empty(ac.attncache_workspace_bytes(db.desc, 64, 64), dtype=torch.uint8, device="cuda")
-        out = (torch.empty(64, 64, dtype=torch.int32, device="cuda"), torch.empty(64, 64, device="cuda"),
-               torch.empty(64, dtype=torch.int32, device="cuda"))
-        times = []
-        for _ in range(12):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            for _ in range(10):
-                ac.attncache_search(db, q, 64, 0.5, *out, ws)
-            b.record()
-            b.synchronize()
-            times.append(100 * a.elapsed_time(b))
-        us.append(min(times))
-        db.close()
+        us.append(_search_us(ac, emb, emb[torch.randint(0, N, (64,), generator=g).cuda()].contiguous(), 64))
     assert us[1] <= 1.6 * us[0], us
+
+
+def test_eight_ranks_cost_no_more_than_nine(ac):  # noqa: F811
+    """Few more items than waves have lanes for: 271 queries on 295 x 64 fp32 take 19.9 and 20.9 us, with a bound that is
+    looked for in waves without items, so that all items are compared, 27.0 and 20.9."""
+    g = _gen(13)
+    emb = torch.nn.functional.normalize(torch.randn(295, 64, generator=g), dim=-1).cuda()
+    q = torch.nn.functional.normalize(torch.randn(271, 64, generator=g), dim=-1).cuda()
+    us = [_search_us(ac, emb, q, k) for k in (8, 9)]
+    assert us[0] <= 1.15 * us[1], us
