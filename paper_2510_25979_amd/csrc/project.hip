@@ -522,7 +522,7 @@ struct FusedPlan { bool fits, use; int nz, Q, rows, parts, rows2; };
 static double fused_gain(const FusedPlan& f, int32_t B, int32_t S, int32_t dm, int32_t hid, bool f32) {
   const int z = ceil_div(hid, f.rows), bytes = f32 ? 4 : 2;
   const double kilo_rows = (double)ceil_div(f.nz * ceil_div(B, f.Q) * z, 256) * f.rows / 1024;   // rows of W1 a compute unit reads
-  const double steps2 = (double)ceil_div(B * f.parts, 256) * stream_steps(4, f.rows2, hid, stream_unroll(4, f.rows2, hid));
+  const double steps2 = (double)ceil_div(B * f.parts, 256) * stream_least(4, f.rows2, hid);
   const int pools = ceil_div(dm, kWave * (f32 ? PoolVec<float>::VEC : PoolVec<bf16_t>::VEC)) * B;   // workgroups of pool_kernel
   double us = 6 - 2.6 * hid / 1024 - 1.1 * kilo_rows * f.Q;
   if (dm % 32) us -= 1.4 * kilo_rows;
@@ -536,7 +536,7 @@ static double fused_gain(const FusedPlan& f, int32_t B, int32_t S, int32_t dm, i
 static FusedPlan fused_plan(int32_t B, int32_t S, int32_t dm, int32_t hid, int32_t E, bool f32) {
   FusedPlan f = {false, false, ceil_div(dm, kFusedCols), 4, 0, 1, E};
   if (B > kFusedBatch || hid > 1024) return f;
-  const long wgs4 = (long)f.nz * ceil_div(B, 4), steps = stream_steps(4, E, hid, stream_unroll(4, E, hid));
+  const long wgs4 = (long)f.nz * ceil_div(B, 4), steps = stream_least(4, E, hid);
   if (steps > 16 || steps * B > 1024 || wgs4 > 512 || wgs4 * hid > 128 * 1024) return f;
   f.fits = true;   // (whatever the length of the sentences, which the size of the workspace does not know)
   long least = 0;

@@ -1,5 +1,7 @@
 // Rows times one vector, by one workgroup: sums over a row's columns on the vector ALUs.
 #pragma once
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ac {
@@ -126,12 +128,20 @@ inline long stream_steps(int P, int n_rows, int n_cols, int u) {
   const int rows = kStreamThreads / 8 * u, cols = 64 * P / u;
   return (((long)n_rows + rows - 1) / rows) * ((n_cols + cols - 1) / cols);
 }
-// The U of the fewest steps (of equals the most rows, whose parts are added up the fewest times).
+// The fewest that any U takes.
+inline long stream_least(int P, int n_rows, int n_cols) {
+  long least = stream_steps(P, n_rows, n_cols, 8);
+  for (int u = 4; u >= 1; u /= 2) least = std::min(least, stream_steps(P, n_rows, n_cols, u));
+  return least;
+}
+// The U of the fewest steps (of equals the most rows, whose parts are added up the fewest times).  A single row of each
+// thread is a longer step: it has to save a third of them.  Search, us with one row / more: 640 x 256 fp32 (5 / 6 steps)
+// 9.6 / 9.0, the best 4 of 300 x 512 fp16 (3 / 4) 11.2 / 9.4, 300 x 512 fp32 (6 / 8) 10.4 / 10.6, 100 x 640 fp16 (2 / 3) 6.2 / 6.7.
 inline int stream_unroll(int P, int n_rows, int n_cols) {
   int best = 8;
-  for (int u = 4; u >= 1; u /= 2)
+  for (int u = 4; u >= 2; u /= 2)
     if (stream_steps(P, n_rows, n_cols, u) < stream_steps(P, n_rows, n_cols, best)) best = u;
-  return best;
+  return 3 * stream_steps(P, n_rows, n_cols, 1) <= 2 * stream_steps(P, n_rows, n_cols, best) ? 1 : best;
 }
 
 }  // namespace ac

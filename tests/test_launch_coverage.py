@@ -94,6 +94,12 @@ def test_every_projector_kernel_is_reached(tmp_path):
     ((20000, 20, 8, 1, "f32", "ip"), "search_row_kernel<float"),
     ((20000, 37, 8, 1, "f32", "ip"), "search_stream_kernel<float, false, 4"),
     ((100000, 128, 64, 1, "f32", "l2"), "search_valu_kernel<float, true, 4"),
+    ((640, 256, 4, 1, "f32", "ip"), "search_small_kernel<float, false, false, 2"),   # one row of a thread 9.6, two 9.0
+    ((300, 512, 4, 4, "f16", "ip"), "search_small_kernel<half, false, true, 4"),     # 11.2, four 9.4
+    ((100, 640, 16, 1, "f16", "ip"), "search_small_kernel<half, false, false, 1"),   # 6.2, 6.7
+    ((2000, 15, 4, 1, "f32", "ip"), "search_row_kernel<float"),                      # 6.7 in one launch, 5.6
+    ((2000, 16, 4, 1, "f32", "ip"), "search_small_kernel<float"),                    # 4.8, 5.3
+    ((250, 8, 4, 1, "f16", "l2"), "search_row_kernel<half"),                         # 5.2, 5.0
 ], ids=str)
 def test_the_kernel_that_measured_best_serves_the_shape(tmp_path, case, kernel):
     (status, ls), = launches.record([("search", *case)], tmp_path)
