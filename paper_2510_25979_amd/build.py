@@ -1,6 +1,7 @@
 """Build libattncache.so (HIP, gfx950 only) and the binding's tensor check in-tree next to the sources."""
 import os
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -17,11 +18,16 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno
          "-Wno-unused-command-line-argument", "-Wl,-z,defs"]
 
 
+def _older(out, sources) -> bool:
+    return not os.path.exists(out) or any(os.path.getmtime(os.path.join(CSRC, f)) > os.path.getmtime(out) for f in sources)
+
+
 def stale() -> bool:
-    def older(out, sources):
-        return not os.path.exists(out) or any(os.path.getmtime(os.path.join(CSRC, f)) > os.path.getmtime(out)
-                                              for f in sources)
-    return older(LIB, SOURCES + HEADERS) or older(ARG, [ARG_SOURCE])
+    return _older(LIB, SOURCES + HEADERS) or _older(ARG, [ARG_SOURCE])
+
+
+def _lib_command():
+    return ["hipcc"] + FLAGS + [os.path.join(CSRC, f) for f in SOURCES] + ["-o", LIB]
 
 
 def _arg_command():
@@ -34,18 +40,34 @@ def _arg_command():
             [os.path.join(CSRC, ARG_SOURCE), f"-L{torch_lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", ARG])
 
 
+def _build_arg(verbose: bool) -> None:
+    """The tensor check needs torch's headers, Python's and g++; the library needs none of them, and the binding does
+    without the check (slower), so a machine that lacks one is told so and gets the library all the same."""
+    try:
+        cmd = _arg_command()
+        if verbose:
+            print(" ".join(cmd))
+        subprocess.run(cmd, check=True)
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(ARG):   # one of other sources
+            os.remove(ARG)
+        print(f"{os.path.basename(ARG)} is not built ({e}): tensor arguments are checked in Python", file=sys.stderr)
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    if not force and not stale():
-        return LIB
-    commands = [["hipcc"] + FLAGS + [os.path.join(CSRC, f) for f in SOURCES] + ["-o", LIB], _arg_command()]
-    if verbose:
-        for c in commands:
-            print(" ".join(c))
-    running = [subprocess.Popen(c) for c in commands]
-    codes = [p.wait() for p in running]
-    for c, code in zip(commands, codes):
-        if code:
-            raise subprocess.CalledProcessError(code, c)
+    lib = None
+    if force or _older(LIB, SOURCES + HEADERS):
+        cmd = _lib_command()
+        if verbose:
+            print(" ".join(cmd))
+        lib = subprocess.Popen(cmd)
+    try:
+        if force or _older(ARG, [ARG_SOURCE]):
+            _build_arg(verbose)
+    finally:
+        code = lib.wait() if lib else 0
+    if code:
+        raise subprocess.CalledProcessError(code, cmd)
     return LIB
 
 
