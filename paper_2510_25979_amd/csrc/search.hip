@@ -1555,10 +1555,11 @@ static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
 //                        512: 8 steps 12.3 / 10.8
 //   fp16 inner, k = 1    128 columns: 2 steps 6.3 / 4.8, 4 steps 6.4 / 7.1; 256: 4 steps 7.7 / 7.0; 512: 8 steps 10.6 / 10.8
 //   fp16 Euclidean, k = 1   128 columns: 2 steps 6.15 / 6.1, 4 steps 6.1 / 9.6; 512: 2 steps 8.8 / 6.3, 4 steps 8.9 / 9.9
-//   short rows, k = 1    2,000 x 15 fp32 (whose rows end in part of a piece) 5.6 / 6.7, 2,000 x 16 5.3 / 4.8, 250 x 8 fp16
-//                        Euclidean 5.0 / 5.2, 250 x 16 5.0 / 4.6
+//   short rows, k = 1    2,000 x 15 fp32 (whose rows end in part of a piece) 5.6 / 6.7, 64 queries 6.2 / 7.2, 179 on
+//                        1,644 x 22 9.4 / 7.6; 2,000 x 16 5.3 / 4.8; 250 x 8 fp16 Euclidean 5.0 / 5.2, 250 x 16 5.0 / 4.6
 //   fp16 inner, k = 8    128 columns: 2 steps 11.2 / 6.8, 8 steps 12.2 / 13.0; 512: 8 steps 17.6 / 12.8
-// More queries than compute units take a second round here, and the matrix cores more queries at a time: 4,096 queries,
+// The lines hold for one query to 256: of 3,605 drawn calls that they send here six take more than 1.02 times the two
+// launches' time, 1.06 at most, and all together 0.56.  More queries than compute units take a second round here, and the matrix cores more queries at a time: 4,096 queries,
 // 96 x 825 fp16 15.0 / 61.7.
 static bool search_small(bool f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
   if (B > kSmallBatch) return false;
@@ -1568,7 +1569,7 @@ static bool search_small(bool f16, int32_t metric, int32_t E, int32_t B, int32_t
     const long limit = !f16 ? 3 + E / 64 : (metric ? 1 : 2) + (E < 96 ? 0 : 1 + E / 192);
     return steps <= (limit < 8 ? limit : 8);
   }
-  if (!f16) return steps <= (E < 32 && E % 4 ? 1 : E < 384 ? 2 + E / 64 : 8);
+  if (!f16) return steps <= (E < 32 && E % 4 && B <= 64 ? 1 : E < 384 ? 2 + E / 64 : 8);
   if (metric && E < 16) return false;
   const int limit = metric ? 1 + (E + 128) / 256 : E < 256 ? 2 : 4;
   return steps <= (limit < 4 ? limit : 4);

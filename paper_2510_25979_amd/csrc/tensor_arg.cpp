@@ -1,7 +1,7 @@
 // What the ctypes binding asks of every tensor argument, in one native call: is it a plain GPU tensor,
 // contiguous, of the expected type and shape, and where does it start?  In Python these are six attribute look-ups and
-// two tuples, 0.5 us a tensor and half of what a call of the library costs on the host (attention_exact with five
-// tensors: 7.3 us a call so far, 5.9 us so).
+// two tuples, 0.5 us a tensor (0.1 here).  attention_exact with five tensors takes 5.2 us of the host's time a call, 7.0 to
+// 8.1 in Python; that is what small calls cost, and nothing where the kernel takes longer (64 x 12 heads of 64 x 64: 7.6 either way).
 //
 // Only the answer "yes" is given here.  Anything else -- a subclass, a tensor without storage, a wrong shape -- is None,
 // and the Python code behind it decides and says what is wrong.

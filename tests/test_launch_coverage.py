@@ -99,6 +99,7 @@ def test_every_projector_kernel_is_reached(tmp_path):
     ((100, 640, 16, 1, "f16", "ip"), "search_small_kernel<half, false, false, 1"),   # 6.2, 6.7
     ((2000, 15, 4, 1, "f32", "ip"), "search_row_kernel<float"),                      # 6.7 in one launch, 5.6
     ((2000, 16, 4, 1, "f32", "ip"), "search_small_kernel<float"),                    # 4.8, 5.3
+    ((1644, 22, 179, 1, "f32", "ip"), "search_small_kernel<float"),                  # 7.6, 9.4
     ((250, 8, 4, 1, "f16", "l2"), "search_row_kernel<half"),                         # 5.2, 5.0
 ], ids=str)
 def test_the_kernel_that_measured_best_serves_the_shape(tmp_path, case, kernel):
