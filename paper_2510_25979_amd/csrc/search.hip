@@ -1179,33 +1179,41 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
         fetch(x0 + lane);
       }
       __syncthreads();
-      if (__builtin_expect(count <= (uint32_t)MOST, 1)) break;
+      // (256 threads select among up to 1,024 items with k <= 8 or among 256: k of 64 parts hold at most 128)
+      if (NT == 256 || __builtin_expect(count <= (uint32_t)MOST, 1)) break;
       raise();
       fetch(tid);
     }
   };
   int m = n;
-  const bool all = n > 4 * kWave;   // waves (uniform)
-  if (k <= (all ? 2 : kDrawRanks) && n <= 4 * NT && n > kDrawItems * (k - 2)) {
-    if (all || wave == 0) {
-      uint64_t it[4], last = ~0ull;
+  const bool many = n > 4 * kWave;   // uniform
+  auto draw = [&](auto all_waves) {
+    const bool all = all_waves;
+    if (!all && wave != 0) return;
+    uint64_t it[4], last = ~0ull;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) it[t] = item_at(t * (all ? NT : kWave) + tid);
+    for (int t = 0; t < 4; ++t) it[t] = item_at(t * (all ? NT : kWave) + tid);
 #pragma unroll 1
-      for (int r = 0; r < k; ++r) {
-        uint64_t best = 0;
+    for (int r = 0; r < k; ++r) {
+      uint64_t best = 0;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) best = max(best, it[t] < last ? it[t] : 0);
-        last = wave_best(best);
-        if (all) {
-          if (lane == 0) list[16 * r + wave] = last;
-          __syncthreads();
-          last = list[16 * r + (lane & (NT / kWave - 1))];
-          last = NT == 1024 ? row_best(last) : quad_best(last);
-        }
-        if (tid == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
+      for (int t = 0; t < 4; ++t) best = max(best, it[t] < last ? it[t] : 0);
+      last = wave_best(best);
+      if (all) {
+        if (lane == 0) list[16 * r + wave] = last;
+        __syncthreads();
+        last = list[16 * r + (lane & (NT / kWave - 1))];
+        last = NT == 1024 ? row_best(last) : quad_best(last);
       }
+      if (tid == 0) put(r, last ? key_score((uint32_t)(last >> 32)) : -INFINITY, last ? (int)~(uint32_t)last : kIdxNone);
     }
+  };
+  if (k <= (many ? 2 : kDrawRanks) && n <= 4 * NT && n > kDrawItems * (k - 2)) {
+    // One loop for both, or two: 3,000 x 128, 64 queries, k = 8 14.1 / 13.7 us (256 threads), but the second loop's code costs
+    // every larger call, 100,000 x 256, k = 8 24.1 / 24.3 (1,024 threads).
+    if (NT > 256) draw(many);
+    else if (many) draw(std::true_type{});
+    else draw(std::false_type{});
     __syncthreads();
     return;
   }

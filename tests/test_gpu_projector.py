@@ -223,6 +223,7 @@ def test_a_workspace_for_four_launches_takes_four(ac, oracle_mod, B, S, dm, hid,
     assert (ws[least:] == 0xA5).all()
     with pytest.raises(ac.AttnCacheError) as e:
         ac.attncache_project(*(t.cuda() for t in x), feat, ws[:least - 16])
+    assert e.value.status == -6
 
 
 def test_infinite_weights_of_the_last_columns_stay_where_they_are(ac, oracle_mod):

@@ -131,6 +131,26 @@ def test_the_projector_takes_the_launches_that_measured_best(tmp_path, case, lau
     assert status == 0 and len(ls) == launched, ls
 
 
+@pytest.mark.parametrize("case", [(64, 20, 2048, 512, 256), (12, 9, 4096, 1024, 256)], ids=str)
+def test_a_workspace_for_four_launches_takes_four(tmp_path, case):
+    B, S, dm, hid, E = case
+    least = 4 * B * (dm + 4 * hid + 4 * E)   # the pooled input and four partial results of each layer
+    calls = [("project", *case, "bf16", "f32", True, *ws) for ws in ((), (least,), (least - 16,))]
+    (_, few), (status, four), (refused, none) = launches.record(calls, tmp_path)
+    assert len(few) < 4 and status == 0 and len(four) == 4 and refused == -6 and not none
+
+
+@pytest.mark.parametrize("dt,metric", [("f16", "ip"), ("f16", "l2"), ("f32", "ip")])
+def test_selections_of_256_threads_are_small(tmp_path, dt, metric):
+    """What lets them do without a bound that rises: no more than 1,024 groups, of 32 rows at least, of which 256 rows are no
+    more than eight."""
+    calls = [("search", N, E, 300, min(k, N), dt, metric) for N in (200, 250, 257, 513, 4096, 32768, 32769, 65536, 65600)
+             for E in (40, 64, 256) for k in (2, 3, 4, 8, 9, 16, 64)]
+    for call, (status, ls) in zip(calls, launches.record(calls, tmp_path)):
+        small = any(la[0].startswith("finalize_topk_kernel") and ", 256, " in la[0] for la in ls)
+        assert status == 0 and (not small or call[4] <= 8 or call[1] <= 256), call
+
+
 def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
     """Where the launches depend on the sentences' length, the workspace, which does not know it, is enough for the fewest."""
     import ctypes
