@@ -15,7 +15,8 @@
 //     those k groups are re-scored row by row and the k best rows selected.
 //     Groups are contiguous and ascend, so among equal maxima the lower group
 //     number stands for the lower row and only the score has to be kept.
-// fp32 databases (and the L2 metric) use a vector-ALU phase 1 of the same shape.
+// fp32 databases (and the L2 metric) use a vector-ALU phase 1 of the same shape, or, for more work, matrix-core
+// bounds that tell which rows have to be scored (search_bound_kernel).
 // Both phases are one launch, a workgroup per query, for databases of some 100 KB to 1 MB (search_small).
 #include <type_traits>
 
@@ -30,6 +31,7 @@ constexpr int kValuRowsPerWg = 256;
 constexpr int kNarrowBytes = 160;   // widest rows of search_row_kernel
 constexpr int kIdxNone = 0x7fffffff;
 constexpr int kMaxK = 64;           // AC_MAX_K of the C interface
+constexpr int kUnsure = -2;         // idx[b][0] between two launches: what the bounds leave open is searched row by row
 // Maximum of a group (k > 1) in which no row ranks, every score being NaN.  -infinity is a score like
 // any other: a group that holds one comes before a group that holds none.  (Rows past the end count as
 // -infinity: they are in the last group only, which no other group has to come after.)
@@ -47,6 +49,7 @@ struct SearchArgs {
   float* part_s;           // [B][G] best score of each group (k > 1: kNoRow where no row ranks)
   int32_t* part_i;         // [B][G] its row (k = 1 only)
   float* cand;             // [B][k * rows] scores of the selected groups' rows (k > 1 only)
+  int32_t* unsure;         // 1 where a query is left open: the launches that get it search those with idx[b][0] == kUnsure
   int32_t* idx;
   float* score;
   int32_t* hit;
@@ -707,16 +710,16 @@ struct TileSlice {
 };
 
 template <typename T, bool L2, int QW, bool TOPK>
-__global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs a) {
+__device__ __forceinline__ void search_valu_tile(const SearchArgs& a, int tile, int nqb, float* el, float* ql) {
   constexpr int R = kValuRowsPerWg / kWave;   // rows of a lane
-  __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
-  __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];   // 4 QW <= 32 rows used
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the query blocks of one group get ids equal mod 8: one XCD reads the group's rows once
-  const int nqb = (a.nq + 4 * QW - 1) / (4 * QW), slot = blockIdx.x >> 3;
-  const int gidx = slot / nqb * 8 + (blockIdx.x & 7), q0 = a.q0 + slot % nqb * (4 * QW);
+  const int slot = tile >> 3;
+  const int gidx = slot / nqb * 8 + (tile & 7), q0 = a.q0 + slot % nqb * (4 * QW);
   if (gidx >= (a.N + kValuRowsPerWg - 1) / kValuRowsPerWg) return;
+  const int q_end = min(a.q0 + a.nq, q0 + 4 * QW);
+  if (a.unsure && !__ballot(lane < q_end - q0 && a.idx[(size_t)(q0 + lane) * a.k] == kUnsure)) return;   // the same for all waves
   const T* emb = reinterpret_cast<const T*>(a.emb);
   const T* qs = reinterpret_cast<const T*>(a.q);
   const int row0 = gidx * kValuRowsPerWg;
@@ -728,7 +731,6 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
     for (int j = 0; j < QW; ++j) acc[r][j] = 0.f;
   TileSlice<T, kValuRowsPerWg * 8 / kThreads> es;
   TileSlice<T, 1> qt;
-  const int q_end = min(a.q0 + a.nq, q0 + 4 * QW);
   es.load(emb, row0, a.N, a.E, 0, tid);
   qt.load(qs, q0, q_end, a.E, 0, tid);
   for (int e0 = 0; e0 < a.E; e0 += kTileCols) {
@@ -803,7 +805,262 @@ __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs 
   }
 }
 
+template <typename T, bool L2, int QW, bool TOPK>
+__global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs a) {
+  __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
+  __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];   // 4 QW <= 32 rows used
+  if (a.unsure && *a.unsure == 0) return;   // the usual case there, with a grid that is quickly through
+  const int nqb = (a.nq + 4 * QW - 1) / (4 * QW);
+  const unsigned tiles = ((unsigned)a.N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * nqb;
+  for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) search_valu_tile<T, L2, QW, TOPK>(a, tile, nqb, el, ql);
+}
+
+// ---------------------------------------------------------------- phase 1, bounds from the matrix cores
+// Binary32 inner products and Euclidean distances of a larger search: the tiles above are bound by the vector ALUs (two
+// instructions per element of q - e), a contraction on the matrix cores would lose digits where it cancels.  So the matrix
+// cores only say which rows can be among the best: for every (query, group) this kernel writes an upper bound of the score
+// that the vector ALUs would compute, less the query's own part, and the second phase scores the rows of the groups with the
+// best bounds exactly, then those of every other group whose bound reaches the k-th best score found (finalize_bounds_kernel).
+//   bound[q][g] = max over the rows e of g of  2 <q, e> - (1 - c) |e|^2   (Euclidean)   or   <q, e> + c/2 |e|^2   (inner product);
+// with (c - 1) |q|^2 or c/2 |q|^2 added no row's computed score lies above it.  Values of a magnitude for
+// which this does not hold, and NaN, become +infinity: the group is scored.
+// c, relative to (|q|^2 + |e|^2) >= 2 |q| |e| >= 2 sum |q_i e_i|: a binary32 value is taken as the sum of two bf16 (rest 2^-18 of it)
+// and the product of the two low parts is left out: 3 * 2^-18 |q| |e|; each of at most 3 (E + 15) additions on the matrix cores
+// costs no more than 2^-23 of the sum of magnitudes; |e|^2, in E / 2 steps, E 2^-25 of itself; the exact scores, |q|^2 and the last
+// few steps (E + 4) 2^-23: together below 2^-16 + (E + 16) 2^-20.
+// The rows are read once for 32 NQB queries, straight into registers as the row-stationary kernel reads them.
+__host__ __device__ inline float bound_slack(int E) { return 0x1p-16f + (float)(E + 16) * 0x1p-20f; }
+constexpr float kBoundMost = 0x1p100f;   // larger magnitudes of a bound, or of its parts, are not relied on
+constexpr float kBoundLeast = 0x1p-90f;  // what products lost below the smallest normal numbers add up to, at most
+
+template <typename T> struct BoundParts;   // eight columns of a row or query as operands of the matrix cores
+template <>
+struct BoundParts<float> {
+  static constexpr int N = 2;
+  typedef bf16x8 op;
+  op p[2];
+  // (the low part is what the 16 bits kept above leave: the difference is exact)
+  __device__ __forceinline__ void set(const f32x4& a, const f32x4& b) {
+    u32x4 high, low;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float x = t < 2 ? a[2 * t] : b[2 * t - 4], y = t < 2 ? a[2 * t + 1] : b[2 * t - 3];
+      high[t] = pack_bf16(x, y);
+      low[t] = pack_bf16(x - __builtin_bit_cast(float, high[t] << 16), y - __builtin_bit_cast(float, high[t] & 0xffff0000u));
+    }
+    p[0] = __builtin_bit_cast(bf16x8, high);
+    p[1] = __builtin_bit_cast(bf16x8, low);
+  }
+  static __device__ __forceinline__ f32x16 product(const BoundParts& e, const BoundParts& q, f32x16 acc) {
+    acc = mfma_bf16(e.p[0], q.p[0], acc);
+    acc = mfma_bf16(e.p[1], q.p[0], acc);
+    return mfma_bf16(e.p[0], q.p[1], acc);
+  }
+};
+template <>
+struct BoundParts<f16_t> {
+  static constexpr int N = 1;
+  typedef f16x8 op;
+  op p[1];
+  static __device__ __forceinline__ f32x16 product(const BoundParts& e, const BoundParts& q, f32x16 acc) {
+    return mfma_f16(e.p[0], q.p[0], acc);
+  }
+};
+
+// Columns of a step of 16 that a lane of half kh holds, as they come from memory: fp16 columns 8 kh .. + 8, fp32 columns
+// 4 kh .. + 4 and 8 + 4 kh .. + 4, so that the two lanes of a row read neighbouring 16-byte pieces.  Zeros past E.
+template <typename T> struct BoundPiece;
+template <>
+struct BoundPiece<float> {
+  f32x4 a, b;
+  __device__ __forceinline__ void load(const float* row, int c0, int kh, int E, bool whole) {
+    typedef f32x4 f32x4_dw __attribute__((aligned(4)));
+    const int c = c0 + 4 * kh;
+    if (whole) {
+      a = *reinterpret_cast<const f32x4_dw*>(row + c);
+      b = *reinterpret_cast<const f32x4_dw*>(row + c + 8);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        a[t] = c + t < E ? row[c + t] : 0.f;
+        b[t] = c + 8 + t < E ? row[c + 8 + t] : 0.f;
+      }
+    }
+  }
+  __device__ __forceinline__ void parts(BoundParts<float>& p) const { p.set(a, b); }
+  __device__ __forceinline__ float squares(float s) const {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) s = fmaf(a[t], a[t], fmaf(b[t], b[t], s));
+    return s;
+  }
+};
+template <>
+struct BoundPiece<f16_t> {
+  f16x8 a;
+  __device__ __forceinline__ void load(const f16_t* row, int c0, int kh, int E, bool whole) {
+    if (whole || c0 + 8 * kh < E) {   // (E % 8 == 0)
+      a = *reinterpret_cast<const f16x8*>(row + c0 + 8 * kh);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) a[t] = (f16_t)0.f;
+    }
+  }
+  __device__ __forceinline__ void parts(BoundParts<f16_t>& p) const { p.p[0] = a; }
+  __device__ __forceinline__ float squares(float s) const {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s = fmaf((float)a[t], (float)a[t], s);
+    return s;
+  }
+};
+
+template <typename T, bool L2, int NQB>
+__global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs a) {
+  typedef BoundParts<T> Parts;
+  typedef BoundPiece<T> Piece;
+  typedef typename Parts::op op;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int E = a.E, nks = (E + 15) >> 4, QS = 16 * nks + kQPad;   // 16-bit elements of a staged query
+  uint16_t* qs = reinterpret_cast<uint16_t*>(smem);                // [Parts::N][32 NQB][QS]
+  float* red = reinterpret_cast<float*>(qs + (size_t)Parts::N * 32 * NQB * QS);   // [4][32 NQB]
+  float* own = red + 4 * 32 * NQB;                                                // [4][32]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31, kh = lane >> 5;
+  const int q0 = 32 * NQB * blockIdx.y, nq = min(a.B - q0, 32 * NQB);
+  const T* emb = reinterpret_cast<const T*>(a.emb);
+  const int row_begin = blockIdx.x * a.wg_rows, row_end = min(row_begin + a.wg_rows, a.N);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *a.unsure = 0;
+
+  struct Four { Piece p[4]; };
+  auto fetch = [&](const T* row, int ks0) {   // steps past the end repeat the last one, their products are skipped
+    Four f;
+    if (16 * (ks0 + 4) <= E) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) f.p[t].load(row, 16 * (ks0 + t), kh, E, true);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int c = 16 * min(ks0 + t, nks - 1);
+        f.p[t].load(row, c, kh, E, c + 16 <= E);
+      }
+    }
+    return f;
+  };
+  auto row_of = [&](int pass) { return emb + (size_t)min(pass + 32 * wave + il, a.N - 1) * E; };   // past the end: the last row again
+  const T* row = row_of(row_begin);
+  Four now = fetch(row, 0);   // on its way while the queries are staged
+
+  // eight threads a query; a thread's pieces of all query blocks are in flight together
+#pragma unroll 2
+  for (int c = tid & 7; c < 2 * nks; c += 8) {   // half step
+    Piece w[NQB];
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+      w[qb].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + min(32 * qb + (tid >> 3), nq - 1)) * E, 16 * (c >> 1), c & 1, E,
+                 16 * (c >> 1) + 16 <= E);
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      Parts p;
+      w[qb].parts(p);
+#pragma unroll
+      for (int n = 0; n < Parts::N; ++n)
+        *reinterpret_cast<op*>(qs + (size_t)(32 * NQB * n + 32 * qb + (tid >> 3)) * QS + 8 * c) = p.p[n];
+    }
+  }
+  __syncthreads();
+
+  for (int pass = row_begin; pass < row_end; pass += 128) {   // the same trips for all four waves
+    const int rb = pass + 32 * wave;
+    const bool more = pass + 128 < row_end;
+    const T* next_row = row_of(more ? pass + 128 : pass);
+    f32x16 acc[NQB];
+    float sq = 0.f;
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[qb][v] = 0.f;
+    auto step = [&](const Piece& piece, int ks) {
+      Parts e;
+      piece.parts(e);
+      sq = piece.squares(sq);
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) {
+        Parts q;
+#pragma unroll
+        for (int n = 0; n < Parts::N; ++n)
+          q.p[n] = *reinterpret_cast<const op*>(qs + (size_t)(32 * NQB * n + 32 * qb + il) * QS + 16 * ks + 8 * kh);
+        acc[qb] = Parts::product(e, q, acc[qb]);
+      }
+    };
+    int ks0 = 0;
+    for (; ks0 + 4 <= nks; ks0 += 4) {
+      const bool last = ks0 + 4 >= nks;
+      Four next;
+      if (!last || more) next = fetch(last ? next_row : row, last ? 0 : ks0 + 4);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) step(now.p[t], ks0 + t);
+      now = next;
+    }
+    if (ks0 < nks) {
+      Four next;
+      if (more) next = fetch(next_row, 0);
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        if (ks0 + t < nks) step(now.p[t], ks0 + t);
+      now = next;
+    }
+    row = next_row;
+    // acc[qb][v] = <emb[rb + mfma_row(v)], q[32 qb + il]>; lane il has half of that row's |e|^2.  Where all squares stay below
+    // kBoundMost so do the products; a block with a row where they don't is scored whatever its other rows are.
+    sq += __shfl_xor(sq, 32);
+    const bool all = __ballot(!(sq < kBoundMost)) != 0;
+    const float c = L2 ? bound_slack(E) - 1.f : 0.5f * bound_slack(E);
+    if (kh == 0) own[32 * wave + il] = c * sq;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    f32x4 part[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[v] = *reinterpret_cast<const f32x4*>(own + 32 * wave + mfma_row(4 * v, kh));
+    const bool per_wave = a.rows == 32;   // a wave's 32 rows are a group
+    const int gi = (per_wave ? rb : pass) / a.rows;
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+      float best = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float w = part[v >> 2][v & 3];
+        best = fmaxf(best, L2 ? fmaf(2.f, acc[qb][v], w) : acc[qb][v] + w);
+      }
+      const float s = all ? INFINITY : max_with_other_half(best);
+      const int t = 32 * qb + il;
+      if (!per_wave) {
+        if (kh == 0) red[wave * 32 * NQB + t] = s;
+      } else if (kh == 0 && t < nq && rb < a.N) {
+        a.part_s[(size_t)(q0 + t) * a.G + gi] = s;
+      }
+    }
+    if (!per_wave) {
+      __syncthreads();
+      if (a.rows == 64) {
+        for (int x = tid; x < 2 * 32 * NQB; x += kThreads) {
+          const int t = x % (32 * NQB), half = x / (32 * NQB), first = pass + 64 * half;
+          if (t < nq && first < a.N)
+            a.part_s[(size_t)(q0 + t) * a.G + first / 64] = fmaxf(red[64 * NQB * half + t], red[64 * NQB * half + 32 * NQB + t]);
+        }
+      } else {
+        for (int t = tid; t < nq; t += kThreads)
+          a.part_s[(size_t)(q0 + t) * a.G + gi] =
+              fmaxf(fmaxf(red[t], red[32 * NQB + t]), fmaxf(red[64 * NQB + t], red[96 * NQB + t]));
+      }
+      __syncthreads();
+    }
+  }
+}
+
 constexpr size_t kGridThreads = ((size_t)1 << 32) - 1;   // most threads of a launch in one dimension
+
+constexpr size_t kUnsureTiles = 768;   // three workgroups a compute unit, as many as its LDS holds
 
 template <typename T, bool L2, int QW, bool TOPK>
 static hipError_t launch_tiles(SearchArgs a, size_t groups8, hipStream_t stream) {
@@ -813,8 +1070,9 @@ static hipError_t launch_tiles(SearchArgs a, size_t groups8, hipStream_t stream)
   for (size_t q0 = 0; q0 < (size_t)a.B; q0 += fit) {
     a.q0 = (int32_t)q0;
     a.nq = (int32_t)((size_t)a.B - q0 < fit ? (size_t)a.B - q0 : fit);
-    const size_t blocks = (size_t)((a.nq + 4 * QW - 1) / (4 * QW));
-    hipLaunchKernelGGL((search_valu_kernel<T, L2, QW, TOPK>), dim3((unsigned)(groups8 * blocks)), dim3(kThreads), 0, stream, a);
+    size_t tiles = groups8 * ((a.nq + 4 * QW - 1) / (4 * QW));
+    if (a.unsure && tiles > kUnsureTiles) tiles = kUnsureTiles;
+    hipLaunchKernelGGL((search_valu_kernel<T, L2, QW, TOPK>), dim3((unsigned)tiles), dim3(kThreads), 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -925,6 +1183,7 @@ __global__ __launch_bounds__(kThreads) void finalize_top1_kernel(const SearchArg
   __shared__ float red_s[4];
   __shared__ int red_i[4];
   const int b = blockIdx.x;
+  if (a.unsure && (*a.unsure == 0 || a.idx[b] != kUnsure)) return;
   float s = -INFINITY;
   int i = kIdxNone;
   for (int gi = threadIdx.x; gi < a.G; gi += kThreads) {
@@ -1227,14 +1486,20 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
   rank(m);
 }
 
+constexpr int kMoreGroups = 64;
+constexpr size_t kMoreBytes = 2 << 20;   // some 25 us of one compute unit, half of what the tiles take for 16 queries
 // k > 1: pick the k best groups, re-score their rows, pick the k best rows.  One workgroup per
 // query.  Rows are re-scored by eight threads each, reading 16-byte pieces side by side, four rows
 // in flight per thread.  100,000 x 256, 64 queries, k = 8: 70 us with 256-row groups, a row per
 // thread read two bytes at a time, and k rounds of a workgroup-wide arg-max; 10 us so.  Bound by the serial
 // chain of a selection among 1,563 groups, 512 rows (260 KB through one compute unit's 64 bytes per clock) and
 // a selection among those, on as many compute units as queries.
-template <typename T, int NT, bool L2>
-__global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {
+// BOUNDS: the groups' values are those of search_bound_kernel.  The groups with the best bounds are scored, usually holding
+// the answer: then no other group's bound reaches the k-th best score found, and that is all.  Groups whose bound does are scored
+// as well, while they are few; of a query with more of them (rows alike by the thousand, or values so far from the origin that
+// the bounds say nothing) idx[b][0] is set to kUnsure, and the two launches that follow search it on the vector ALUs.
+template <typename T, int NT, bool L2, bool BOUNDS>
+__global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {   // (rows that fit in LDS, or 0)
   typedef RowPiece<T> Piece;
   constexpr int P = Piece::P, RPT = NT / 8;   // rows per step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1243,6 +1508,10 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
   float* qf = reinterpret_cast<float*>(sel + kMaxK);          // [E rounded up to 4]
   const int b = a.q0 + blockIdx.x, tid = threadIdx.x;
   float* cand = cand_in_lds ? qf + ((a.E + 3) & ~3) : a.cand + (size_t)b * a.k * a.rows;
+  __shared__ uint64_t found[BOUNDS ? kMaxK : 1];    // the best so far
+  __shared__ int more[BOUNDS ? kMoreGroups : 1];    // groups still to be scored
+  __shared__ int n_more;
+  if (!BOUNDS && a.unsure && (*a.unsure == 0 || a.idx[(size_t)b * a.k] != kUnsure)) return;
   const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
   for (int e = tid; e < ((a.E + 3) & ~3); e += NT) qf[e] = e < a.E ? (float)q[e] : 0.f;
 
@@ -1253,7 +1522,8 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
       a.G, ng, [&](int x) { return item_key(part[x], x); }, [&](int r, float, int i) { sel[r] = i; }, lists);
 
   // 2. the scores of their rows
-  const int n_rows = ng * a.rows, shift = __builtin_ctz(a.rows);   // group sizes are powers of two
+  const int shift = __builtin_ctz(a.rows);   // group sizes are powers of two
+  int n_rows = ng * a.rows;
   const int part8 = tid & 7;
   // (the last RPT rows or fewer alone: the other three of every thread would be repeats.  The large form
   // does without this and with less unrolling above: every call pays for the code it brings in, 0.3 us of 32
@@ -1300,25 +1570,168 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
         cand[slot0 + u * RPT] = live[u] ? acc[u] : __builtin_nanf("");   // never ranks
     }
   };
-  for (int first = 0; first < n_rows; first += 4 * RPT) {
-    if (NT > 256 || n_rows - first > RPT) score_rows(std::integral_constant<int, 4>{}, first + (tid >> 3));
-    else score_rows(std::integral_constant<int, 1>{}, first + (tid >> 3));
-  }
-  __syncthreads();
+  auto score_all = [&] {
+    for (int first = 0; first < n_rows; first += 4 * RPT) {
+      if ((NT > 256 && !BOUNDS) || n_rows - first > RPT) score_rows(std::integral_constant<int, 4>{}, first + (tid >> 3));
+      else score_rows(std::integral_constant<int, 1>{}, first + (tid >> 3));
+    }
+    __syncthreads();
+  };
+  auto item = [&](int x) {
+    const float s = cand[x];
+    return s == s ? item_key(s, (sel[x >> shift] << shift) + (x & (a.rows - 1))) : 0;
+  };
+  auto write = [&](int r, float s, int i) {
+    a.idx[(size_t)b * a.k + r] = i == kIdxNone ? -1 : i;
+    a.score[(size_t)b * a.k + r] = s;
+    if (r == 0) write_hit(a, b, s, i);
+  };
 
   // 3. the k best rows among them
-  select_best<NT>(
-      n_rows, a.k,
-      [&](int x) {
-        const float s = cand[x];
-        return s == s ? item_key(s, (sel[x >> shift] << shift) + (x & (a.rows - 1))) : 0;
-      },
-      [&](int r, float s, int i) {
-        a.idx[(size_t)b * a.k + r] = i == kIdxNone ? -1 : i;
-        a.score[(size_t)b * a.k + r] = s;
-        if (r == 0) write_hit(a, b, s, i);
-      },
-      lists);
+  if (!BOUNDS) {
+    score_all();
+    select_best<NT>(n_rows, a.k, item, write, lists);
+    return;
+  }
+  int had = 0, done = 0, many = 0;   // best rows in found; groups of `more` scored, of how many
+  const int g_last = min(sel[ng - 1], a.G - 1);
+  const uint64_t last = item_key(part[g_last], g_last);   // of the groups scored first
+  do {
+    score_all();
+    select_best<NT>(
+        n_rows + had, a.k, [&](int x) { return x < n_rows ? item(x) : found[x - n_rows]; },
+        [&](int r, float s, int i) { found[r] = i == kIdxNone ? 0 : item_key(s, i); }, lists);
+    __syncthreads();
+    if (had == 0) {   // 4. the groups that may hold a better row than the last of them
+      had = a.k;
+      float qq = 0.f;
+      for (int e = tid & 63; e < a.E; e += kWave) qq = fmaf(qf[e], qf[e], qq);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) qq += __shfl_xor(qq, off);
+      const uint64_t kth = found[a.k - 1];
+      const float c = bound_slack(a.E), s = key_score((uint32_t)(kth >> 32));
+      float reach = s - 0x1p-20f * fabsf(s) + (L2 ? (1.f - c) * qq : -0.5f * c * qq) - kBoundLeast;
+      if (kth == 0 || !(qq < kBoundMost) || !(reach > -kBoundMost)) reach = -INFINITY;   // every one
+      if (tid == 0) n_more = 0;
+      __syncthreads();
+      for (int x = tid; x < a.G; x += NT)
+        if (part[x] >= reach && item_key(part[x], x) < last) {
+          const int at = atomicAdd(&n_more, 1);
+          if (at < kMoreGroups) more[at] = x;
+        }
+      __syncthreads();
+      many = n_more;
+      if (many > kMoreGroups || (size_t)many * a.rows * a.E * sizeof(T) > kMoreBytes) {
+        if (tid == 0) {
+          a.idx[(size_t)b * a.k] = kUnsure;
+          *a.unsure = 1;
+        }
+        return;
+      }
+    }
+    const int now = min(many - done, max(cand_in_lds / a.rows, min(a.k, kMaxK)));
+    if (now > 0) {
+      if (tid < now) sel[tid] = more[done + tid];
+      n_rows = now * a.rows;
+      __syncthreads();
+    }
+    done += now;
+    many = now > 0 ? many : -1;
+  } while (many >= 0);
+  if (tid < a.k)
+    write(tid, found[tid] ? key_score((uint32_t)(found[tid] >> 32)) : -INFINITY, found[tid] ? (int)~(uint32_t)found[tid] : kIdxNone);
+}
+
+// k = 1 after search_bound_kernel: the same in fewer steps.  The group with the best bound is scored, eight threads a row, then
+// every other group whose bound reaches the best score.
+template <typename T, bool L2>
+__global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs a) {
+  constexpr int NT = 1024, KEEP = 4;   // bounds of a thread that stay in registers
+  typedef RowPiece<T> Piece;
+  constexpr int P = Piece::P;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* qf = reinterpret_cast<float*>(smem);   // [E rounded up to 8]
+  __shared__ uint64_t wave_top[2][NT / kWave];
+  __shared__ int more[kMoreGroups], n_more;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, part8 = tid & 7;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* part = a.part_s + (size_t)b * a.G;
+  const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
+  float u[KEEP];
+#pragma unroll
+  for (int t = 0; t < KEEP; ++t) u[t] = part[min(tid + t * NT, a.G - 1)];
+  for (int e = tid; e < ((a.E + 7) & ~7); e += NT) qf[e] = e < a.E ? (float)q[e] : 0.f;
+  if (tid == 0) n_more = 0;
+  uint64_t best = 0;
+#pragma unroll
+  for (int t = 0; t < KEEP; ++t) best = max(best, item_key(u[t], min(tid + t * NT, a.G - 1)));
+  for (int x = tid + KEEP * NT; x < a.G; x += NT) best = max(best, item_key(part[x], x));
+  auto block_best = [&](uint64_t x, int which) {   // in every lane
+    x = wave_best(x);
+    if (lane == 0) wave_top[which][wave] = x;
+    __syncthreads();
+    return row_best(wave_top[which][lane & (NT / kWave - 1)]);
+  };
+  auto score_group = [&](int g) {   // its rows, 128 at most; 0 where a row does not rank
+    const int r = g * a.rows + (tid >> 3);
+    if ((tid >> 3) >= a.rows || r >= a.N) return (uint64_t)0;   // (all eight threads of a row)
+    const T* row = reinterpret_cast<const T*>(a.emb) + (size_t)r * a.E;
+    float acc = 0.f;
+#pragma unroll 4
+    for (int c = P * part8; c < a.E; c += 8 * P) {
+      Piece e;
+      e.load(row, c, a.E);
+#pragma unroll
+      for (int t = 0; t < P; ++t) {
+        const float d = qf[c + t] - e.at(t);
+        acc = L2 ? fmaf(-d, d, acc) : fmaf(qf[c + t], e.at(t), acc);
+      }
+    }
+    acc += __shfl_xor(acc, 1);
+    acc += __shfl_xor(acc, 2);
+    acc += __shfl_xor(acc, 4);
+    return acc == acc ? item_key(acc, r) : 0;
+  };
+  best = block_best(best, 0);   // (qf is there, too)
+  const int first = (int)~(uint32_t)best;
+  best = score_group(first);
+  float qq = 0.f;
+  for (int e = lane; e < a.E; e += kWave) qq = fmaf(qf[e], qf[e], qq);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) qq += __shfl_xor(qq, off);
+  best = block_best(best, 1);
+  const float c = bound_slack(a.E), s = key_score((uint32_t)(best >> 32));
+  float reach = s - 0x1p-20f * fabsf(s) + (L2 ? (1.f - c) * qq : -0.5f * c * qq) - kBoundLeast;
+  if (best == 0 || !(qq < kBoundMost) || !(reach > -kBoundMost)) reach = -INFINITY;   // every group
+  auto look = [&](float bound, int x) {
+    if (bound >= reach && x < a.G && x != first) {
+      const int at = atomicAdd(&n_more, 1);
+      if (at < kMoreGroups) more[at] = x;
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < KEEP; ++t) look(u[t], tid + t * NT);
+  for (int x = tid + KEEP * NT; x < a.G; x += NT) look(part[x], x);
+  __syncthreads();
+  const int many = n_more;
+  if (many > 0) {
+    if (many > kMoreGroups || (size_t)many * a.rows * a.E * sizeof(T) > kMoreBytes) {
+      if (tid == 0) {
+        a.idx[b] = kUnsure;
+        *a.unsure = 1;
+      }
+      return;
+    }
+    for (int x = 0; x < many; ++x) best = max(best, score_group(more[x]));
+    best = block_best(best, 0);
+  }
+  if (tid == 0) {
+    const float top = best ? key_score((uint32_t)(best >> 32)) : -INFINITY;
+    const int i = best ? (int)~(uint32_t)best : kIdxNone;
+    a.idx[b] = i == kIdxNone ? -1 : i;
+    a.score[b] = top;
+    write_hit(a, b, top, i);
+  }
 }
 
 // ------------------------------------------------------------- both phases in one launch
@@ -1531,29 +1944,97 @@ static hipError_t launch_f16_phase1(const SearchArgs& a, int nqb, dim3 grid, siz
 // pick from, or many or very wide rows to re-score (those of k groups, or of all there are); below that the barriers of
 // sixteen waves cost more.  Time with them over time without, 8 queries: 256 rows of 1,024 bytes 1.10,
 // 512 of them 0.84; 64 rows of 4,800 bytes 0.90, 256 of them 1.18; 128 rows of 9,600 bytes 0.83, 256 0.89.
-template <typename T, int NT, bool L2>
+template <typename T, int NT, bool L2, bool BOUNDS>
 static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
   const size_t lists = (size_t)NT * 8 + kMaxK * 4, query = (size_t)((a.E + 3) & ~3) * 4;
-  const size_t cand = (size_t)a.k * a.rows * 4;
-  const int in_lds = lists + query + cand <= 64 * 1024;   // the rows' scores: in LDS, else in the workspace
+  const size_t cand = (size_t)(BOUNDS && a.k < 4 ? 4 : a.k) * a.rows * 4;
+  const int in_lds = lists + query + cand <= 62 * 1024 ? (int)(cand / 4) : 0;   // the rows' scores: in LDS, else in the workspace
   const size_t lds = lists + query + (in_lds ? cand : 0);
-  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT, L2>>(lds);
+  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT, L2, BOUNDS>>(lds);
   if (e != hipSuccess) return e;
   constexpr int kFit = (int)(kGridThreads / NT);   // queries of a launch
   for (a.q0 = 0; e == hipSuccess && a.q0 < a.B; a.q0 += a.nq) {
     a.nq = a.B - a.q0 < kFit ? a.B - a.q0 : kFit;
-    hipLaunchKernelGGL((finalize_topk_kernel<T, NT, L2>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
+    hipLaunchKernelGGL((finalize_topk_kernel<T, NT, L2, BOUNDS>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
     e = hipGetLastError();
   }
   return e;
 }
 
+static bool topk_large(const SearchArgs& a, size_t esz) {
+  return a.G > 1024 || (a.k < a.G ? a.k : a.G) * a.rows > 256 || a.E * esz > 6000;
+}
 template <typename T>
 static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
-  const int rows = (a.k < a.G ? a.k : a.G) * a.rows;
-  const bool large = a.G > 1024 || rows > 256 || a.E * sizeof(T) > 6000;
-  if (a.metric) return large ? launch_topk_n<T, 1024, true>(a, stream) : launch_topk_n<T, 256, true>(a, stream);
-  return large ? launch_topk_n<T, 1024, false>(a, stream) : launch_topk_n<T, 256, false>(a, stream);
+  const bool large = topk_large(a, sizeof(T));
+  if (a.metric) return large ? launch_topk_n<T, 1024, true, false>(a, stream) : launch_topk_n<T, 256, true, false>(a, stream);
+  return large ? launch_topk_n<T, 1024, false, false>(a, stream) : launch_topk_n<T, 256, false, false>(a, stream);
+}
+template <typename T, bool L2>
+static hipError_t launch_bounded_finish(const SearchArgs& a, hipStream_t stream) {
+  if (a.k > 1) return launch_topk_n<T, 1024, L2, true>(a, stream);
+  hipLaunchKernelGGL((finalize_bound1_kernel<T, L2>), dim3((unsigned)a.B), dim3(1024), ((size_t)a.E + 7) / 8 * 32, stream, a);
+  return hipGetLastError();
+}
+
+// ---- bounds, exact scores of what they leave, tiles for what they leave open
+static size_t bound_lds(int nqb, int E, size_t parts) {
+  return (size_t)32 * nqb * ((((size_t)E + 15) & ~15) + kQPad) * 2 * parts + (size_t)4 * 32 * nqb * 4 + 4 * 32 * 4;
+}
+constexpr size_t kBoundLds = 150 * 1024;
+
+// Where bounds first are faster than exact scores of all rows: four launches (two of which usually find nothing to do) and a
+// second phase that reads whole groups of wide rows, against work that grows with N B E.  us per call (graph), all rows / bounds:
+//   fp32 Euclidean, k = 1   100,000 x 128, 64 queries 57 / 24; 32,000 x 128: 9 queries 15.1 / 15.2, 40 25.7 / 16.5; 8,000 x 128, 64
+//                           15.3 / 15.5; 2,000 x 256, 128 17.4 / 24.3, 400 36.6 / 25.6; 32,000 x 512, 9 37.4 / 27.9; 2,000 x 1,024, 128 46.8 / 49.6
+//   fp32 inner, k = 1       32,000 x 128, 40 queries 23.5 / 16.5; 500,000 x 256, 9 110 / 113 (both bound by the stream)
+//   fp16 Euclidean, k = 1   32,000 x 32, 40 queries 15.6 / 12.2; 128,000 x 256, 64 147 / 27; 8,000 x 64, 64 11.2 / 12.3
+//   k = 8                   fp32 Euclidean 8,000 x 128, 64 queries 21.9 / 24.5, 128 29.6 / 27.2; 8,000 x 512, 40 53.8 / 44.3;
+//                           fp16 8,000 x 256, 64 25.3 / 25.4; 32,000 x 512, 16 40.8 / 39.5, 40 69 / 41
+// Up to eight queries are streams, which follow the memory.  Rows below 64 columns leave the bounds' kernel little work a
+// row: 500,000 x 32 fp32, 16 queries 33.4 / 35.2, 40 69 / 37.
+static bool use_bounds(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
+  if (B <= 8 || B > 1 << 20 || (is_f16 && !metric) || bound_lds(1, E, is_f16 ? 1 : 2) > kBoundLds) return false;
+  const double work = (double)N * B * E, bytes = (double)N * E * (is_f16 ? 2 : 4);
+  if (B <= 16 && !is_f16 && (E < 64 || (!metric && bytes > 256e6))) return false;
+  const double least = is_f16 && E <= 64 ? 4e7 : k == 1 ? 6.6e7 : 1.05e8;
+  return work >= least && work >= (k > 1 && is_f16 ? 5e5 : 2.8e5) * E;
+}
+
+// Groups of the bounds: as small as the workspace of search_plan allows (8 bytes for each 256 rows of a query and, for
+// k > 1, 4 for each row of k of those groups).
+static void bound_plan(int32_t N, int32_t k, int32_t* rows, int32_t* G) {
+  const size_t space = (size_t)8 * ((N + kValuRowsPerWg - 1) / kValuRowsPerWg) + (k > 1 ? (size_t)4 * k * kValuRowsPerWg : 0);
+  int32_t r = 32;
+  while ((size_t)4 * ((N + r - 1) / r) + (k > 1 ? (size_t)4 * k * r : 0) > space) r *= 2;   // 128 always fits
+  *rows = r;
+  *G = (N + r - 1) / r;
+}
+
+template <typename T, bool L2, int NQB>
+static hipError_t launch_bound_n(const SearchArgs& a, hipStream_t stream) {
+  const size_t lds = bound_lds(NQB, a.E, BoundParts<T>::N);
+  hipError_t e = ensure_lds<&search_bound_kernel<T, L2, NQB>>(lds);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)((a.N + a.wg_rows - 1) / a.wg_rows), (unsigned)((a.B + 32 * NQB - 1) / (32 * NQB)));
+  hipLaunchKernelGGL((search_bound_kernel<T, L2, NQB>), grid, dim3(kThreads), lds, stream, a);
+  return hipGetLastError();
+}
+
+template <typename T, bool L2>
+static hipError_t launch_bounded(SearchArgs a, hipStream_t stream) {
+  bound_plan(a.N, a.k, &a.rows, &a.G);
+  // a second pass shares the staged queries, while there are workgroups for all compute units: 100,000 x 128 fp32, 64 queries 18.5 us
+  // with one pass, 15.9 with two, 21 with four; 20,000 x 768, 32 queries 21.8, 33, 59
+  a.wg_rows = a.N > 65536 ? 256 : 128;
+  const size_t used = ((size_t)a.B * a.G * 4 + 255) / 256 * 256;
+  unsigned char* ws = reinterpret_cast<unsigned char*>(a.part_s);
+  a.cand = reinterpret_cast<float*>(ws + used);
+  auto fits = [&](int nqb) { return bound_lds(nqb, a.E, BoundParts<T>::N) <= kBoundLds; };
+  hipError_t e = a.B > 32 && fits(2) ? (a.B > 64 && fits(4) ? launch_bound_n<T, L2, 4>(a, stream) : launch_bound_n<T, L2, 2>(a, stream))
+                                     : launch_bound_n<T, L2, 1>(a, stream);
+  if (e != hipSuccess) return e;
+  return launch_bounded_finish<T, L2>(a, stream);
 }
 
 // Where one launch is faster than two.  A step of 128 KB costs 1 us (fp16 Euclidean, which converts and subtracts
@@ -1601,9 +2082,18 @@ static hipError_t launch_small(const SearchArgs& a, hipStream_t stream) {
   return a.k > 1 ? launch_small_k<T, false, true>(a, stream) : launch_small_k<T, false, false>(a, stream);
 }
 
+template <typename T>
+static hipError_t launch_unsure(const SearchArgs& a, hipStream_t stream) {
+  const size_t groups8 = ((size_t)(a.N + kValuRowsPerWg - 1) / kValuRowsPerWg + 7) / 8 * 8;
+  if (a.k > 1)
+    return a.metric ? launch_tiles<T, true, 4, true>(a, groups8, stream) : launch_tiles<T, false, 4, true>(a, groups8, stream);
+  return a.metric ? launch_tiles<T, true, 4, false>(a, groups8, stream) : launch_tiles<T, false, 4, false>(a, groups8, stream);
+}
+
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   if (p.B == 0) return hipSuccess;
   SearchArgs a;
+  a.unsure = nullptr;
   a.emb = p.emb; a.q = p.q; a.map_of = p.map_of;
   a.N = p.N; a.E = p.E; a.B = p.B; a.k = p.k; a.metric = p.metric;
   a.threshold = p.threshold;
@@ -1663,6 +2153,15 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
       else e = launch_f16_phase1<32>(a, nqb, grid, lds, stream);
       if (e != hipSuccess) return e;
     }
+  } else if (use_bounds(p.is_f16, p.metric, p.E, p.B, p.N, p.k)) {
+    // the last 256 bytes of the workspace are behind what the searches use
+    a.unsure = reinterpret_cast<int32_t*>(ws + search_workspace_bytes(p.N, p.E, p.B, p.k, p.is_f16) - 256);
+    hipError_t e = p.is_f16    ? launch_bounded<f16_t, true>(a, stream)
+                   : p.metric ? launch_bounded<float, true>(a, stream)
+                              : launch_bounded<float, false>(a, stream);
+    if (e != hipSuccess) return e;
+    e = p.is_f16 ? launch_unsure<f16_t>(a, stream) : launch_unsure<float>(a, stream);
+    if (e != hipSuccess) return e;
   } else {
     const hipError_t e = p.is_f16 ? launch_valu<f16_t>(a, stream) : launch_valu<float>(a, stream);
     if (e != hipSuccess) return e;

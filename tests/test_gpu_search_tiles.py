@@ -89,6 +89,73 @@ VARIANT_CASES = [(*c, k, torch.float16, "ip") for k in (1, 3) for c in [
 ]] + [(2501, 8, 1, 1, torch.float16, "ip")]
 
 
+# Bounds from the matrix cores, then exact scores of the groups that may hold the best: whole and ragged rows, columns, query
+# blocks, groups of 32, 64 and 128 rows.
+BOUND_CASES = [
+    # N, E, B, k, dtype, metric
+    (20011, 128, 32, 1, torch.float32, "l2"), (20011, 131, 33, 1, torch.float32, "ip"), (20011, 72, 50, 1, torch.float32, "l2"),
+    (9001, 97, 130, 3, torch.float32, "l2"), (9001, 200, 64, 8, torch.float32, "ip"), (33001, 259, 17, 64, torch.float32, "l2"),
+    (9001, 1160, 33, 1, torch.float32, "l2"), (33000, 64, 70, 2, torch.float32, "ip"), (150001, 33, 20, 1, torch.float32, "ip"),
+    (120001, 20, 48, 16, torch.float32, "l2"), (5001, 72, 600, 1, torch.float32, "ip"),
+    (40000, 136, 40, 4, torch.float16, "l2"), (30001, 24, 140, 1, torch.float16, "l2"), (50001, 256, 9, 1, torch.float16, "l2"),
+    (70001, 64, 40, 8, torch.float16, "l2"), (9001, 520, 65, 5, torch.float16, "l2"), (3001, 2304, 170, 2, torch.float16, "l2"),
+    # what stays in tiles: queries too wide for the bounds' kernel
+    (8000, 2384, 215, 1, torch.float16, "l2"), (8000, 2384, 215, 3, torch.float16, "l2"),
+    (8192, 2384, 257, 1, torch.float16, "l2"), (8192, 2384, 257, 3, torch.float16, "l2"),
+]
+
+
+@pytest.mark.parametrize("case", BOUND_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
+    *c[:4], str(c[4]).split(".")[-1], c[5]))
+def test_bounded_search_matches_the_oracle(ac, oracle_mod, case):  # noqa: F811
+    _check(ac, oracle_mod, *case)
+
+
+@pytest.mark.parametrize("k", [1, 5])
+@pytest.mark.parametrize("dt,metric", [(torch.float32, "ip"), (torch.float32, "l2"), (torch.float16, "l2")])
+@pytest.mark.parametrize("what", ["alike", "far", "one far", "huge", "tiny", "nan", "nan queries"])
+def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, dt, metric, k):  # noqa: F811
+    """Rows that the bounds cannot tell apart, in few groups (scored there) and in many (searched again)."""
+    N, E, B = 30003, 96, 40
+    g = _gen(9)
+    emb = torch.randn(N, E, generator=g) / E ** 0.5
+    q = emb[torch.randint(0, N, (B,), generator=g)] + 0.02 * torch.randn(B, E, generator=g)
+    if what == "alike":      # of 40 kinds, each in most groups; half of the queries next to a row there is ten times
+        kinds = emb[:40].clone()
+        emb[100:] = kinds[torch.randint(0, 40, (N - 100,), generator=g)]
+        emb[100:N:2000] = q[0] + 0.01
+        q[1::2] = q[0]
+    elif what == "far":
+        emb, q = emb + 30.0, q + 30.0
+    elif what == "one far":  # of the queries
+        q[5] += 200.0
+    elif what == "huge":
+        big = 1e18 if dt == torch.float32 else 200.0
+        emb[:300] *= big
+        q[:9] *= big
+    elif what == "tiny":     # fp16: below the normal numbers
+        emb, q = emb * 2.0 ** -19, q * 2.0 ** -19
+    elif what == "nan":
+        emb[::3, 7] = float("nan")
+        emb[1::3, 5] = float("inf")
+    else:
+        q[::4, 3] = float("nan")
+        q[2, 0] = float("inf")
+    emb, q = emb.to(dt), q.to(dt)
+    m = ac.AC_IP if metric == "ip" else ac.AC_L2
+    idx, score, hit = _run_search(ac, emb, q, k, 0.8, m)
+    if what in ("far", "one far", "huge", "tiny", "alike"):
+        parity.check_search(oracle_mod, q, emb, k, 0.8, m, None, idx, score, hit)
+    # and the same rows as a search by itself, which is too small for bounds, says, eight queries at a time
+    for b in range(0, B, 8):
+        i2, s2, h2 = _run_search(ac, emb, q[b:b + 8].contiguous(), k, 0.8, m)
+        s1 = score[b:b + 8]
+        same = (s1 == s2) | (s1.isnan() & s2.isnan())
+        scale = s2.abs().clamp_min(torch.finfo(torch.float32).tiny)
+        assert (same | ((s1 - s2).abs() <= (E + 4) * 2.0 ** -23 * scale * (1 if metric == "l2" else 40))).all()
+        assert ((idx[b:b + 8] < 0) == (i2 < 0)).all()
+
+
 @pytest.mark.parametrize("case", VARIANT_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
     *c[:4], str(c[4]).split(".")[-1], c[5]))
 def test_every_variant_matches_the_oracle(ac, oracle_mod, case):  # noqa: F811

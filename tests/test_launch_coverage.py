@@ -37,7 +37,7 @@ def _search(c):
 
 
 def test_every_search_kernel_is_reached(tmp_path):
-    cases = (tiles.VALU_CASES + tiles.VARIANT_CASES + tiles.TOPK_CASES + small.SEARCH_CASES +
+    cases = (tiles.VALU_CASES + tiles.VARIANT_CASES + tiles.TOPK_CASES + tiles.BOUND_CASES + small.SEARCH_CASES +
              small._random_search_shapes(40, 20251128))
     missing = _kernels("search_", "finalize_") - _reached(tmp_path, [_search(c) for c in cases])
     assert missing == NOT_RUN
@@ -93,7 +93,7 @@ def test_every_projector_kernel_is_reached(tmp_path):
     ((300000, 8, 8, 1, "f16", "l2"), "search_row_kernel<half"),                  # 28 in streams, 11
     ((20000, 20, 8, 1, "f32", "ip"), "search_row_kernel<float"),
     ((20000, 37, 8, 1, "f32", "ip"), "search_stream_kernel<float, false, 4"),
-    ((100000, 128, 64, 1, "f32", "l2"), "search_valu_kernel<float, true, 4"),
+    ((100000, 128, 64, 1, "f32", "l2"), "search_bound_kernel<float, true, 2"),   # 57 in tiles of all rows, 24
     ((640, 256, 4, 1, "f32", "ip"), "search_small_kernel<float, false, false, 2"),   # one row of a thread 9.6, two 9.0
     ((300, 512, 4, 4, "f16", "ip"), "search_small_kernel<half, false, true, 4"),     # 11.2, four 9.4
     ((100, 640, 16, 1, "f16", "ip"), "search_small_kernel<half, false, false, 1"),   # 6.2, 6.7
