@@ -709,17 +709,16 @@ struct TileSlice {
   }
 };
 
-template <typename T, bool L2, int QW, bool TOPK>
-__device__ __forceinline__ void search_valu_tile(const SearchArgs& a, int tile, int nqb, float* el, float* ql) {
+template <typename T, bool L2, int QW, bool TOPK, typename Index>
+__device__ __forceinline__ void search_valu_tile(const SearchArgs& a, Index tile, int nqb, float* el, float* ql) {
   constexpr int R = kValuRowsPerWg / kWave;   // rows of a lane
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the query blocks of one group get ids equal mod 8: one XCD reads the group's rows once
-  const int slot = tile >> 3;
-  const int gidx = slot / nqb * 8 + (tile & 7), q0 = a.q0 + slot % nqb * (4 * QW);
+  const Index slot = tile >> 3;
+  const int gidx = (int)(slot / nqb) * 8 + (int)(tile & 7), q0 = a.q0 + (int)(slot % nqb) * (4 * QW);
   if (gidx >= (a.N + kValuRowsPerWg - 1) / kValuRowsPerWg) return;
   const int q_end = min(a.q0 + a.nq, q0 + 4 * QW);
-  if (a.unsure && !__ballot(lane < q_end - q0 && a.idx[(size_t)(q0 + lane) * a.k] == kUnsure)) return;   // the same for all waves
   const T* emb = reinterpret_cast<const T*>(a.emb);
   const T* qs = reinterpret_cast<const T*>(a.q);
   const int row0 = gidx * kValuRowsPerWg;
@@ -809,10 +808,22 @@ template <typename T, bool L2, int QW, bool TOPK>
 __global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs a) {
   __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
   __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];   // 4 QW <= 32 rows used
-  if (a.unsure && *a.unsure == 0) return;   // the usual case there, with a grid that is quickly through
+  search_valu_tile<T, L2, QW, TOPK>(a, (int)blockIdx.x, (a.nq + 4 * QW - 1) / (4 * QW), el, ql);
+}
+
+// The same for the queries that bounds have left open (below): usually none, so the grid is one that is quickly through.
+template <typename T, bool L2, int QW, bool TOPK>
+__global__ __launch_bounds__(kThreads) void search_unsure_kernel(const SearchArgs a) {
+  __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
+  __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];
+  if (*a.unsure == 0) return;
   const int nqb = (a.nq + 4 * QW - 1) / (4 * QW);
-  const unsigned tiles = ((unsigned)a.N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * nqb;
-  for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) search_valu_tile<T, L2, QW, TOPK>(a, tile, nqb, el, ql);
+  const int64_t tiles = ((int64_t)a.N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * nqb;
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int q = a.q0 + (int)((tile >> 3) % nqb) * (4 * QW) + (threadIdx.x & 63);   // a wave looks at the tile's queries
+    if (__ballot((threadIdx.x & 63) < 4 * QW && q < a.q0 + a.nq && a.idx[(size_t)min(q, a.B - 1) * a.k] == kUnsure))
+      search_valu_tile<T, L2, QW, TOPK>(a, tile, nqb, el, ql);
+  }
 }
 
 // ---------------------------------------------------------------- phase 1, bounds from the matrix cores
@@ -1060,8 +1071,6 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
 
 constexpr size_t kGridThreads = ((size_t)1 << 32) - 1;   // most threads of a launch in one dimension
 
-constexpr size_t kUnsureTiles = 768;   // three workgroups a compute unit, as many as its LDS holds
-
 template <typename T, bool L2, int QW, bool TOPK>
 static hipError_t launch_tiles(SearchArgs a, size_t groups8, hipStream_t stream) {
   // the grid is one-dimensional (groups x query blocks, so that it can choose the XCD): a large index
@@ -1070,8 +1079,7 @@ static hipError_t launch_tiles(SearchArgs a, size_t groups8, hipStream_t stream)
   for (size_t q0 = 0; q0 < (size_t)a.B; q0 += fit) {
     a.q0 = (int32_t)q0;
     a.nq = (int32_t)((size_t)a.B - q0 < fit ? (size_t)a.B - q0 : fit);
-    size_t tiles = groups8 * ((a.nq + 4 * QW - 1) / (4 * QW));
-    if (a.unsure && tiles > kUnsureTiles) tiles = kUnsureTiles;
+    const size_t tiles = groups8 * ((a.nq + 4 * QW - 1) / (4 * QW));
     hipLaunchKernelGGL((search_valu_kernel<T, L2, QW, TOPK>), dim3((unsigned)tiles), dim3(kThreads), 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -2082,12 +2090,19 @@ static hipError_t launch_small(const SearchArgs& a, hipStream_t stream) {
   return a.k > 1 ? launch_small_k<T, false, true>(a, stream) : launch_small_k<T, false, false>(a, stream);
 }
 
+constexpr int kUnsureTiles = 768;   // workgroups: three a compute unit, as many as its LDS holds
+
+template <typename T, bool L2, bool TOPK>
+static hipError_t launch_unsure_k(SearchArgs a, hipStream_t stream) {
+  a.nq = a.B;
+  hipLaunchKernelGGL((search_unsure_kernel<T, L2, 4, TOPK>), dim3(kUnsureTiles), dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
+}
 template <typename T>
 static hipError_t launch_unsure(const SearchArgs& a, hipStream_t stream) {
-  const size_t groups8 = ((size_t)(a.N + kValuRowsPerWg - 1) / kValuRowsPerWg + 7) / 8 * 8;
-  if (a.k > 1)
-    return a.metric ? launch_tiles<T, true, 4, true>(a, groups8, stream) : launch_tiles<T, false, 4, true>(a, groups8, stream);
-  return a.metric ? launch_tiles<T, true, 4, false>(a, groups8, stream) : launch_tiles<T, false, 4, false>(a, groups8, stream);
+  if (a.metric) return a.k > 1 ? launch_unsure_k<T, true, true>(a, stream) : launch_unsure_k<T, true, false>(a, stream);
+  if constexpr (std::is_same<T, f16_t>::value) return hipErrorInvalidValue;   // (fp16 inner products have no bounds)
+  else return a.k > 1 ? launch_unsure_k<T, false, true>(a, stream) : launch_unsure_k<T, false, false>(a, stream);
 }
 
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {

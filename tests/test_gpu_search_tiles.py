@@ -102,6 +102,7 @@ BOUND_CASES = [
     # what stays in tiles: queries too wide for the bounds' kernel
     (8000, 2384, 215, 1, torch.float16, "l2"), (8000, 2384, 215, 3, torch.float16, "l2"),
     (8192, 2384, 257, 1, torch.float16, "l2"), (8192, 2384, 257, 3, torch.float16, "l2"),
+    (8192, 2384, 513, 1, torch.float16, "l2"), (8192, 2384, 513, 3, torch.float16, "l2"),
 ]
 
 
