@@ -61,9 +61,10 @@ struct InsertArgs {
 // rows of one head per workgroup and all keys multiplied, 132 to 139 us so (several boxes),
 // without an extra launch for the feature vectors (520 MB, 93 us at the copy rate).
 constexpr int kIChunk = 64;   // keys per staged chunk
+constexpr float kNoScore = -3.402823466e38f;
 
 template <int D, bool CAUSAL, bool PACKED, bool RESIDENT>
-__global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertArgs a) {
+__global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void insert_bf16_kernel(const InsertArgs a) {
   constexpr int PPR = D / 8;                          // 16-byte pieces per row
   constexpr int NCOPY = kIChunk * PPR / kWave / 4;    // copy instructions per wave, tensor, chunk
   __shared__ __attribute__((aligned(16))) bf16_t kb0[kIChunk * D];
@@ -121,21 +122,18 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
   const int crow = slot0 / PPR, cpos = slot0 % PPR;
   const int kpiece = cpos ^ k_piece_swizzle<D>(crow);
   const int vpiece = cpos ^ v_piece_swizzle<D>(crow);
-  auto prefetch = [&](bf16_t* kb, bf16_t* vb, int c, const bool WITH_V) {
+  auto copy_in = [&](bf16_t* to, const bf16_t* from, int piece, int c) {
     const int nj = min(kIChunk, S - c * kIChunk);
-    const bf16_t* ksrc = Ksrc + (size_t)c * kIChunk * D;
-    const bf16_t* vsrc = Vsrc + (size_t)c * kIChunk * D;
+    const bf16_t* src = from + (size_t)c * kIChunk * D;
 #pragma unroll
     for (int i = 0; i < NCOPY; ++i) {
       const int rr = min(crow + (256 / PPR) * i, nj - 1);
-      __builtin_amdgcn_global_load_lds(ksrc + (size_t)rr * D + 8 * kpiece,
-                                       kb + kWave * 8 * (wave + 4 * i), 16, 0, 0);
-      if (WITH_V)
-        __builtin_amdgcn_global_load_lds(vsrc + (size_t)rr * D + 8 * vpiece,
-                                         vb + kWave * 8 * (wave + 4 * i), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(src + (size_t)rr * D + 8 * piece, to + kWave * 8 * (wave + 4 * i), 16, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
+  auto copy_k = [&](bf16_t* kb, int c) { copy_in(kb, Ksrc, kpiece, c); };
+  auto copy_v = [&](bf16_t* vb, int c) { copy_in(vb, Vsrc, vpiece, c); };
   // this wave's copies have landed (they are counted like loads), then everybody's; the
   // barrier also retires the stage that the next copy overwrites
   auto publish = [&]() {
@@ -202,7 +200,9 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
     return s;
   };
 
-  float m_run = -INFINITY, l_run = 0.f, inv_l = 0.f;
+  // Every lane has the running maximum and the sum of ITS keys of a row (half of them); the halves meet between the passes.
+  // (The lowest finite value stands for "none yet": a lane may see no key in the first blocks.)
+  float m_run = kNoScore, l_run = 0.f, m_all = 0.f;
   f32x16 acc[D / 32];
   // where register group q4 (scores 4 q4 .. 4 q4 + 3 of this lane) of 32-key block kb goes
   const int r16 = (r0 >> 4) + (il >> 4);
@@ -214,80 +214,130 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
     return reinterpret_cast<u32x2*>(At + (size_t)(r0 + il) * S + 32 * kb + 8 * q4 + 4 * kh);
   };
 
-  // one staged chunk.  First pass: row maximum m (log2 domain, scale folded in) and row sum l of
-  // 2^(score - m).  Second pass: normalised weights, rounded, stored, multiplied with V.
+  // First pass: row maximum m (log2 domain, scale folded in) and row sum l of 2^(score - m).
+  auto note = [&](float mx, auto sum) {
+    const float m_new = fmaxf(m_run, mx * a.scale_log2e);
+    l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + sum(m_new);
+    m_run = m_new;
+  };
+  auto largest = [](const f32x16& s) {
+    float mx = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
+    return mx;
+  };
+  auto sum_of = [&](const f32x16& s, float m) {
+    float sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2e, -m));
+    return sum;
+  };
+  // Second pass: normalised weights 2^(score - m_all), m_all = m + log2 l, rounded, stored, multiplied with V.
+  auto weigh = [&](const f32x16& s, const bf16_t* vb, int kb32, int jb) {
+#pragma unroll
+    for (int s2 = 0; s2 < 2; ++s2) {
+      u32x4 pw;
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        pw[w] = pack_bf16(__builtin_amdgcn_exp2f(fmaf(s[8 * s2 + 2 * w], a.scale_log2e, -m_all)),
+                          __builtin_amdgcn_exp2f(fmaf(s[8 * s2 + 2 * w + 1], a.scale_log2e, -m_all)));
+      if (keep) {
+        if constexpr (PACKED) {   // 256-byte runs either way
+          *map_piece(kb32, 2 * s2) = u32x2{pw.x, pw.y};
+          *map_piece(kb32, 2 * s2 + 1) = u32x2{pw.z, pw.w};
+        } else {
+          // The lane halves exchange, so that the lower one has all eight columns of group 2 s2 and the
+          // upper one those of the next: rows get 16 instead of 8 bytes at a time (160 x 12 heads of
+          // 512 x 128, causal, padded: 582 -> 484 us).
+          uint32_t x = pw.x, y = pw.y, z = pw.z, w = pw.w;
+          swap_halves(x, z);
+          swap_halves(y, w);
+          *reinterpret_cast<u32x4*>(map_piece(kb32, 2 * s2 + kh) - kh) = u32x4{x, y, z, w};
+        }
+      }
+      const bf16x8 pop = __builtin_bit_cast(bf16x8, pw);
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db) acc[db] = mfma_bf16(vop(vb, db, jb, s2), pop, acc[db]);
+    }
+  };
+  // one staged chunk
   auto chunk = [&](const bf16_t* kb, const bf16_t* vb, int c, const bool SECOND)
                    __attribute__((always_inline)) {
     const int nblk = blocks(c);
     for (int jb = 0; jb < nblk; ++jb) {
-      f32x16 s = scores(kb, c, jb);
-      if (!SECOND) {
-        float mx = s[0];
-#pragma unroll
-        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[v]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m_run, mx * a.scale_log2e);
-        float psum = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2e, -m_new));
-        l_run = l_run * __builtin_amdgcn_exp2f(m_run - m_new) + psum;
-        m_run = m_new;
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2e, -m_run)) * inv_l;
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-          u32x4 pw;
-          pw.x = pack_bf16(s[8 * s2 + 0], s[8 * s2 + 1]);
-          pw.y = pack_bf16(s[8 * s2 + 2], s[8 * s2 + 3]);
-          pw.z = pack_bf16(s[8 * s2 + 4], s[8 * s2 + 5]);
-          pw.w = pack_bf16(s[8 * s2 + 6], s[8 * s2 + 7]);
-          if (keep) {
-            const int kb32 = 2 * c + jb;
-            if constexpr (PACKED) {   // 256-byte runs either way
-              *map_piece(kb32, 2 * s2) = u32x2{pw.x, pw.y};
-              *map_piece(kb32, 2 * s2 + 1) = u32x2{pw.z, pw.w};
-            } else {
-              // The lane halves exchange, so that the lower one has all eight columns of group 2 s2 and the
-              // upper one those of the next: rows get 16 instead of 8 bytes at a time (160 x 12 heads of
-              // 512 x 128, causal, padded: 582 -> 484 us).
-              uint32_t x = pw.x, y = pw.y, z = pw.z, w = pw.w;
-              swap_halves(x, z);
-              swap_halves(y, w);
-              *reinterpret_cast<u32x4*>(map_piece(kb32, 2 * s2 + kh) - kh) = u32x4{x, y, z, w};
-            }
-          }
-          const bf16x8 pop = __builtin_bit_cast(bf16x8, pw);
-#pragma unroll
-          for (int db = 0; db < D / 32; ++db) acc[db] = mfma_bf16(vop(vb, db, jb, s2), pop, acc[db]);
-        }
-      }
+      const f32x16 s = scores(kb, c, jb);
+      if (!SECOND) note(largest(s), [&](float m) { return sum_of(s, m); });
+      else weigh(s, vb, 2 * c + jb, jb);
     }
   };
-  // all chunks of the row block, two per trip so that the stages are named statically (the
-  // compiler then knows that the copy in flight and the reads of the other stage do not meet)
-  auto pass = [&](const bool SECOND) __attribute__((always_inline)) {
-    prefetch(kb0, vb0, 0, SECOND);
+  auto join_halves = [&]() {
+    const float m = max_with_other_half(m_run), l = l_run * __builtin_amdgcn_exp2f(m_run - m);
+    m_all = m + __builtin_amdgcn_logf(l + __shfl_xor(l, 32));
+  };
+  // All chunks of the row block, chunk c in stage c & 1; two per trip so that the stages are named statically (the
+  // compiler then knows that the copy in flight and the reads of the other stage do not meet).  The second pass takes them
+  // from the last to the first: K of the last two is still there, and their V arrives under the end of the first pass.
+  auto both_passes = [&]() __attribute__((always_inline)) {
+    auto copy_last_v = [&]() {
+      if ((n_chunk - 1) & 1) {
+        copy_v(vb1, n_chunk - 1);
+        copy_v(vb0, n_chunk - 2);
+      } else {
+        copy_v(vb0, n_chunk - 1);
+        if (n_chunk > 1) copy_v(vb1, n_chunk - 2);
+      }
+    };
+    copy_k(kb0, 0);
     publish();
     int c = 0;
     for (; c + 1 < n_chunk; c += 2) {
-      prefetch(kb1, vb1, c + 1, SECOND);
-      chunk(kb0, vb0, c, SECOND);
+      copy_k(kb1, c + 1);
+      chunk(kb0, vb0, c, false);
       publish();
-      if (c + 2 < n_chunk) prefetch(kb0, vb0, c + 2, SECOND);
-      chunk(kb1, vb1, c + 1, SECOND);
+      if (c + 2 < n_chunk) copy_k(kb0, c + 2);
+      else copy_last_v();
+      chunk(kb1, vb1, c + 1, false);
       publish();
     }
     if (c < n_chunk) {   // odd count: the last chunk sits in the first stage
-      chunk(kb0, vb0, c, SECOND);
-      publish();         // everybody is done with it before the next pass overwrites it
+      copy_last_v();
+      chunk(kb0, vb0, c, false);
+      publish();
+    }
+    join_halves();
+    c = n_chunk - 1;
+    if (!(c & 1)) {
+      chunk(kb0, vb0, c, true);
+      if (c >= 2) {
+        publish();
+        copy_k(kb0, c - 2);
+        copy_v(vb0, c - 2);
+      }
+      --c;
+    }
+    for (; c > 0; c -= 2) {
+      chunk(kb1, vb1, c, true);
+      if (n_chunk > 2) publish();
+      if (c >= 3) {
+        copy_k(kb1, c - 2);
+        copy_v(vb1, c - 2);
+      }
+      chunk(kb0, vb0, c - 1, true);
+      if (c >= 3) {
+        publish();
+        copy_k(kb0, c - 3);
+        copy_v(vb0, c - 3);
+      }
     }
   };
 
   if (RESIDENT) {
-    prefetch(kb0, vb0, 0, true);
-    if (n_chunk > 1) prefetch(kb1, vb1, 1, true);
+    copy_k(kb0, 0);
+    copy_v(vb0, 0);
+    if (n_chunk > 1) {
+      copy_k(kb1, 1);
+      copy_v(vb1, 1);
+    }
     publish();
   }
   const int n_heads = RESIDENT ? g : 1;   // streaming: one unit per wave
@@ -301,7 +351,7 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks) q[ks] = *reinterpret_cast<const u32x4*>(qrow + 16 * ks);
     }
-    m_run = -INFINITY;
+    m_run = kNoScore;
     l_run = 0.f;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
@@ -311,13 +361,11 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_kernel(const InsertAr
     if (RESIDENT) {
       chunk(kb0, vb0, 0, false);
       if (n_chunk > 1) chunk(kb1, vb1, 1, false);
-      inv_l = 1.0f / (l_run + __shfl_xor(l_run, 32));
+      join_halves();
       chunk(kb0, vb0, 0, true);
       if (n_chunk > 1) chunk(kb1, vb1, 1, true);
     } else {
-      pass(false);
-      inv_l = 1.0f / (l_run + __shfl_xor(l_run, 32));
-      pass(true);
+      both_passes();
     }
 
     if (active) {
