@@ -1175,23 +1175,25 @@ static hipError_t launch_valu(const SearchArgs& a, hipStream_t stream) {
 }
 
 // ------------------------------------------------------------------- phase 2
-__device__ __forceinline__ void write_hit(const SearchArgs& a, int b, float s0, int i0) {
-  if (i0 == kIdxNone) {   // no row ranked at all (every score of the query is NaN): a miss
-    a.hit[b] = -1;
-    return;
-  }
+__device__ __forceinline__ int entry_of(const SearchArgs& a, int row) { return a.map_of ? a.map_of[row] : row; }
+__device__ __forceinline__ void write_entry(const SearchArgs& a, int b, float s0, int entry) {
   float sim = s0;
   if (a.metric == 1) sim = 1.0f - sqrtf(-s0);
-  int entry = a.map_of ? a.map_of[i0] : i0;
   a.hit[b] = (sim >= a.threshold) ? entry : -1;
 }
+__device__ __forceinline__ void write_hit(const SearchArgs& a, int b, float s0, int i0) {
+  if (i0 == kIdxNone) a.hit[b] = -1;   // no row ranked at all (every score of the query is NaN): a miss
+  else write_entry(a, b, s0, entry_of(a, i0));
+}
 
-// k = 1: best of the group maxima.
+// k = 1: best of the group maxima.  UNSURE: of the queries that bounds have left open (a test at run time costs the other
+// calls 0.2 us of 9).
+template <bool UNSURE>
 __global__ __launch_bounds__(kThreads) void finalize_top1_kernel(const SearchArgs a) {
   __shared__ float red_s[4];
   __shared__ int red_i[4];
   const int b = blockIdx.x;
-  if (a.unsure && (*a.unsure == 0 || a.idx[b] != kUnsure)) return;
+  if (UNSURE && (*a.unsure == 0 || a.idx[b] != kUnsure)) return;
   float s = -INFINITY;
   int i = kIdxNone;
   for (int gi = threadIdx.x; gi < a.G; gi += kThreads) {
@@ -1226,8 +1228,9 @@ __global__ __launch_bounds__(kThreads) void finalize_top1_block_kernel(const Sea
   const f16_t* q = reinterpret_cast<const f16_t*>(a.q) + (size_t)b * a.E;
   const int row = i + (tid >> 3), part = tid & 7;
   float rs = -INFINITY;
-  int ri = kIdxNone;
+  int ri = kIdxNone, entry = -1;
   if (i != kIdxNone && row < a.N) {
+    entry = entry_of(a, row);   // (with the row: of the winner later it would be a round trip to memory more)
     const f16_t* e = reinterpret_cast<const f16_t*>(a.emb) + (size_t)row * a.E;
     float acc = 0.f;
     for (int c = 8 * part; c < a.E; c += 64) {   // 16-byte pieces, eight threads side by side
@@ -1246,8 +1249,9 @@ __global__ __launch_bounds__(kThreads) void finalize_top1_block_kernel(const Sea
   if (tid == 0) {
     a.idx[b] = ri == kIdxNone ? -1 : ri;
     a.score[b] = s;
-    write_hit(a, b, s, ri);
+    if (ri == kIdxNone) a.hit[b] = -1;
   }
+  if (row == ri && part == 0) write_entry(a, b, s, entry);
 }
 
 // An item of a selection: score and number in one word that orders like them (higher score, then
@@ -1502,13 +1506,15 @@ constexpr size_t kMoreBytes = 2 << 20;   // some 25 us of one compute unit, half
 // thread read two bytes at a time, and k rounds of a workgroup-wide arg-max; 10 us so.  Bound by the serial
 // chain of a selection among 1,563 groups, 512 rows (260 KB through one compute unit's 64 bytes per clock) and
 // a selection among those, on as many compute units as queries.
-// BOUNDS: the groups' values are those of search_bound_kernel.  The groups with the best bounds are scored, usually holding
+// kBounds: the groups' values are those of search_bound_kernel.  The groups with the best bounds are scored, usually holding
 // the answer: then no other group's bound reaches the k-th best score found, and that is all.  Groups whose bound does are scored
 // as well, while they are few; of a query with more of them (rows alike by the thousand, or values so far from the origin that
-// the bounds say nothing) idx[b][0] is set to kUnsure, and the two launches that follow search it on the vector ALUs.
-template <typename T, int NT, bool L2, bool BOUNDS>
+// the bounds say nothing) idx[b][0] is set to kUnsure, and the two launches that follow search it on the vector ALUs, the second of them kUnsureOnly.
+enum { kPlain = 0, kBounds = 1, kUnsureOnly = 2 };
+template <typename T, int NT, bool L2, int KIND>
 __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {   // (rows that fit in LDS, or 0)
   typedef RowPiece<T> Piece;
+  constexpr bool BOUNDS = KIND == kBounds;
   constexpr int P = Piece::P, RPT = NT / 8;   // rows per step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   uint64_t* lists = reinterpret_cast<uint64_t*>(smem);        // [NT] for the selections
@@ -1519,7 +1525,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
   __shared__ uint64_t found[BOUNDS ? kMaxK : 1];    // the best so far
   __shared__ int more[BOUNDS ? kMoreGroups : 1];    // groups still to be scored
   __shared__ int n_more;
-  if (!BOUNDS && a.unsure && (*a.unsure == 0 || a.idx[(size_t)b * a.k] != kUnsure)) return;
+  if (KIND == kUnsureOnly && (*a.unsure == 0 || a.idx[(size_t)b * a.k] != kUnsure)) return;
   const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
   for (int e = tid; e < ((a.E + 3) & ~3); e += NT) qf[e] = e < a.E ? (float)q[e] : 0.f;
 
@@ -1702,7 +1708,9 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
   };
   best = block_best(best, 0);   // (qf is there, too)
   const int first = (int)~(uint32_t)best;
-  best = score_group(first);
+  const int own_row = min(first * a.rows + (tid >> 3), a.N - 1), own_entry = part8 == 0 ? entry_of(a, own_row) : -1;   // (with the rows)
+  const uint64_t own = score_group(first);
+  best = own;
   float qq = 0.f;
   for (int e = lane; e < a.E; e += kWave) qq = fmaf(qf[e], qf[e], qq);
 #pragma unroll
@@ -1738,8 +1746,9 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
     const int i = best ? (int)~(uint32_t)best : kIdxNone;
     a.idx[b] = i == kIdxNone ? -1 : i;
     a.score[b] = top;
-    write_hit(a, b, top, i);
+    if (many > 0 || best == 0) write_hit(a, b, top, i);
   }
+  if (many == 0 && part8 == 0 && own == best && best != 0) write_entry(a, b, key_score((uint32_t)(best >> 32)), own_entry);
 }
 
 // ------------------------------------------------------------- both phases in one launch
@@ -1952,18 +1961,18 @@ static hipError_t launch_f16_phase1(const SearchArgs& a, int nqb, dim3 grid, siz
 // pick from, or many or very wide rows to re-score (those of k groups, or of all there are); below that the barriers of
 // sixteen waves cost more.  Time with them over time without, 8 queries: 256 rows of 1,024 bytes 1.10,
 // 512 of them 0.84; 64 rows of 4,800 bytes 0.90, 256 of them 1.18; 128 rows of 9,600 bytes 0.83, 256 0.89.
-template <typename T, int NT, bool L2, bool BOUNDS>
+template <typename T, int NT, bool L2, int KIND>
 static hipError_t launch_topk_n(SearchArgs a, hipStream_t stream) {
   const size_t lists = (size_t)NT * 8 + kMaxK * 4, query = (size_t)((a.E + 3) & ~3) * 4;
-  const size_t cand = (size_t)(BOUNDS && a.k < 4 ? 4 : a.k) * a.rows * 4;
+  const size_t cand = (size_t)(KIND == kBounds && a.k < 4 ? 4 : a.k) * a.rows * 4;
   const int in_lds = lists + query + cand <= 62 * 1024 ? (int)(cand / 4) : 0;   // the rows' scores: in LDS, else in the workspace
   const size_t lds = lists + query + (in_lds ? cand : 0);
-  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT, L2, BOUNDS>>(lds);
+  hipError_t e = ensure_lds<&finalize_topk_kernel<T, NT, L2, KIND>>(lds);
   if (e != hipSuccess) return e;
   constexpr int kFit = (int)(kGridThreads / NT);   // queries of a launch
   for (a.q0 = 0; e == hipSuccess && a.q0 < a.B; a.q0 += a.nq) {
     a.nq = a.B - a.q0 < kFit ? a.B - a.q0 : kFit;
-    hipLaunchKernelGGL((finalize_topk_kernel<T, NT, L2, BOUNDS>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
+    hipLaunchKernelGGL((finalize_topk_kernel<T, NT, L2, KIND>), dim3((unsigned)a.nq), dim3(NT), lds, stream, a, in_lds);
     e = hipGetLastError();
   }
   return e;
@@ -1975,12 +1984,12 @@ static bool topk_large(const SearchArgs& a, size_t esz) {
 template <typename T>
 static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
   const bool large = topk_large(a, sizeof(T));
-  if (a.metric) return large ? launch_topk_n<T, 1024, true, false>(a, stream) : launch_topk_n<T, 256, true, false>(a, stream);
-  return large ? launch_topk_n<T, 1024, false, false>(a, stream) : launch_topk_n<T, 256, false, false>(a, stream);
+  if (a.metric) return large ? launch_topk_n<T, 1024, true, kPlain>(a, stream) : launch_topk_n<T, 256, true, kPlain>(a, stream);
+  return large ? launch_topk_n<T, 1024, false, kPlain>(a, stream) : launch_topk_n<T, 256, false, kPlain>(a, stream);
 }
 template <typename T, bool L2>
 static hipError_t launch_bounded_finish(const SearchArgs& a, hipStream_t stream) {
-  if (a.k > 1) return launch_topk_n<T, 1024, L2, true>(a, stream);
+  if (a.k > 1) return launch_topk_n<T, 1024, L2, kBounds>(a, stream);
   hipLaunchKernelGGL((finalize_bound1_kernel<T, L2>), dim3((unsigned)a.B), dim3(1024), ((size_t)a.E + 7) / 8 * 32, stream, a);
   return hipGetLastError();
 }
@@ -2092,17 +2101,24 @@ static hipError_t launch_small(const SearchArgs& a, hipStream_t stream) {
 
 constexpr int kUnsureTiles = 768;   // workgroups: three a compute unit, as many as its LDS holds
 
-template <typename T, bool L2, bool TOPK>
+template <typename T, bool L2>
 static hipError_t launch_unsure_k(SearchArgs a, hipStream_t stream) {
   a.nq = a.B;
-  hipLaunchKernelGGL((search_unsure_kernel<T, L2, 4, TOPK>), dim3(kUnsureTiles), dim3(kThreads), 0, stream, a);
+  if (a.k > 1)
+    hipLaunchKernelGGL((search_unsure_kernel<T, L2, 4, true>), dim3(kUnsureTiles), dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((search_unsure_kernel<T, L2, 4, false>), dim3(kUnsureTiles), dim3(kThreads), 0, stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (a.k > 1) return launch_topk_n<T, 1024, L2, kUnsureOnly>(a, stream);
+  hipLaunchKernelGGL((finalize_top1_kernel<true>), dim3((unsigned)a.B), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }
 template <typename T>
 static hipError_t launch_unsure(const SearchArgs& a, hipStream_t stream) {
-  if (a.metric) return a.k > 1 ? launch_unsure_k<T, true, true>(a, stream) : launch_unsure_k<T, true, false>(a, stream);
+  if (a.metric) return launch_unsure_k<T, true>(a, stream);
   if constexpr (std::is_same<T, f16_t>::value) return hipErrorInvalidValue;   // (fp16 inner products have no bounds)
-  else return a.k > 1 ? launch_unsure_k<T, false, true>(a, stream) : launch_unsure_k<T, false, false>(a, stream);
+  else return launch_unsure_k<T, false>(a, stream);
 }
 
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
@@ -2175,8 +2191,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
                    : p.metric ? launch_bounded<float, true>(a, stream)
                               : launch_bounded<float, false>(a, stream);
     if (e != hipSuccess) return e;
-    e = p.is_f16 ? launch_unsure<f16_t>(a, stream) : launch_unsure<float>(a, stream);
-    if (e != hipSuccess) return e;
+    return p.is_f16 ? launch_unsure<f16_t>(a, stream) : launch_unsure<float>(a, stream);
   } else {
     const hipError_t e = p.is_f16 ? launch_valu<f16_t>(a, stream) : launch_valu<float>(a, stream);
     if (e != hipSuccess) return e;
@@ -2185,7 +2200,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   if (p.k == 1 && mode == kModeMfmaBig) {
     hipLaunchKernelGGL(finalize_top1_block_kernel, dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
   } else if (p.k == 1) {
-    hipLaunchKernelGGL(finalize_top1_kernel, dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL((finalize_top1_kernel<false>), dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
   } else {
     return p.is_f16 ? launch_topk<f16_t>(a, stream) : launch_topk<float>(a, stream);
   }
