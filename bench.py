@@ -71,7 +71,9 @@ def exact_flops(w, n_items, dense_equivalent=False):
 def apply_kernel_name(w):
     if w.map_dtype != "bf16":
         return "apply_f32_kernel"
-    return "apply_bf16_kernel" if w.seq_len <= 128 else "apply_bf16_long_kernel"
+    if w.seq_len > 128:
+        return "apply_bf16_long_kernel"
+    return "apply_bf16_kernel" if w.seq_len == 128 and w.head_dim == 64 and w.causal else "apply_bf16_short_kernel"
 
 
 def exact_kernel_name(w):

@@ -2,8 +2,8 @@
 // place from the database (the hit index selects the entry; nothing is
 // gathered or copied first).
 //
-// bf16 path (matrix cores, v_mfma_f32_16x16x32_bf16).  One workgroup = one
-// (query, layer, head group, block of 128 map rows).  The product is formed
+// bf16 path (matrix cores).  Three kernels: apply_bf16_short_kernel for up to 128 rows, apply_bf16_long_kernel for more, and
+// this one, v_mfma_f32_16x16x32_bf16, for many tiles of 128.  One workgroup = one (query, layer, head group).  The product is formed
 // transposed, O^T = V^T A^T, so that
 //   - the map operand is eight consecutive bf16 of one map row per lane: a
 //     plain 16-byte global load straight into the MFMA operand, no LDS;
@@ -25,6 +25,7 @@
 // HBM-bound: per (query, layer, head) the kernel moves S(S+32) map bytes
 // (causal bf16), V once per head group and O once.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "f32_tile.hpp"
@@ -40,6 +41,7 @@ struct ApplyArgs {
   int32_t M, L, layer_begin, Lc, Hq, Hkv, S;
   int32_t heads_per_wg;  // query heads handled by one workgroup (shares V)
   int32_t n_rblk;        // ceil(S / 128)
+  int32_t tiles_per_wg;  // (item, layer, KV head) of one workgroup, S <= 128
   int32_t n_tiles;       // B' * Lc * (Hq / heads_per_wg)
   int32_t tile0;         // first tile of the launch (fp32 path, see launch_apply_f32)
   int32_t fixed_entry;   // >= 0: every listed query uses maps as this single entry
@@ -52,25 +54,19 @@ __device__ __forceinline__ f32x4 mfma16_bf16(u32x4 a, u32x4 b, f32x4 c) {
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// PREFETCH: the map pieces of the next (head, chunk) step are requested before the products of
-// the current one, so a workgroup that walks several steps always has loads in flight.
-template <int D, bool CAUSAL, bool PACKED, bool PREFETCH>
-__global__ __launch_bounds__(kThreads, (D == 64 ? (PREFETCH ? 3 : 4) : 2))
-void apply_bf16_kernel(const ApplyArgs a) {
+// 128 rows of packed causal maps, 64 columns of V, many tiles (launch_apply).  PREFETCH: the map pieces of the next head are
+// requested before the products of the current one, so a workgroup that walks several heads always has loads in flight.
+template <bool PREFETCH>
+__global__ __launch_bounds__(kThreads, PREFETCH ? 3 : 4) void apply_bf16_kernel(const ApplyArgs a) {
+  constexpr int D = 64, S = kChunk, OS = D + 4;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   bf16_t* vt = reinterpret_cast<bf16_t*>(smem);                 // [D][kVtStride]
   bf16_t* ost_all = vt + D * kVtStride;                          // [4][32][D + 4]
-  constexpr int OS = D + 4;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, kq = lane >> 4;
-
-  // Block id -> (tile, 128-row block R).  The row blocks of one tile share V, and workgroups
-  // are handed to the 8 XCDs round-robin by id, so ids that differ by a multiple of 8 (same
-  // XCD, same L2) are given to one tile.  Heaviest (last) row block first.
-  const int bid = blockIdx.x;
-  const int tile = (bid >> 3) / a.n_rblk * 8 + (bid & 7);
-  const int R = a.n_rblk - 1 - (bid >> 3) % a.n_rblk;
+  const int tile = blockIdx.x;
   if (tile >= a.n_tiles) return;
   const int hgroups = a.Hq / a.heads_per_wg;
   const int hg = tile % hgroups;
@@ -87,48 +83,28 @@ void apply_bf16_kernel(const ApplyArgs a) {
     if (entry < 0 || entry >= a.M) return;   // miss (or invalid index): O[b] untouched
   }
 
-  const int S = a.S, g = a.Hq / a.Hkv;
+  const int g = a.Hq / a.Hkv;
   const int h0 = hg * a.heads_per_wg;
   const int kvh = h0 / g;
-  const int n16 = S >> 4, n32 = S >> 5;
-  const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
+  const size_t tile_elems = (size_t)packed_blocks(S, 1) * 512;
   const bf16_t* Vt_src = reinterpret_cast<const bf16_t*>(a.V) +
                          (((size_t)b * a.Lc + l) * a.Hkv + kvh) * (size_t)S * D;
   const bf16_t* A_layer = reinterpret_cast<const bf16_t*>(a.maps) +
                           ((size_t)entry * a.L + (a.layer_begin + l)) * ((size_t)a.Hq * tile_elems);
 
-  const int nloc = min(8, n16 - 8 * R);       // 16-row blocks present in this 128-row block
-  const int rA = wave, rB = 7 - wave;         // the two row blocks of this wave
-  const bool hasA = rA < nloc, hasB = rB < nloc;
-  const int n_chunk = CAUSAL ? R + 1 : (S + kChunk - 1) / kChunk;
-
-  // 16-byte operand piece of (16-row block r, 32-column block cb) for this lane
-  auto piece = [&](const bf16_t* At, int r, int cb) -> const u32x4* {
-    if (PACKED)
-      return reinterpret_cast<const u32x4*>(
-          At + (size_t)((CAUSAL ? packed_prefix(r) : r * n32) + cb) * 512 + lane * 8);
-    return reinterpret_cast<const u32x4*>(At + (size_t)(16 * r + i16) * S + 32 * cb + 8 * kq);
-  };
-  // column blocks (of the 128-column chunk c) that row blocks A and B need
-  auto steps = [&](int c, int& nA, int& nB) {
-    const int nk = min(kChunk, S - c * kChunk) >> 5;
-    const bool diag = CAUSAL && c == R;
-    nA = hasA ? (diag ? (rA >> 1) + 1 : nk) : 0;
-    nB = hasB ? (diag ? (rB >> 1) + 1 : nk) : 0;
-  };
-  auto issue = [&](const bf16_t* At, int c, u32x4 (&am)[8]) {
-    int nA, nB;
-    steps(c, nA, nB);
+  const int rA = wave, rB = 7 - wave;                         // the two 16-row blocks of this wave
+  const int nA = (rA >> 1) + 1;                               // 32-column blocks the first one needs, of five for both
+  auto issue = [&](const bf16_t* At, u32x4 (&am)[5]) {        // this lane's 16-byte operand pieces
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-      if (t < nA + nB) {
-        const bool inA = t < nA;
-        am[t] = *piece(At, 8 * R + (inA ? rA : rB), 4 * c + (inA ? t : t - nA));
-      }
+    for (int t = 0; t < 5; ++t) {
+      const bool inA = t < nA;
+      am[t] = *reinterpret_cast<const u32x4*>(
+          At + (size_t)(packed_prefix(inA ? rA : rB) + (inA ? t : t - nA)) * 512 + lane * 8);
+    }
   };
 
-  u32x4 am[8], am_next[8];
-  if (PREFETCH) issue(A_layer + (size_t)h0 * tile_elems, 0, am_next);
+  u32x4 am[5], am_next[5];
+  if (PREFETCH) issue(A_layer + (size_t)h0 * tile_elems, am_next);
   for (int hl = 0; hl < a.heads_per_wg; ++hl) {
     const int h = h0 + hl;
     const bf16_t* At = A_layer + (size_t)h * tile_elems;
@@ -138,58 +114,34 @@ void apply_bf16_kernel(const ApplyArgs a) {
       accA[db] = f32x4{0.f, 0.f, 0.f, 0.f};
       accB[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int c = 0; c < n_chunk; ++c) {
-      int nA, nB;
-      steps(c, nA, nB);
-      // 1. map pieces: requested first, so that they are in flight while V is staged
-      if (PREFETCH) {
+    // 1. map pieces: requested first, so that they are in flight while V is staged
+    if (PREFETCH) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) am[t] = am_next[t];
-      } else {
-        issue(At, c, am);
-      }
-      // 2. V^T of this chunk into LDS (once per workgroup; shared by its heads)
-      if (hl == 0 || n_chunk > 1) {
-        if (c > 0 || hl > 0) __syncthreads();
-        stage_v_transposed<D>(Vt_src + (size_t)c * kChunk * D, min(kChunk, S - c * kChunk), vt, tid);
-        __syncthreads();
-      }
-      if (PREFETCH) {
-        if (c + 1 < n_chunk) issue(At, c + 1, am_next);
-        else if (hl + 1 < a.heads_per_wg) issue(At + tile_elems, 0, am_next);
-      }
-      // 3. O^T[d][i] += sum_j V^T[d][j] A^T[j][i]
-      auto vop = [&](int db, int ks) {
-        const u32x2* src = reinterpret_cast<const u32x2*>(vt + (16 * db + i16) * kVtStride +
-                                                          32 * ks + 8 * kq);
-        u32x2 lo = src[0], hi = src[1];
-        return u32x4{lo.x, lo.y, hi.x, hi.y};
-      };
-      if (nA == 4 && nB == 4) {
-        // full chunk: both row blocks need the same four column blocks, so every V^T operand
-        // read from LDS feeds two products (LDS bandwidth, not HBM, would bound long rows else)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int db = 0; db < D / 16; ++db) {
-            const u32x4 v = vop(db, t);
-            accA[db] = mfma16_bf16(v, am[t], accA[db]);
-            accB[db] = mfma16_bf16(v, am[t + 4], accB[db]);
-          }
-      } else {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          if (t < nA) {
-#pragma unroll
-            for (int db = 0; db < D / 16; ++db) accA[db] = mfma16_bf16(vop(db, t), am[t], accA[db]);
-          } else if (t < nA + nB) {
-#pragma unroll
-            for (int db = 0; db < D / 16; ++db)
-              accB[db] = mfma16_bf16(vop(db, t - nA), am[t], accB[db]);
-          }
-        }
-      }
+      for (int t = 0; t < 5; ++t) am[t] = am_next[t];
+    } else {
+      issue(At, am);
     }
+    // 2. V^T into LDS (once per workgroup; shared by its heads)
+    if (hl == 0) {
+      stage_v_transposed<D>(Vt_src, S, vt, tid);
+      __syncthreads();
+    }
+    if (PREFETCH && hl + 1 < a.heads_per_wg) issue(At + tile_elems, am_next);
+    // 3. O^T[d][i] += sum_j V^T[d][j] A^T[j][i]
+    auto vop = [&](int db, int ks) {
+      const u32x2* src = reinterpret_cast<const u32x2*>(vt + (16 * db + i16) * kVtStride + 32 * ks + 8 * kq);
+      u32x2 lo = src[0], hi = src[1];
+      return u32x4{lo.x, lo.y, hi.x, hi.y};
+    };
+    auto product = [&](f32x4 (&acc)[D / 16], int t, int ks) {
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db) acc[db] = mfma16_bf16(vop(db, ks), am[t], acc[db]);
+    };
+    product(accA, 0, 0);   // (the first row block needs one or two of the five)
+    if (nA == 2) product(accA, 1, 1);
+    else product(accB, 1, 0);
+#pragma unroll
+    for (int t = 2; t < 5; ++t) product(accB, t, t - nA);
 
     // 4. result registers: out[row i16 of the block][d = 16 db + 4 kq + v].  Both row blocks go
     // through a wave-private LDS buffer so that global stores are contiguous 16-byte pieces.
@@ -208,25 +160,152 @@ void apply_bf16_kernel(const ApplyArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    bf16_t* Ot = reinterpret_cast<bf16_t*>(a.O) +
-                 ((((size_t)b * a.Lc + l) * a.Hq + h) * S + (size_t)R * kChunk) * D;
+    bf16_t* Ot = reinterpret_cast<bf16_t*>(a.O) + ((((size_t)b * a.Lc + l) * a.Hq + h) * S) * D;
     constexpr int PIECES = 32 * D / 8;
 #pragma unroll
     for (int it = 0; it < PIECES / kWave; ++it) {
       const int p = it * kWave + lane;
       const int row = p / (D / 8), c8 = p % (D / 8);
-      const bool low = row < 16;
-      if (low ? hasA : hasB) {
-        const u32x2* s = reinterpret_cast<const u32x2*>(ost + row * OS + 8 * c8);
-        u32x2 x = s[0], y = s[1];
-        u32x4 w = {x.x, x.y, y.x, y.y};
-        const int lrow = low ? 16 * rA + row : 16 * rB + row - 16;
-        // written once, never re-read by this kernel: streaming store
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(Ot + (size_t)lrow * D + 8 * c8));
-      }
+      const u32x2* s = reinterpret_cast<const u32x2*>(ost + row * OS + 8 * c8);
+      u32x2 x = s[0], y = s[1];
+      u32x4 w = {x.x, x.y, y.x, y.y};
+      const int lrow = row < 16 ? 16 * rA + row : 16 * rB + row - 16;
+      // written once, never re-read by this kernel: streaming store
+      __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(Ot + (size_t)lrow * D + 8 * c8));
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Sequences of up to 128 rows.  With the kernel above a workgroup has one (item, layer, K/V head) and its heads one after the
+// other, 128 map rows at a time: of 32 rows two of its four waves would have none, and LDS for 128 keys of 128 columns leaves room for two
+// workgroups on a compute unit.  Here a wave takes units of 32 rows of one head, the next unit's map pieces on their way
+// during the products of this one, the workgroup as many K/V heads as give its waves a unit each, and LDS holds their V
+// and no more.  V is copied and read as in the long kernel below.
+// us per call, with 128 rows at a time / so: 118 x 16 x 3 heads on one K/V head of 32 x 128, half of them misses 21.3 / 9.2; 100 x 32 x 8 of 32 x
+// 128 160 / 74; 123 x 2 x 16 on 4 of 64 x 64 17.3 / 11.2; 100 x 4 x 24 on 12 of 64 x 128 51.4 / 35.1; 64 x 4 x 32 of 96 x 128 95 / 75;
+// 64 x 16 x 32 of 96 x 64 213 / 186 (5.4 TB/s); a small one, 11 x 4 x 3 on one of 96 x 128 11.6 / 5.9.  Bound by the memory where it is large
+// (64 x 8 x 32 on 8 of 128 x 128, 161 us, 5.0 TB/s), else by the chain hit -> map, V -> products -> stores.
+template <int D, bool CAUSAL, bool PACKED, int NRB>
+__global__ __launch_bounds__(kThreads, (D == 64 ? (NRB == 4 ? 3 : 4) : NRB == 4 ? 2 : 3)) void apply_bf16_short_kernel(const ApplyArgs a) {
+  constexpr int S = 32 * NRB, PPR = D / 8, NCOPY = S * PPR / kWave / 4;   // copy instructions per wave and tile
+  constexpr int kMostTiles = 4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  bf16_t* vb = reinterpret_cast<bf16_t*>(smem);   // [tiles_per_wg][S][D]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31, kh = lane >> 5;
+  bf16_t* ost = vb + (size_t)a.tiles_per_wg * S * D + wave * (16 * kSmallOutStride);
+  const int g = a.Hq / a.Hkv, per = g * NRB;      // units of a tile
+  const int tile0 = blockIdx.x / a.n_rblk * a.tiles_per_wg, part = blockIdx.x % a.n_rblk;   // (n_rblk: parts of a tile's units)
+  const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
+
+  // the tiles: query (-1: a miss, past the end or an invalid index) and entry
+  int qb[kMostTiles], entry[kMostTiles];
+#pragma unroll
+  for (int t = 0; t < kMostTiles; ++t) {
+    qb[t] = -1;
+    entry[t] = 0;
+    if (t < a.tiles_per_wg && tile0 + t < a.n_tiles) {
+      const int bslot = (tile0 + t) / (a.Hkv * a.Lc);
+      if (a.fixed_entry >= 0) {
+        qb[t] = a.q_list[bslot];
+      } else {
+        entry[t] = a.hit[bslot];
+        qb[t] = entry[t] >= 0 && entry[t] < a.M ? bslot : -1;
+      }
+    }
+  }
+  if (max(max(qb[0], qb[1]), max(qb[2], qb[3])) < 0) return;   // nothing to do
+  struct Unit { int t, head, rb; };
+  // (rows rotate with the head, so that a causal map's heavy ones fall to all waves in turn)
+  auto unit = [&](int u) {
+    const int head = u % per / NRB;
+    return Unit{u / per, head, (u + head) % NRB};
+  };
+  auto query = [&](int t) { return t == 0 ? qb[0] : t == 1 ? qb[1] : t == 2 ? qb[2] : qb[3]; };
+  auto entry_at = [&](int t) { return t == 0 ? entry[0] : t == 1 ? entry[1] : t == 2 ? entry[2] : entry[3]; };
+  auto layer_of = [&](int t) { return (tile0 + t) / a.Hkv % a.Lc; };
+  auto head_of = [&](const Unit& w) { return (tile0 + w.t) % a.Hkv * g + w.head; };
+
+  // 16 columns of 32 map rows a step: eight elements of row il
+  struct Pieces { u32x4 p[2 * NRB]; };
+  auto steps = [&](const Unit& w) { return CAUSAL ? 2 * (w.rb + 1) : 2 * NRB; };
+  auto issue = [&](int u) {
+    Pieces m;
+    const Unit w = unit(u);
+    if (query(w.t) < 0) return m;
+    const bf16_t* At = reinterpret_cast<const bf16_t*>(a.maps) +
+                       (((size_t)entry_at(w.t) * a.L + (a.layer_begin + layer_of(w.t))) * a.Hq + head_of(w)) * tile_elems;
+    const int r16 = 2 * w.rb + (il >> 4);
+    const unsigned row = PACKED ? (unsigned)((CAUSAL ? packed_prefix(r16) : r16 * NRB) * 512 + (kh * 16 + (il & 15)) * 8)
+                                : (unsigned)((32 * w.rb + il) * S + 8 * kh);
+#pragma unroll
+    for (int ks = 0; ks < 2 * NRB; ++ks)
+      if (ks < steps(w)) m.p[ks] = *reinterpret_cast<const u32x4*>(At + ks * (PACKED ? 256 : 16) + row);
+    return m;
+  };
+
+  const int u_end = a.n_rblk > 1 ? min(4 * part + 4, per) : a.tiles_per_wg * per;
+  int u = 4 * part + wave;
+  Pieces now;
+  if (u < u_end) now = issue(u);
+  // copy instruction wave + 4 i of a tile fills its LDS slots [64 k, 64 k + 64), 16-byte piece p of row r at p ^ v_piece_swizzle(r)
+  const int slot0 = kWave * wave + lane;
+  const unsigned copy_off = (unsigned)((slot0 / PPR) * D + 8 * ((slot0 % PPR) ^ v_piece_swizzle<D>(slot0 / PPR)));
+#pragma unroll
+  for (int t = 0; t < kMostTiles; ++t)
+    if (qb[t] >= 0) {
+      const bf16_t* src = reinterpret_cast<const bf16_t*>(a.V) +
+                          (((size_t)qb[t] * a.Lc + layer_of(t)) * a.Hkv + (tile0 + t) % a.Hkv) * (size_t)(S * D);
+#pragma unroll
+      for (int i = 0; i < NCOPY; ++i)
+        __builtin_amdgcn_global_load_lds(src + (copy_off + 2048u * i), vb + t * (S * D) + kWave * 8 * (wave + 4 * i), 16, 0, 0);
+    }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  int voff[2][D / 32];   // as in the long kernel
+#pragma unroll
+  for (int half = 0; half < 2; ++half)
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db) {
+      const int t = lane & 15, j = 8 * kh + 4 * half + (t >> 2), d0 = 32 * db + 16 * (il >> 4) + 4 * (t & 3);
+      voff[half][db] = j * D + 8 * ((d0 >> 3) ^ v_piece_swizzle<D>(j)) + (d0 & 7);
+    }
+  for (; u < u_end; u += 4) {
+    Pieces next;
+    if (u + 4 < u_end) next = issue(u + 4);
+    const Unit w = unit(u);
+    const int b = query(w.t);
+    if (b >= 0) {
+      const bf16_t* v = vb + w.t * (S * D);
+      f32x16 acc[D / 32];
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) acc[db][x] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 2 * NRB; ++ks)
+        if (ks < steps(w)) {
+#pragma unroll
+          for (int db = 0; db < D / 32; ++db) {
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (s16x4 __attribute__((address_space(3)))*)(v + voff[0][db] + 16 * ks * D));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (s16x4 __attribute__((address_space(3)))*)(v + voff[1][db] + 16 * ks * D));
+            const s16x8 op = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            acc[db] = mfma_bf16(__builtin_bit_cast(bf16x8, op), __builtin_bit_cast(bf16x8, now.p[ks]), acc[db]);
+          }
+        }
+      bf16_t* out = reinterpret_cast<bf16_t*>(a.O) +
+                    ((((size_t)b * a.Lc + layer_of(w.t)) * a.Hq + head_of(w)) * S + 32 * w.rb) * (size_t)D;
+      store_tile_bf16_small<D>(acc, 1.0f, ost, out, lane);
+    }
+    now = next;
   }
 }
 
@@ -704,29 +783,14 @@ static hipError_t launch_apply_f32(ApplyArgs a, int D, int causal, hipStream_t s
   return hipSuccess;
 }
 
-static size_t apply_lds_bytes(int D) {
-  return (size_t)(D * kVtStride + 4 * 32 * (D + 4)) * sizeof(bf16_t);
-}
+// Up to so many workgroups of four units each take a tile's units side by side, each with its own copy of V.
+constexpr size_t kShortSplit = 1024;
 
-template <int D, bool CAUSAL, bool PACKED, bool PREFETCH>
-static hipError_t launch_bf16(const ApplyArgs& a, dim3 grid, hipStream_t stream) {
-  const size_t lds = apply_lds_bytes(D);
-  hipError_t e = ensure_lds<&apply_bf16_kernel<D, CAUSAL, PACKED, PREFETCH>>(lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((apply_bf16_kernel<D, CAUSAL, PACKED, PREFETCH>), grid, dim3(kThreads), lds,
-                     stream, a);
+template <bool PREFETCH>
+static hipError_t launch_halves(const ApplyArgs& a, hipStream_t stream) {
+  constexpr size_t lds = (size_t)(64 * kVtStride + 4 * 32 * (64 + 4)) * sizeof(bf16_t);
+  hipLaunchKernelGGL((apply_bf16_kernel<PREFETCH>), dim3((unsigned)a.n_tiles), dim3(kThreads), lds, stream, a);
   return hipGetLastError();
-}
-
-template <int D, bool CAUSAL>
-static hipError_t launch_bf16_dc(const ApplyArgs& a, dim3 grid, bool packed, bool prefetch,
-                                 hipStream_t stream) {
-  if (packed) {
-    return prefetch ? launch_bf16<D, CAUSAL, true, true>(a, grid, stream)
-                    : launch_bf16<D, CAUSAL, true, false>(a, grid, stream);
-  }
-  return prefetch ? launch_bf16<D, CAUSAL, false, true>(a, grid, stream)
-                  : launch_bf16<D, CAUSAL, false, false>(a, grid, stream);
 }
 
 template <int D, bool CAUSAL, bool PACKED>
@@ -745,6 +809,30 @@ static hipError_t launch_long_d(const ApplyArgs& a, int tiles8, bool causal, boo
                             : launch_long<D, true, false>(a, tiles8, stream);
   return packed ? launch_long<D, false, true>(a, tiles8, stream)
                 : launch_long<D, false, false>(a, tiles8, stream);
+}
+
+static hipError_t launch_short(ApplyArgs a, int D, int S, bool causal, bool packed, int nb, hipStream_t stream) {
+  const int units = a.Hq / a.Hkv * (S >> 5);
+  a.n_tiles = nb * a.Lc * a.Hkv;
+  a.tiles_per_wg = units < 4 ? 4 / units : 1;
+  a.n_rblk = 1;
+  if (units > 4 && (size_t)a.n_tiles * ((units + 3) / 4) <= kShortSplit) a.n_rblk = (units + 3) / 4;
+  const dim3 grid((unsigned)((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg * a.n_rblk));
+  const size_t lds = ((size_t)a.tiles_per_wg * S * D + 4 * 16 * kSmallOutStride) * sizeof(bf16_t);
+  auto go = [&](auto d, auto c, auto pk, auto nrb) {
+    hipLaunchKernelGGL((apply_bf16_short_kernel<decltype(d)::value, decltype(c)::value, decltype(pk)::value, decltype(nrb)::value>),
+                       grid, dim3(kThreads), lds, stream, a);
+    return hipGetLastError();
+  };
+  auto rows = [&](auto d, auto c, auto pk) {
+    return S == 32   ? go(d, c, pk, std::integral_constant<int, 1>{})
+           : S == 64 ? go(d, c, pk, std::integral_constant<int, 2>{})
+           : S == 96 ? go(d, c, pk, std::integral_constant<int, 3>{})
+                     : go(d, c, pk, std::integral_constant<int, 4>{});
+  };
+  auto layout = [&](auto d, auto c) { return packed ? rows(d, c, std::true_type{}) : rows(d, c, std::false_type{}); };
+  auto mask = [&](auto d) { return causal ? layout(d, std::true_type{}) : layout(d, std::false_type{}); };
+  return D == 64 ? mask(std::integral_constant<int, 64>{}) : mask(std::integral_constant<int, 128>{});
 }
 
 // Host launcher.  Shapes were validated by the caller (api.hip).
@@ -777,22 +865,23 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
     if (p.D <= 128) return launch_apply_f32<2>(a, p.D, p.causal, stream);
     return launch_apply_f32<4>(a, p.D, p.causal, stream);
   }
+  // 128 rows of packed causal maps of 64 columns of V, many tiles: the kernel with the two balanced 16-row blocks a wave is
+  // as fast or faster.  us per call, that one / units of 32 rows: 120 x 8 x 24 heads on 2 K/V heads 78 / 84, 32 x 16 x 32 on 32 147 / 147,
+  // 35 x 16 x 16 on 4 53.3 / 53.4, 16 x 2 x 32 on 8 (256 tiles) 11.8 / 11.7, 8 x 2 x 32 on 8 11.3 / 6.9.  All others gain: 128 columns,
+  // 64 x 8 x 32 heads on 8 170 / 161, 3 x 16 on 8, dense 10.1 / 6.3; dense maps, 64 columns, 16 x 6 x 32 on 8 29.0 / 24.0; no mask,
+  // 60 x 8 x 24 on 12 80.5 / 72.7.
+  const bool halves = p.S == 128 && p.D == 64 && p.causal && p.packed && (size_t)nb * p.Lc * p.Hkv > 512;
+  if (p.S <= 128 && !halves) return launch_short(a, p.D, p.S, p.causal, p.packed, nb, stream);
   a.n_rblk = (p.S + kChunk - 1) / kChunk;
   const int g = p.Hq / p.Hkv;
-  a.heads_per_wg = (a.n_rblk == 1) ? g : 1;
+  a.heads_per_wg = halves ? g : 1;
   a.n_tiles = nb * p.Lc * (p.Hq / a.heads_per_wg);
   const int tiles8 = (a.n_tiles + 7) / 8 * 8;
-  const dim3 grid((unsigned)(tiles8 * a.n_rblk));
-  if (a.n_rblk > 1)   // long rows: 32-row blocks per wave, full-rate matrix instruction
+  if (!halves)   // long rows: 32-row blocks per wave, full-rate matrix instruction
     return p.D == 64 ? launch_long_d<64>(a, tiles8, p.causal, p.packed, stream)
                      : launch_long_d<128>(a, tiles8, p.causal, p.packed, stream);
   // a workgroup that walks several heads prefetches the next head's map pieces
-  const bool prefetch = a.heads_per_wg > 1;
-  if (p.D == 64)
-    return p.causal ? launch_bf16_dc<64, true>(a, grid, p.packed, prefetch, stream)
-                    : launch_bf16_dc<64, false>(a, grid, p.packed, prefetch, stream);
-  return p.causal ? launch_bf16_dc<128, true>(a, grid, p.packed, prefetch, stream)
-                  : launch_bf16_dc<128, false>(a, grid, p.packed, prefetch, stream);
+  return g > 1 ? launch_halves<true>(a, stream) : launch_halves<false>(a, stream);
 }
 
 hipError_t launch_pack_maps(const void* dense, void* packed, int64_t n_tiles, int32_t S,
