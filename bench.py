@@ -79,7 +79,7 @@ def apply_kernel_name(w):
 def exact_kernel_name(w):
     if w.map_dtype != "bf16":
         return "exact_f32_kernel"
-    return "exact_bf16_kernel (resident)" if w.seq_len <= 128 else "exact_bf16_kernel (streaming)"
+    return "exact_bf16_short_kernel" if w.seq_len <= 128 else "exact_bf16_kernel (streaming)"
 
 
 # --------------------------------------------------------------------- timing helpers

@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattncache.so")
 SOURCES = ["api.hip", "apply.hip", "exact.hip", "insert.hip", "project.hip", "search.hip"]
-HEADERS = ["common.hpp", "f32_tile.hpp", "launch.hpp", "row_stream.hpp", "split_tile.hpp", os.path.join("..", "..", "include", "attncache.h")]
+HEADERS = ["common.hpp", "f32_tile.hpp", "launch.hpp", "row_stream.hpp", "short_tile.hpp", "split_tile.hpp", os.path.join("..", "..", "include", "attncache.h")]
 ARG = os.path.join(HERE, "_tensor_arg.so")
 ARG_SOURCE = "tensor_arg.cpp"
 

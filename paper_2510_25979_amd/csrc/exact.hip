@@ -1,8 +1,10 @@
 // Recompute branch of Algorithm 2: O = softmax(scale * Q K^T) V, causal or
 // dense, without ever writing the S x S map (flash-style online softmax).
 //
-// bf16 path (matrix cores, v_mfma_f32_32x32x16_bf16), one kernel in two variants and a second one:
-//   * resident (S <= 128): one workgroup = one (batch item, KV head); both 64-key chunks of K
+// bf16 path (matrix cores, v_mfma_f32_32x32x16_bf16), one kernel in two variants and two more:
+//   * short (S <= 128): K and V of one or several K/V heads in LDS, a wave takes units of 32 query rows of one head
+//     (short_tile.hpp);
+//   * resident (S <= 128, routed launches of many tiles): one workgroup = one (batch item, KV head); both 64-key chunks of K
 //     and V are copied into LDS once and the workgroup walks all g query heads that share
 //     them; after the one barrier behind the copy its four waves never meet again;
 //   * streaming (S > 128): one workgroup = four units of 32 query rows of the heads that share K
@@ -24,7 +26,9 @@
 #include "common.hpp"
 #include "f32_tile.hpp"
 #include "launch.hpp"
+#include "short_tile.hpp"
 #include "split_tile.hpp"
+#include <type_traits>
 
 namespace ac {
 
@@ -948,6 +952,43 @@ static hipError_t launch_exact_bf16(const ExactArgs& a, dim3 grid, hipStream_t s
                        : launch_exact_bf16_r<D, CAUSAL, false>(a, grid, stream);
 }
 
+// Sequences of up to 128 keys (short_tile.hpp); us per call, the resident kernel / this one: 64 x 12 heads
+// of 64 x 64, padded 7.6 / 7.4; 128 x 12 of 32 x 64 9.9 / 7.4; 192 x 8 of 32 x 128 (1,536 units) 17.4 / 11.2; 100 x 32 of 64 x 128 44 / 36; 51 x 8 on 2
+// of 96 x 64 10.8 / 7.2; 48 x 8 on one of 128 x 64 (1,536 units) 21.5 / 7.9; 64 x 512 of 128 x 64, causal 399 / 357 (6.0 TB/s), half of them
+// routed away 197 / 187, all 5.5 / 23.  Bound by the memory where it is large, else by the chain of Q, K and V -> scores -> weights -> products -> stores.
+template <int D, bool CAUSAL, int NRB>
+__global__ __launch_bounds__(kThreads, 2) void exact_bf16_short_kernel(const ShortArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char short_smem[];
+  short_attention<D, CAUSAL, NRB, false>(
+      a, reinterpret_cast<bf16_t*>(short_smem), [](const ShortUnit&, int, const u32x4 (&)[2]) {}, [](const ShortUnit&, int) {});
+}
+
+static ShortArgs exact_short_args(const ExactLaunch& p, float scale_log2e) {
+  ShortArgs a;
+  a.Q = static_cast<const bf16_t*>(p.Q); a.K = static_cast<const bf16_t*>(p.K); a.V = static_cast<const bf16_t*>(p.V);
+  a.O = static_cast<bf16_t*>(p.O); a.row_sel = p.row_sel; a.key_len = p.key_len;
+  a.Hq = p.Hq; a.Hkv = p.Hkv; a.Lc = 1; a.n_tiles = p.B * p.Hkv; a.scale_log2e = scale_log2e;
+  return a;
+}
+static hipError_t launch_exact_short(const ExactLaunch& p, const ShortArgs& a, unsigned grid, hipStream_t stream) {
+  const size_t lds = short_lds(a, p.S, p.D);
+  auto go = [&](auto d, auto c, auto nrb) {
+    constexpr auto kernel = &exact_bf16_short_kernel<decltype(d)::value, decltype(c)::value, decltype(nrb)::value>;
+    const hipError_t e = ensure_lds<kernel>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, stream, a);
+    return hipGetLastError();
+  };
+  auto rows = [&](auto d, auto c) {
+    return p.S == 32   ? go(d, c, std::integral_constant<int, 1>{})
+           : p.S == 64 ? go(d, c, std::integral_constant<int, 2>{})
+           : p.S == 96 ? go(d, c, std::integral_constant<int, 3>{})
+                       : go(d, c, std::integral_constant<int, 4>{});
+  };
+  auto mask = [&](auto d) { return p.causal ? rows(d, std::true_type{}) : rows(d, std::false_type{}); };
+  return p.D == 64 ? mask(std::integral_constant<int, 64>{}) : mask(std::integral_constant<int, 128>{});
+}
+
 constexpr int kSplitWaves = 4;   // eight: 8 heads of 1024 x 128 16.1 us, four 14.0
 template <int D, bool CAUSAL>
 static hipError_t launch_exact_split(const ExactArgs& a, size_t units, hipStream_t stream) {
@@ -970,22 +1011,24 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
     return launch_exact_f32<4>(a, p.D, p.causal, scale, stream);
   }
   const size_t units = (size_t)p.B * p.Hq * (p.S / 32);
-  // One unit per workgroup while that leaves room on the chip (as above).  The resident kernel walks
-  // the heads of a group one after the other and is left later where there are several, or one
-  // block of keys.  us per call, split / not: 8 heads of 1024 x 128 causal (256 units) 14.0 / 23.7, 64 of
-  // 288 x 128 (576) 12.2 / 10.2, 64 of 288 x 64 (576) 7.6 / 7.9, 24 of 512 x 64 dense (384) 9.0 / 9.7, 64
-  // of 512 x 64 (1,024) 14.0 / 11.3; 128 of 128 x 128 (512) 7.8 / 8.4, 160 (640) 9.8 / 8.0, 160 on 40 K and V
-  // (640) 10.0 / 16.0; 256 of 128 x 64 (1,024) 7.8 / 6.7, on 64 K and V 8.9 / 15.6; 640 of 32 x 128 8.5 / 9.7, but
-  // 600 on 150 K and V 8.8 / 7.1: two workgroups fit on a compute unit, the 513th begins a second round, which
-  // pays only where the resident kernel walks one head (few workgroups per XCD) or many.
-  // The lines lie where neither side loses more than 0.6 us over S; so some measured winners are beyond them.
+  // One unit per workgroup while that leaves room on the chip (as above).  us per call, split / not: 8 heads of 1024 x 128 causal
+  // (256 units) 14.0 / 23.7, 64 of 288 x 128 (576) 12.2 / 10.2, 64 of 288 x 64 (576) 7.6 / 7.9, 24 of 512 x 64 dense (384) 9.0 / 9.7, 64
+  // of 512 x 64 (1,024) 14.0 / 11.3.  Up to 128 keys: 64 heads of 128 x 128 (256) 7.5 / 8.2, 96 (384) 8.7 / 8.3; 256 of 32 x 64 (256)
+  // 5.1 / 5.6, 384 5.7 / 5.8, 192 pairs (384) 5.6 / 5.5, 192 of 64 x 64, causal (384) 5.9 / 6.0, 256 (512) 6.2 / 6.4, 96 of 128 x 64, causal (384)
+  // 6.4 / 6.7, 128 (512) 6.7 / 6.8, not causal (384) 7.4 / 6.4.
   const int g = p.Hq / p.Hkv;
   const size_t most = p.S > 128 ? (p.D == 64 ? 576 : 320) / (p.causal ? 1 : 2)
-                      : p.S > 32 && g == 1 ? (p.causal ? 512 : 256)
-                      : p.D == 64 ? 1024 : p.S == 32 && g > 1 && g < 8 ? 512 : 640;
+                      : p.D == 64 && p.causal && (p.S == 128 || (g == 1 && p.S <= 64)) ? 512 : p.D == 64 ? 320 : 256;
   if (units <= most) {
     if (p.D == 64) return p.causal ? launch_exact_split<64, true>(a, units, stream) : launch_exact_split<64, false>(a, units, stream);
     return p.causal ? launch_exact_split<128, true>(a, units, stream) : launch_exact_split<128, false>(a, units, stream);
+  }
+  if (p.S <= 128) {
+    // A routed launch of many tiles may find few of them to do: the resident kernel tests 64 at a time, here each costs the launch
+    // of a workgroup (32,768 tiles, none to do, 5.5 us and 23).
+    ShortArgs sa = exact_short_args(p, a.scale_log2e);
+    const unsigned wgs = short_plan(sa, p.S, p.D);
+    if (!p.row_sel || wgs <= 2048) return launch_exact_short(p, sa, wgs, stream);
   }
   const int u8 = (a.n_kvtiles + 7) / 8 * 8;
   const int per_u = a.n_rblk == 1 ? 1 : (g * (p.S / 32) + 3) / 4;   // workgroups of a K/V tile

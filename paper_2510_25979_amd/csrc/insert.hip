@@ -25,7 +25,9 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "short_tile.hpp"
 #include "split_tile.hpp"
+#include <type_traits>
 
 namespace ac {
 
@@ -505,6 +507,9 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_split_kernel(const In
 }
 
 template <int D, bool CAUSAL, bool PACKED>
+static hipError_t launch_insert_short(const InsertArgs& a, hipStream_t stream);
+
+template <int D, bool CAUSAL, bool PACKED>
 static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t stream) {
   // One unit per workgroup while that leaves room on the chip (beyond, K and V, which only the other
   // kernel shares between rows, cost more).  Up to 128 keys the other kernel walks the heads of a group
@@ -518,6 +523,15 @@ static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t st
   const size_t most = a.S > 128 ? (CAUSAL ? (D == 64 ? 768 : 480) : (D == 64 ? 448 : 320))
                       : g == 1  ? (a.S > 64 ? 128 : 0)
                                 : std::min(1024, g * (D == 64 ? 256 : a.S > 64 ? 176 : 128));
+  // Up to 128 rows: one pass over the keys (below) wherever the launch is not small.  us per call, split or two passes / one: two heads on one K and
+  // V, 32 rows of 64 (384 units) 6.9 / 6.4, 96 rows (384) 7.4 / 7.7, (768) 10.5 / 8.0, 128 x 128 (256) 8.7 / 9.8, (384) 14.0 / 9.8; one head each, 32 x 64 (768)
+  // 7.0 / 7.4, (1,024) 8.9 / 7.5, 64 x 64 (1,536) 8.3 / 9.1, (2,048) 12.1 / 10.0, 64 x 128 (1,024) 9.1 / 9.5, (1,536) 16.8 / 13.5, 128 x 128 (768)
+  // 10.0 / 10.1, (1,024) 11.1 / 10.8; 64 x 16 x 32 heads of 32 x 64 (49,152) 295 / 163, of 64 x 64 204 / 170, 32 on 8 of 128 x 128 262 / 249.
+  // Dense causal maps of 128 x 64 are slower so for some thousands of units: 23.3 / 25.7, 18.4 / 20.0.
+  const size_t few = g > 1 ? (a.S >= 96 && D == 64 ? 576 : 320)
+                     : a.S == 32 ? (D == 64 ? 896 : 576) : a.S == 64 ? (D == 64 ? 1792 : 1152) : 1024;
+  const bool slower = CAUSAL && !PACKED && D == 64 && a.S == 128 && units > 1800 && units < 10000;
+  if (a.S <= kChunk && units > few && !slower) return launch_insert_short<D, CAUSAL, PACKED>(a, stream);
   if (units <= most) {
     hipLaunchKernelGGL((insert_bf16_split_kernel<D, CAUSAL, PACKED>), dim3((unsigned)units), dim3(kThreads), 0, stream, a);
     return hipGetLastError();
@@ -527,6 +541,92 @@ static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t st
   else
     hipLaunchKernelGGL((insert_bf16_kernel<D, CAUSAL, PACKED, false>), grid, dim3(kThreads), 0, stream, a);
   return hipGetLastError();
+}
+
+// Sequences of up to 128 rows (short_tile.hpp): the scores of a row are all there before its first weight is, so one pass does.
+template <int D, bool CAUSAL, bool PACKED, int NRB>
+__global__ __launch_bounds__(kThreads, 2) void insert_bf16_short_kernel(const ShortArgs s, const InsertArgs a) {
+  constexpr int S = 32 * NRB;
+  extern __shared__ __attribute__((aligned(16))) unsigned char short_smem[];
+  const int lane = threadIdx.x & 63, il = lane & 31, kh = lane >> 5;
+  const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
+  auto slot_of = [&](int b) {   // -1: compute O only
+    const int entry = a.slot ? a.slot[b] : -1;
+    return entry < a.M ? entry : -1;
+  };
+  int slots[kShortTiles];   // of the workgroup's tiles
+#pragma unroll
+  for (int t = 0; t < kShortTiles; ++t) {
+    const int tile = blockIdx.x / s.parts * s.tiles_per_wg + t, b = tile / (s.Hkv * s.Lc);
+    slots[t] = -1;
+    if (t >= s.tiles_per_wg || tile >= s.n_tiles) continue;
+    slots[t] = slot_of(b);
+    // the item's first workgroup also copies its feature vector into the same slot
+    if (a.feat && blockIdx.x % s.parts == 0 && tile % (s.Hkv * s.Lc) == 0 && slots[t] >= 0 && !(a.row_sel && a.row_sel[b] >= 0))
+      for (int p = threadIdx.x; p < a.feat_pieces; p += kThreads)
+        a.emb[(size_t)slots[t] * a.feat_pieces + p] = a.feat[(size_t)b * a.feat_pieces + p];
+  }
+  auto slot_at = [&](int t) { return t == 0 ? slots[0] : t == 1 ? slots[1] : t == 2 ? slots[2] : slots[3]; };
+  auto map_of = [&](const ShortUnit& w, int entry) {
+    const int l = w.tile / s.Hkv % s.Lc;
+    return reinterpret_cast<bf16_t*>(a.maps) + (((size_t)entry * a.L + (a.layer_begin + l)) * a.Hq + w.head) * tile_elems;
+  };
+  // where register group q4 (scores 4 q4 .. 4 q4 + 3 of this lane) of key block kb goes
+  auto map_piece = [&](const ShortUnit& w, bf16_t* At, int kb, int q4) -> u32x2* {
+    const int r16 = 2 * w.rb + (il >> 4);
+    if (PACKED)
+      return reinterpret_cast<u32x2*>(At + (size_t)((CAUSAL ? packed_prefix(r16) : r16 * NRB) + kb) * 512 +
+                                      (16 * q4 + (il & 15)) * 8 + 4 * kh);
+    return reinterpret_cast<u32x2*>(At + (size_t)(32 * w.rb + il) * S + 32 * kb + 8 * q4 + 4 * kh);
+  };
+  short_attention<D, CAUSAL, NRB, true>(
+      s, reinterpret_cast<bf16_t*>(short_smem),
+      [&](const ShortUnit& w, int jb, const u32x4 (&p)[2]) {
+        const int entry = slot_at(w.t);
+        if (entry < 0) return;
+        bf16_t* At = map_of(w, entry);
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          if constexpr (PACKED) {
+            *map_piece(w, At, jb, 2 * s2) = u32x2{p[s2].x, p[s2].y};
+            *map_piece(w, At, jb, 2 * s2 + 1) = u32x2{p[s2].z, p[s2].w};
+          } else {   // 16 bytes a row, as above
+            uint32_t x = p[s2].x, y = p[s2].y, z = p[s2].z, v = p[s2].w;
+            swap_halves(x, z);
+            swap_halves(y, v);
+            *reinterpret_cast<u32x4*>(map_piece(w, At, jb, 2 * s2 + kh) - kh) = u32x4{x, y, z, v};
+          }
+        }
+      },
+      [&](const ShortUnit& w, int n) {   // zeros: blocks in the padding and, in a dense causal map, right of the diagonal block
+        const int entry = slot_at(w.t);
+        if (entry < 0) return;
+        bf16_t* At = map_of(w, entry);
+        for (int kb = n; kb < (PACKED && CAUSAL ? w.rb + 1 : NRB); ++kb)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) *map_piece(w, At, kb, q4) = u32x2{0u, 0u};
+      });
+}
+
+template <int D, bool CAUSAL, bool PACKED>
+static hipError_t launch_insert_short(const InsertArgs& a, hipStream_t stream) {
+  ShortArgs s;
+  s.Q = static_cast<const bf16_t*>(a.Q); s.K = static_cast<const bf16_t*>(a.K); s.V = static_cast<const bf16_t*>(a.V);
+  s.O = static_cast<bf16_t*>(a.O); s.row_sel = a.row_sel; s.key_len = a.key_len;
+  s.Hq = a.Hq; s.Hkv = a.Hkv; s.Lc = a.Lc; s.n_tiles = a.n_tiles; s.scale_log2e = a.scale_log2e;
+  const dim3 grid(short_plan(s, a.S, D));
+  const size_t lds = short_lds(s, a.S, D);
+  auto go = [&](auto nrb) {
+    constexpr auto kernel = &insert_bf16_short_kernel<D, CAUSAL, PACKED, decltype(nrb)::value>;
+    const hipError_t e = ensure_lds<kernel>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), lds, stream, s, a);
+    return hipGetLastError();
+  };
+  return a.S == 32   ? go(std::integral_constant<int, 1>{})
+         : a.S == 64 ? go(std::integral_constant<int, 2>{})
+         : a.S == 96 ? go(std::integral_constant<int, 3>{})
+                     : go(std::integral_constant<int, 4>{});
 }
 
 template <int D>

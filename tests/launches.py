@@ -3,7 +3,7 @@ HIP runtime (launch_recorder.c), in a process of its own, without a GPU.
 
 record(calls) -> one (status, [(kernel, grid_x, grid_y, grid_z, block, lds), ...]) per call; apply_f32_small_kernel
 adds the (query, layer, head) that its launch starts with.  A call is
-("search", N, E, B, k, "f16"|"f32", "ip"|"l2"), ("exact", B, Hq, Hkv, S, D, causal, "bf16"|"f32"),
+("search", N, E, B, k, "f16"|"f32", "ip"|"l2"), ("exact", B, Hq, Hkv, S, D, causal, "bf16"|"f32"[, routed]),
 ("insert", B, Lc, Hq, Hkv, S, D, causal, packed), ("apply", B, Lc, Hq, Hkv, S, D, causal, "bf16"|"f32") or
 ("project", B, S, dm, hid, E, "bf16"|"f32", "f16"|"f32", biases[, bytes of workspace])."""
 import ctypes
@@ -60,8 +60,8 @@ def _main(rec, path):
             h = db(N, E, F16 if emb == "f16" else F32, int(metric == "l2"), 1, 1, 1, 1, 8, 32, F32, 1, 0)
             st = L.attncache_search(h, p, B, k, f32(0.5), p, p, p, p, sz(HUGE), None)
         elif fn == "exact":
-            B, Hq, Hkv, S, D, causal, dt = c
-            st = L.attention_exact(p, p, p, p, None, None, B, Hq, Hkv, S, D, BF16 if dt == "bf16" else F32, int(causal),
+            B, Hq, Hkv, S, D, causal, dt, *routed = c
+            st = L.attention_exact(p, p, p, p, p if any(routed) else None, None, B, Hq, Hkv, S, D, BF16 if dt == "bf16" else F32, int(causal),
                                    f32(0), None)
         elif fn == "insert":
             B, Lc, Hq, Hkv, S, D, causal, packed = c

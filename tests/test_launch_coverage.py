@@ -10,6 +10,7 @@ from tests import test_gpu_parity_small as small
 from tests import test_gpu_projector as proj
 from tests import test_gpu_row_units as rows
 from tests import test_gpu_search_tiles as tiles
+from tests import test_gpu_short_attention as short
 from tests import test_gpu_split_units as split
 
 # fp16 rows of more than 2,360 columns, more than 64 queries and 128 groups: 5e9 products and more for
@@ -67,6 +68,8 @@ def test_every_attention_kernel_is_reached(tmp_path):
     calls += [("exact", *c, "f32") for c in f32.CASES]
     calls += [("exact", len(c[6]) * n, *c[:5], _dt(c[5])) for c in split.CASES for n in (1, split.copies(c))]
     calls += [("insert", *c, packed) for c in small.INSERT_CASES for packed in (False, True)]
+    calls += [("exact", *c, "bf16", routed) for c in short.EXACT_CASES for routed in (False, True)]
+    calls += [("insert", *c, packed) for c in short.INSERT_CASES for packed in (False, True)]
     calls += [("apply", c[0], c[9], *c[3:8], _dt(c[10])) for c in small.APPLY_CASES]
     calls += [("apply", c[0], 2, *c[1:], "f32") for c in f32.CASES]
     missing = _kernels("exact_", "insert_", "apply_f32") - _reached(tmp_path, calls)
