@@ -396,7 +396,8 @@ def run_insert(ac, args, traffic, w, Q, K, V):
     dbi.close()
     g = Hq // Hkv
     nbytes = (S * D * 2 * (2 + 2 / g) + tile * 2) * B * L * Hq
-    kernel = "insert_bf16_kernel"
+    two_passes = S > 128 or (D == 128 and S == 128 and w.causal and B * L * Hq * S // 32 > 100000)
+    kernel = "insert_bf16_kernel" if two_passes else "insert_bf16_short_kernel"
     reading = traffic.lookup(kernel, w.name, "packed") if not args.entries else None
     return {"ms": ms, "tokens_per_s": B * S / (ms * 1e-3),
             "roofline": {"kernel": kernel, "bound": "hbm",

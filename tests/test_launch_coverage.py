@@ -165,3 +165,16 @@ def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
                  for bytes in ((), (ws,))]
         got = launches.record(calls, tmp_path)
         assert got[::2] == got[1::2] and all(status == 0 for status, _ in got)
+
+
+@pytest.mark.parametrize("case,kernel", [
+    ((64, 16, 32, 32, 128, 64, True, True), "insert_bf16_short_kernel<64, true, true"),
+    ((64, 12, 32, 32, 128, 128, True, True), "insert_bf16_short_kernel<128, true, true"),   # us, two passes over the keys 651, one 639
+    ((64, 16, 32, 32, 128, 128, True, True), "insert_bf16_kernel<128, true, true"),         # 852, 874
+    ((64, 16, 32, 32, 128, 64, True, False), "insert_bf16_kernel<64, true, false"),         # 618, 788
+    ((64, 8, 32, 32, 96, 128, True, False), "insert_bf16_kernel<128, true, false"),         # 354, 382
+    ((64, 8, 32, 16, 128, 128, True, False), "insert_bf16_short_kernel<128, true, false"),  # 415, 405
+], ids=str)
+def test_large_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp_path, case, kernel):
+    (status, ls), = launches.record([("insert", *case)], tmp_path)
+    assert status == 0 and ls[0][0].startswith(kernel), ls
