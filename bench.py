@@ -79,7 +79,11 @@ def apply_kernel_name(w):
 def exact_kernel_name(w):
     if w.map_dtype != "bf16":
         return "exact_f32_kernel"
-    return "exact_bf16_short_kernel" if w.seq_len <= 128 else "exact_bf16_kernel (streaming)"
+    if w.seq_len > 128:
+        return "exact_bf16_kernel (streaming)"
+    rows = w.batch * w.n_layers * w.n_q_heads * w.seq_len
+    shared = w.causal and w.head_dim == 128 and w.seq_len == 128 and w.n_q_heads > w.n_kv_heads
+    return "exact_bf16_kernel (resident)" if shared and rows // 32 > 200000 else "exact_bf16_short_kernel"
 
 
 # --------------------------------------------------------------------- timing helpers

@@ -1025,10 +1025,12 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
   }
   if (p.S <= 128) {
     // A routed launch of many tiles may find few of them to do: the resident kernel tests 64 at a time, here each costs the launch
-    // of a workgroup (32,768 tiles, none to do, 5.5 us and 23).
+    // of a workgroup (32,768 tiles, none to do, 5.5 us and 23).  Very large causal launches of 128 x 128 with shared K and V are faster
+    // there too: 2,048 x 32 heads on 16 (262,144 units) 1,210 / 1,290 us, 4,096 x 32 on 8 1,997 / 2,008, 1,024 x 32 on 8 (131,072) 497 / 494.
+    const bool slower = p.causal && p.D == 128 && p.S == 128 && g > 1 && units > 200000;
     ShortArgs sa = exact_short_args(p, a.scale_log2e);
     const unsigned wgs = short_plan(sa, p.S, p.D);
-    if (!p.row_sel || wgs <= 2048) return launch_exact_short(p, sa, wgs, stream);
+    if (!slower && (!p.row_sel || wgs <= 2048)) return launch_exact_short(p, sa, wgs, stream);
   }
   const int u8 = (a.n_kvtiles + 7) / 8 * 8;
   const int per_u = a.n_rblk == 1 ? 1 : (g * (p.S / 32) + 3) / 4;   // workgroups of a K/V tile
