@@ -534,7 +534,7 @@ static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t st
   const size_t few = g > 1 ? (a.S >= 96 && D == 64 ? 576 : 320)
                      : a.S == 32 ? (D == 64 ? 896 : 576) : a.S == 64 ? (D == 64 ? 1792 : 1152) : 1024;
   const bool slower = PACKED ? CAUSAL && D == 128 && a.S == 128 && units > 100000
-                             : a.S >= 96 && ((CAUSAL && D == 64 && units > 1800) || (g == 1 && units > 10000));
+                             : a.S >= 96 && (g == 1 || (CAUSAL && D == 64)) && units > (CAUSAL && D == 64 && a.S == 128 ? 1800 : 10000);
   if (a.S <= kChunk && units > few && !slower) return launch_insert_short<D, CAUSAL, PACKED>(a, stream);
   if (units <= most) {
     hipLaunchKernelGGL((insert_bf16_split_kernel<D, CAUSAL, PACKED>), dim3((unsigned)units), dim3(kThreads), 0, stream, a);
