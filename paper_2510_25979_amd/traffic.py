@@ -20,10 +20,10 @@ Regenerate (from the repo root, on a GPU machine; ``cd /tmp && export TMPDIR=/tmp`` 
     python3 -m paper_2510_25979_amd.traffic --fetch <dirF> --write <dirW> \
         --workload llama-3.2-1b-shaped --layout packed --kernel apply_bf16_kernel
     python3 -m paper_2510_25979_amd.traffic --fetch <dirF> --write <dirW> \
-        --workload llama-3.2-1b-shaped --kernel exact_bf16_kernel --largest
+        --workload llama-3.2-1b-shaped --kernel exact_bf16_short_kernel --largest
 
 (the same with ``--workload 3 --workloads 3`` / ``4`` and the kernels that serve them:
-``apply_bf16_kernel`` and ``apply_bf16_long_kernel``).
+``apply_bf16_short_kernel`` and ``exact_bf16_kernel``; ``apply_bf16_long_kernel``).
 """
 from __future__ import annotations
 
