@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void insert_bf16_kerne
 
   // Every lane has the running maximum and the sum of ITS keys of a row (half of them); the halves meet between the passes.
   // (The lowest finite value stands for "none yet": a lane may see no key in the first blocks.)
-  float m_run = kNoScore, l_run = 0.f, m_all = 0.f;
+  float m_run = kNoScore, l_run = 0.f, inv_l = 0.f;
   f32x16 acc[D / 32];
   // where register group q4 (scores 4 q4 .. 4 q4 + 3 of this lane) of 32-key block kb goes
   const int r16 = (r0 >> 4) + (il >> 4);
@@ -234,15 +234,16 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void insert_bf16_kerne
     for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2e, -m));
     return sum;
   };
-  // Second pass: normalised weights 2^(score - m_all), m_all = m + log2 l, rounded, stored, multiplied with V.
+  // Second pass: normalised weights 2^(score - m) / l, rounded, stored, multiplied with V.  (log2 l is not added to m: the rounding of
+  // m is the same in l and cancels, that of the sum would not: rows of scores around 1e6 added up to anything from 0.96 to 1.04.)
   auto weigh = [&](const f32x16& s, const bf16_t* vb, int kb32, int jb) {
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
       u32x4 pw;
 #pragma unroll
       for (int w = 0; w < 4; ++w)
-        pw[w] = pack_bf16(__builtin_amdgcn_exp2f(fmaf(s[8 * s2 + 2 * w], a.scale_log2e, -m_all)),
-                          __builtin_amdgcn_exp2f(fmaf(s[8 * s2 + 2 * w + 1], a.scale_log2e, -m_all)));
+        pw[w] = pack_bf16(__builtin_amdgcn_exp2f(fmaf(s[8 * s2 + 2 * w], a.scale_log2e, -m_run)) * inv_l,
+                          __builtin_amdgcn_exp2f(fmaf(s[8 * s2 + 2 * w + 1], a.scale_log2e, -m_run)) * inv_l);
       if (keep) {
         if constexpr (PACKED) {   // 256-byte runs either way
           *map_piece(kb32, 2 * s2) = u32x2{pw.x, pw.y};
@@ -274,7 +275,8 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? 3 : 2)) void insert_bf16_kerne
   };
   auto join_halves = [&]() {
     const float m = max_with_other_half(m_run), l = l_run * __builtin_amdgcn_exp2f(m_run - m);
-    m_all = m + __builtin_amdgcn_logf(l + __shfl_xor(l, 32));
+    inv_l = 1.0f / (l + __shfl_xor(l, 32));
+    m_run = m;
   };
   // All chunks of the row block, chunk c in stage c & 1; two per trip so that the stages are named statically (the
   // compiler then knows that the copy in flight and the reads of the other stage do not meet).  The second pass takes them
