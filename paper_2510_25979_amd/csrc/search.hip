@@ -49,7 +49,8 @@ struct SearchArgs {
   float* part_s;           // [B][G] best score of each group (k > 1: kNoRow where no row ranks)
   int32_t* part_i;         // [B][G] its row (k = 1 only)
   float* cand;             // [B][k * rows] scores of the selected groups' rows (k > 1 only)
-  int32_t* unsure;         // 1 where a query is left open: the launches that get it search those with idx[b][0] == kUnsure
+  int32_t* unsure;         // 1 where a query is left open: the launches that get it search those with idx[b][0] == kUnsure, whose
+                           // score[b][0] is the k-th best score found
   int32_t* idx;
   float* score;
   int32_t* hit;
@@ -709,16 +710,17 @@ struct TileSlice {
   }
 };
 
-template <typename T, bool L2, int QW, bool TOPK, typename Index>
-__device__ __forceinline__ void search_valu_tile(const SearchArgs& a, Index tile, int nqb, float* el, float* ql) {
+template <typename T, bool L2, int QW, bool TOPK>
+__global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs a) {
   constexpr int R = kValuRowsPerWg / kWave;   // rows of a lane
+  __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
+  __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];   // 4 QW <= 32 rows used
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // the query blocks of one group get ids equal mod 8: one XCD reads the group's rows once
-  const Index slot = tile >> 3;
-  const int gidx = (int)(slot / nqb) * 8 + (int)(tile & 7), q0 = a.q0 + (int)(slot % nqb) * (4 * QW);
+  const int nqb = (a.nq + 4 * QW - 1) / (4 * QW), slot = blockIdx.x >> 3;
+  const int gidx = slot / nqb * 8 + (blockIdx.x & 7), q0 = a.q0 + slot % nqb * (4 * QW);
   if (gidx >= (a.N + kValuRowsPerWg - 1) / kValuRowsPerWg) return;
-  const int q_end = min(a.q0 + a.nq, q0 + 4 * QW);
   const T* emb = reinterpret_cast<const T*>(a.emb);
   const T* qs = reinterpret_cast<const T*>(a.q);
   const int row0 = gidx * kValuRowsPerWg;
@@ -730,6 +732,7 @@ __device__ __forceinline__ void search_valu_tile(const SearchArgs& a, Index tile
     for (int j = 0; j < QW; ++j) acc[r][j] = 0.f;
   TileSlice<T, kValuRowsPerWg * 8 / kThreads> es;
   TileSlice<T, 1> qt;
+  const int q_end = min(a.q0 + a.nq, q0 + 4 * QW);
   es.load(emb, row0, a.N, a.E, 0, tid);
   qt.load(qs, q0, q_end, a.E, 0, tid);
   for (int e0 = 0; e0 < a.E; e0 += kTileCols) {
@@ -804,28 +807,6 @@ __device__ __forceinline__ void search_valu_tile(const SearchArgs& a, Index tile
   }
 }
 
-template <typename T, bool L2, int QW, bool TOPK>
-__global__ __launch_bounds__(kThreads) void search_valu_kernel(const SearchArgs a) {
-  __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
-  __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];   // 4 QW <= 32 rows used
-  search_valu_tile<T, L2, QW, TOPK>(a, (int)blockIdx.x, (a.nq + 4 * QW - 1) / (4 * QW), el, ql);
-}
-
-// The same for the queries that bounds have left open (below): usually none, so the grid is one that is quickly through.
-template <typename T, bool L2, int QW, bool TOPK>
-__global__ __launch_bounds__(kThreads) void search_unsure_kernel(const SearchArgs a) {
-  __shared__ __attribute__((aligned(16))) float el[kValuRowsPerWg * kTileLd];
-  __shared__ __attribute__((aligned(16))) float ql[kThreads / 8 * kTileLd];
-  if (*a.unsure == 0) return;
-  const int nqb = (a.nq + 4 * QW - 1) / (4 * QW);
-  const int64_t tiles = ((int64_t)a.N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * nqb;
-  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int q = a.q0 + (int)((tile >> 3) % nqb) * (4 * QW) + (threadIdx.x & 63);   // a wave looks at the tile's queries
-    if (__ballot((threadIdx.x & 63) < 4 * QW && q < a.q0 + a.nq && a.idx[(size_t)min(q, a.B - 1) * a.k] == kUnsure))
-      search_valu_tile<T, L2, QW, TOPK>(a, tile, nqb, el, ql);
-  }
-}
-
 // ---------------------------------------------------------------- phase 1, bounds from the matrix cores
 // Binary32 inner products and Euclidean distances of a larger search: the tiles above are bound by the vector ALUs (two
 // instructions per element of q - e), a contraction on the matrix cores would lose digits where it cancels.  So the matrix
@@ -843,6 +824,14 @@ __global__ __launch_bounds__(kThreads) void search_unsure_kernel(const SearchArg
 __host__ __device__ inline float bound_slack(int E) { return 0x1p-16f + (float)(E + 16) * 0x1p-20f; }
 constexpr float kBoundMost = 0x1p100f;   // larger magnitudes of a bound, or of its parts, are not relied on
 constexpr float kBoundLeast = 0x1p-90f;  // what products lost below the smallest normal numbers add up to, at most
+
+// What the bound of a row has to reach that may score s with a query of |q|^2 = qq; -infinity where bounds are not relied on.
+template <bool L2>
+__device__ __forceinline__ float bound_reach(float s, float qq, int E) {
+  const float c = bound_slack(E), reach = s - 0x1p-20f * fabsf(s) + (L2 ? (1.f - c) * qq : -0.5f * c * qq) - kBoundLeast;
+  return qq < kBoundMost && reach > -kBoundMost ? reach : -INFINITY;
+}
+__host__ __device__ inline int bound_query(int E) { return ((E + 15) & ~15) + kQPad; }   // 16-bit elements of a staged query
 
 template <typename T> struct BoundParts;   // eight columns of a row or query as operands of the matrix cores
 template <>
@@ -899,6 +888,11 @@ struct BoundPiece<float> {
     }
   }
   __device__ __forceinline__ void parts(BoundParts<float>& p) const { p.set(a, b); }
+  __device__ __forceinline__ void load_whole(const float* row, int c0, int kh) {   // (16-byte aligned)
+    a = *reinterpret_cast<const f32x4*>(row + c0 + 4 * kh);
+    b = *reinterpret_cast<const f32x4*>(row + c0 + 4 * kh + 8);
+  }
+  __device__ __forceinline__ void values(f32x4& x, f32x4& y) const { x = a; y = b; }
   __device__ __forceinline__ float squares(float s) const {
 #pragma unroll
     for (int t = 0; t < 4; ++t) s = fmaf(a[t], a[t], fmaf(b[t], b[t], s));
@@ -917,6 +911,14 @@ struct BoundPiece<f16_t> {
     }
   }
   __device__ __forceinline__ void parts(BoundParts<f16_t>& p) const { p.p[0] = a; }
+  __device__ __forceinline__ void load_whole(const f16_t* row, int c0, int kh) { a = *reinterpret_cast<const f16x8*>(row + c0 + 8 * kh); }
+  __device__ __forceinline__ void values(f32x4& x, f32x4& y) const {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      x[t] = (float)a[t];
+      y[t] = (float)a[4 + t];
+    }
+  }
   __device__ __forceinline__ float squares(float s) const {
 #pragma unroll
     for (int t = 0; t < 8; ++t) s = fmaf((float)a[t], (float)a[t], s);
@@ -924,23 +926,24 @@ struct BoundPiece<f16_t> {
   }
 };
 
-template <typename T, bool L2, int NQB>
-__global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs a) {
-  typedef BoundParts<T> Parts;
+// The products of rows [row_begin, row_end) with queries [q0, q0 + nq), up to 32 NQB.  done(pass, rb, acc, part, all, same) has those of
+// the wave's rows rb .. rb + 31 in each of the passes of 128 rows: acc[qb][v] = <row rb + mfma_row(v, kh), query 32 qb + il>, that
+// row's share of the bound in part[v >> 2][v & 3], and whether the block has a row whose bound is not relied on.
+// kAgain and kCentred (search_unsure_kernel): bit t > 0 of `same` is set where rows rb + t and rb + t - 1 are the same, and qq[t] is |q|^2
+// of query t.  kCentred: row row_begin is subtracted from rows and queries first, which leaves their distance as it is.
+// LDS: qs [Parts::N][32 NQB][QS]; own [4][32]; qq [32 NQB] (not kFirst); ref [QS] (kCentred).
+enum { kFirst = 0, kAgain = 1, kCentred = 2 };
+template <typename T, bool L2, int NQB, int MODE, typename Done>
+__device__ __forceinline__ void bound_products(const SearchArgs& a, int row_begin, int row_end, int q0, int nq, uint16_t* qs, float* own,
+                                               T* ref, float* qq, Done done) {
+  typedef BoundParts<std::conditional_t<MODE == kCentred, float, T>> Parts;
   typedef BoundPiece<T> Piece;
   typedef typename Parts::op op;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int E = a.E, nks = (E + 15) >> 4, QS = 16 * nks + kQPad;   // 16-bit elements of a staged query
-  uint16_t* qs = reinterpret_cast<uint16_t*>(smem);                // [Parts::N][32 NQB][QS]
-  float* red = reinterpret_cast<float*>(qs + (size_t)Parts::N * 32 * NQB * QS);   // [4][32 NQB]
-  float* own = red + 4 * 32 * NQB;                                                // [4][32]
+  const int E = a.E, nks = (E + 15) >> 4, QS = bound_query(E);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int il = lane & 31, kh = lane >> 5;
-  const int q0 = 32 * NQB * blockIdx.y, nq = min(a.B - q0, 32 * NQB);
   const T* emb = reinterpret_cast<const T*>(a.emb);
-  const int row_begin = blockIdx.x * a.wg_rows, row_end = min(row_begin + a.wg_rows, a.N);
-  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *a.unsure = 0;
 
   struct Four { Piece p[4]; };
   auto fetch = [&](const T* row, int ks0) {   // steps past the end repeat the last one, their products are skipped
@@ -961,6 +964,10 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
   const T* row = row_of(row_begin);
   Four now = fetch(row, 0);   // on its way while the queries are staged
 
+  const T* ref_row = emb + (size_t)row_begin * E;
+  if (MODE == kCentred)
+    for (int c = tid; c < 16 * nks; c += kThreads) ref[c] = c < E ? ref_row[c] : (T)0.f;
+  float own_qq[NQB] = {};
   // eight threads a query; a thread's pieces of all query blocks are in flight together
 #pragma unroll 2
   for (int c = tid & 7; c < 2 * nks; c += 8) {   // half step
@@ -972,10 +979,36 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
       Parts p;
-      w[qb].parts(p);
+      if constexpr (MODE == kFirst) {
+        w[qb].parts(p);
+      } else {
+        f32x4 x, y;
+        w[qb].values(x, y);
+        if constexpr (MODE == kCentred) {
+          Piece r;
+          f32x4 rx, ry;
+          r.load(ref_row, 16 * (c >> 1), c & 1, E, 16 * (c >> 1) + 16 <= E);
+          r.values(rx, ry);
+          x -= rx;
+          y -= ry;
+          p.set(x, y);
+        } else {
+          w[qb].parts(p);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) own_qq[qb] = fmaf(x[t], x[t], fmaf(y[t], y[t], own_qq[qb]));
+      }
 #pragma unroll
       for (int n = 0; n < Parts::N; ++n)
         *reinterpret_cast<op*>(qs + (size_t)(32 * NQB * n + 32 * qb + (tid >> 3)) * QS + 8 * c) = p.p[n];
+    }
+  }
+  if (MODE != kFirst) {
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) {
+#pragma unroll
+      for (int off = 1; off < 8; off <<= 1) own_qq[qb] += __shfl_xor(own_qq[qb], off);
+      if ((tid & 7) == 0) qq[32 * qb + (tid >> 3)] = own_qq[qb];
     }
   }
   __syncthreads();
@@ -986,14 +1019,36 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
     const T* next_row = row_of(more ? pass + 128 : pass);
     f32x16 acc[NQB];
     float sq = 0.f;
+    uint32_t differ = 0;   // bits that the row does not share with the one before it
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[qb][v] = 0.f;
     auto step = [&](const Piece& piece, int ks) {
       Parts e;
-      piece.parts(e);
-      sq = piece.squares(sq);
+      if (MODE != kFirst) {   // (from the lane before it)
+        constexpr int W = sizeof(Piece) / 4;
+        typedef uint32_t words __attribute__((ext_vector_type(W)));
+        const words w = __builtin_bit_cast(words, piece);
+#pragma unroll
+        for (int t = 0; t < W; ++t) differ |= w[t] ^ (uint32_t)__builtin_amdgcn_update_dpp((int)~w[t], (int)w[t], 0x138, 0xf, 0xf, false);
+      }
+      if constexpr (MODE == kCentred) {
+        f32x4 x, y, rx, ry;
+        piece.values(x, y);
+        Piece r;
+        r.load_whole(ref, 16 * ks, kh);
+        r.values(rx, ry);
+        x -= rx;
+        y -= ry;
+        e.set(x, y);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sq = fmaf(x[t], x[t], fmaf(y[t], y[t], sq));
+      }
+      if constexpr (MODE != kCentred) {
+        piece.parts(e);
+        sq = piece.squares(sq);
+      }
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
         Parts q;
@@ -1033,6 +1088,24 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
     f32x4 part[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) part[v] = *reinterpret_cast<const f32x4*>(own + 32 * wave + mfma_row(4 * v, kh));
+    if (MODE != kFirst) differ |= __shfl_xor((int)differ, 32);
+    done(pass, rb, acc, part, all, MODE == kFirst ? 0u : (uint32_t)__ballot(il > 0 && differ == 0));
+  }
+}
+
+template <typename T, bool L2, int NQB>
+__global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint16_t* qs = reinterpret_cast<uint16_t*>(smem);
+  float* red = reinterpret_cast<float*>(qs + (size_t)BoundParts<T>::N * 32 * NQB * bound_query(a.E));   // [4][32 NQB]
+  float* own = red + 4 * 32 * NQB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int il = lane & 31, kh = lane >> 5;
+  const int q0 = 32 * NQB * blockIdx.y, nq = min(a.B - q0, 32 * NQB);
+  const int row_begin = blockIdx.x * a.wg_rows, row_end = min(row_begin + a.wg_rows, a.N);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *a.unsure = 0;
+  auto keep = [&](int pass, int rb, const f32x16 (&acc)[NQB], const f32x4 (&part)[4], bool all, uint32_t) __attribute__((always_inline)) {
     const bool per_wave = a.rows == 32;   // a wave's 32 rows are a group
     const int gi = (per_wave ? rb : pass) / a.rows;
 #pragma unroll
@@ -1066,6 +1139,150 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
       }
       __syncthreads();
     }
+  };
+  bound_products<T, L2, NQB, kFirst>(a, row_begin, row_end, q0, nq, qs, own, (T*)nullptr, nullptr, keep);
+}
+
+// The scores of what bounds have left open: for a query with idx[b][0] == kUnsure every row whose own bound reaches score[b][0], the
+// k-th best score found so far, is scored, and the best of each group takes the place of the group's bound (kNoRow: none reaches).
+// Rows alike are few of a group, and rows far from the origin are not far from each other, so the bounds are formed again, by
+// row and (Euclidean) of the differences to one of the workgroup's rows.  A workgroup takes wg_rows rows (128 or 256) and 32 NQB queries,
+// eight threads the score of a row and query; of neighbours that are the same they take the first.  Where more than kUnsurePairs reach, all
+// are scored, eight queries to a row.  (A thread a row and query, each reading its own lines, took three times as long.)
+// Usually nothing is open, so the grid is one that is quickly through.
+// us per call, 100,000 x 128 fp32 Euclidean, 64 queries; exact scores of all rows first, / all rows of what is left open in tiles / so: 40 rows
+// at random places alike for each query 58 / 75 / 48; all rows of 40 kinds 59 / 77 / 58; rows 100 times their spread from the origin 57 / 73 / 47; all
+// rows the same 58 / 75 / 58.  Two kinds in random order, of which every third row reaches, 57 / 73 / 168.
+constexpr int kUnsurePairs = 2048;   // (twice as many cost fp16 rows of 256 columns the second workgroup of a compute unit)
+template <typename T, bool L2, int NQB, int MODE>
+__global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const SearchArgs a) {
+  typedef RowPiece<T> Piece;
+  constexpr int P = Piece::P, NQ = 32 * NQB, Parts = MODE == kCentred ? 2 : BoundParts<T>::N;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  __shared__ uint16_t pairs[kUnsurePairs * NQB];   // row of the workgroup << 6 | query
+  __shared__ uint32_t top[NQ][8];                  // best of the query's rows 32 t .. 32 t + 31
+  __shared__ int n_pairs;
+  if (*a.unsure == 0) return;
+  uint16_t* qs = reinterpret_cast<uint16_t*>(smem);
+  T* ref = reinterpret_cast<T*>(qs + (size_t)Parts * NQ * bound_query(a.E));
+  float* own = reinterpret_cast<float*>(ref + bound_query(a.E));
+  float* qq = own + 4 * 32;
+  T* raw = reinterpret_cast<T*>(smem);             // [NQ][QE], once the products are done
+  const int QE = (a.E + 7) & ~7;
+  const int tid = threadIdx.x, lane = tid & 63, il = lane & 31, kh = lane >> 5;
+  const int nqb = (a.B + NQ - 1) / NQ, n_rows = (a.N + a.wg_rows - 1) / a.wg_rows;
+  const int64_t units = ((int64_t)n_rows + 7) / 8 * 8 * nqb;   // (the query blocks of the same rows on one XCD)
+  for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
+    const int ri = (int)((unit >> 3) / nqb) * 8 + (int)(unit & 7), q0 = (int)((unit >> 3) % nqb) * NQ;
+    if (ri >= n_rows) continue;
+    const int row0 = ri * a.wg_rows, row_end = min(row0 + a.wg_rows, a.N), nq = min(a.B - q0, NQ);
+    const bool open_here = lane < nq && a.idx[(size_t)(q0 + min(lane, nq - 1)) * a.k] == kUnsure;
+    const unsigned long long opens = __ballot(open_here);   // the same in all waves
+    if (opens == 0) continue;
+    for (int x = tid; x < NQ * 8; x += kThreads) top[x >> 3][x & 7] = 0;
+    if (tid == 0) n_pairs = 0;
+    float least[NQB];   // score to be reached
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) least[qb] = a.score[(size_t)(q0 + min(32 * qb + il, nq - 1)) * a.k];
+    auto note = [&](int, int rb, const f32x16 (&acc)[NQB], const f32x4 (&part)[4], bool all, uint32_t same) __attribute__((always_inline)) {
+      // rows there are, that are not the row before (whose score the group has)
+      const uint32_t rows = (rb >= row_end ? 0u : row_end - rb >= 32 ? ~0u : (1u << (row_end - rb)) - 1) & ~same;
+#pragma unroll
+      for (int qb = 0; qb < NQB; ++qb) {
+        const float reach = bound_reach<L2>(least[qb], qq[32 * qb + il], a.E);
+        uint32_t mask = 0;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float w = part[v >> 2][v & 3], bound = L2 ? fmaf(2.f, acc[qb][v], w) : acc[qb][v] + w;
+          if (all || !(bound < reach)) mask |= 1u << mfma_row(v, kh);
+        }
+        mask &= rows;
+        if (((opens >> (32 * qb + il)) & 1) == 0 || mask == 0) continue;
+        int at = atomicAdd(&n_pairs, __popc(mask));
+        for (; mask; mask &= mask - 1, ++at)
+          if (at < kUnsurePairs * NQB) pairs[at] = (uint16_t)((rb - row0 + __ffs(mask) - 1) << 6 | (32 * qb + il));
+      }
+    };
+    // (a barrier between the zeros above and note())
+    bound_products<T, L2, NQB, MODE>(a, row0, row_end, q0, nq, qs, own, ref, qq, note);
+    __syncthreads();
+    const int many = n_pairs, part8 = tid & 7;
+    // scores of eight rows and queries: a row each, or one row and eight queries in LDS; thread u of the eight has the u-th
+    auto score = [&](auto dense, const int (&r)[8], const int (&t)[8], bool live) __attribute__((always_inline)) {
+      constexpr bool DENSE = decltype(dense)::value;
+      constexpr int ROWS = DENSE ? 1 : 8;
+      float acc[8] = {};
+      auto add = [&](int c) __attribute__((always_inline)) {
+        Piece e[ROWS], x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (u < ROWS) e[u].load(reinterpret_cast<const T*>(a.emb) + (size_t)(row0 + r[u]) * a.E, c, a.E);
+          if constexpr (DENSE) x[u].w = *reinterpret_cast<const decltype(x[u].w)*>(raw + t[u] * QE + c);   // (zeros past E)
+          else x[u].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + t[u]) * a.E, c, a.E);
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const float y = e[DENSE ? 0 : u].at(i), d = x[u].at(i) - y;
+            acc[u] = L2 ? fmaf(-d, d, acc[u]) : fmaf(x[u].at(i), y, acc[u]);
+          }
+      };
+      if constexpr (DENSE) {
+#pragma unroll 4
+        for (int c = P * part8; c < a.E; c += 8 * P) add(c);
+      } else {
+#pragma unroll 1
+        for (int c = P * part8; c < a.E; c += 8 * P) add(c);
+      }
+      const float s = row_of_eight(acc, part8);
+      if (live && s == s) {
+        int mr = r[0], mt = t[0];
+#pragma unroll
+        for (int u = 1; u < 8; ++u) {
+          mr = part8 == u ? r[u] : mr;
+          mt = part8 == u ? t[u] : mt;
+        }
+        atomicMax(&top[mt][mr >> 5], score_key(s));
+      }
+    };
+    int r[8], t[8];
+    if (many <= kUnsurePairs * NQB) {
+      for (int p = tid & ~7; p < many; p += kThreads) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int pair = pairs[min(p + u, many - 1)];
+          r[u] = pair >> 6;
+          t[u] = pair & 63;
+        }
+        score(std::false_type{}, r, t, p + part8 < many);
+      }
+    } else {
+      for (int x = tid; x < NQ * QE; x += kThreads) {
+        const int c = x % QE;
+        raw[x] = c < a.E ? reinterpret_cast<const T*>(a.q)[(size_t)(q0 + min(x / QE, nq - 1)) * a.E + c] : (T)0.f;
+      }
+      __syncthreads();
+      for (int p = tid >> 3; p < (row_end - row0) * (NQ / 8); p += kThreads / 8) {   // (the eights of a wave have the same queries)
+        const int t0 = 8 * (p / (row_end - row0));
+        if (((opens >> t0) & 0xff) == 0) continue;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          r[u] = p % (row_end - row0);
+          t[u] = t0 + u;
+        }
+        score(std::true_type{}, r, t, (opens >> (t0 + part8)) & 1);
+      }
+    }
+    __syncthreads();
+    for (int x = tid; x < NQ * 8; x += kThreads) {   // groups of 32, 64 or 128 rows
+      const int t = x >> 3, per = a.rows >> 5, first = (x & 7) * a.rows;
+      if (((opens >> t) & 1) == 0 || first >= row_end - row0) continue;
+      uint32_t best = 0;
+      for (int y = (x & 7) * per; y < (x & 7) * per + per; ++y) best = max(best, top[t][y]);
+      a.part_s[(size_t)(q0 + t) * a.G + (row0 + first) / a.rows] = key_score(best);
+    }
+    __syncthreads();
   }
 }
 
@@ -1186,14 +1403,11 @@ __device__ __forceinline__ void write_hit(const SearchArgs& a, int b, float s0, 
   else write_entry(a, b, s0, entry_of(a, i0));
 }
 
-// k = 1: best of the group maxima.  UNSURE: of the queries that bounds have left open (a test at run time costs the other
-// calls 0.2 us of 9).
-template <bool UNSURE>
+// k = 1: best of the group maxima.
 __global__ __launch_bounds__(kThreads) void finalize_top1_kernel(const SearchArgs a) {
   __shared__ float red_s[4];
   __shared__ int red_i[4];
   const int b = blockIdx.x;
-  if (UNSURE && (*a.unsure == 0 || a.idx[b] != kUnsure)) return;
   float s = -INFINITY;
   int i = kIdxNone;
   for (int gi = threadIdx.x; gi < a.G; gi += kThreads) {
@@ -1498,8 +1712,10 @@ __device__ __forceinline__ void select_best(int n, int k, Get get, Put put, uint
   rank(m);
 }
 
-constexpr int kMoreGroups = 64;
-constexpr size_t kMoreBytes = 2 << 20;   // some 25 us of one compute unit, half of what the tiles take for 16 queries
+// Groups that a query's own workgroup scores beside the first, 0.4 us for one of 16 KB and 1.0 for one of 64: up to what
+// search_unsure_kernel takes (100,000 x 128 fp32, 64 queries, 20 such groups each: 49 us per call there, 40 here; of 64: 48 and 75).
+constexpr int kMoreGroups = 24;
+constexpr size_t kMoreBytes = 3 << 19;
 // k > 1: pick the k best groups, re-score their rows, pick the k best rows.  One workgroup per
 // query.  Rows are re-scored by eight threads each, reading 16-byte pieces side by side, four rows
 // in flight per thread.  100,000 x 256, 64 queries, k = 8: 70 us with 256-row groups, a row per
@@ -1508,8 +1724,8 @@ constexpr size_t kMoreBytes = 2 << 20;   // some 25 us of one compute unit, half
 // a selection among those, on as many compute units as queries.
 // kBounds: the groups' values are those of search_bound_kernel.  The groups with the best bounds are scored, usually holding
 // the answer: then no other group's bound reaches the k-th best score found, and that is all.  Groups whose bound does are scored
-// as well, while they are few; of a query with more of them (rows alike by the thousand, or values so far from the origin that
-// the bounds say nothing) idx[b][0] is set to kUnsure, and the two launches that follow search it on the vector ALUs, the second of them kUnsureOnly.
+// as well, while they are few; of a query with more of them (rows alike in many groups, or values far from the origin) idx[b][0] is set to
+// kUnsure, and the two launches that follow search it: search_unsure_kernel and this one as kUnsureOnly.
 enum { kPlain = 0, kBounds = 1, kUnsureOnly = 2 };
 template <typename T, int NT, bool L2, int KIND>
 __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, int cand_in_lds) {   // (rows that fit in LDS, or 0)
@@ -1623,12 +1839,10 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) qq += __shfl_xor(qq, off);
       const uint64_t kth = found[a.k - 1];
-      const float c = bound_slack(a.E), s = key_score((uint32_t)(kth >> 32));
-      float reach = s - 0x1p-20f * fabsf(s) + (L2 ? (1.f - c) * qq : -0.5f * c * qq) - kBoundLeast;
-      if (kth == 0 || !(qq < kBoundMost) || !(reach > -kBoundMost)) reach = -INFINITY;   // every one
+      const float s = kth ? key_score((uint32_t)(kth >> 32)) : -INFINITY, reach = bound_reach<L2>(s, qq, a.E);
       if (tid == 0) n_more = 0;
       __syncthreads();
-      for (int x = tid; x < a.G; x += NT)
+      for (int x = tid; x < a.G && qq == qq; x += NT)   // (of a query with NaN no row ranks)
         if (part[x] >= reach && item_key(part[x], x) < last) {
           const int at = atomicAdd(&n_more, 1);
           if (at < kMoreGroups) more[at] = x;
@@ -1638,6 +1852,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
       if (many > kMoreGroups || (size_t)many * a.rows * a.E * sizeof(T) > kMoreBytes) {
         if (tid == 0) {
           a.idx[(size_t)b * a.k] = kUnsure;
+          a.score[(size_t)b * a.k] = s;
           *a.unsure = 1;
         }
         return;
@@ -1657,8 +1872,9 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
 }
 
 // k = 1 after search_bound_kernel: the same in fewer steps.  The group with the best bound is scored, eight threads a row, then
-// every other group whose bound reaches the best score.
-template <typename T, bool L2>
+// every other group whose bound reaches the best score, four at a time.  UNSURE: after search_unsure_kernel, which leaves the best
+// scores of the groups in place of their bounds, so the first group holds the answer.
+template <typename T, bool L2, bool UNSURE>
 __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs a) {
   constexpr int NT = 1024, KEEP = 4;   // bounds of a thread that stay in registers
   typedef RowPiece<T> Piece;
@@ -1669,6 +1885,7 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
   __shared__ int more[kMoreGroups], n_more;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, part8 = tid & 7;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (UNSURE && (*a.unsure == 0 || a.idx[b] != kUnsure)) return;
   const float* part = a.part_s + (size_t)b * a.G;
   const T* q = reinterpret_cast<const T*>(a.q) + (size_t)b * a.E;
   float u[KEEP];
@@ -1686,60 +1903,79 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
     __syncthreads();
     return row_best(wave_top[which][lane & (NT / kWave - 1)]);
   };
-  auto score_group = [&](int g) {   // its rows, 128 at most; 0 where a row does not rank
-    const int r = g * a.rows + (tid >> 3);
-    if ((tid >> 3) >= a.rows || r >= a.N) return (uint64_t)0;   // (all eight threads of a row)
-    const T* row = reinterpret_cast<const T*>(a.emb) + (size_t)r * a.E;
-    float acc = 0.f;
-#pragma unroll 4
-    for (int c = P * part8; c < a.E; c += 8 * P) {
-      Piece e;
-      e.load(row, c, a.E);
+  // Best of the thread's rows of U groups of 128 rows at most; 0 where none ranks.  A row's sum takes the same steps whatever U is.
+  auto score_groups = [&](auto groups, auto group) {
+    constexpr int U = decltype(groups)::value;
+    const T* row[U];
+    int r[U];
+    float acc[U];
 #pragma unroll
-      for (int t = 0; t < P; ++t) {
-        const float d = qf[c + t] - e.at(t);
-        acc = L2 ? fmaf(-d, d, acc) : fmaf(qf[c + t], e.at(t), acc);
-      }
+    for (int u = 0; u < U; ++u) {
+      r[u] = group(u) * a.rows + (tid >> 3);
+      if ((tid >> 3) >= a.rows || r[u] >= a.N) r[u] = -1;   // (all eight threads of a row)
+      row[u] = reinterpret_cast<const T*>(a.emb) + (size_t)max(r[u], 0) * a.E;
+      acc[u] = 0.f;
     }
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
-    acc += __shfl_xor(acc, 4);
-    return acc == acc ? item_key(acc, r) : 0;
+#pragma unroll 2
+    for (int c = P * part8; c < a.E; c += 8 * P) {
+      Piece e[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) e[u].load(row[u], c, a.E);
+#pragma unroll
+      for (int t = 0; t < P; ++t)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float d = qf[c + t] - e[u].at(t);
+          acc[u] = L2 ? fmaf(-d, d, acc[u]) : fmaf(qf[c + t], e[u].at(t), acc[u]);
+        }
+    }
+    uint64_t top = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      acc[u] += __shfl_xor(acc[u], 1);
+      acc[u] += __shfl_xor(acc[u], 2);
+      acc[u] += __shfl_xor(acc[u], 4);
+      if (r[u] >= 0 && acc[u] == acc[u]) top = max(top, item_key(acc[u], r[u]));
+    }
+    return top;
   };
   best = block_best(best, 0);   // (qf is there, too)
   const int first = (int)~(uint32_t)best;
   const int own_row = min(first * a.rows + (tid >> 3), a.N - 1), own_entry = part8 == 0 ? entry_of(a, own_row) : -1;   // (with the rows)
-  const uint64_t own = score_group(first);
+  const uint64_t own = score_groups(std::integral_constant<int, 1>{}, [&](int) { return first; });
   best = own;
   float qq = 0.f;
   for (int e = lane; e < a.E; e += kWave) qq = fmaf(qf[e], qf[e], qq);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) qq += __shfl_xor(qq, off);
   best = block_best(best, 1);
-  const float c = bound_slack(a.E), s = key_score((uint32_t)(best >> 32));
-  float reach = s - 0x1p-20f * fabsf(s) + (L2 ? (1.f - c) * qq : -0.5f * c * qq) - kBoundLeast;
-  if (best == 0 || !(qq < kBoundMost) || !(reach > -kBoundMost)) reach = -INFINITY;   // every group
-  auto look = [&](float bound, int x) {
-    if (bound >= reach && x < a.G && x != first) {
-      const int at = atomicAdd(&n_more, 1);
-      if (at < kMoreGroups) more[at] = x;
-    }
-  };
+  int many = 0;
+  if (!UNSURE) {
+    const float s = best ? key_score((uint32_t)(best >> 32)) : -INFINITY, reach = bound_reach<L2>(s, qq, a.E);
+    auto look = [&](float bound, int x) {
+      if (bound >= reach && x < a.G && x != first && qq == qq) {   // (of a query with NaN no row ranks)
+        const int at = atomicAdd(&n_more, 1);
+        if (at < kMoreGroups) more[at] = x;
+      }
+    };
 #pragma unroll
-  for (int t = 0; t < KEEP; ++t) look(u[t], tid + t * NT);
-  for (int x = tid + KEEP * NT; x < a.G; x += NT) look(part[x], x);
-  __syncthreads();
-  const int many = n_more;
-  if (many > 0) {
+    for (int t = 0; t < KEEP; ++t) look(u[t], tid + t * NT);
+    for (int x = tid + KEEP * NT; x < a.G; x += NT) look(part[x], x);
+    __syncthreads();
+    many = n_more;
     if (many > kMoreGroups || (size_t)many * a.rows * a.E * sizeof(T) > kMoreBytes) {
       if (tid == 0) {
         a.idx[b] = kUnsure;
+        a.score[b] = s;
         *a.unsure = 1;
       }
       return;
     }
-    for (int x = 0; x < many; ++x) best = max(best, score_group(more[x]));
-    best = block_best(best, 0);
+    if (many > 0) {
+      for (int x = 0; x < many; x += 4)   // (past the last one: that one again)
+        best = max(best, score_groups(std::integral_constant<int, 4>{}, [&](int u) { return more[min(x + u, many - 1)]; }));
+      best = block_best(best, 0);
+    }
   }
   if (tid == 0) {
     const float top = best ? key_score((uint32_t)(best >> 32)) : -INFINITY;
@@ -1987,16 +2223,20 @@ static hipError_t launch_topk(const SearchArgs& a, hipStream_t stream) {
   if (a.metric) return large ? launch_topk_n<T, 1024, true, kPlain>(a, stream) : launch_topk_n<T, 256, true, kPlain>(a, stream);
   return large ? launch_topk_n<T, 1024, false, kPlain>(a, stream) : launch_topk_n<T, 256, false, kPlain>(a, stream);
 }
+template <typename T, bool L2, bool UNSURE>
+static hipError_t launch_bound1(const SearchArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((finalize_bound1_kernel<T, L2, UNSURE>), dim3((unsigned)a.B), dim3(1024), ((size_t)a.E + 7) / 8 * 32, stream, a);
+  return hipGetLastError();
+}
 template <typename T, bool L2>
 static hipError_t launch_bounded_finish(const SearchArgs& a, hipStream_t stream) {
   if (a.k > 1) return launch_topk_n<T, 1024, L2, kBounds>(a, stream);
-  hipLaunchKernelGGL((finalize_bound1_kernel<T, L2>), dim3((unsigned)a.B), dim3(1024), ((size_t)a.E + 7) / 8 * 32, stream, a);
-  return hipGetLastError();
+  return launch_bound1<T, L2, false>(a, stream);
 }
 
 // ---- bounds, exact scores of what they leave, tiles for what they leave open
 static size_t bound_lds(int nqb, int E, size_t parts) {
-  return (size_t)32 * nqb * ((((size_t)E + 15) & ~15) + kQPad) * 2 * parts + (size_t)4 * 32 * nqb * 4 + 4 * 32 * 4;
+  return (size_t)32 * nqb * bound_query(E) * 2 * parts + (size_t)4 * 32 * nqb * 4 + 4 * 32 * 4;
 }
 constexpr size_t kBoundLds = 150 * 1024;
 
@@ -2012,8 +2252,6 @@ constexpr size_t kBoundLds = 150 * 1024;
 // row: 500,000 x 32 fp32, 16 queries 33.4 / 35.2, 40 69 / 37.
 static bool use_bounds(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
   if (B <= 8 || B > 1 << 20 || (is_f16 && !metric) || bound_lds(1, E, is_f16 ? 1 : 2) > kBoundLds) return false;
-  // (what the bounds leave open is one launch of tiles)
-  if (((size_t)N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * ((B + 15) / 16) > kGridThreads / kThreads) return false;
   const double work = (double)N * B * E, bytes = (double)N * E * (is_f16 ? 2 : 4);
   if (B <= 16 && !is_f16 && (E < 64 || (!metric && bytes > 256e6))) return false;
   const double least = is_f16 && E <= 64 ? 4e7 : k == 1 ? 6.6e7 : 1.05e8;
@@ -2040,6 +2278,37 @@ static hipError_t launch_bound_n(const SearchArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+constexpr size_t kUnsureGrid = 512;   // workgroups: two a compute unit
+
+static size_t unsure_lds(int nqb, int E, size_t parts, size_t esz) {
+  return ((size_t)32 * nqb * parts * 2 + esz) * bound_query(E) + (4 * 32 + 32 * nqb) * 4;
+}
+
+template <typename T, bool L2, int NQB, int MODE>
+static hipError_t launch_unsure_n(const SearchArgs& a, hipStream_t stream) {
+  const size_t lds = unsure_lds(NQB, a.E, MODE == kCentred ? 2 : BoundParts<T>::N, sizeof(T));
+  hipError_t e = ensure_lds<&search_unsure_kernel<T, L2, NQB, MODE>>(lds);
+  if (e != hipSuccess) return e;
+  const size_t units = ((size_t)(a.N + a.wg_rows - 1) / a.wg_rows + 7) / 8 * 8 * ((a.B + 32 * NQB - 1) / (32 * NQB));
+  hipLaunchKernelGGL((search_unsure_kernel<T, L2, NQB, MODE>), dim3((unsigned)(units < kUnsureGrid ? units : kUnsureGrid)), dim3(kThreads),
+                     lds, stream, a);
+  return hipGetLastError();
+}
+template <typename T, bool L2>
+static hipError_t launch_unsure(const SearchArgs& a, hipStream_t stream) {
+  constexpr size_t most = 160 * 1024 - 5500;   // (the rest is for pairs; rows that use_bounds takes leave room for 32 queries, but fp16
+                                               // ones of more than 1,170 columns not for their two parts)
+  constexpr int kBest = L2 ? kCentred : kAgain;
+  constexpr size_t parts = L2 ? 2 : BoundParts<T>::N;
+  hipError_t e;
+  if (a.B > 32 && unsure_lds(2, a.E, parts, sizeof(T)) <= most - 5500) e = launch_unsure_n<T, L2, 2, kBest>(a, stream);
+  else if (std::is_same<T, float>::value || unsure_lds(1, a.E, parts, sizeof(T)) <= most) e = launch_unsure_n<T, L2, 1, kBest>(a, stream);
+  else e = launch_unsure_n<T, L2, 1, kAgain>(a, stream);
+  if (e != hipSuccess) return e;
+  if (a.k > 1) return launch_topk_n<T, 1024, L2, kUnsureOnly>(a, stream);
+  return launch_bound1<T, L2, true>(a, stream);
+}
+
 template <typename T, bool L2>
 static hipError_t launch_bounded(SearchArgs a, hipStream_t stream) {
   bound_plan(a.N, a.k, &a.rows, &a.G);
@@ -2052,8 +2321,8 @@ static hipError_t launch_bounded(SearchArgs a, hipStream_t stream) {
   auto fits = [&](int nqb) { return bound_lds(nqb, a.E, BoundParts<T>::N) <= kBoundLds; };
   hipError_t e = a.B > 32 && fits(2) ? (a.B > 64 && fits(4) ? launch_bound_n<T, L2, 4>(a, stream) : launch_bound_n<T, L2, 2>(a, stream))
                                      : launch_bound_n<T, L2, 1>(a, stream);
-  if (e != hipSuccess) return e;
-  return launch_bounded_finish<T, L2>(a, stream);
+  if (e == hipSuccess) e = launch_bounded_finish<T, L2>(a, stream);
+  return e == hipSuccess ? launch_unsure<T, L2>(a, stream) : e;
 }
 
 // Where one launch is faster than two.  A step of 128 KB costs 1 us (fp16 Euclidean, which converts and subtracts
@@ -2099,28 +2368,6 @@ template <typename T>
 static hipError_t launch_small(const SearchArgs& a, hipStream_t stream) {
   if (a.metric) return a.k > 1 ? launch_small_k<T, true, true>(a, stream) : launch_small_k<T, true, false>(a, stream);
   return a.k > 1 ? launch_small_k<T, false, true>(a, stream) : launch_small_k<T, false, false>(a, stream);
-}
-
-constexpr int kUnsureTiles = 768;   // workgroups: three a compute unit, as many as its LDS holds
-
-template <typename T, bool L2>
-static hipError_t launch_unsure_k(SearchArgs a, hipStream_t stream) {
-  a.nq = a.B;
-  if (a.k > 1)
-    hipLaunchKernelGGL((search_unsure_kernel<T, L2, 4, true>), dim3(kUnsureTiles), dim3(kThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL((search_unsure_kernel<T, L2, 4, false>), dim3(kUnsureTiles), dim3(kThreads), 0, stream, a);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.k > 1) return launch_topk_n<T, 1024, L2, kUnsureOnly>(a, stream);
-  hipLaunchKernelGGL((finalize_top1_kernel<true>), dim3((unsigned)a.B), dim3(kThreads), 0, stream, a);
-  return hipGetLastError();
-}
-template <typename T>
-static hipError_t launch_unsure(const SearchArgs& a, hipStream_t stream) {
-  if (a.metric) return launch_unsure_k<T, true>(a, stream);
-  if constexpr (std::is_same<T, f16_t>::value) return hipErrorInvalidValue;   // (fp16 inner products have no bounds)
-  else return launch_unsure_k<T, false>(a, stream);
 }
 
 hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
@@ -2189,11 +2436,9 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   } else if (use_bounds(p.is_f16, p.metric, p.E, p.B, p.N, p.k)) {
     // the last 256 bytes of the workspace are behind what the searches use
     a.unsure = reinterpret_cast<int32_t*>(ws + search_workspace_bytes(p.N, p.E, p.B, p.k, p.is_f16) - 256);
-    hipError_t e = p.is_f16    ? launch_bounded<f16_t, true>(a, stream)
-                   : p.metric ? launch_bounded<float, true>(a, stream)
-                              : launch_bounded<float, false>(a, stream);
-    if (e != hipSuccess) return e;
-    return p.is_f16 ? launch_unsure<f16_t>(a, stream) : launch_unsure<float>(a, stream);
+    return p.is_f16   ? launch_bounded<f16_t, true>(a, stream)
+           : p.metric ? launch_bounded<float, true>(a, stream)
+                      : launch_bounded<float, false>(a, stream);
   } else {
     const hipError_t e = p.is_f16 ? launch_valu<f16_t>(a, stream) : launch_valu<float>(a, stream);
     if (e != hipSuccess) return e;
@@ -2202,7 +2447,7 @@ hipError_t launch_search(const SearchLaunch& p, hipStream_t stream) {
   if (p.k == 1 && mode == kModeMfmaBig) {
     hipLaunchKernelGGL(finalize_top1_block_kernel, dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
   } else if (p.k == 1) {
-    hipLaunchKernelGGL((finalize_top1_kernel<false>), dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL(finalize_top1_kernel, dim3((unsigned)p.B), dim3(kThreads), 0, stream, a);
   } else {
     return p.is_f16 ? launch_topk<f16_t>(a, stream) : launch_topk<float>(a, stream);
   }

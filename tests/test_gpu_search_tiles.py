@@ -93,10 +93,10 @@ VARIANT_CASES = [(*c, k, torch.float16, "ip") for k in (1, 3) for c in [
 # blocks, groups of 32, 64 and 128 rows.
 BOUND_CASES = [
     # N, E, B, k, dtype, metric
-    (20011, 128, 32, 1, torch.float32, "l2"), (20011, 131, 33, 1, torch.float32, "ip"), (20011, 72, 50, 1, torch.float32, "l2"),
-    (9001, 97, 130, 3, torch.float32, "l2"), (9001, 200, 64, 8, torch.float32, "ip"), (33001, 259, 17, 64, torch.float32, "l2"),
-    (9001, 1160, 33, 1, torch.float32, "l2"), (33000, 64, 70, 2, torch.float32, "ip"), (150001, 33, 20, 1, torch.float32, "ip"),
-    (120001, 20, 48, 16, torch.float32, "l2"), (5001, 72, 600, 1, torch.float32, "ip"),
+    (30011, 128, 32, 1, torch.float32, "l2"), (40011, 131, 33, 1, torch.float32, "ip"), (40011, 72, 50, 1, torch.float32, "l2"),
+    (12001, 97, 130, 3, torch.float32, "l2"), (15001, 200, 64, 8, torch.float32, "ip"), (33001, 259, 17, 64, torch.float32, "l2"),
+    (9001, 1160, 33, 1, torch.float32, "l2"), (40000, 64, 70, 2, torch.float32, "ip"), (250001, 33, 20, 1, torch.float32, "ip"),
+    (150001, 20, 48, 16, torch.float32, "l2"), (5001, 72, 600, 1, torch.float32, "ip"), (40001, 1183, 9, 1, torch.float32, "l2"),
     (40000, 136, 40, 4, torch.float16, "l2"), (30001, 24, 140, 1, torch.float16, "l2"), (50001, 256, 9, 1, torch.float16, "l2"),
     (70001, 64, 40, 8, torch.float16, "l2"), (9001, 520, 65, 5, torch.float16, "l2"), (3001, 2304, 170, 2, torch.float16, "l2"),
     # what stays in tiles: queries too wide for the bounds' kernel
@@ -112,12 +112,16 @@ def test_bounded_search_matches_the_oracle(ac, oracle_mod, case):  # noqa: F811
     _check(ac, oracle_mod, *case)
 
 
-@pytest.mark.parametrize("k", [1, 5])
-@pytest.mark.parametrize("dt,metric", [(torch.float32, "ip"), (torch.float32, "l2"), (torch.float16, "l2")])
-@pytest.mark.parametrize("what", ["alike", "far", "one far", "huge", "tiny", "nan", "nan queries"])
-def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, dt, metric, k):  # noqa: F811
-    """Rows that the bounds cannot tell apart, in few groups (scored there) and in many (searched again)."""
-    N, E, B = 30003, 96, 40
+# one block of 32 queries and two, workgroups of 128 and of 256 rows, rows that end in part of a piece, fp16 rows of more than 1,170 columns
+OPEN_FULL = [(70001, 96, 64, torch.float32, "l2"), (70001, 97, 25, torch.float32, "ip"), (70001, 96, 64, torch.float16, "l2")]
+OPEN_SHORT = [(70001, 97, 25, torch.float32, "l2"), (70001, 96, 64, torch.float32, "ip"), (4099, 104, 400, torch.float32, "l2"),
+              (70001, 104, 25, torch.float16, "l2"), (66001, 1208, 32, torch.float16, "l2")]
+OPEN_WHAT = ["alike", "two kinds", "zeros", "the same", "one open", "far", "one far", "huge", "tiny", "nan", "nan queries"]
+OPEN_CASES = [(w, c) for c in OPEN_FULL for w in OPEN_WHAT] + [(w, c) for c in OPEN_SHORT for w in OPEN_WHAT[:3]]
+
+
+def _open_data(what, N, E, B, dt):
+    """Rows that the bounds cannot tell apart, in few groups (scored with the first) and in many (bounds again, by row)."""
     g = _gen(9)
     emb = torch.randn(N, E, generator=g) / E ** 0.5
     q = emb[torch.randint(0, N, (B,), generator=g)] + 0.02 * torch.randn(B, E, generator=g)
@@ -126,6 +130,16 @@ def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, dt, 
         emb[100:] = kinds[torch.randint(0, 40, (N - 100,), generator=g)]
         emb[100:N:2000] = q[0] + 0.01
         q[1::2] = q[0]
+    elif what == "two kinds":   # a row in three of every workgroup
+        emb = emb[:2][torch.randint(0, 2, (N,), generator=g)]
+        q = emb[:B] + 0.02 * torch.randn(B, E, generator=g)
+    elif what == "the same":
+        emb = emb[:1].repeat(N, 1)
+    elif what == "zeros":    # neighbours that are the same, the nearest to most queries
+        emb[N // 3:2 * N // 3 + 5] = 0
+        q[1::2] = torch.randn(len(q[1::2]), E, generator=g) / E ** 0.5
+    elif what == "one open":   # query
+        emb[torch.randint(0, N, (300,), generator=g)] = q[5] + 0.01
     elif what == "far":
         emb, q = emb + 30.0, q + 30.0
     elif what == "one far":  # of the queries
@@ -142,19 +156,70 @@ def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, dt, 
     else:
         q[::4, 3] = float("nan")
         q[2, 0] = float("inf")
-    emb, q = emb.to(dt), q.to(dt)
+    return emb.to(dt), q.to(dt)
+
+
+@pytest.mark.parametrize("k", [1, 5])
+@pytest.mark.parametrize("what,case", OPEN_CASES, ids=lambda c: c if isinstance(c, str) else "N%d-E%d-B%d-%s-%s" % (
+    *c[:3], str(c[3]).split(".")[-1], c[4]))
+def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, case, k):  # noqa: F811
+    N, E, B, dt, metric = case
+    emb, q = _open_data(what, N, E, B, dt)
     m = ac.AC_IP if metric == "ip" else ac.AC_L2
     idx, score, hit = _run_search(ac, emb, q, k, 0.8, m)
-    if what in ("far", "one far", "huge", "tiny", "alike"):
-        parity.check_search(oracle_mod, q, emb, k, 0.8, m, None, idx, score, hit)
+    few = torch.arange(0, B, max(1, B // 20))   # (the oracle)
+    if what not in ("nan", "nan queries"):
+        parity.check_search(oracle_mod, q[few], emb, k, 0.8, m, None, idx[few], score[few], hit[few])
+    if k == 1 and what in ("alike", "two kinds", "the same", "zeros"):   # of rows that are the same the first
+        first = {}
+        for i, row in reversed(list(enumerate(emb.numpy()))):
+            first[row.tobytes()] = i
+        assert all(first[emb[i].numpy().tobytes()] == i for i in idx[:, 0].tolist())
     # and the same rows as a search by itself, which is too small for bounds, says, eight queries at a time
-    for b in range(0, B, 8):
-        i2, s2, h2 = _run_search(ac, emb, q[b:b + 8].contiguous(), k, 0.8, m)
-        s1 = score[b:b + 8]
+    for b in range(0, B, max(8, B // 8)):
+        some = slice(b, min(b + 8, B))
+        i2, s2, h2 = _run_search(ac, emb, q[some].contiguous(), k, 0.8, m)
+        s1 = score[some]
         same = (s1 == s2) | (s1.isnan() & s2.isnan())
         scale = s2.abs().clamp_min(torch.finfo(torch.float32).tiny)
         assert (same | ((s1 - s2).abs() <= (E + 4) * 2.0 ** -23 * scale * (1 if metric == "l2" else 40))).all()
-        assert ((idx[b:b + 8] < 0) == (i2 < 0)).all()
+        assert ((idx[some] < 0) == (i2 < 0)).all()
+
+
+def test_rows_alike_take_less_than_three_times_as_long(ac):  # noqa: F811
+    """60 rows alike for every query, in as many groups: their rows are scored by the whole chip (36 us a call, 19 without them; 74
+    where a workgroup a query scored group after group)."""
+    N, E, B = 100000, 64, 64
+    g = _gen(3)
+    emb = torch.randn(N, E, generator=g) / E ** 0.5
+    q = (emb[:B] + 0.02 * torch.randn(B, E, generator=g)).cuda()
+    alike = emb.clone()
+    alike[torch.randint(0, N, (60 * B,), generator=g)] = q.cpu().repeat(60, 1) + 0.01
+    least = []
+    for rows in (emb, alike):
+        db = ac.attncache_build_db(rows.cuda(), torch.zeros(1, 1, 1, 8, 8, device="cuda"), n_kv_heads=1, head_dim=8, metric=ac.AC_L2,
+                                   map_of=torch.zeros(N, dtype=torch.int32, device="cuda"))
+        ws = torch.empty(ac.attncache_workspace_bytes(db.desc, B, 1), dtype=torch.uint8, device="cuda")
+        out = (torch.empty(B, 1, dtype=torch.int32, device="cuda"), torch.empty(B, 1, device="cuda"),
+               torch.empty(B, dtype=torch.int32, device="cuda"))
+        run = lambda: ac.attncache_search(db, q, 1, 0.5, *out, ws)   # noqa: E731
+        run()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                run()
+        times = []
+        for _ in range(30):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        least.append(min(times))
+        db.close()
+    assert least[1] < 3 * least[0], least
 
 
 @pytest.mark.parametrize("case", VARIANT_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (

@@ -39,6 +39,7 @@ def _search(c):
 
 def test_every_search_kernel_is_reached(tmp_path):
     cases = (tiles.VALU_CASES + tiles.VARIANT_CASES + tiles.TOPK_CASES + tiles.BOUND_CASES + small.SEARCH_CASES +
+             [(*c[:3], k, *c[3:]) for _, c in tiles.OPEN_CASES for k in (1, 5)] +
              small._random_search_shapes(40, 20251128))
     missing = _kernels("search_", "finalize_") - _reached(tmp_path, [_search(c) for c in cases])
     assert missing == NOT_RUN
