@@ -2234,7 +2234,7 @@ static hipError_t launch_bounded_finish(const SearchArgs& a, hipStream_t stream)
   return launch_bound1<T, L2, false>(a, stream);
 }
 
-// ---- bounds, exact scores of what they leave, tiles for what they leave open
+// ---- bounds, exact scores of what they leave, bounds by row for what they leave open
 static size_t bound_lds(int nqb, int E, size_t parts) {
   return (size_t)32 * nqb * bound_query(E) * 2 * parts + (size_t)4 * 32 * nqb * 4 + 4 * 32 * 4;
 }
@@ -2252,6 +2252,8 @@ constexpr size_t kBoundLds = 150 * 1024;
 // row: 500,000 x 32 fp32, 16 queries 33.4 / 35.2, 40 69 / 37.
 static bool use_bounds(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
   if (B <= 8 || B > 1 << 20 || (is_f16 && !metric) || bound_lds(1, E, is_f16 ? 1 : 2) > kBoundLds) return false;
+  // (so many rows and queries that tiles of them take several launches have not been measured, and stay there)
+  if (((size_t)N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * ((B + 15) / 16) > kGridThreads / kThreads) return false;
   const double work = (double)N * B * E, bytes = (double)N * E * (is_f16 ? 2 : 4);
   if (B <= 16 && !is_f16 && (E < 64 || (!metric && bytes > 256e6))) return false;
   const double least = is_f16 && E <= 64 ? 4e7 : k == 1 ? 6.6e7 : 1.05e8;
