@@ -2242,21 +2242,27 @@ constexpr size_t kBoundLds = 150 * 1024;
 
 // Where bounds first are faster than exact scores of all rows: four launches (two of which usually find nothing to do) and a
 // second phase that reads whole groups of wide rows, against work that grows with N B E.  us per call (graph), all rows / bounds:
-//   fp32 Euclidean, k = 1   100,000 x 128, 64 queries 57 / 24; 32,000 x 128: 9 queries 15.1 / 15.2, 40 25.7 / 16.5; 8,000 x 128, 64
-//                           15.3 / 15.5; 2,000 x 256, 128 17.4 / 24.3, 400 36.6 / 25.6; 32,000 x 512, 9 37.4 / 27.9; 2,000 x 1,024, 128 46.8 / 49.6
-//   fp32 inner, k = 1       32,000 x 128, 40 queries 23.5 / 16.5; 500,000 x 256, 9 110 / 113 (both bound by the stream)
-//   fp16 Euclidean, k = 1   32,000 x 32, 40 queries 15.6 / 12.2; 128,000 x 256, 64 147 / 27; 8,000 x 64, 64 11.2 / 12.3
-//   k = 8                   fp32 Euclidean 8,000 x 128, 64 queries 21.9 / 24.5, 128 29.6 / 27.2; 8,000 x 512, 40 53.8 / 44.3;
-//                           fp16 8,000 x 256, 64 25.3 / 25.4; 32,000 x 512, 16 40.8 / 39.5, 40 69 / 41
-// Up to eight queries are streams, which follow the memory.  Rows below 64 columns leave the bounds' kernel little work a
-// row: 500,000 x 32 fp32, 16 queries 33.4 / 35.2, 40 69 / 37.
+//   fp32 Euclidean, k = 1   32,000 x 256, 9 queries 20.6 / 19.7, 16 21.0 / 20.1; 100,000 x 32, 24 14.6 / 15.8, 40 19.9 / 17.0; 100,000 x 128, 9 23.9 / 22.4, 64
+//                           57 / 24; 32,000 x 128, 40 23.5 / 16.5; 2,000 x 128, 400 20.6 / 21.1; 2,000 x 256, 400 33.0 / 26.8
+//   fp32 inner, k = 1       100,000 x 32, 24 queries 13.7 / 15.9, 64 21.9 / 17.1; 2,000 x 128, 400 18.9 / 21.2; 32,000 x 256, 16 19.7 / 19.9; 8,000 x 128, 128
+//                           19.6 / 17.8; 300,000 x 64, 9 27.4 / 28.6; 500,000 x 256, 9 110 / 113 (both bound by the stream)
+//   fp16 Euclidean, k = 1   2,000 x 64, 400 queries 14.2 / 16.4; 32,000 x 64, 24 12.2 / 11.9; 100,000 x 64, 9 15.3 / 13.8; 32,000 x 256, 9 14.7 / 15.6;
+//                           8,000 x 256, 40 16.8 / 15.0; 128,000 x 256, 64 147 / 27
+//   k = 8                   fp32 Euclidean 100,000 x 32, 40 queries 25.0 / 25.4; 8,000 x 256, 64 31.8 / 31.8; 32,000 x 64, 64 27.2 / 21.9; inner 100,000 x 64, 24
+//                           23.7 / 27.9; 8,000 x 256, 64 29.8 / 31.3; 32,000 x 128, 40 30.1 / 27.4; fp16 2,000 x 64, 400 26.1 / 29.4; 8,000 x 256, 64 24.7 / 25.2;
+//                           32,000 x 512, 16 40.8 / 39.5, 40 69 / 41
+// Of 106 sizes just past these lines (9 to 400 queries, 2,000 to 300,000 rows of 32 to 1,024 columns) nine take longer than all rows, up to 1.06 times as long
+// (8,000 x 256, 64 queries, inner products 19.0 / 20.1; fp16 Euclidean, k = 8 24.2 / 25.6), and all together 0.83.
+// Up to eight queries are streams, which follow the memory.  Rows below 64 columns (inner products 128) leave the bounds' kernel little
+// work a row with up to 16 queries: 500,000 x 32 fp32, 16 queries 33.4 / 35.2, 40 69 / 37.
+// What the bounds cannot tell apart costs the launches that follow as well (search_unsure_kernel).
 static bool use_bounds(int32_t is_f16, int32_t metric, int32_t E, int32_t B, int32_t N, int32_t k) {
   if (B <= 8 || B > 1 << 20 || (is_f16 && !metric) || bound_lds(1, E, is_f16 ? 1 : 2) > kBoundLds) return false;
   // (so many rows and queries that tiles of them take several launches have not been measured, and stay there)
   if (((size_t)N + 8 * kValuRowsPerWg - 1) / (8 * kValuRowsPerWg) * 8 * ((B + 15) / 16) > kGridThreads / kThreads) return false;
   const double work = (double)N * B * E, bytes = (double)N * E * (is_f16 ? 2 : 4);
-  if (B <= 16 && !is_f16 && (E < 64 || (!metric && bytes > 256e6))) return false;
-  const double least = is_f16 && E <= 64 ? 4e7 : k == 1 ? 6.6e7 : 1.05e8;
+  if (B <= 16 && !is_f16 && (E < (metric ? 64 : 128) || (!metric && bytes > 256e6))) return false;
+  const double least = is_f16 ? (E <= 64 ? 5.5e7 : k == 1 ? 8e7 : 1.1e8) : metric ? (k == 1 ? 1.1e8 : 1.3e8) : k == 1 ? 1.3e8 : 1.6e8;
   return work >= least && work >= (k > 1 && is_f16 ? 5e5 : 2.8e5) * E;
 }
 

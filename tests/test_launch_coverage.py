@@ -98,6 +98,13 @@ def test_every_projector_kernel_is_reached(tmp_path):
     ((20000, 20, 8, 1, "f32", "ip"), "search_row_kernel<float"),
     ((20000, 37, 8, 1, "f32", "ip"), "search_stream_kernel<float, false, 4"),
     ((100000, 128, 64, 1, "f32", "l2"), "search_bound_kernel<float, true, 2"),   # 57 in tiles of all rows, 24
+    ((100000, 32, 24, 1, "f32", "l2"), "search_valu_kernel<float, true, 2"),      # bounds 15.8, 14.6
+    ((100000, 32, 40, 8, "f32", "ip"), "search_valu_kernel<float, false, 4"),    # bounds 26.1, 22.6
+    ((2000, 128, 400, 1, "f32", "ip"), "search_valu_kernel<float, false, 1"),    # bounds 21.2, 18.9
+    ((2000, 64, 400, 1, "f16", "l2"), "search_stream_kernel<half, true, 4"),     # bounds 16.4, 14.2
+    ((300000, 64, 9, 1, "f32", "ip"), "search_valu_kernel<float, false, 4"),     # bounds 28.6, 27.4
+    ((32000, 64, 64, 1, "f32", "ip"), "search_bound_kernel<float, false, 2"),    # 19.4 in tiles of all rows, 13.7
+    ((32000, 64, 40, 1, "f16", "l2"), "search_bound_kernel<half, true, 2"),      # 15.5, 12.3
     ((640, 256, 4, 1, "f32", "ip"), "search_small_kernel<float, false, false, 2"),   # one row of a thread 9.6, two 9.0
     ((300, 512, 4, 4, "f16", "ip"), "search_small_kernel<half, false, true, 4"),     # 11.2, four 9.4
     ((100, 640, 16, 1, "f16", "ip"), "search_small_kernel<half, false, false, 1"),   # 6.2, 6.7
