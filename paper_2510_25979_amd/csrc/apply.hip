@@ -40,7 +40,8 @@ struct ApplyArgs {
   void* O;
   int32_t M, L, layer_begin, Lc, Hq, Hkv, S;
   int32_t heads_per_wg;  // query heads handled by one workgroup (shares V)
-  int32_t n_rblk;        // ceil(S / 128)
+  int32_t n_rblk;        // ceil(S / 128); S <= 128: workgroups that share a tile's units
+  int32_t xcd_bits;      // S <= 128: 3 if those get ids equal mod 8 (one XCD, one L2), else 0
   int32_t tiles_per_wg;  // (item, layer, KV head) of one workgroup, S <= 128
   int32_t n_tiles;       // B' * Lc * (Hq / heads_per_wg)
   int32_t tile0;         // first tile of the launch (fp32 path, see launch_apply_f32)
@@ -198,7 +199,9 @@ __global__ __launch_bounds__(kThreads, (D == 64 ? (NRB == 4 ? 3 : 4) : NRB == 4 
   const int il = lane & 31, kh = lane >> 5;
   bf16_t* ost = vb + (size_t)a.tiles_per_wg * S * D + wave * (16 * kSmallOutStride);
   const int g = a.Hq / a.Hkv, per = g * NRB;      // units of a tile
-  const int tile0 = blockIdx.x / a.n_rblk * a.tiles_per_wg, part = blockIdx.x % a.n_rblk;   // (n_rblk: parts of a tile's units)
+  const unsigned slot = blockIdx.x >> a.xcd_bits, group = slot / a.n_rblk;
+  const int part = (int)(slot - group * a.n_rblk);
+  const int tile0 = (int)(group << a.xcd_bits | (blockIdx.x & ((1u << a.xcd_bits) - 1))) * a.tiles_per_wg;
   const size_t tile_elems = PACKED ? (size_t)packed_blocks(S, CAUSAL) * 512 : (size_t)S * S;
 
   // the tiles: query (-1: a miss, past the end or an invalid index) and entry
@@ -783,8 +786,15 @@ static hipError_t launch_apply_f32(ApplyArgs a, int D, int causal, hipStream_t s
   return hipSuccess;
 }
 
-// Up to so many workgroups of four units each take a tile's units side by side, each with its own copy of V.
-constexpr size_t kShortSplit = 1024;
+// Up to kShortFew workgroups of four units each take a tile's units side by side, each with its own copy of V, as the launch leaves
+// room on the chip; from kShortMany on again, on one XCD: what a large launch reads and writes together then lies closer together, and
+// memory gives more (V comes from the L2 after the first time).  us per call with one workgroup a tile / so, packed causal maps of 128 x 128, twice as
+// many entries as queries: 4,096 tiles (item, layer, K/V head) of two heads 86.7 / 86.9, 8,192 197 / 180, 16,384 429 / 365, 32,768 886 / 774; of eight heads 1,024 72.2 / 71.0,
+// 4,096 347 / 318, 16,384 1,355 / 1,265; dense ones without mask, 32,768 of two 1,015 / 914; 64 x 128, 8,192 of eight 270 / 255; 128 x 64 dense, 8,192 of
+// four 294 / 278; of 32 x 64 16,384 of eight 129 / 130.  Six units (two heads of 96 rows) leave two waves without one: 8,192 127 / 135.
+// kShortFew is 700 for 128 x 128, which two workgroups of a compute unit hold, if the tiles go round by themselves: 512 tiles of two heads in 512
+// workgroups 11.9, in 1,024 16.8; 256 of four 12.7 / 17.8; but 128 of eight 18.8 / 17.1, and 528 workgroups instead of 264 8.7 / 10.1.
+constexpr size_t kShortFew = 1024, kShortMany = 16384;
 
 template <bool PREFETCH>
 static hipError_t launch_halves(const ApplyArgs& a, hipStream_t stream) {
@@ -816,8 +826,13 @@ static hipError_t launch_short(ApplyArgs a, int D, int S, bool causal, bool pack
   a.n_tiles = nb * a.Lc * a.Hkv;
   a.tiles_per_wg = units < 4 ? 4 / units : 1;
   a.n_rblk = 1;
-  if (units > 4 && (size_t)a.n_tiles * ((units + 3) / 4) <= kShortSplit) a.n_rblk = (units + 3) / 4;
-  const dim3 grid((unsigned)((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg * a.n_rblk));
+  const size_t apart = (size_t)a.n_tiles * ((units + 3) / 4);
+  const bool many = units > 4 && units % 4 == 0 && apart >= kShortMany && apart < (size_t)1 << 23;   // (a grid has 2^32 threads at most)
+  const size_t few = D == 128 && S == 128 && a.n_tiles >= 256 ? 700 : kShortFew;
+  if (many || (units > 4 && apart <= few)) a.n_rblk = (units + 3) / 4;
+  a.xcd_bits = many ? 3 : 0;
+  const int wgs = many ? (a.n_tiles + 7) / 8 * 8 : (a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg;
+  const dim3 grid((unsigned)wgs * a.n_rblk);
   const size_t lds = ((size_t)a.tiles_per_wg * S * D + 4 * 16 * kSmallOutStride) * sizeof(bf16_t);
   auto go = [&](auto d, auto c, auto pk, auto nrb) {
     hipLaunchKernelGGL((apply_bf16_short_kernel<decltype(d)::value, decltype(c)::value, decltype(pk)::value, decltype(nrb)::value>),

@@ -4,7 +4,7 @@ HIP runtime (launch_recorder.c), in a process of its own, without a GPU.
 record(calls) -> one (status, [(kernel, grid_x, grid_y, grid_z, block, lds), ...]) per call; apply_f32_small_kernel
 adds the (query, layer, head) that its launch starts with.  A call is
 ("search", N, E, B, k, "f16"|"f32", "ip"|"l2"), ("exact", B, Hq, Hkv, S, D, causal, "bf16"|"f32"[, routed]),
-("insert", B, Lc, Hq, Hkv, S, D, causal, packed), ("apply", B, Lc, Hq, Hkv, S, D, causal, "bf16"|"f32") or
+("insert", B, Lc, Hq, Hkv, S, D, causal, packed), ("apply", B, Lc, Hq, Hkv, S, D, causal, "bf16"|"f32"[, packed]) or
 ("project", B, S, dm, hid, E, "bf16"|"f32", "f16"|"f32", biases[, bytes of workspace])."""
 import ctypes
 import json
@@ -73,8 +73,8 @@ def _main(rec, path):
             st = L.attncache_project(p, p, p, bias, p, bias, p, B, S, dm, hid, E, BF16 if dt == "bf16" else F32,
                                      F16 if feat == "f16" else F32, 1, p, sz(ws[0] if ws else HUGE), None)
         else:
-            B, Lc, Hq, Hkv, S, D, causal, dt = c
-            h = db(1, 16, F16, 0, 1, Lc, Hq, Hkv, D, S, BF16 if dt == "bf16" else F32, int(causal), 0)
+            B, Lc, Hq, Hkv, S, D, causal, dt, *packed = c
+            h = db(1, 16, F16, 0, 1, Lc, Hq, Hkv, D, S, BF16 if dt == "bf16" else F32, int(causal), int(any(packed)))
             st = L.attncache_apply(h, p, p, p, B, 0, Lc, None)
         if h:
             L.attncache_destroy_db(h)

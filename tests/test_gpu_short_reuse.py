@@ -51,3 +51,30 @@ def test_short_maps(ac, oracle_mod, case, S, D, causal, layout):  # noqa: F811
     hits = [b for b in range(B) if 0 <= hit[b] < M]
     want = torch.matmul(maps[hit[hits].long(), 1:].float(), V[hits].float().repeat_interleave(g, 2))
     assert ((O[hits].float().cpu() - want).abs() <= 2.0 ** -8 * 1.01 * want.abs() + 1e-4).all()
+
+
+# B, Lc, Hkv, heads on one K/V head, S, D, causal, layout: a workgroup has four units of a tile, those of a tile are on one XCD; the
+# number of tiles is no multiple of the eight XCDs
+LARGE_CASES = [(1639, 5, 1, 8, 32, 64, True, "dense"), (683, 4, 3, 4, 64, 128, False, "packed"), (1639, 5, 1, 2, 128, 128, True, "packed"),
+               (1093, 5, 1, 3, 128, 128, True, "dense")]
+
+
+@pytest.mark.parametrize("case", LARGE_CASES, ids=lambda c: "B%d-L%d-%dx%d-S%d-D%d-%s-%s" % c)
+def test_large_launches(ac, case):  # noqa: F811
+    B, Lc, Hkv, g, S, D, causal, layout = case
+    M, Hq, gen = 4, Hkv * g, torch.Generator(device="cuda").manual_seed(B)
+    maps = _maps(M, Lc, Hq, S, torch.bfloat16, causal, S + D)
+    V = torch.randn(B, Lc, Hkv, S, D, generator=gen, device="cuda").bfloat16()
+    hit = torch.randint(-1, M + 1, (B,), generator=gen, device="cuda", dtype=torch.int32)   # -1: a miss, M: no such entry
+    db = _build(ac, torch.zeros(M, 16), maps, layout, causal, n_kv_heads=Hkv, head_dim=D)
+    O = torch.full((B, Lc, Hq, S, D), 7.0, dtype=torch.bfloat16, device="cuda")
+    ac.attncache_apply(db, hit, V, O)
+    torch.cuda.synchronize()
+    db.close()
+    assert (O[(hit < 0) | (hit >= M)] == 7.0).all()
+    maps = maps.cuda().float()
+    for e in range(M):
+        of = torch.nonzero(hit == e).flatten()
+        for some in of.split(64):
+            want = torch.matmul(maps[e][None], V[some].float().repeat_interleave(g, 2))
+            assert ((O[some].float() - want).abs() <= 2.0 ** -8 * 1.01 * want.abs() + 1e-4).all()

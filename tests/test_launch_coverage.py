@@ -186,3 +186,20 @@ def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
 def test_large_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp_path, case, kernel):
     (status, ls), = launches.record([("insert", *case)], tmp_path)
     assert status == 0 and ls[0][0].startswith(kernel), ls
+
+
+@pytest.mark.parametrize("case,grid", [
+    # B, layers, heads, K/V heads, S, D, causal, packed; workgroups                              us, one workgroup a tile / workgroups of four units
+    ((64, 32, 32, 16, 128, 128, True, True), 2 * 32768),   # 886 / 774
+    ((64, 32, 32, 16, 128, 128, False, False), 2 * 32768),   # 1,015 / 914
+    ((64, 4, 32, 16, 128, 128, True, True), 4096),         # 86.7 / 86.9
+    ((64, 16, 32, 16, 96, 128, True, True), 16384),        # 127 / 135 (six units)
+    ((63, 21, 72, 9, 32, 64, True, False), 2 * 11912),     # (11,907 tiles, rounded up to eight)
+    ((16, 4, 16, 8, 128, 128, True, True), 512),           # 11.9 / 16.8
+    ((16, 2, 16, 8, 128, 128, True, True), 2 * 256),
+    ((16, 1, 64, 8, 128, 128, True, True), 8 * 128),       # 18.8 / 17.1
+    ((16, 2, 64, 8, 64, 128, True, True), 4 * 256),        # 11.1 / 10.9
+], ids=str)
+def test_workgroups_of_short_reuse(tmp_path, case, grid):
+    (status, ls), = launches.record([("apply", *case[:7], "bf16", case[7])], tmp_path)
+    assert status == 0 and [(la[0].split("<")[0], la[1]) for la in ls] == [("apply_bf16_short_kernel", grid)]
