@@ -12,8 +12,12 @@ pytestmark = pytest.mark.gpu
 EXACT = [(57, 12, 12), (60, 10, 5), (43, 9, 3), (50, 12, 1), (700, 6, 3), (1100, 2, 2)]
 EXACT_CASES = [(*c, S, D, causal) for S in (32, 64, 96, 128) for D in (64, 128) for causal in (True, False)
                for c in EXACT if c[0] < 500 or S < 96]
+# the last workgroup has fewer K/V heads than the others (four of one row block, two of two), the last one of them a miss or short
+EXACT_CASES += [(*c, S, D, causal) for c, S in (((1101, 1, 1), 32), ((701, 6, 3), 32), ((1101, 1, 1), 64), ((577, 3, 3), 64))
+                for D in (64, 128) for causal in (True, False)]
 INSERT_CASES = [(*c, S, D, causal) for S in (32, 64, 96, 128) for D in (64, 128) for causal in (True, False)
                 for c in [(70, 2, 13, 13), (40, 2, 8, 4), (41, 1, 18, 6), (50, 1, 12, 1)]]
+INSERT_CASES += [(641, 1, 3, 3, S, D, causal) for S in (32, 64) for D in (64, 128) for causal in (True, False)]   # (as above)
 INSERT_CASES += [(50, 1, 3, 3, 64, D, causal) for D in (64, 128) for causal in (True, False)]   # two passes: a few units, one head each
 
 
@@ -21,7 +25,7 @@ def _data(B, Lc, Hq, Hkv, S, D, seed):
     g = torch.Generator(device="cuda").manual_seed(seed)
     r = lambda h: torch.randn(B, Lc, h, S, D, generator=g, device="cuda").bfloat16()  # noqa: E731
     lens = torch.randint(1, S + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
-    lens[0], lens[1] = S, 1
+    lens[0], lens[1], lens[-1] = S, 1, 3
     return r(Hq), r(Hkv), r(Hkv), lens
 
 
@@ -47,7 +51,8 @@ def test_exact(ac, case, padded, routed):  # noqa: F811
     B, Hq, Hkv, S, D, causal = case
     Q, K, V, lens = (t if t.dim() == 1 else t[:, 0].contiguous() for t in _data(B, 1, Hq, Hkv, S, D, S + D + B))
     sel = torch.where(torch.arange(B, device="cuda") % 3 == 1, 5, -1).int() if routed else None
-    O = torch.full_like(Q, 7.0)
+    room = torch.full((B + 1, *Q.shape[1:]), 7.0, dtype=Q.dtype, device="cuda")
+    O = room[:B]
     ac.attention_exact(Q, K, V, O, causal=causal, key_len=lens if padded else None, row_sel=sel)
     torch.cuda.synchronize()
     some = torch.tensor(sorted({0, 2, 3, 5, B // 2, B - 3, B - 2, B - 1}), device="cuda")
@@ -58,6 +63,7 @@ def test_exact(ac, case, padded, routed):  # noqa: F811
         n = lens[b:b + 1] if padded else torch.full((1,), S, device="cuda")
         _, want, terms = _reference(Q[b][None, None], K[b][None, None], V[b][None, None], causal, n)
         _check_result(O[b], want[0, 0], terms[0, 0])
+    assert (room[B] == 7.0).all()
     done = torch.ones(B, dtype=torch.bool, device="cuda") if sel is None else sel < 0
     assert O[done].isfinite().all() and (O[done] != 7.0).any(-1).all() and (O[~done] == 7.0).all()
 
@@ -89,12 +95,14 @@ def test_insert(ac, case):  # noqa: F811
     maps, emb, out = [], [], []
     for layout in ("dense", "packed"):
         shape = (M, Lc, Hq, S, S) if layout == "dense" else (M, Lc, Hq, ac.packed_tile_elems(S, causal))
-        store, e = torch.full(shape, 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((M, 64), 7.0, device="cuda").half()
+        room, e = torch.full((M + 1, *shape[1:]), 7.0, dtype=torch.bfloat16, device="cuda"), torch.full((M, 64), 7.0, device="cuda").half()
+        store, O_room = room[:M], torch.full((B + 1, *Q.shape[1:]), 7.0, dtype=Q.dtype, device="cuda")
         db = ac.attncache_build_db(e, store, n_kv_heads=Hkv, head_dim=D, causal=causal, **({} if layout == "dense" else {"seq_len": S}))
-        O = torch.full_like(Q, 7.0)
+        O = O_room[:B]
         ac.attncache_insert(db, Q, K, V, O, slot=slot, feat=feat, key_len=lens, row_sel=sel)
         torch.cuda.synchronize()
         db.close()
+        assert (room[M] == 7.0).all() and (O_room[B] == 7.0).all()
         maps, emb, out = maps + [store], emb + [e], out + [O]
     one_kernel = not (causal and S == 128 and D == 64)   # (dense maps take the two passes there)
     assert (torch.equal(out[0], out[1]) or not one_kernel) and torch.equal(emb[0], emb[1])
