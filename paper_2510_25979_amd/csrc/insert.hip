@@ -563,12 +563,12 @@ __global__ __launch_bounds__(kThreads, 2) void insert_bf16_short_kernel(const Sh
   int slots[kShortTiles];   // of the workgroup's tiles
 #pragma unroll
   for (int t = 0; t < kShortTiles; ++t) {
-    const int tile = blockIdx.x / s.parts * s.tiles_per_wg + t, b = tile / (s.Hkv * s.Lc);
+    const int tile = short_tile0(s) + t, b = tile / (s.Hkv * s.Lc);
     slots[t] = -1;
     if (t >= s.tiles_per_wg || tile >= s.n_tiles) continue;
     slots[t] = slot_of(b);
     // the item's first workgroup also copies its feature vector into the same slot
-    if (a.feat && blockIdx.x % s.parts == 0 && tile % (s.Hkv * s.Lc) == 0 && slots[t] >= 0 && !(a.row_sel && a.row_sel[b] >= 0))
+    if (a.feat && (blockIdx.x >> s.xcd_bits) % s.parts == 0 && tile % (s.Hkv * s.Lc) == 0 && slots[t] >= 0 && !(a.row_sel && a.row_sel[b] >= 0))
       for (int p = threadIdx.x; p < a.feat_pieces; p += kThreads)
         a.emb[(size_t)slots[t] * a.feat_pieces + p] = a.feat[(size_t)b * a.feat_pieces + p];
   }

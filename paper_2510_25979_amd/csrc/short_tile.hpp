@@ -19,6 +19,7 @@ struct ShortArgs {
   int32_t n_tiles;        // (item, layer, K/V head)
   int32_t tiles_per_wg;   // up to kShortTiles
   int32_t parts;          // workgroups that share a tile's units (tiles_per_wg is 1 then)
+  int32_t xcd_bits;       // 3 if those get ids equal mod 8 (one XCD, one L2), else 0
   float scale_log2e;
 };
 constexpr int kShortTiles = 4;
@@ -28,13 +29,29 @@ inline size_t short_lds(const ShortArgs& a, int S, int D) {
 }
 // Tiles of a workgroup and parts of a tile (as many as the chip holds at once: a second round of workgroups takes longer than
 // units one after the other: 192 tiles of 4 heads on one of 128 x 128, causal 21.3 us in four parts, 17.9 in two); the grid.
+// In large launches of 32 rows a workgroup takes four units again, those of a tile on one XCD: they read and write closer together (K and V,
+// which the others find in the L2, are few bytes there).  us per call, one workgroup a tile / so, exact: 8,192 tiles of eight heads on one K and V of 32 x 128
+// 238 / 207 (228 in the resident kernel), 32,768 954 / 841; 2,048 of sixteen 100 / 99; 32 x 64, 8,192 of twelve 158 / 149, of eight 105 / 104, 4,096 47.5 / 48.4.
+// With 64 rows and more it costs what it gains or more: 8,192 tiles of four heads of 64 x 128 246 / 254, inserted packed 280 / 305.
 inline unsigned short_plan(ShortArgs& a, int S, int D) {
   const int units = a.Hq / a.Hkv * (S >> 5), slots = 256 * (D == 64 ? (S <= 64 ? 4 : 3) : S == 32 ? 3 : 2);
   a.tiles_per_wg = units < 4 ? 4 / units : 1;
   const int most = (units + 3) / 4, fit = slots / a.n_tiles;
   a.parts = fit < 1 ? 1 : fit < most ? fit : most;
   if (a.tiles_per_wg > 1) a.parts = 1;
+  a.xcd_bits = 0;
+  const size_t apart = (size_t)a.n_tiles * most;   // (a grid has 2^32 threads at most)
+  if (S == 32 && units > 4 && units % 4 == 0 && apart >= (D == 64 ? 16384 : 8192) && apart < (size_t)1 << 23) {
+    a.parts = most;
+    a.xcd_bits = 3;
+    return (unsigned)((size_t)((a.n_tiles + 7) / 8 * 8) * a.parts);
+  }
   return (unsigned)((size_t)((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg) * a.parts);
+}
+
+__device__ __forceinline__ int short_tile0(const ShortArgs& a) {   // first tile of the workgroup
+  const unsigned group = (blockIdx.x >> a.xcd_bits) / a.parts;
+  return (int)(group << a.xcd_bits | (blockIdx.x & ((1u << a.xcd_bits) - 1))) * a.tiles_per_wg;
 }
 
 struct ShortUnit { int t, head, rb, tile, b, len; };   // tile of the workgroup, head of all, 32-row block, tile of all, item, its keys
@@ -54,7 +71,7 @@ __device__ __forceinline__ void short_attention(const ShortArgs& a, bf16_t* smem
   bf16_t* kb = smem;                          // [T][S][D]
   bf16_t* vb = smem + (size_t)T * S * D;      // [T][S][D]
   bf16_t* ost = smem + (size_t)2 * T * S * D + wave * (16 * kSmallOutStride);
-  const int tile0 = blockIdx.x / a.parts * T, part = blockIdx.x % a.parts;
+  const int tile0 = short_tile0(a), part = (int)((blockIdx.x >> a.xcd_bits) % a.parts);
   // as a scalar that a vector instruction wrote (see exact.hip)
   const float scale = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.scale_log2e) + (lane & 0)));
 

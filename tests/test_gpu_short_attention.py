@@ -45,6 +45,36 @@ def _check_result(O, want, terms):
     assert ((O.float() - want).abs() <= 2.0 ** -8 * 1.05 * (want.abs() + 2 * terms) + 1e-5).all()
 
 
+# workgroups of four units of a K and V of 32 rows, those of one on an XCD; no multiple of eight K and V
+LARGE_CASES = [(547, 120, 15, 32, 64, True), (1367, 24, 2, 32, 128, False), (683, 96, 6, 32, 128, True)]
+
+
+@pytest.mark.parametrize("case", LARGE_CASES, ids=lambda c: "B%d-%d/%d-S%d-D%d-%s" % c)
+def test_large_launches_of_32_rows(ac, case):  # noqa: F811
+    B, Hq, Hkv, S, D, causal = case
+    Q, K, V, lens = _data(B, 1, Hq, Hkv, S, D, B)
+    _, want, terms = _reference(Q, K, V, causal, lens)
+    O = torch.full_like(Q, 7.0)
+    ac.attention_exact(Q[:, 0], K[:, 0], V[:, 0], O[:, 0], causal=causal, key_len=lens)
+    _check_result(O, want, terms)
+    M = B + 1
+    maps, emb = torch.full((M, 1, Hq, S, S), 7.0, dtype=torch.bfloat16, device="cuda"), torch.zeros(M, 64, device="cuda").half()
+    slot = torch.randperm(M, generator=torch.Generator().manual_seed(B)).int()[:B].cuda()
+    feat = torch.randn(B, 64, device="cuda").half()
+    O2 = torch.full_like(Q, 7.0)
+    db = ac.attncache_build_db(emb, maps, n_kv_heads=Hkv, head_dim=D, causal=causal)
+    ac.attncache_insert(db, Q, K, V, O2, slot=slot, feat=feat, key_len=lens)
+    torch.cuda.synchronize()
+    db.close()
+    _check_result(O2, want, terms)
+    p = _reference(Q, K, V, causal, lens)[0][:, 0]
+    got = maps[slot.long(), 0].float()
+    assert ((got - p).abs() <= 2.0 ** -8 * 1.05 * p).all() and torch.equal(emb[slot.long()], feat)
+    left = torch.ones(M, dtype=torch.bool, device="cuda")
+    left[slot.long()] = False
+    assert (maps[left] == 7.0).all()
+
+
 @pytest.mark.parametrize("padded,routed", [(False, False), (True, True)])
 @pytest.mark.parametrize("case", EXACT_CASES, ids=lambda c: "B%d-%d/%d-S%d-D%d-%s" % c)
 def test_exact(ac, case, padded, routed):  # noqa: F811

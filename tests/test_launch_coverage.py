@@ -203,3 +203,17 @@ def test_large_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp
 def test_workgroups_of_short_reuse(tmp_path, case, grid):
     (status, ls), = launches.record([("apply", *case[:7], "bf16", case[7])], tmp_path)
     assert status == 0 and [(la[0].split("<")[0], la[1]) for la in ls] == [("apply_bf16_short_kernel", grid)]
+
+
+@pytest.mark.parametrize("case,grid", [
+    # B, heads, K/V heads, S, D, causal; workgroups                us, one workgroup a K/V head / workgroups of four units
+    ((512, 128, 16, 32, 128, True), 2 * 8192),       # 238 / 207
+    ((128, 256, 16, 32, 128, True), 4 * 2048),       # 100 / 99
+    ((512, 128, 16, 32, 64, True), 2 * 8192),        # 105 / 105
+    ((256, 128, 16, 32, 64, True), 4096),            # 47.5 / 48.4
+    ((512, 64, 16, 64, 128, True), 8192),            # 246 / 254
+    ((1367, 24, 2, 32, 128, False), 3 * 2736),       # (2,734 K/V heads, rounded up to eight)
+], ids=str)
+def test_workgroups_of_short_exact_attention(tmp_path, case, grid):
+    (status, ls), = launches.record([("exact", *case, "bf16")], tmp_path)
+    assert status == 0 and [(la[0].split("<")[0], la[1]) for la in ls] == [("exact_bf16_short_kernel", grid)]
