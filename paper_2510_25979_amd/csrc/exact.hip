@@ -1025,9 +1025,10 @@ hipError_t launch_exact(const ExactLaunch& p, hipStream_t stream) {
   }
   if (p.S <= 128) {
     // A routed launch of many tiles may find few of them to do: the resident kernel tests 64 at a time, here each costs the launch
-    // of a workgroup (32,768 tiles, none to do, 5.5 us and 23).  Very large causal launches of 128 x 128 with shared K and V are faster
-    // there too: 2,048 x 32 heads on 16 (262,144 units) 1,210 / 1,290 us, 4,096 x 32 on 8 1,997 / 2,008, 1,024 x 32 on 8 (131,072) 497 / 494.
-    const bool slower = p.causal && p.D == 128 && p.S == 128 && g > 1 && units > 200000;
+    // of a workgroup (32,768 tiles, none to do, 5.5 us and 23).  Very large causal launches of 128 x 128 of two heads on a K and V
+    // are faster there too: 1,024 x 32 heads on 16 (131,072 units) 586 / 620 us, 2,048 1,198 / 1,259, 512 298 / 296; not of four, 2,048 x 64 on 16
+    // 1,970 / 1,981, 1,024 989 / 995.
+    const bool slower = p.causal && p.D == 128 && p.S == 128 && g == 2 && units > 100000;
     ShortArgs sa = exact_short_args(p, a.scale_log2e);
     const unsigned wgs = short_plan(sa, p.S, p.D);
     if (!slower && (!p.row_sel || wgs <= 2048)) return launch_exact_short(p, sa, wgs, stream);

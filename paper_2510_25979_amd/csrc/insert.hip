@@ -530,13 +530,14 @@ static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t st
   // 7.0 / 7.4, (1,024) 8.9 / 7.5, 64 x 64 (1,536) 8.3 / 9.1, (2,048) 12.1 / 10.0, 64 x 128 (1,024) 9.1 / 9.5, (1,536) 16.8 / 13.5, 128 x 128 (768)
   // 10.0 / 10.1, (1,024) 11.1 / 10.8; 64 x 16 x 32 heads of 32 x 64 (49,152) 295 / 163, of 64 x 64 204 / 170, 32 on 8 of 128 x 128 262 / 249.
   // Rows of dense maps, 96 and more of them, are written in shorter runs by the units of one pass than by two passes over a whole tile, which
-  // shows where no heads share K and V and at D = 64 (two passes / one: 1,024 x 32 heads of 128 x 64 causal 618 / 788, of 96 x 64 428 / 451, 512 x 32 of
-  // 128 x 128 484 / 537, 256 x 32 251 / 270, 64 x 32 62.4 / 61.4).  So do packed maps of 128 x 128, but only in very large
-  // launches (64 x L x 32 heads, L = 12 (98,304 units) 651 / 639, 14 757 / 761, 16 852 / 874, 32 on 16 K and V 1,406 / 1,514).
+  // shows where every head has its own K and V (two passes / one: 4,096 heads of 128 x 64 causal 87 / 98, 16,384 314 / 397, 16,384 of 96 x 64 428 / 451, of
+  // 128 x 128 485 / 550, 8,192 251 / 270, 2,048 62.4 / 61.4; where two share them, 8,192 of 128 x 64 297 / 286, four 563 / 513, two of 96 x 64 196 / 186, of
+  // 128 x 128 8,192 418 / 409).  So do packed maps of 128 x 128, but only in very large launches of one or two heads on a K and V (32,768 heads
+  // 852 / 874, 24,576 651 / 639; 16,384 of two 713 / 746, 8,192 361 / 363; of four 1,282 / 1,287, of eight 8,192 1,216 / 1,188).
   const size_t few = g > 1 ? (a.S >= 96 && D == 64 ? 576 : 320)
                      : a.S == 32 ? (D == 64 ? 896 : 576) : a.S == 64 ? (D == 64 ? 1792 : 1152) : 1024;
-  const bool slower = PACKED ? CAUSAL && D == 128 && a.S == 128 && units > 100000
-                             : a.S >= 96 && (g == 1 || (CAUSAL && D == 64)) && units > (CAUSAL && D == 64 && a.S == 128 ? 1800 : 10000);
+  const bool slower = PACKED ? CAUSAL && D == 128 && a.S == 128 && g <= 2 && units > 100000
+                             : a.S >= 96 && g == 1 && units > (CAUSAL && D == 64 && a.S == 128 ? 1800 : 10000);
   if (a.S <= kChunk && units > few && !slower) return launch_insert_short<D, CAUSAL, PACKED>(a, stream);
   if (units <= most) {
     hipLaunchKernelGGL((insert_bf16_split_kernel<D, CAUSAL, PACKED>), dim3((unsigned)units), dim3(kThreads), 0, stream, a);

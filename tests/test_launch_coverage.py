@@ -180,6 +180,10 @@ def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
     ((64, 12, 32, 32, 128, 128, True, True), "insert_bf16_short_kernel<128, true, true"),   # us, two passes over the keys 651, one 639
     ((64, 16, 32, 32, 128, 128, True, True), "insert_bf16_kernel<128, true, true"),         # 852, 874
     ((64, 16, 32, 32, 128, 64, True, False), "insert_bf16_kernel<64, true, false"),         # 618, 788
+    ((64, 8, 64, 16, 128, 64, True, False), "insert_bf16_short_kernel<64, true, false"),    # 563, 513
+    ((64, 16, 32, 16, 96, 64, True, False), "insert_bf16_short_kernel<64, true, false"),    # 372, 360
+    ((64, 16, 32, 16, 128, 128, True, True), "insert_bf16_kernel<128, true, true"),         # 713, 746
+    ((64, 8, 128, 16, 128, 128, True, True), "insert_bf16_short_kernel<128, true, true"),   # 1,216, 1,188
     ((64, 8, 32, 32, 96, 128, True, False), "insert_bf16_kernel<128, true, false"),         # 354, 382
     ((64, 8, 32, 16, 128, 128, True, False), "insert_bf16_short_kernel<128, true, false"),  # 415, 405
 ], ids=str)
@@ -217,3 +221,14 @@ def test_workgroups_of_short_reuse(tmp_path, case, grid):
 def test_workgroups_of_short_exact_attention(tmp_path, case, grid):
     (status, ls), = launches.record([("exact", *case, "bf16")], tmp_path)
     assert status == 0 and [(la[0].split("<")[0], la[1]) for la in ls] == [("exact_bf16_short_kernel", grid)]
+
+
+@pytest.mark.parametrize("case,kernel", [
+    ((1024, 32, 16, 128, 128, True), "exact_bf16_kernel<128, true, true"),          # us, resident 586, short 620
+    ((512, 32, 16, 128, 128, True), "exact_bf16_short_kernel<128, true, 4"),        # 298, 296
+    ((2048, 64, 16, 128, 128, True), "exact_bf16_short_kernel<128, true, 4"),       # 1,970, 1,981
+    ((2048, 32, 16, 128, 64, True), "exact_bf16_short_kernel<64, true, 4"),         # 577, 543
+], ids=str)
+def test_large_exact_launches_of_128_rows_take_the_kernel_that_measured_best(tmp_path, case, kernel):
+    (status, ls), = launches.record([("exact", *case, "bf16")], tmp_path)
+    assert status == 0 and ls[0][0].startswith(kernel), ls
