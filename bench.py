@@ -68,22 +68,54 @@ def exact_flops(w, n_items, dense_equivalent=False):
     return 4.0 * scores * D * n_items * w.n_layers * w.n_q_heads
 
 
-def apply_kernel_name(w):
+# The kernels that the library's launch rules choose for a workload's whole batch (tests/test_launch_coverage.py compares).
+def apply_kernel_name(w, layout="packed"):
     if w.map_dtype != "bf16":
         return "apply_f32_kernel"
     if w.seq_len > 128:
         return "apply_bf16_long_kernel"
-    return "apply_bf16_kernel" if w.seq_len == 128 and w.head_dim == 64 and w.causal else "apply_bf16_short_kernel"
+    tiles = w.batch * w.n_layers * w.n_kv_heads
+    halves = w.seq_len == 128 and w.head_dim == 64 and w.causal and layout == "packed" and tiles > 512
+    return "apply_bf16_kernel" if halves else "apply_bf16_short_kernel"
+
+
+def _units(w):
+    """Heads' blocks of 32 query rows."""
+    return w.batch * w.n_layers * w.n_q_heads * (w.seq_len // 32)
 
 
 def exact_kernel_name(w):
+    S, D, g, units = w.seq_len, w.head_dim, w.n_q_heads // w.n_kv_heads, _units(w)
     if w.map_dtype != "bf16":
-        return "exact_f32_kernel"
-    if w.seq_len > 128:
+        few = 512 if S <= 64 else 768 if S < 128 else 1536   # blocks of 16 rows
+        rows16 = w.batch * w.n_layers * w.n_q_heads * ((S + 15) // 16)
+        return "exact_f32_split_kernel" if D % 16 == 0 and rows16 <= few else "exact_f32_kernel"
+    if S > 128:
+        few = (576 if D == 64 else 320) // (1 if w.causal else 2)
+    else:
+        few = 512 if D == 64 and w.causal and (S == 128 or (g == 1 and S <= 64)) else 320 if D == 64 else 256
+    if units <= few:
+        return "exact_bf16_split_kernel"
+    if S > 128:
         return "exact_bf16_kernel (streaming)"
-    rows = w.batch * w.n_layers * w.n_q_heads * w.seq_len
-    shared = w.causal and w.head_dim == 128 and w.seq_len == 128 and w.n_q_heads > w.n_kv_heads
-    return "exact_bf16_kernel (resident)" if shared and rows // 32 > 200000 else "exact_bf16_short_kernel"
+    resident = w.causal and D == 128 and S == 128 and g == 2 and units > 100000
+    return "exact_bf16_kernel (resident)" if resident else "exact_bf16_short_kernel"
+
+
+def insert_kernel_name(w):
+    """Maps in the packed layout."""
+    S, D, g, units = w.seq_len, w.head_dim, w.n_q_heads // w.n_kv_heads, _units(w)
+    if S > 128:
+        few = ((768 if D == 64 else 480) if w.causal else (448 if D == 64 else 320))
+        return "insert_bf16_split_kernel" if units <= few else "insert_bf16_kernel"
+    if g > 1:
+        few = 576 if S >= 96 and D == 64 else 320
+    else:
+        few = {32: (896, 576), 64: (1792, 1152)}.get(S, (1024, 1024))[D == 128]
+    if units > few and not (w.causal and D == 128 and S == 128 and g <= 2 and units > 100000):
+        return "insert_bf16_short_kernel"
+    split = (128 if S > 64 else 0) if g == 1 else min(1024, g * (256 if D == 64 else 176 if S > 64 else 128))
+    return "insert_bf16_split_kernel" if units <= split else "insert_bf16_kernel"
 
 
 # --------------------------------------------------------------------- timing helpers
@@ -229,7 +261,7 @@ def run_resident(ac, synth, synthdb, traffic, args, cfg, *, extras=False):
     a_bytes = apply_bytes(w, n_hits)
     a_dense = apply_bytes(w, n_hits, dense_equivalent=True)
     achieved = a_bytes / (apply_ms * 1e-3) / 1e9
-    reading = traffic.lookup(apply_kernel_name(w), w.name, layout) if not args.entries else None
+    reading = traffic.lookup(apply_kernel_name(w, layout), w.name, layout) if not args.entries else None
     x_s = exact_ms * 1e-3
     rec = {
         "value": tokens / (ms_step * 1e-3), "unit": "tokens/s",
@@ -245,7 +277,7 @@ def run_resident(ac, synth, synthdb, traffic, args, cfg, *, extras=False):
         "exact_tokens_per_s": tokens / x_s,
         "speedup_reuse_vs_exact": (exact_ms / apply_ms) * (n_hits / B) if n_hits else None,
         "search_qps": B / (search_ms * 1e-3),
-        "roofline": {"kernel": apply_kernel_name(w), "bound": "hbm", "achieved": achieved,
+        "roofline": {"kernel": apply_kernel_name(w, layout), "bound": "hbm", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": reading["bytes"] if reading else None,
                      "algorithmic_bytes_per_launch": a_bytes,
@@ -400,8 +432,7 @@ def run_insert(ac, args, traffic, w, Q, K, V):
     dbi.close()
     g = Hq // Hkv
     nbytes = (S * D * 2 * (2 + 2 / g) + tile * 2) * B * L * Hq
-    two_passes = S > 128 or (D == 128 and S == 128 and w.causal and B * L * Hq * S // 32 > 100000)
-    kernel = "insert_bf16_kernel" if two_passes else "insert_bf16_short_kernel"
+    kernel = insert_kernel_name(w)
     reading = traffic.lookup(kernel, w.name, "packed") if not args.entries else None
     return {"ms": ms, "tokens_per_s": B * S / (ms * 1e-3),
             "roofline": {"kernel": kernel, "bound": "hbm",

@@ -13,12 +13,13 @@ CASES = [
     # without one; parts of a K/V head's units, and all of them one after the other
     (5, 2, 1, 1), (3, 1, 5, 1), (4, 2, 3, 2), (5, 2, 2, 3), (4, 1, 2, 4), (3, 2, 1, 7), (180, 2, 1, 4), (150, 3, 1, 6), (175, 2, 1, 12),
 ]
+CASES_128 = [(180, 3, 1, 1), (180, 3, 1, 4), (4, 1, 2, 3), (3, 2, 5, 1)]
 
 
 @pytest.mark.parametrize("layout", ["dense", "packed"])
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("case", [(180, 3, 1, 1), (180, 3, 1, 4), (4, 1, 2, 3), (3, 2, 5, 1)], ids=lambda c: "B%d-L%d-%dx%d" % c)
+@pytest.mark.parametrize("case", CASES_128, ids=lambda c: "B%d-L%d-%dx%d" % c)
 def test_maps_of_128_rows(ac, oracle_mod, case, D, causal, layout):  # noqa: F811
     # few tiles and more than 512 of them, which packed causal maps of 64 columns have a kernel for
     test_short_maps(ac, oracle_mod, case, 128, D, causal, layout)

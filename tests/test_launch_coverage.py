@@ -4,6 +4,8 @@ import subprocess
 
 import pytest
 
+import bench
+from paper_2510_25979_amd import synth
 from tests import launches
 from tests import test_gpu_f32_tiles as f32
 from tests import test_gpu_parity_small as small
@@ -11,6 +13,7 @@ from tests import test_gpu_projector as proj
 from tests import test_gpu_row_units as rows
 from tests import test_gpu_search_tiles as tiles
 from tests import test_gpu_short_attention as short
+from tests import test_gpu_short_reuse as reuse
 from tests import test_gpu_split_units as split
 
 # fp16 rows of more than 2,360 columns, more than 64 queries and 128 groups: 5e9 products and more for
@@ -73,7 +76,13 @@ def test_every_attention_kernel_is_reached(tmp_path):
     calls += [("insert", *c, packed) for c in short.INSERT_CASES for packed in (False, True)]
     calls += [("apply", c[0], c[9], *c[3:8], _dt(c[10])) for c in small.APPLY_CASES]
     calls += [("apply", c[0], 2, *c[1:], "f32") for c in f32.CASES]
-    missing = _kernels("exact_", "insert_", "apply_f32") - _reached(tmp_path, calls)
+    for layout in (False, True):
+        calls += [("apply", c[0], c[9], *c[3:8], _dt(c[10]), layout) for c in small.APPLY_CASES if "bf" in _dt(c[10])]
+        calls += [("apply", B, Lc, Hkv * g, Hkv, S, D, causal, "bf16", layout) for B, Lc, Hkv, g in reuse.CASES for S in (32, 64, 96)
+                  for D in (64, 128) for causal in (True, False)]
+        calls += [("apply", B, Lc, Hkv * g, Hkv, 128, D, causal, "bf16", layout) for B, Lc, Hkv, g in reuse.CASES_128 for D in (64, 128)
+                  for causal in (True, False)]
+    missing = _kernels("exact_", "insert_", "apply_") - _reached(tmp_path, calls)
     assert not missing
 
 
@@ -232,3 +241,27 @@ def test_workgroups_of_short_exact_attention(tmp_path, case, grid):
 def test_large_exact_launches_of_128_rows_take_the_kernel_that_measured_best(tmp_path, case, kernel):
     (status, ls), = launches.record([("exact", *case, "bf16")], tmp_path)
     assert status == 0 and ls[0][0].startswith(kernel), ls
+
+
+@pytest.mark.parametrize("heads", [{}, dict(n_q_heads=8, n_kv_heads=8), dict(n_q_heads=32, n_kv_heads=16)], ids=str)
+@pytest.mark.parametrize("scale", [{}, dict(batch=1), dict(batch=5, n_layers=1), dict(seq_len=64), dict(seq_len=32, n_layers=2),
+                                   dict(head_dim=64), dict(head_dim=128, batch=16), dict(seq_len=96, n_layers=3)], ids=str)
+def test_the_benchmark_names_the_kernels_that_run(tmp_path, scale, heads):
+    calls, names = [], []
+    for w in synth.WORKLOADS.values():
+        w = w.scaled(**scale, **heads)
+        bf16 = w.map_dtype == "bf16"
+        size = (w.n_q_heads, w.n_kv_heads, w.seq_len, w.head_dim, w.causal)
+        for layout in ("packed", "dense") if bf16 else ("dense",):
+            calls.append(("apply", w.batch, w.n_layers, *size, w.map_dtype, layout == "packed"))
+            names.append(bench.apply_kernel_name(w, layout))
+        calls.append(("exact", w.batch, w.n_layers * w.n_q_heads, w.n_layers * w.n_kv_heads, *size[2:], w.map_dtype))
+        names.append(bench.exact_kernel_name(w))
+        if bf16:
+            calls.append(("insert", w.batch, w.n_layers, *size, True))
+            names.append(bench.insert_kernel_name(w))
+    for call, name, (status, ls) in zip(calls, names, launches.record(calls, tmp_path)):
+        ran = ls[0][0]
+        if ran.startswith("exact_bf16_kernel<"):
+            ran = "exact_bf16_kernel (%s)" % ("resident" if ran.endswith("true>") else "streaming")
+        assert status == 0 and ran.split("<")[0] == name, (call, ran, name)
