@@ -1148,12 +1148,14 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
 // Rows alike are few of a group, and rows far from the origin are not far from each other, so the bounds are formed again, by
 // row and (Euclidean) of the differences to one of the workgroup's rows.  A workgroup takes wg_rows rows (128 or 256) and 32 NQB queries,
 // eight threads the score of a row and query; of neighbours that are the same they take the first.  Where more than kUnsurePairs reach, all
-// are scored, eight queries to a row.  (A thread a row and query, each reading its own lines, took three times as long.)
+// are scored, kUnsureRows rows of an eight by eight queries.  (A thread a row and query, each reading its own lines, took three times as long.)
 // Usually nothing is open, so the grid is one that is quickly through.
 // us per call, 100,000 x 128 fp32 Euclidean, 64 queries; exact scores of all rows first, / all rows of what is left open in tiles / so: 40 rows
 // at random places alike for each query 58 / 75 / 48; all rows of 40 kinds 59 / 77 / 58; rows 100 times their spread from the origin 57 / 73 / 47; all
-// rows the same 58 / 75 / 58.  Two kinds in random order, of which every third row reaches, 57 / 73 / 168.
+// rows the same 58 / 75 / 58.  Two kinds in random order, of which every third row reaches, so that all are scored, 57 / 73 / 124 (one row at a time 166; fp16
+// 100,000 x 256 118 / 139 / 213, 335): the vector ALUs take 55 of it, on 391 workgroups for 256 compute units.
 constexpr int kUnsurePairs = 2048;   // (twice as many cost fp16 rows of 256 columns the second workgroup of a compute unit)
+constexpr int kUnsureRows = 4;
 template <typename T, bool L2, int NQB, int MODE>
 __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const SearchArgs a) {
   typedef RowPiece<T> Piece;
@@ -1168,6 +1170,7 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
   float* own = reinterpret_cast<float*>(ref + bound_query(a.E));
   float* qq = own + 4 * 32;
   T* raw = reinterpret_cast<T*>(smem);             // [NQ][QE], once the products are done
+  const T* emb = reinterpret_cast<const T*>(a.emb);
   const int QE = (a.E + 7) & ~7;
   const int tid = threadIdx.x, lane = tid & 63, il = lane & 31, kh = lane >> 5;
   const int nqb = (a.B + NQ - 1) / NQ, n_rows = (a.N + a.wg_rows - 1) / a.wg_rows;
@@ -1207,55 +1210,42 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
     bound_products<T, L2, NQB, MODE>(a, row0, row_end, q0, nq, qs, own, ref, qq, note);
     __syncthreads();
     const int many = n_pairs, part8 = tid & 7;
-    // scores of eight rows and queries: a row each, or one row and eight queries in LDS; thread u of the eight has the u-th
-    auto score = [&](auto dense, const int (&r)[8], const int (&t)[8], bool live) __attribute__((always_inline)) {
-      constexpr bool DENSE = decltype(dense)::value;
-      constexpr int ROWS = DENSE ? 1 : 8;
-      float acc[8] = {};
-      auto add = [&](int c) __attribute__((always_inline)) {
-        Piece e[ROWS], x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          if (u < ROWS) e[u].load(reinterpret_cast<const T*>(a.emb) + (size_t)(row0 + r[u]) * a.E, c, a.E);
-          if constexpr (DENSE) x[u].w = *reinterpret_cast<const decltype(x[u].w)*>(raw + t[u] * QE + c);   // (zeros past E)
-          else x[u].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + t[u]) * a.E, c, a.E);
-        }
-#pragma unroll
-        for (int i = 0; i < P; ++i)
-#pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            const float y = e[DENSE ? 0 : u].at(i), d = x[u].at(i) - y;
-            acc[u] = L2 ? fmaf(-d, d, acc[u]) : fmaf(x[u].at(i), y, acc[u]);
-          }
-      };
-      if constexpr (DENSE) {
-#pragma unroll 4
-        for (int c = P * part8; c < a.E; c += 8 * P) add(c);
-      } else {
-#pragma unroll 1
-        for (int c = P * part8; c < a.E; c += 8 * P) add(c);
-      }
-      const float s = row_of_eight(acc, part8);
-      if (live && s == s) {
-        int mr = r[0], mt = t[0];
-#pragma unroll
-        for (int u = 1; u < 8; ++u) {
-          mr = part8 == u ? r[u] : mr;
-          mt = part8 == u ? t[u] : mt;
-        }
-        atomicMax(&top[mt][mr >> 5], score_key(s));
-      }
-    };
-    int r[8], t[8];
-    if (many <= kUnsurePairs * NQB) {
+    if (many <= kUnsurePairs * NQB) {   // scores of eight rows and queries, thread u of the eight has the u-th
       for (int p = tid & ~7; p < many; p += kThreads) {
+        int r[8], t[8];
+        float acc[8] = {};
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const int pair = pairs[min(p + u, many - 1)];
           r[u] = pair >> 6;
           t[u] = pair & 63;
         }
-        score(std::false_type{}, r, t, p + part8 < many);
+#pragma unroll 1
+        for (int c = P * part8; c < a.E; c += 8 * P) {
+          Piece e[8], x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            e[u].load(emb + (size_t)(row0 + r[u]) * a.E, c, a.E);
+            x[u].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + t[u]) * a.E, c, a.E);
+          }
+#pragma unroll
+          for (int i = 0; i < P; ++i)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              const float y = e[u].at(i), d = x[u].at(i) - y;
+              acc[u] = L2 ? fmaf(-d, d, acc[u]) : fmaf(x[u].at(i), y, acc[u]);
+            }
+        }
+        const float s = row_of_eight(acc, part8);
+        if (p + part8 < many && s == s) {
+          int mr = r[0], mt = t[0];
+#pragma unroll
+          for (int u = 1; u < 8; ++u) {
+            mr = part8 == u ? r[u] : mr;
+            mt = part8 == u ? t[u] : mt;
+          }
+          atomicMax(&top[mt][mr >> 5], score_key(s));
+        }
       }
     } else {
       for (int x = tid; x < NQ * QE; x += kThreads) {
@@ -1263,15 +1253,40 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
         raw[x] = c < a.E ? reinterpret_cast<const T*>(a.q)[(size_t)(q0 + min(x / QE, nq - 1)) * a.E + c] : (T)0.f;
       }
       __syncthreads();
-      for (int p = tid >> 3; p < (row_end - row0) * (NQ / 8); p += kThreads / 8) {   // (the eights of a wave have the same queries)
-        const int t0 = 8 * (p / (row_end - row0));
-        if (((opens >> t0) & 0xff) == 0) continue;
+      // Rows r0 + 32 j of an eight by eight queries; the sums take the steps of those above.
+      const int n = row_end - row0;
+      for (int r0 = tid >> 3; r0 < n; r0 += 32 * kUnsureRows) {
+        const T* row[kUnsureRows];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          r[u] = p % (row_end - row0);
-          t[u] = t0 + u;
+        for (int j = 0; j < kUnsureRows; ++j) row[j] = emb + (size_t)(row0 + min(r0 + 32 * j, n - 1)) * a.E;
+        for (int t0 = 0; t0 < NQ; t0 += 8) {
+          if (((opens >> t0) & 0xff) == 0) continue;
+          const T* x0 = raw + t0 * QE;
+          float acc[kUnsureRows][8] = {};
+#pragma unroll 2
+          for (int c = P * part8; c < a.E; c += 8 * P) {
+            Piece e[kUnsureRows];
+#pragma unroll
+            for (int j = 0; j < kUnsureRows; ++j) e[j].load(row[j], c, a.E);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              Piece x;
+              x.w = *reinterpret_cast<const decltype(x.w)*>(x0 + u * QE + c);   // (zeros past E)
+#pragma unroll
+              for (int i = 0; i < P; ++i)
+#pragma unroll
+                for (int j = 0; j < kUnsureRows; ++j) {
+                  const float y = e[j].at(i), d = x.at(i) - y;
+                  acc[j][u] = L2 ? fmaf(-d, d, acc[j][u]) : fmaf(x.at(i), y, acc[j][u]);
+                }
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < kUnsureRows; ++j) {
+            const float s = row_of_eight(acc[j], part8);
+            if (r0 + 32 * j < n && s == s && ((opens >> (t0 + part8)) & 1)) atomicMax(&top[t0 + part8][(r0 >> 5) + j], score_key(s));
+          }
         }
-        score(std::true_type{}, r, t, (opens >> (t0 + part8)) & 1);
       }
     }
     __syncthreads();

@@ -186,15 +186,20 @@ def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, case
         assert ((idx[some] < 0) == (i2 < 0)).all()
 
 
-def test_rows_alike_take_less_than_three_times_as_long(ac):  # noqa: F811
-    """60 rows alike for every query, in as many groups: their rows are scored by the whole chip (36 us a call, 19 without them; 74
-    where a workgroup a query scored group after group)."""
-    N, E, B = 100000, 64, 64
+@pytest.mark.parametrize("what,E,most", [("alike", 64, 3.0), ("two kinds", 128, 6.2)])
+def test_what_the_bounds_leave_open_takes_so_much_longer_at_most(ac, what, E, most):  # noqa: F811
+    """60 rows alike for every query, in as many groups: their rows are scored by the whole chip (33 us a call, 18 without them; 54
+    to 74 where a workgroup a query scored group after group).  Rows of two kinds, of which one in three reaches, so that all are scored:
+    124 us, 23.5 of rows that differ; 166 with one row a thread at a time."""
+    N, B = 100000, 64
     g = _gen(3)
     emb = torch.randn(N, E, generator=g) / E ** 0.5
     q = (emb[:B] + 0.02 * torch.randn(B, E, generator=g)).cuda()
-    alike = emb.clone()
-    alike[torch.randint(0, N, (60 * B,), generator=g)] = q.cpu().repeat(60, 1) + 0.01
+    if what == "alike":
+        alike = emb.clone()
+        alike[torch.randint(0, N, (60 * B,), generator=g)] = q.cpu().repeat(60, 1) + 0.01
+    else:
+        alike = emb[:2][torch.randint(0, 2, (N,), generator=g)]
     least = []
     for rows in (emb, alike):
         db = ac.attncache_build_db(rows.cuda(), torch.zeros(1, 1, 1, 8, 8, device="cuda"), n_kv_heads=1, head_dim=8, metric=ac.AC_L2,
@@ -219,7 +224,7 @@ def test_rows_alike_take_less_than_three_times_as_long(ac):  # noqa: F811
             times.append(start.elapsed_time(end))
         least.append(min(times))
         db.close()
-    assert least[1] < 3 * least[0], least
+    assert least[1] < most * least[0], least
 
 
 @pytest.mark.parametrize("case", VARIANT_CASES, ids=lambda c: "N%d-E%d-B%d-k%d-%s-%s" % (
