@@ -935,13 +935,12 @@ struct BoundPiece<f16_t> {
 enum { kFirst = 0, kAgain = 1, kCentred = 2 };
 template <typename T, bool L2, int NQB, int MODE, typename Done>
 __device__ __forceinline__ void bound_products(const SearchArgs& a, int row_begin, int row_end, int q0, int nq, uint16_t* qs, float* own,
-                                               T* ref, float* qq, Done done) {
+                                               T* ref, float* qq, int wave, Done done) {
   typedef BoundParts<std::conditional_t<MODE == kCentred, float, T>> Parts;
   typedef BoundPiece<T> Piece;
   typedef typename Parts::op op;
-  const int E = a.E, nks = (E + 15) >> 4, QS = bound_query(E);
+  const int E = a.E, nks = (E + 15) >> 4, QS = 16 * nks + kQPad;   // (bound_query(E))
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int il = lane & 31, kh = lane >> 5;
   const T* emb = reinterpret_cast<const T*>(a.emb);
 
@@ -1140,7 +1139,7 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
       __syncthreads();
     }
   };
-  bound_products<T, L2, NQB, kFirst>(a, row_begin, row_end, q0, nq, qs, own, (T*)nullptr, nullptr, keep);
+  bound_products<T, L2, NQB, kFirst>(a, row_begin, row_end, q0, nq, qs, own, (T*)nullptr, nullptr, wave, keep);
 }
 
 // The scores of what bounds have left open: for a query with idx[b][0] == kUnsure every row whose own bound reaches score[b][0], the
@@ -1173,6 +1172,7 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
   const T* emb = reinterpret_cast<const T*>(a.emb);
   const int QE = (a.E + 7) & ~7;
   const int tid = threadIdx.x, lane = tid & 63, il = lane & 31, kh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nqb = (a.B + NQ - 1) / NQ, n_rows = (a.N + a.wg_rows - 1) / a.wg_rows;
   const int64_t units = ((int64_t)n_rows + 7) / 8 * 8 * nqb;   // (the query blocks of the same rows on one XCD)
   for (int64_t unit = blockIdx.x; unit < units; unit += gridDim.x) {
@@ -1207,7 +1207,7 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
       }
     };
     // (a barrier between the zeros above and note())
-    bound_products<T, L2, NQB, MODE>(a, row0, row_end, q0, nq, qs, own, ref, qq, note);
+    bound_products<T, L2, NQB, MODE>(a, row0, row_end, q0, nq, qs, own, ref, qq, wave, note);
     __syncthreads();
     const int many = n_pairs, part8 = tid & 7;
     if (many <= kUnsurePairs * NQB) {   // scores of eight rows and queries, thread u of the eight has the u-th
@@ -1887,7 +1887,7 @@ __global__ __launch_bounds__(NT) void finalize_topk_kernel(const SearchArgs a, i
 }
 
 // k = 1 after search_bound_kernel: the same in fewer steps.  The group with the best bound is scored, eight threads a row, then
-// every other group whose bound reaches the best score, four at a time.  UNSURE: after search_unsure_kernel, which leaves the best
+// every other group whose bound reaches the best score, of three and more four at a time.  UNSURE: after search_unsure_kernel, which leaves the best
 // scores of the groups in place of their bounds, so the first group holds the answer.
 template <typename T, bool L2, bool UNSURE>
 __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs a) {
@@ -1931,8 +1931,7 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
       row[u] = reinterpret_cast<const T*>(a.emb) + (size_t)max(r[u], 0) * a.E;
       acc[u] = 0.f;
     }
-#pragma unroll 2
-    for (int c = P * part8; c < a.E; c += 8 * P) {
+    auto add = [&](int c) __attribute__((always_inline)) {
       Piece e[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) e[u].load(row[u], c, a.E);
@@ -1943,6 +1942,13 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
           const float d = qf[c + t] - e[u].at(t);
           acc[u] = L2 ? fmaf(-d, d, acc[u]) : fmaf(qf[c + t], e[u].at(t), acc[u]);
         }
+    };
+    if constexpr (U == 1) {   // (as many loads in flight as of four groups)
+#pragma unroll 4
+      for (int c = P * part8; c < a.E; c += 8 * P) add(c);
+    } else {
+#pragma unroll 2
+      for (int c = P * part8; c < a.E; c += 8 * P) add(c);
     }
     uint64_t top = 0;
 #pragma unroll
@@ -1987,8 +1993,11 @@ __global__ __launch_bounds__(1024) void finalize_bound1_kernel(const SearchArgs 
       return;
     }
     if (many > 0) {
-      for (int x = 0; x < many; x += 4)   // (past the last one: that one again)
-        best = max(best, score_groups(std::integral_constant<int, 4>{}, [&](int u) { return more[min(x + u, many - 1)]; }));
+      if (many < 3)   // (as fours 64 queries of 100,000 x 128 fp32, most with one or none, take 7.4 us for 5.8)
+        for (int x = 0; x < many; ++x) best = max(best, score_groups(std::integral_constant<int, 1>{}, [&](int) { return more[x]; }));
+      else
+        for (int x = 0; x < many; x += 4)   // (past the last one: that one again)
+          best = max(best, score_groups(std::integral_constant<int, 4>{}, [&](int u) { return more[min(x + u, many - 1)]; }));
       best = block_best(best, 0);
     }
   }
