@@ -75,7 +75,8 @@ def apply_kernel_name(w, layout="packed"):
     if w.seq_len > 128:
         return "apply_bf16_long_kernel"
     tiles = w.batch * w.n_layers * w.n_kv_heads
-    halves = w.seq_len == 128 and w.head_dim == 64 and w.causal and layout == "packed" and tiles > 512
+    halves = (w.seq_len == 128 and w.head_dim == 64 and w.causal and layout == "packed" and tiles > 512
+              and (w.n_q_heads == w.n_kv_heads or w.batch * w.n_layers * w.n_q_heads <= 20000))
     return "apply_bf16_kernel" if halves else "apply_bf16_short_kernel"
 
 

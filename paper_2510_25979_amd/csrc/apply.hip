@@ -880,12 +880,15 @@ hipError_t launch_apply(const ApplyLaunch& p, hipStream_t stream) {
     if (p.D <= 128) return launch_apply_f32<2>(a, p.D, p.causal, stream);
     return launch_apply_f32<4>(a, p.D, p.causal, stream);
   }
-  // 128 rows of packed causal maps of 64 columns of V, many tiles: the kernel with the two balanced 16-row blocks a wave is
-  // as fast or faster.  us per call, that one / units of 32 rows: 120 x 8 x 24 heads on 2 K/V heads 78 / 84, 32 x 16 x 32 on 32 147 / 147,
-  // 35 x 16 x 16 on 4 53.3 / 53.4, 16 x 2 x 32 on 8 (256 tiles) 11.8 / 11.7, 8 x 2 x 32 on 8 11.3 / 6.9.  All others gain: 128 columns,
-  // 64 x 8 x 32 heads on 8 170 / 161, 3 x 16 on 8, dense 10.1 / 6.3; dense maps, 64 columns, 16 x 6 x 32 on 8 29.0 / 24.0; no mask,
-  // 60 x 8 x 24 on 12 80.5 / 72.7.
-  const bool halves = p.S == 128 && p.D == 64 && p.causal && p.packed && (size_t)nb * p.Lc * p.Hkv > 512;
+  // 128 rows of packed causal maps of 64 columns of V, many tiles: the kernel with the two balanced 16-row blocks a wave is 2 to 4 %
+  // faster, unless heads share V and a launch is so large that units on one XCD read and write closer together (kShortMany).  us per call,
+  // that one / units of 32 rows, K/V heads of one head: 768 5.8 / 6.4, 2,048 17.0 / 17.2, 8,192 61.3 / 63.8, 32,768 290 / 289; of two 1,024 13.4 / 13.7,
+  // 4,096 52.5 / 54.3, 8,192 113 / 111, 16,384 248 / 235; of three 4,096 75.7 / 77.2, 8,192 165 / 157; of four 768 18.1 / 18.9, 4,096 96.5 / 100, 8,192
+  // 235 / 211, 32,768 1,009 / 923; of eight 2,048 92.5 / 95.1, 4,096 215 / 197; of twelve 768 49.3 / 49.1, 2,048 145 / 146, 4,096 351 / 301.  Up to 512 tiles:
+  // 16 x 2 x 32 heads on 8 11.8 / 11.7, 8 x 2 x 32 on 8 11.3 / 6.9.  All others gain: 128 columns, 64 x 8 x 32 heads on 8 170 / 161, 3 x 16
+  // on 8, dense 10.1 / 6.3; dense maps, 64 columns, 16 x 6 x 32 on 8 29.0 / 24.0; no mask, 60 x 8 x 24 on 12 80.5 / 72.7.
+  const bool halves = p.S == 128 && p.D == 64 && p.causal && p.packed && (size_t)nb * p.Lc * p.Hkv > 512 &&
+                      (p.Hq == p.Hkv || (size_t)nb * p.Lc * p.Hq <= 20000);
   if (p.S <= 128 && !halves) return launch_short(a, p.D, p.S, p.causal, p.packed, nb, stream);
   a.n_rblk = (p.S + kChunk - 1) / kChunk;
   const int g = p.Hq / p.Hkv;

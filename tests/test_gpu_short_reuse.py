@@ -57,7 +57,7 @@ def test_short_maps(ac, oracle_mod, case, S, D, causal, layout):  # noqa: F811
 # B, Lc, Hkv, heads on one K/V head, S, D, causal, layout: a workgroup has four units of a tile, those of a tile are on one XCD; the
 # number of tiles is no multiple of the eight XCDs
 LARGE_CASES = [(1639, 5, 1, 8, 32, 64, True, "dense"), (683, 4, 3, 4, 64, 128, False, "packed"), (1639, 5, 1, 2, 128, 128, True, "packed"),
-               (1093, 5, 1, 3, 128, 128, True, "dense")]
+               (1093, 5, 1, 3, 128, 128, True, "dense"), (1639, 5, 1, 3, 128, 64, True, "packed")]
 
 
 @pytest.mark.parametrize("case", LARGE_CASES, ids=lambda c: "B%d-L%d-%dx%d-S%d-D%d-%s-%s" % c)

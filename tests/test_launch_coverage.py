@@ -218,6 +218,22 @@ def test_workgroups_of_short_reuse(tmp_path, case, grid):
     assert status == 0 and [(la[0].split("<")[0], la[1]) for la in ls] == [("apply_bf16_short_kernel", grid)]
 
 
+@pytest.mark.parametrize("case,kernel", [
+    # B, layers, heads, K/V heads                      us, two halves / units of 32 rows
+    ((8, 8, 32, 8), "apply_bf16_short_kernel<64"),     # (512 tiles)
+    ((12, 8, 32, 8), "apply_bf16_kernel<true>"),       # 18.1 / 18.9
+    ((64, 8, 32, 8), "apply_bf16_kernel<true>"),       # 96.5 / 100
+    ((128, 8, 24, 8), "apply_bf16_short_kernel<64"),   # 165 / 157
+    ((128, 8, 32, 8), "apply_bf16_short_kernel<64"),   # 235 / 211
+    ((64, 8, 96, 8), "apply_bf16_short_kernel<64"),    # 351 / 301
+    ((128, 8, 8, 8), "apply_bf16_kernel<false>"),      # 61.3 / 63.8
+    ((512, 8, 8, 8), "apply_bf16_kernel<false>"),      # 290 / 289
+], ids=str)
+def test_packed_causal_maps_of_128_x_64_take_the_kernel_that_measured_best(tmp_path, case, kernel):
+    (status, ls), = launches.record([("apply", *case, 128, 64, True, "bf16", True)], tmp_path)
+    assert status == 0 and ls[0][0].startswith(kernel), ls
+
+
 @pytest.mark.parametrize("case,grid", [
     # B, heads, K/V heads, S, D, causal; workgroups                us, one workgroup a K/V head / workgroups of four units
     ((512, 128, 16, 32, 128, True), 2 * 8192),       # 238 / 207
