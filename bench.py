@@ -110,12 +110,12 @@ def insert_kernel_name(w):
         few = ((768 if D == 64 else 480) if w.causal else (448 if D == 64 else 320))
         return "insert_bf16_split_kernel" if units <= few else "insert_bf16_kernel"
     if g > 1:
-        few = 576 if S >= 96 and D == 64 else 320
+        few = 512 if S >= 96 and D == 64 else 256
     else:
-        few = {32: (896, 576), 64: (1792, 1152)}.get(S, (1024, 1024))[D == 128]
+        few = (24 if D == 64 else 16) * S if S <= 64 else 1024
     if units > few and not (w.causal and D == 128 and S == 128 and g <= 2 and units > 100000):
         return "insert_bf16_short_kernel"
-    split = (128 if S > 64 else 0) if g == 1 else min(1024, g * (256 if D == 64 else 176 if S > 64 else 128))
+    split = few if g > 1 else 128 if S > 64 else 0
     return "insert_bf16_split_kernel" if units <= split else "insert_bf16_kernel"
 
 

@@ -513,32 +513,34 @@ static hipError_t launch_insert_short(const InsertArgs& a, hipStream_t stream);
 
 template <int D, bool CAUSAL, bool PACKED>
 static hipError_t launch_insert_t(const InsertArgs& a, dim3 grid, hipStream_t stream) {
-  // One unit per workgroup while that leaves room on the chip (beyond, K and V, which only the other
-  // kernel shares between rows, cost more).  Up to 128 keys the other kernel walks the heads of a group
-  // one after the other, so the line rises with their number.  us per call, split / not: 8 heads of
-  // 1024 x 128 causal (256 units) 22.9 / 43.8, 32 of 512 x 128 (512) 19.9 / 25.3, 108 of 160 x 128 (540)
-  // 13.0 / 11.9, 72 of it dense (360) 12.5 / 11.4, 96 of 288 x 64 (864) 13.2 / 15.4, 64 of 512 x 64 (1,024) 20.4 / 20.9; 64 on 16 K and V of
-  // 128 x 128 (256) 7.3 / 22.3, 384 on 96 of 64 x 128 (768) 12.9 / 15.0, 8 on 8 of 128 x 128 (32) 6.8 / 8.1,
-  // 128 on 128 (512) 10.2 / 8.8, 256 on 256 of 32 x 64 (256) 5.0 / 4.4.
   const int g = a.Hq / a.Hkv;
   const size_t units = (size_t)(a.n_tiles / a.Hkv) * a.Hq * (a.S / 32);
-  const size_t most = a.S > 128 ? (CAUSAL ? (D == 64 ? 768 : 480) : (D == 64 ? 448 : 320))
-                      : g == 1  ? (a.S > 64 ? 128 : 0)
-                                : std::min(1024, g * (D == 64 ? 256 : a.S > 64 ? 176 : 128));
-  // Up to 128 rows: one pass over the keys (below) wherever the launch is not small.  us per call, split or two passes / one: two heads on one K and
-  // V, 32 rows of 64 (384 units) 6.9 / 6.4, 96 rows (384) 7.4 / 7.7, (768) 10.5 / 8.0, 128 x 128 (256) 8.7 / 9.8, (384) 14.0 / 9.8; one head each, 32 x 64 (768)
-  // 7.0 / 7.4, (1,024) 8.9 / 7.5, 64 x 64 (1,536) 8.3 / 9.1, (2,048) 12.1 / 10.0, 64 x 128 (1,024) 9.1 / 9.5, (1,536) 16.8 / 13.5, 128 x 128 (768)
-  // 10.0 / 10.1, (1,024) 11.1 / 10.8; 64 x 16 x 32 heads of 32 x 64 (49,152) 295 / 163, of 64 x 64 204 / 170, 32 on 8 of 128 x 128 262 / 249.
+  // Up to 128 rows: one pass over the keys (below), but in small launches one unit per workgroup if heads share K and V or there are more than
+  // 64 rows, else two passes.  The lines are where the workgroups of those begin a second round.  us per call, split or two passes / one: two heads on one K
+  // and V, 32 x 64 (192 units) 4.7 / 4.8, (320) 5.7 / 5.0, 64 x 64 (256) 5.1 / 5.7, (320) 5.9 / 5.7, 64 x 128 (256) 6.6 / 6.8, (320) 9.3 / 7.0, 96 x 128
+  // (240) 7.0 / 7.6, (288) 9.2 / 7.7, 128 x 128 (256) 7.5 / 8.6, (320) 9.6 / 8.7, 96 x 64 (480) 6.6 / 6.5, (528) 9.3 / 6.6, 128 x 64 (512) 6.9 / 7.2,
+  // (576) 10.7 / 7.3; four and eight alike; one head each, 32 x 64 (768) 5.7 / 5.7, (776) 7.5 / 5.7, 32 x 128 (512) 6.0 / 6.6, (520) 8.9 / 6.7, 64 x 64
+  // (1,536) 7.0 / 7.7, (1,552) 9.7 / 7.8, 64 x 128 (1,024) 7.8 / 8.2, (1,040) 11.9 / 9.6, 96 x 128 (768) 8.0 / 7.7, (1,032) 9.5 / 9.2, 128 x 128 (1,024) 9.9 /
+  // 9.5, (1,152) 11.3 / 11.5, (1,600) 14.8 / 13.9; 64 x 16 x 32 heads of 32 x 64 (49,152) 295 / 163, of 64 x 64 204 / 170, 32 on 8 of 128 x 128 262 / 249.
+  const size_t few = g > 1 ? (a.S >= 96 && D == 64 ? 512 : 256) : a.S <= 64 ? (D == 64 ? 24 : 16) * a.S : 1024;
   // Rows of dense maps, 96 and more of them, are written in shorter runs by the units of one pass than by two passes over a whole tile, which
-  // shows where every head has its own K and V (two passes / one: 4,096 heads of 128 x 64 causal 87 / 98, 16,384 314 / 397, 16,384 of 96 x 64 428 / 451, of
-  // 128 x 128 485 / 550, 8,192 251 / 270, 2,048 62.4 / 61.4; where two share them, 8,192 of 128 x 64 297 / 286, four 563 / 513, two of 96 x 64 196 / 186, of
-  // 128 x 128 8,192 418 / 409).  So do packed maps of 128 x 128, but only in very large launches of one or two heads on a K and V (32,768 heads
+  // shows where every head has its own K and V (two passes / one: causal, 128 x 64, 512 heads 11.9 / 12.0, 600 13.5 / 16.3, 4,096 84 / 96, 16,384 308 / 385;
+  // 96 x 64, 4,096 46.8 / 45.1, 6,000 81 / 85, 16,384 215 / 226; 96 x 128, 1,488 33.7 / 33.4, 6,000 134 / 143, 16,384 352 / 386; 128 x 128, 1,488 44.0 / 42.6, 2,992
+  // 96 / 103, 16,384 478 / 528; not causal, 128 x 128, 2,992 94 / 100, 16,384 485 / 513, 128 x 64, 6,000 115 / 114, 32,768 606 / 581, 96 x 64 alike).  With
+  // two heads on a K and V: causal, 128 x 64, 512 heads 13.0 / 12.4, 592 15.5 / 16.6, 1,488 23.0 / 26.1, 4,096 55.5 / 57.7, 6,000 118 / 111, 16,384 296 / 281; 64 x
+  // 128, 8,192 96 / 96, 32,768 364 / 374, 65,536 719 / 753; four of 128 x 64 2,976 38.7 / 39.8, 5,984 121 / 112, two of 96 x 64 6,000 55.9 / 53.0, of
+  // 128 x 128 2,992 82.7 / 79.0.  So do packed maps of 128 x 128, but only in very large launches of one or two heads on a K and V (32,768 heads
   // 852 / 874, 24,576 651 / 639; 16,384 of two 713 / 746, 8,192 361 / 363; of four 1,282 / 1,287, of eight 8,192 1,216 / 1,188).
-  const size_t few = g > 1 ? (a.S >= 96 && D == 64 ? 576 : 320)
-                     : a.S == 32 ? (D == 64 ? 896 : 576) : a.S == 64 ? (D == 64 ? 1792 : 1152) : 1024;
-  const bool slower = PACKED ? CAUSAL && D == 128 && a.S == 128 && g <= 2 && units > 100000
-                             : a.S >= 96 && g == 1 && units > (CAUSAL && D == 64 && a.S == 128 ? 1800 : 10000);
+  const bool slower = PACKED                ? CAUSAL && D == 128 && a.S == 128 && g <= 2 && units > 100000
+                      : g == 1 && a.S >= 96 ? (CAUSAL || D == 128) && units > (D == 128 ? 10000 : a.S == 128 ? 2100 : 14000)
+                      : g == 2 && D == 64   ? CAUSAL && a.S == 128 && units > 2100 && units <= 20000
+                                            : g == 2 && a.S == 64 && units > 50000;
   if (a.S <= kChunk && units > few && !slower) return launch_insert_short<D, CAUSAL, PACKED>(a, stream);
+  // Else one unit per workgroup while that leaves room on the chip (beyond, K and V, which only the other kernel shares between rows, cost
+  // more).  us per call, split / not: 8 heads of 1024 x 128 causal (256 units) 22.9 / 43.8, 32 of 512 x 128 (512) 19.9 / 25.3, 108 of 160 x 128
+  // (540) 13.0 / 11.9, 72 of it dense (360) 12.5 / 11.4, 96 of 288 x 64 (864) 13.2 / 15.4, 64 of 512 x 64 (1,024) 20.4 / 20.9; 64 on 16 K and V of
+  // 128 x 128 (256) 7.3 / 22.3, 8 on 8 of 128 x 128 (32) 6.8 / 8.1, 128 on 128 (512) 10.2 / 8.8, 256 on 256 of 32 x 64 (256) 5.0 / 4.4.
+  const size_t most = a.S > 128 ? (CAUSAL ? (D == 64 ? 768 : 480) : (D == 64 ? 448 : 320)) : g > 1 ? few : a.S > 64 ? 128 : 0;
   if (units <= most) {
     hipLaunchKernelGGL((insert_bf16_split_kernel<D, CAUSAL, PACKED>), dim3((unsigned)units), dim3(kThreads), 0, stream, a);
     return hipGetLastError();

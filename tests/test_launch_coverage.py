@@ -195,8 +195,25 @@ def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
     ((64, 8, 128, 16, 128, 128, True, True), "insert_bf16_short_kernel<128, true, true"),   # 1,216, 1,188
     ((64, 8, 32, 32, 96, 128, True, False), "insert_bf16_kernel<128, true, false"),         # 354, 382
     ((64, 8, 32, 16, 128, 128, True, False), "insert_bf16_short_kernel<128, true, false"),  # 415, 405
+    ((128, 1, 32, 16, 128, 64, True, False), "insert_bf16_kernel<64, true, false"),         # 55.5, 57.7
+    ((32, 1, 16, 8, 128, 64, True, False), "insert_bf16_short_kernel<64, true, false"),     # 13.0, 12.4
+    ((64, 8, 32, 16, 128, 64, True, False), "insert_bf16_short_kernel<64, true, false"),    # 296, 281
+    ((128, 1, 32, 32, 96, 64, True, False), "insert_bf16_short_kernel<64, true, false"),    # 46.8, 45.1
+    ((256, 1, 32, 32, 96, 64, True, False), "insert_bf16_kernel<64, true, false"),          # 111, 116
+    ((64, 16, 32, 32, 128, 64, False, False), "insert_bf16_short_kernel<64, false, false"),   # 606, 581
+    ((64, 32, 32, 16, 64, 128, True, False), "insert_bf16_kernel<128, true, false"),        # 719, 753
+    ((64, 32, 32, 16, 64, 128, True, True), "insert_bf16_short_kernel<128, true, true"),    # 686, 650
+    # the workgroups of the kernels for small launches would begin a second round
+    ((40, 1, 8, 4, 32, 64, True, True), "insert_bf16_short_kernel<64, true, true"),         # 5.7, 5.0
+    ((16, 1, 8, 4, 64, 64, True, True), "insert_bf16_split_kernel<64, true, true"),         # 5.1, 5.7
+    ((12, 1, 8, 4, 96, 128, True, True), "insert_bf16_short_kernel<128, true, true"),       # 9.2, 7.7
+    ((22, 1, 8, 4, 96, 64, True, True), "insert_bf16_short_kernel<64, true, true"),         # 9.3, 6.6
+    ((16, 1, 8, 1, 128, 64, True, True), "insert_bf16_split_kernel<64, true, true"),        # 7.0, 7.3
+    ((96, 1, 8, 8, 64, 64, True, True), "insert_bf16_kernel<64, true, true"),               # 7.0, 7.7
+    ((97, 1, 8, 8, 64, 64, True, True), "insert_bf16_short_kernel<64, true, true"),         # 9.7, 7.8
+    ((65, 1, 8, 8, 32, 128, True, True), "insert_bf16_short_kernel<128, true, true"),       # 8.9, 6.7
 ], ids=str)
-def test_large_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp_path, case, kernel):
+def test_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp_path, case, kernel):
     (status, ls), = launches.record([("insert", *case)], tmp_path)
     assert status == 0 and ls[0][0].startswith(kernel), ls
 
