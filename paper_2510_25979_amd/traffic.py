@@ -23,7 +23,8 @@ Regenerate (from the repo root, on a GPU machine; ``cd /tmp && export TMPDIR=/tmp`` 
         --workload llama-3.2-1b-shaped --kernel exact_bf16_short_kernel --largest
 
 (the same with ``--workload 3 --workloads 3`` / ``4`` and the kernels that serve them:
-``apply_bf16_short_kernel`` and ``exact_bf16_kernel``; ``apply_bf16_long_kernel``).
+``apply_bf16_short_kernel`` and ``exact_bf16_short_kernel``; ``apply_bf16_long_kernel`` and
+``exact_bf16_kernel``; with ``--extras insert`` in place of ``--no-extras`` the insert kernels, too).
 """
 from __future__ import annotations
 
