@@ -50,6 +50,7 @@ inline unsigned short_plan(ShortArgs& a, int S, int D) {
 }
 
 __device__ __forceinline__ int short_tile0(const ShortArgs& a) {   // first tile of the workgroup
+  if (a.parts == 1) return (int)blockIdx.x * a.tiles_per_wg;   // (a division less in small launches)
   const unsigned group = (blockIdx.x >> a.xcd_bits) / a.parts;
   return (int)(group << a.xcd_bits | (blockIdx.x & ((1u << a.xcd_bits) - 1))) * a.tiles_per_wg;
 }
@@ -71,7 +72,7 @@ __device__ __forceinline__ void short_attention(const ShortArgs& a, bf16_t* smem
   bf16_t* kb = smem;                          // [T][S][D]
   bf16_t* vb = smem + (size_t)T * S * D;      // [T][S][D]
   bf16_t* ost = smem + (size_t)2 * T * S * D + wave * (16 * kSmallOutStride);
-  const int tile0 = short_tile0(a), part = (int)((blockIdx.x >> a.xcd_bits) % a.parts);
+  const int tile0 = short_tile0(a), part = a.parts == 1 ? 0 : (int)((blockIdx.x >> a.xcd_bits) % a.parts);
   // as a scalar that a vector instruction wrote (see exact.hip)
   const float scale = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, a.scale_log2e) + (lane & 0)));
 
