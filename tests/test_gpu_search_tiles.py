@@ -99,6 +99,10 @@ BOUND_CASES = [
     (150001, 20, 48, 16, torch.float32, "l2"), (5001, 72, 600, 1, torch.float32, "ip"), (40001, 1183, 9, 1, torch.float32, "l2"),
     (40000, 136, 40, 4, torch.float16, "l2"), (30001, 24, 140, 1, torch.float16, "l2"), (50001, 256, 9, 1, torch.float16, "l2"),
     (70001, 64, 40, 8, torch.float16, "l2"), (9001, 520, 65, 5, torch.float16, "l2"), (3001, 2304, 170, 2, torch.float16, "l2"),
+    # just below the lines of the bounds
+    (20011, 128, 32, 1, torch.float32, "l2"), (20011, 131, 33, 1, torch.float32, "ip"), (20011, 72, 50, 1, torch.float32, "l2"),
+    (9001, 97, 130, 3, torch.float32, "l2"), (9001, 200, 64, 8, torch.float32, "ip"), (33000, 64, 70, 2, torch.float32, "ip"),
+    (150001, 33, 20, 1, torch.float32, "ip"), (120001, 20, 48, 16, torch.float32, "l2"),
     # what stays in tiles: queries too wide for the bounds' kernel
     (8000, 2384, 215, 1, torch.float16, "l2"), (8000, 2384, 215, 3, torch.float16, "l2"),
     (8192, 2384, 257, 1, torch.float16, "l2"), (8192, 2384, 257, 3, torch.float16, "l2"),
@@ -117,7 +121,9 @@ OPEN_FULL = [(70001, 96, 64, torch.float32, "l2"), (70001, 97, 25, torch.float32
 OPEN_SHORT = [(70001, 97, 25, torch.float32, "l2"), (70001, 96, 64, torch.float32, "ip"), (4099, 104, 400, torch.float32, "l2"),
               (70001, 104, 25, torch.float16, "l2"), (66001, 1208, 32, torch.float16, "l2")]
 OPEN_WHAT = ["alike", "two kinds", "zeros", "the same", "one open", "far", "one far", "huge", "tiny", "nan", "nan queries"]
-OPEN_CASES = [(w, c) for c in OPEN_FULL for w in OPEN_WHAT] + [(w, c) for c in OPEN_SHORT for w in OPEN_WHAT[:3]]
+OPEN_SMALL = [(30003, 96, 40, torch.float32, "ip"), (30003, 96, 40, torch.float32, "l2"), (30003, 96, 40, torch.float16, "l2")]
+OPEN_CASES = ([(w, c) for c in OPEN_FULL for w in OPEN_WHAT] + [(w, c) for c in OPEN_SHORT for w in OPEN_WHAT[:3]] +
+              [(w, c) for c in OPEN_SMALL for w in OPEN_WHAT if w not in ("two kinds", "zeros", "the same", "one open")])
 
 
 def _open_data(what, N, E, B, dt):
@@ -167,7 +173,7 @@ def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, case
     emb, q = _open_data(what, N, E, B, dt)
     m = ac.AC_IP if metric == "ip" else ac.AC_L2
     idx, score, hit = _run_search(ac, emb, q, k, 0.8, m)
-    few = torch.arange(0, B, max(1, B // 20))   # (the oracle)
+    few = torch.arange(0, B, max(1, B // 40))   # (the oracle)
     if what not in ("nan", "nan queries"):
         parity.check_search(oracle_mod, q[few], emb, k, 0.8, m, None, idx[few], score[few], hit[few])
     if k == 1 and what in ("alike", "two kinds", "the same", "zeros"):   # of rows that are the same the first

@@ -203,7 +203,7 @@ def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
     ((64, 16, 32, 32, 128, 64, False, False), "insert_bf16_short_kernel<64, false, false"),   # 606, 581
     ((64, 32, 32, 16, 64, 128, True, False), "insert_bf16_kernel<128, true, false"),        # 719, 753
     ((64, 32, 32, 16, 64, 128, True, True), "insert_bf16_short_kernel<128, true, true"),    # 686, 650
-    # the workgroups of the kernels for small launches would begin a second round
+    # and small ones: the workgroups of the other kernels would begin a second round
     ((40, 1, 8, 4, 32, 64, True, True), "insert_bf16_short_kernel<64, true, true"),         # 5.7, 5.0
     ((16, 1, 8, 4, 64, 64, True, True), "insert_bf16_split_kernel<64, true, true"),         # 5.1, 5.7
     ((12, 1, 8, 4, 96, 128, True, True), "insert_bf16_short_kernel<128, true, true"),       # 9.2, 7.7
@@ -213,7 +213,7 @@ def test_the_projector_workspace_holds_every_length_and_smaller_batch(tmp_path):
     ((97, 1, 8, 8, 64, 64, True, True), "insert_bf16_short_kernel<64, true, true"),         # 9.7, 7.8
     ((65, 1, 8, 8, 32, 128, True, True), "insert_bf16_short_kernel<128, true, true"),       # 8.9, 6.7
 ], ids=str)
-def test_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp_path, case, kernel):
+def test_large_inserts_of_short_sequences_take_the_kernel_that_measured_best(tmp_path, case, kernel):
     (status, ls), = launches.record([("insert", *case)], tmp_path)
     assert status == 0 and ls[0][0].startswith(kernel), ls
 
