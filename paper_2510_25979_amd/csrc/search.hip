@@ -1151,8 +1151,8 @@ __global__ __launch_bounds__(kThreads) void search_bound_kernel(const SearchArgs
 // Usually nothing is open, so the grid is one that is quickly through.
 // us per call, 100,000 x 128 fp32 Euclidean, 64 queries; exact scores of all rows first, / all rows of what is left open in tiles / so: 40 rows
 // at random places alike for each query 58 / 75 / 48; all rows of 40 kinds 59 / 77 / 58; rows 100 times their spread from the origin 57 / 73 / 47; all
-// rows the same 58 / 75 / 58.  Two kinds in random order, of which every third row reaches, so that all are scored, 57 / 73 / 124 (one row at a time 166; fp16
-// 100,000 x 256 118 / 139 / 213, 335): the vector ALUs take 55 of it, on 391 workgroups for 256 compute units.
+// rows the same 58 / 75 / 56.  Two kinds in random order, of which every third row reaches, so that all are scored, 57 / 73 / 118 (one row at a time 166; fp16
+// 100,000 x 256 118 / 139 / 201, 335): the vector ALUs take 55 of it, on 391 workgroups for 256 compute units.  Five kinds, one in ten 57 / 73 / 91.
 constexpr int kUnsurePairs = 2048;   // (twice as many cost fp16 rows of 256 columns the second workgroup of a compute unit)
 constexpr int kUnsureRows = 4;
 template <typename T, bool L2, int NQB, int MODE>
@@ -1170,7 +1170,7 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
   float* qq = own + 4 * 32;
   T* raw = reinterpret_cast<T*>(smem);             // [NQ][QE], once the products are done
   const T* emb = reinterpret_cast<const T*>(a.emb);
-  const int QE = (a.E + 7) & ~7;
+  const int QE = ((a.E + 7) & ~7) + kQPad;         // (no more than bound_query, and no multiple of all banks)
   const int tid = threadIdx.x, lane = tid & 63, il = lane & 31, kh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nqb = (a.B + NQ - 1) / NQ, n_rows = (a.N + a.wg_rows - 1) / a.wg_rows;
@@ -1210,6 +1210,19 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
     bound_products<T, L2, NQB, MODE>(a, row0, row_end, q0, nq, qs, own, ref, qq, wave, note);
     __syncthreads();
     const int many = n_pairs, part8 = tid & 7;
+    constexpr bool STAGED = std::is_same<T, float>::value;   // pairs take the query from LDS (fp16 ones 153 us so, 135 from the L1)
+    if (many > (STAGED ? 0 : kUnsurePairs * NQB)) {          // the queries in place of their parts
+#pragma unroll 4
+      for (int c = P * part8; c < QE - kQPad; c += 8 * P) {
+        Piece w[NQB];
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb)
+          w[qb].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + min(32 * qb + (tid >> 3), nq - 1)) * a.E, c, a.E);
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) *reinterpret_cast<decltype(w[qb].w)*>(raw + (32 * qb + (tid >> 3)) * QE + c) = w[qb].w;   // (zeros past E)
+      }
+      __syncthreads();
+    }
     if (many <= kUnsurePairs * NQB) {   // scores of eight rows and queries, thread u of the eight has the u-th
       for (int p = tid & ~7; p < many; p += kThreads) {
         int r[8], t[8];
@@ -1220,13 +1233,13 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
           r[u] = pair >> 6;
           t[u] = pair & 63;
         }
-#pragma unroll 1
-        for (int c = P * part8; c < a.E; c += 8 * P) {
+        auto add = [&](int c) __attribute__((always_inline)) {
           Piece e[8], x[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
             e[u].load(emb + (size_t)(row0 + r[u]) * a.E, c, a.E);
-            x[u].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + t[u]) * a.E, c, a.E);
+            if constexpr (STAGED) x[u].w = *reinterpret_cast<const decltype(x[u].w)*>(raw + t[u] * QE + c);   // (zeros past E)
+            else x[u].load(reinterpret_cast<const T*>(a.q) + (size_t)(q0 + t[u]) * a.E, c, a.E);
           }
 #pragma unroll
           for (int i = 0; i < P; ++i)
@@ -1235,6 +1248,13 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
               const float y = e[u].at(i), d = x[u].at(i) - y;
               acc[u] = L2 ? fmaf(-d, d, acc[u]) : fmaf(x[u].at(i), y, acc[u]);
             }
+        };
+        if constexpr (STAGED) {
+#pragma unroll 2
+          for (int c = P * part8; c < a.E; c += 8 * P) add(c);
+        } else {
+#pragma unroll 1
+          for (int c = P * part8; c < a.E; c += 8 * P) add(c);
         }
         const float s = row_of_eight(acc, part8);
         if (p + part8 < many && s == s) {
@@ -1248,11 +1268,6 @@ __global__ __launch_bounds__(kThreads, 2) void search_unsure_kernel(const Search
         }
       }
     } else {
-      for (int x = tid; x < NQ * QE; x += kThreads) {
-        const int c = x % QE;
-        raw[x] = c < a.E ? reinterpret_cast<const T*>(a.q)[(size_t)(q0 + min(x / QE, nq - 1)) * a.E + c] : (T)0.f;
-      }
-      __syncthreads();
       // Rows r0 + 32 j of an eight by eight queries; the sums take the steps of those above.
       const int n = row_end - row0;
       for (int r0 = tid >> 3; r0 < n; r0 += 32 * kUnsureRows) {

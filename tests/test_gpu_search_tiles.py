@@ -196,7 +196,7 @@ def test_bounded_search_of_what_the_bounds_leave_open(ac, oracle_mod, what, case
 def test_what_the_bounds_leave_open_takes_so_much_longer_at_most(ac, what, E, most):  # noqa: F811
     """60 rows alike for every query, in as many groups: their rows are scored by the whole chip (33 us a call, 18 without them; 54
     to 74 where a workgroup a query scored group after group).  Rows of two kinds, of which one in three reaches, so that all are scored:
-    124 us, 23.5 of rows that differ; 166 with one row a thread at a time."""
+    118 us, 23.5 of rows that differ; 166 with one row a thread at a time."""
     N, B = 100000, 64
     g = _gen(3)
     emb = torch.randn(N, E, generator=g) / E ** 0.5
